@@ -23,10 +23,12 @@ HIPCC_FLAGS = [
 UNITS = [
     # a wavefront per coefficient class (chunk 96, 128, 192, 256; 64 on small shards)
     "split_compress_256.hip", "split_compress_192.hip", "split_compress_128.hip",
-    "split_compress_96.hip", "split_compress_64.hip", "split_decompress.hip",
+    "split_narrow_256.hip", "split_narrow_192.hip", "split_narrow_128.hip",
+    "split_compress_96.hip", "split_compress_64.hip", "split_narrow_96.hip",
+    "split_decompress.hip", "split_decompress_narrow.hip",
     # two lanes per chunk (chunk 96, 128, 192, 256)
     "pair_compress_256.hip", "pair_compress_192.hip", "pair_compress_128.hip",
-    "pair_compress_96.hip", "pair_decompress.hip",
+    "pair_compress_96.hip",
     # lane per chunk, top-k with fp32 values and int32 indices, by chunk size
     "tiled_topk_s96.hip", "tiled_topk_s128.hip",
     # matrix-core kernels (every other multiple of 32)

@@ -132,6 +132,16 @@ __device__ __forceinline__ void st_u4(void* p, uint4 v) {
     }
 }
 
+template <bool NT>
+__device__ __forceinline__ void st_u2(void* p, uint2 v) {
+    if constexpr (NT) {
+        const u32x2_t t = {v.x, v.y};
+        __builtin_nontemporal_store(t, reinterpret_cast<u32x2_t*>(p));
+    } else {
+        *reinterpret_cast<uint2*>(p) = v;
+    }
+}
+
 // Ordering point between the LDS phases of a single-wavefront workgroup.  The LDS queue of
 // one wavefront is processed in program order, so no hardware barrier is needed; this only
 // stops the compiler from moving LDS accesses across the phase boundary.  Unlike

@@ -102,7 +102,7 @@ size_t idx_access(const KParams& p) {
     return p.idx_u8 ? 4 : 16;
 }
 size_t val_access(const KParams& p) {
-    if (p.val_dtype == DETO_TERNARY) return p.k > 16 ? 8 : 4;
+    if (p.val_dtype == DETO_TERNARY) return (p.k > 16 && p.k <= 32) ? 8 : 4;
     if (p.k % 4 != 0) return val_size(p.val_dtype);
     return p.val_dtype == DETO_F32 ? 16 : 8;
 }
@@ -345,10 +345,15 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
                                  val_replica_stride, params, param_dtype == DETO_BF16, presign_dbg,
                                  {0, 0, 0, 0}, st, adam};
         stride_pattern(p, a.stride_mask);
-        const bool done = tiles == 0 ? false
-                          : idx ? (deto::launch_decompress_adamw(a) ||
-                                 deto::launch_decompress_adamw_narrow(a) ||
-                                 deto::launch_decompress_idx_s64(a) ||
+        auto split = [](const deto::DecompressLaunch& d, int classes) -> int64_t {
+            if (classes == 0) return 0;
+            const int64_t c = deto::launch_decompress_split(d, classes);
+            return c ? c : deto::launch_decompress_split_narrow(d, classes);
+        };
+        // transmitted indices: a lane per chunk or a wavefront per coefficient class
+        if (idx) c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, true));
+        const bool done = (c0 > 0 || tiles == 0) ? false
+                          : idx ? (deto::launch_decompress_idx_s64(a) ||
                                  deto::launch_decompress_idx_s32(a) ||
                                  deto::launch_decompress_idx_s16(a) ||
                                  deto::launch_decompress_idx_s96(a) ||
@@ -367,8 +372,9 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
             if (rc) return rc;
             c0 = C;   // the tail chunks rode along in the same launch
         } else {
-            c0 = deto::launch_decompress_split(a);
-            if (c0 == 0) c0 = deto::launch_decompress_pair(a);
+            // no lane-per-chunk kernel for this (s, k, format)
+            if (c0 == 0 && idx)
+                c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, false));
             if (c0 == 0) c0 = deto::launch_decompress_mfma(a);
             if (c0 > 0) {
                 rc = launched();

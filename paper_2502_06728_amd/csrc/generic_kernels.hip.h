@@ -98,6 +98,11 @@ __device__ __forceinline__ uint32_t spread16(uint32_t x) {
     return x;
 }
 
+// sign(v) as its two-bit code
+__device__ __forceinline__ uint32_t ternary_code(float v) {
+    return v < 0.0f ? 3u : (v != 0.0f ? 1u : 0u);
+}
+
 __device__ __forceinline__ float ternary_decode(uint32_t word, int j) {
     const uint32_t code = (word >> (2 * (j & 15))) & 3u;
     return (code & 1u) ? ((code & 2u) ? -1.0f : 1.0f) : 0.0f;

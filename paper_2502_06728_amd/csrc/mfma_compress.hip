@@ -1,4 +1,4 @@
-// Matrix-core compress kernels (chunk sizes 32, 64, ..., 256; any k; top-k selection).
+// Matrix-core compress kernels (chunk sizes 160, 224, and 32, 64 with k > s/2; top-k selection).
 #include "mfma_kernels.hip.h"
 #include "tiled_launch.h"
 
@@ -21,7 +21,7 @@ int64_t launch_compress_mfma(const CompressLaunch& a) {
                                                                    a.val, a.coeff_dbg);         \
         return tiles * kMfmaChunks;                                                             \
     }
-    DETO_MFMA_NB_LIST(X)
+    DETO_MFMA_COMPRESS_LIST(X)
 #undef X
     return 0;
 }

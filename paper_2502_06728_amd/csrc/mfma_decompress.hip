@@ -1,4 +1,4 @@
-// Matrix-core decompress-and-update kernels (chunk sizes 32, 64, ..., 256; any k; transmitted
+// Matrix-core decompress-and-update kernels (chunk sizes 160 and 224; any k; transmitted
 // indices; plain SGD update or Decoupled AdamW).
 #include "mfma_kernels.hip.h"
 #include "tiled_launch.h"
@@ -27,7 +27,7 @@ int64_t launch_decompress_mfma(const DecompressLaunch& a) {
                 a.presign_dbg);                                                                 \
         return tiles * kMfmaChunks;                                                             \
     }
-    DETO_MFMA_NB_LIST(X)
+    DETO_MFMA_DECOMPRESS_LIST(X)
 #undef X
     return 0;
 }

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(kWave) void compress_pair(KParams p, int64_t tiles,
 #pragma unroll
         for (int m = 0; m < H; ++m) row[2 * m + h] = c[m];
         wave_lds_sync();
-        emit_tied_chunks<NB>(buf, p, lane, need, thr_gt, thr_eq, chunk0, idx_out, val_out,
+        emit_tied_chunks<32 * NB>(buf, p, lane, need, thr_gt, thr_eq, chunk0, idx_out, val_out,
                              nullptr);
         wave_lds_sync();
     }
@@ -342,63 +342,6 @@ __global__ __launch_bounds__(kWave) void compress_pair(KParams p, int64_t tiles,
             const int r = e4 / S, col = e4 - r * S;
             st_f4<false>(mom + base + e4, combine_halves<S>(&buf[r * kRow], col));
         }
-    }
-}
-
-// Decompress-and-update half on full tiles of 32 chunks (transmitted indices, DCT domain).
-template <int S, bool PARAM_BF16>
-__global__ __launch_bounds__(kWave) void decompress_pair(
-    KParams p, int64_t tiles, int64_t n, int64_t n_chunks, int vec_scatter,
-    const void* __restrict__ idx, int64_t idx_stride, const void* __restrict__ val,
-    int64_t val_stride, void* __restrict__ params, AdamPtrs ad, float* __restrict__ presign_dbg) {
-    using G = PairGeom<S>;
-    constexpr int NB = G::NB, H = G::H, kRow = G::kRow;
-    __shared__ __attribute__((aligned(16))) float buf[kMfmaChunks * kRow];
-
-    const int lane = threadIdx.x;
-    const int t = lane & 31, h = lane >> 5;
-    const int k = p.k;
-    const uint32_t magic = entry_magic(k);
-    const float scale = p.alpha * p.inv_R, scale0 = p.alpha0 * p.inv_R;
-
-    // One tile per workgroup.  A loop over tiles invites the compiler to hoist what does not
-    // change from tile to tile (the lane's payload index constants, row addresses) out of it
-    // and, with every register taken, to spill it: a scratch reload per coefficient.
-    const int64_t tile = blockIdx.x;
-    if (tile >= tiles) {
-        static_assert(sizeof(GenericDecompressSmem) <= sizeof(buf), "tail code borrows the tile");
-        decompress_generic_chunks<PARAM_BF16>(p, n, tiles * kMfmaChunks + (tile - tiles), n_chunks,
-                                              gridDim.x - tiles,
-                                              *reinterpret_cast<GenericDecompressSmem*>(buf), idx,
-                                              idx_stride, val, val_stride, params, ad,
-                                              presign_dbg);
-        return;
-    }
-    {
-        const int64_t base = tile * static_cast<int64_t>(kMfmaChunks * S);
-        const int64_t entry0 = tile * static_cast<int64_t>(kMfmaChunks) * k;
-        float* row = &buf[t * kRow];
-
-        scatter_tile<NB>(buf, p, lane, vec_scatter, idx, idx_stride, val, val_stride, entry0, magic);
-        wave_lds_sync();
-
-        // ---- the lane's half of the accumulated coefficients: a[2m + h] * alpha_j / R
-        float v[H];
-#pragma unroll
-        for (int q = 0; q < S / 4; ++q) {
-            const float4 a = *reinterpret_cast<const float4*>(row + 4 * q);
-            v[2 * q] = (h ? a.y : a.x) * scale;
-            v[2 * q + 1] = (h ? a.w : a.z) * scale;
-        }
-        if (h == 0) v[0] = row[0] * scale0;
-        inverse_half_to_row<S>(row, h, v);
-        wave_lds_sync();
-
-        update_params_rows<NB, PARAM_BF16>(p, lane, base, params, ad, presign_dbg,
-                                           [&](int r, int col) {
-                                               return combine_halves<S>(&buf[r * kRow], col);
-                                           });
-        wave_lds_sync();
     }
 }
 

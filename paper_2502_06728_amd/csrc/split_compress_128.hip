@@ -21,11 +21,9 @@ int64_t launch_compress_split_128(const CompressLaunch& a) {
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);
     if (tiles <= 0 || grid64 > 0x7FFFFFFF) return 0;
     const unsigned grid = static_cast<unsigned>(grid64);
-    int32_t* io = static_cast<int32_t*>(a.idx);
-    float* vo = static_cast<float*>(a.val);
 #define LAUNCH(W, BF16, TOP)                                                               \
     compress_split<128, W, BF16, TOP><<<grid, SplitGeom<128, W>::kThreads, 0, a.stream>>>( \
-        p, tiles, a.n, a.n_chunks, a.grad, a.mom, io, vo, a.coeff_dbg)
+        p, tiles, a.n, a.n_chunks, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
     if (tiles <= small_shard_tiles()) {
         // a small shard: four classes (32 coefficients per lane, four wavefronts per tile)
         if (p.k <= 16) {

@@ -19,11 +19,9 @@ int64_t launch_compress_split_192(const CompressLaunch& a) {
     const unsigned grid = static_cast<unsigned>(grid64);
     constexpr int kThreads = SplitGeom<192, 4>::kThreads;
     // a launch with k <= 16 (k <= 32) sorts out only every lane's 16 (32) largest magnitudes
-    int32_t* io = static_cast<int32_t*>(a.idx);
-    float* vo = static_cast<float*>(a.val);
 #define LAUNCH(BF16, TOP)                                                                  \
     compress_split<192, 4, BF16, TOP><<<grid, kThreads, 0, a.stream>>>(                 \
-        p, tiles, a.n, a.n_chunks, a.grad, a.mom, io, vo, a.coeff_dbg)
+        p, tiles, a.n, a.n_chunks, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
     if (p.k <= 16) {
         if (a.grad_bf16) LAUNCH(true, 16);
         else LAUNCH(false, 16);

@@ -26,11 +26,9 @@ int64_t launch_compress_split_64(const CompressLaunch& a) {
     if (grid64 > 0x7FFFFFFF) return 0;
     const unsigned grid = static_cast<unsigned>(grid64);
     constexpr int kThreads = SplitGeom<64, 2>::kThreads;
-    int32_t* io = static_cast<int32_t*>(a.idx);
-    float* vo = static_cast<float*>(a.val);
 #define LAUNCH(BF16, TOP)                                                                  \
     compress_split<64, 2, BF16, TOP><<<grid, kThreads, 0, a.stream>>>(                  \
-        p, tiles, a.n, a.n_chunks, a.grad, a.mom, io, vo, a.coeff_dbg)
+        p, tiles, a.n, a.n_chunks, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
     // a launch with k <= 16 sorts out only every lane's 16 largest magnitudes
     if (p.k <= 16) {
         if (a.grad_bf16) LAUNCH(true, 16);

@@ -25,11 +25,9 @@ int64_t launch_compress_split_96(const CompressLaunch& a) {
     // a launch with k <= 16 sorts out only every lane's 16 largest magnitudes
     constexpr int kQ = SplitGeom<96, DETO_SPLIT_W>::Q;
     constexpr int kTop = (kQ % 16 == 0 && kQ > 16) ? 16 : 0;
-    int32_t* io = static_cast<int32_t*>(a.idx);
-    float* vo = static_cast<float*>(a.val);
 #define LAUNCH(BF16, TOP)                                                                  \
     compress_split<96, DETO_SPLIT_W, BF16, TOP><<<grid, kThreads, 0, a.stream>>>(                 \
-        p, tiles, a.n, a.n_chunks, a.grad, a.mom, io, vo, a.coeff_dbg)
+        p, tiles, a.n, a.n_chunks, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
     if (kTop > 0 && p.k <= kTop) {
         if (a.grad_bf16) LAUNCH(true, kTop);
         else LAUNCH(false, kTop);

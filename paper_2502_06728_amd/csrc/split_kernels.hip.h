@@ -313,18 +313,22 @@ __device__ __forceinline__ float4 split_output(const float* __restrict__ row, in
     return make_float4(e.w - o.w, e.z - o.z, e.y - o.y, e.x - o.x);
 }
 
-// Compress half (top-k, DCT domain, fp32 values + int32 indices, k <= S/2) on full tiles of 64
-// chunks; the chunks past the last full tile form one partial tile (one more workgroup).
+// Compress half (top-k, DCT domain, k <= S/2) on full tiles of 64 chunks; the chunks past the
+// last full tile form one partial tile (one more workgroup).
 // TOP > 0: for launches with k <= TOP (see the selection step).
+// NARROW: any payload format, chosen at run time by p.val_dtype and p.idx_u8 (16-bit values or
+// two-bit signs, byte or int32 indices); otherwise fp32 values and int32 indices.  Only the
+// staging step (what a kept coefficient leaves behind) and the payload's way out look at the
+// format, each behind one uniform branch, so one kernel serves all of them.
 // Occupancy: the workgroups of a CU are each in one phase at a time (barriers), so the number
 // of workgroups per CU is what overlaps memory phases with arithmetic.  Chunk 192 with the
 // partial sort fits three (168 registers, 52 KB of LDS with the dump slots inside the rows);
 // chunk 256 two (a 64-row tile alone is 65 KB); chunk 96 / 128 four to six of two wavefronts.
-template <int S, int W, bool GRAD_BF16, int TOP = 0>
+template <int S, int W, bool GRAD_BF16, int TOP = 0, bool NARROW = false>
 __global__ __launch_bounds__(kWave * W)
 __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ grad,
-    float* __restrict__ mom, int32_t* __restrict__ idx_out, float* __restrict__ val_out,
+    float* __restrict__ mom, void* __restrict__ idx_out, void* __restrict__ val_out,
     float* __restrict__ coeff_dbg) {
     using G = SplitGeom<S, W>;
     constexpr int Q = G::Q, kRow = G::kRow, NW = G::NW, kThreads = G::kThreads;
@@ -335,6 +339,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     __shared__ uint32_t s_mask[kWave][W][NW];    // kept sets: chunk, class, word
     __shared__ uint8_t s_cnt[kWave][W];          // kept per class (at most Q <= 64)
     __shared__ unsigned long long s_tie;         // chunks of the tile that took the tie pass
+    __shared__ uint32_t s_words[NARROW ? (S / 2 + 15) / 16 : 1];   // tie pass: one chunk's signs
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -558,8 +563,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
             if (w == 0) {
                 const unsigned long long tl = __ballot(need != 0);
                 if (lane == 0) s_tie = tl;
-                emit_tied_chunks<S / 32, kWave>(buf, p, lane, need, thr_gt, thr_eq, chunk0, idx_out,
-                                                val_out, nullptr);
+                emit_tied_chunks<S, kWave, NARROW>(buf, p, lane, need, thr_gt, thr_eq, chunk0,
+                                                        idx_out, val_out, nullptr, s_words);
             }
             __syncthreads();
             if (need != 0) {
@@ -603,6 +608,12 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                               (kRowDumps ? lane * kRow + G::kRowDump + (lane >> 4) : kTile + tid);
         uint32_t at = static_cast<uint32_t>(sizeof(float)) * (lane * kRow + start);
         const int idx0 = off;
+        // what a kept coefficient leaves behind: the rounding error of a 16-bit format, nothing
+        // otherwise.  Both roundings are computed and one is picked: with a branch per format
+        // around this loop the compiler hoists the loop's common part and keeps it live across
+        // the branch (chunk 128: 193 registers instead of 128, two wavefronts per SIMD instead
+        // of four)
+        const bool as_bf16 = p.val_dtype == 1, as_f16 = p.val_dtype == 2;
         static_for<0, Q>([&](auto m) {
             const uint32_t kb = (own[m / 32] >> (m % 32)) & 1u;
             const uint32_t b0 = (plane0[m / 32] >> (m % 32)) & 1u;
@@ -613,7 +624,14 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 __int_as_float(idx0 + W * m);
             at += 4u * kb + 4u * b0;
             if constexpr (W == 4) at += 8u * ((plane1[m / 32] >> (m % 32)) & 1u);
-            c[m] = (keep ? 0.0f : c[m]) * ((m == 0 && w == 0) ? p.alpha0 : p.alpha);
+            float left = 0.0f;
+            if constexpr (NARROW) {
+                float r = c[m];
+                r = as_bf16 ? __uint_as_float(pack_bf16x2(c[m], 0.0f) << 16) : r;
+                r = as_f16 ? f16_to_f32(f32_to_f16(c[m])) : r;
+                left = c[m] - r;
+            }
+            c[m] = (keep ? left : c[m]) * ((m == 0 && w == 0) ? p.alpha0 : p.alpha);
         });
     }
     __syncthreads();
@@ -621,8 +639,17 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         // the tile's 64*k entries are contiguous in both payload arrays
         const uint32_t magic = entry_magic(k);
         const unsigned long long tie_chunks = s_tie;
-        float* vo = val_out + chunk0 * k;
-        int32_t* io = idx_out + chunk0 * k;
+        // entries e .. e+3 of the tile (k a multiple of 4: they belong to one chunk)
+        auto store_index4 = [&](uint32_t e, const float* src) {
+            const float4 iv = *reinterpret_cast<const float4*>(src + kIdx0);
+            const int4 i4 = make_int4(__float_as_int(iv.x), __float_as_int(iv.y),
+                                      __float_as_int(iv.z), __float_as_int(iv.w));
+            if (NARROW && p.idx_u8)
+                *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(idx_out) + chunk0 * k + e) =
+                    static_cast<uint32_t>(i4.x | (i4.y << 8) | (i4.z << 16) | (i4.w << 24));
+            else
+                *reinterpret_cast<int4*>(static_cast<int32_t*>(idx_out) + chunk0 * k + e) = i4;
+        };
         if (k % 4 == 0) {
             const int quads = live * k / 4;                // 16-byte pieces of the tile
             for (int q = tid; q < quads; q += kThreads) {
@@ -631,11 +658,21 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 const uint32_t j = e - r * static_cast<uint32_t>(k);
                 if ((tie_chunks >> r) & 1ull) continue;    // written by the tie pass
                 const float* src = &buf[r * kRow + j];
-                st_f4<false>(vo + e, *reinterpret_cast<const float4*>(src));
-                const float4 iv = *reinterpret_cast<const float4*>(src + kIdx0);
-                *reinterpret_cast<int4*>(io + e) =
-                    make_int4(__float_as_int(iv.x), __float_as_int(iv.y), __float_as_int(iv.z),
-                              __float_as_int(iv.w));
+                const float4 v = *reinterpret_cast<const float4*>(src);
+                if (!NARROW || p.val_dtype == 0) {
+                    st_f4<false>(static_cast<float*>(val_out) + chunk0 * k + e, v);
+                } else if (p.val_dtype != 3) {
+                    uint2 h;
+                    if (p.val_dtype == 1) {
+                        h.x = pack_bf16x2(v.x, v.y);
+                        h.y = pack_bf16x2(v.z, v.w);
+                    } else {
+                        h.x = f32_to_f16(v.x) | (static_cast<uint32_t>(f32_to_f16(v.y)) << 16);
+                        h.y = f32_to_f16(v.z) | (static_cast<uint32_t>(f32_to_f16(v.w)) << 16);
+                    }
+                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(val_out) + chunk0 * k + e) = h;
+                }
+                store_index4(e, src);
             }
         } else {
             // four entries of a lane could straddle two chunks (and the arrays need not be
@@ -645,8 +682,39 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 const uint32_t j = e - r * static_cast<uint32_t>(k);
                 if ((tie_chunks >> r) & 1ull) continue;
                 const float* src = &buf[r * kRow + j];
-                vo[e] = src[0];
-                io[e] = __float_as_int(src[kIdx0]);
+                const int at = __float_as_int(src[kIdx0]);
+                if constexpr (NARROW) {
+                    if (p.val_dtype != 3)
+                        store_payload_value(val_out, chunk0 * k + e, p.val_dtype, src[0]);
+                    store_payload_index(idx_out, chunk0 * k + e, p.idx_u8, at);
+                } else {
+                    static_cast<float*>(val_out)[chunk0 * k + e] = src[0];
+                    static_cast<int32_t*>(idx_out)[chunk0 * k + e] = at;
+                }
+            }
+        }
+        if (NARROW && p.val_dtype == 3) {
+            // two-bit signs: a thread builds one 16-entry word from the staged values (the
+            // tile's words are contiguous)
+            const uint32_t nw = static_cast<uint32_t>(ternary_words_per_chunk(k));
+            uint32_t* words = static_cast<uint32_t*>(val_out) + chunk0 * nw;
+            for (uint32_t q = tid; q < live * nw; q += kThreads) {
+                const uint32_t r = q / nw;
+                const uint32_t j0 = 16u * (q - r * nw);
+                if ((tie_chunks >> r) & 1ull) continue;
+                const float* src = &buf[r * kRow + j0];
+                uint32_t word = 0u;
+#pragma unroll
+                for (uint32_t v = 0; v < 4; ++v) {
+                    const float4 x = *reinterpret_cast<const float4*>(src + 4 * v);
+                    const float xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+                    for (uint32_t i = 0; i < 4; ++i) {
+                        const uint32_t j = 4 * v + i;
+                        if (j0 + j < static_cast<uint32_t>(k)) word |= ternary_code(xs[i]) << (2 * j);
+                    }
+                }
+                words[q] = word;
             }
         }
     }
@@ -682,25 +750,170 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     }
 }
 
-// Decompress-and-update half (transmitted indices, DCT domain, fp32 values + int32 indices) on
-// full tiles of 64 chunks, W wavefronts per workgroup.
+// One lane's piece of a replica's payload as it is loaded and until it is applied: VEC consecutive
+// entries (four, or one where k is not a multiple of 4).  VAL: value format (0 fp32, 1 bf16,
+// 2 fp16, 3 two-bit signs); U8: byte indices.
+template <int VEC, int VAL, bool U8>
+struct SplitPiece {
+    static_assert(VEC == 1 || VEC == 4, "one entry or four");
+    static constexpr int kIdxWords = U8 ? 1 : VEC;
+    static constexpr int kValWords = (VAL == 0) ? VEC : ((VAL == 3 || VEC == 1) ? 1 : 2);
+    uint32_t i[kIdxWords], v[kValWords];
+
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int c = 0; c < kIdxWords; ++c) i[c] = 0u;
+#pragma unroll
+        for (int c = 0; c < kValWords; ++c) v[c] = 0u;
+    }
+    // entries ie .. / ve .. counted from the arrays' bases; word_byte: the byte with these
+    // entries' signs
+    __device__ __forceinline__ void load(const void* idx, int64_t ie, const void* val, int64_t ve,
+                                         int64_t word_byte) {
+        if constexpr (VEC == 4) {
+            if constexpr (U8) {
+                i[0] = ld_u1<true>(static_cast<const uint8_t*>(idx) + ie);
+            } else {
+                const uint4 t = ld_u4<true>(static_cast<const int32_t*>(idx) + ie);
+                i[0] = t.x; i[1] = t.y; i[2] = t.z; i[3] = t.w;
+            }
+            if constexpr (VAL == 0) {
+                const uint4 t = ld_u4<true>(static_cast<const float*>(val) + ve);
+                v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+            } else if constexpr (VAL == 3) {
+                v[0] = static_cast<const uint8_t*>(val)[word_byte];
+            } else {
+                const uint2 t = ld_u2<true>(static_cast<const uint16_t*>(val) + ve);
+                v[0] = t.x; v[1] = t.y;
+            }
+        } else {
+            i[0] = U8 ? static_cast<uint32_t>(static_cast<const uint8_t*>(idx)[ie])
+                      : static_cast<const uint32_t*>(idx)[ie];
+            if constexpr (VAL == 0) v[0] = static_cast<const uint32_t*>(val)[ve];
+            else if constexpr (VAL == 3) v[0] = static_cast<const uint8_t*>(val)[word_byte];
+            else v[0] = static_cast<const uint16_t*>(val)[ve];
+        }
+    }
+    // indices and values; j: the first entry's place in its chunk
+    __device__ __forceinline__ void get(uint32_t j, uint32_t (&at)[VEC], float (&x)[VEC]) const {
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+            at[c] = (U8 && VEC == 4) ? (i[0] >> (8 * c)) & 0xFFu : i[U8 ? 0 : c];
+            if constexpr (VAL == 0) x[c] = __uint_as_float(v[c]);
+            else if constexpr (VAL == 3) x[c] = ternary_decode(v[0], VEC == 4 ? c : (j & 3u));
+            else x[c] = decode16<VAL>(static_cast<uint16_t>(v[VEC == 1 ? 0 : c / 2] >> (16 * (c & 1))));
+        }
+    }
+};
+
+// Scatter-add of R replicas' entries into `rows` (my_rows chunk rows of kRow floats that belong to
+// the calling wavefront), replica after replica; entry0 / chunk0: the first entry / chunk of
+// those rows.  A step = one batch of replicas for one group of 64 pieces of VEC entries, one
+// piece per lane; the loads of the next step are requested before the present one is applied.
+// Inside a group a replica's entries hit distinct accumulators when the indices of every lane,
+// and the step from the previous lane, ascend strictly (what compress emits): a plain
+// read-add-write then; LDS atomics otherwise (duplicates add; they cost about 3 cycles a lane).
+template <int S, int VEC, int VAL, bool U8>
+__device__ __forceinline__ void split_scatter(const KParams& p, int lane, float* rows, int my_rows,
+                                              const void* __restrict__ idx, int64_t idx_stride,
+                                              const void* __restrict__ val, int64_t val_stride,
+                                              int64_t entry0, int64_t chunk0, uint32_t magic) {
+    constexpr int kRow = S + 4;
+    constexpr int kBatch = 4;                              // replicas per batch
+    using Piece = SplitPiece<VEC, VAL, U8>;
+    const int k = p.k;
+    const int pieces = my_rows * k / VEC;                  // per replica
+    const int chunk_bytes = 4 * ternary_words_per_chunk(k);
+    const int n_batches = (p.R + kBatch - 1) / kBatch;
+    const int steps = ((pieces + kWave - 1) / kWave) * n_batches;
+    // entry number e of the wavefront's rows, its row and its place j in that row's chunk
+    auto locate = [&](int t, bool& in, uint32_t& e, uint32_t& r, uint32_t& j) {
+        const int q = (t / n_batches) * kWave + lane;
+        in = q < pieces;
+        e = VEC * static_cast<uint32_t>(in ? q : 0);
+        if constexpr (VEC == 4) r = (k == 4) ? (e >> 2) : __umulhi(e, magic);
+        else r = (k == 1) ? e : __umulhi(e, magic);
+        j = e - r * static_cast<uint32_t>(k);
+    };
+    auto request = [&](int t, Piece (&b)[kBatch]) {
+        bool in;
+        uint32_t e, r, j;
+        locate(t, in, e, r, j);
+        const int r0 = (t % n_batches) * kBatch;
+        const int64_t word_byte = (chunk0 + r) * chunk_bytes + j / 4;
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            if (r0 + i < p.R && in) {
+                const int64_t rep = r0 + i;
+                b[i].load(idx, rep * idx_stride + entry0 + e, val,
+                          rep * val_stride + entry0 + e, rep * val_stride * 4 + word_byte);
+            } else {
+                b[i].clear();
+            }
+        }
+    };
+    auto apply = [&](int t, const Piece (&b)[kBatch]) {
+        bool in;
+        uint32_t e, r, j;
+        locate(t, in, e, r, j);
+        const int r0 = (t % n_batches) * kBatch;
+        const bool chunk_start = lane == 0 || j == 0u;
+        float* arow = rows + r * kRow;
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            if (r0 + i < p.R) {
+                uint32_t at[VEC];
+                float v[VEC];
+                b[i].get(j, at, v);
+                // (what an index outside the chunk, or a lane without a piece, adds goes to the
+                // row's padding; unsigned: a negative index is a large one)
+#pragma unroll
+                for (int c = 0; c < VEC; ++c)
+                    at[c] = in ? min(at[c], static_cast<uint32_t>(S)) : static_cast<uint32_t>(S);
+                // the previous lane's last index (a shift over the whole wavefront)
+                const uint32_t prev = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+                    0, static_cast<int>(at[VEC - 1]), 0x138, 0xf, 0xf, false));
+                bool asc = chunk_start || prev < at[0];
+#pragma unroll
+                for (int c = 1; c < VEC; ++c) asc = asc && at[c - 1] < at[c];
+                if (__any(in && !asc)) {
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) atomicAdd(&arow[at[c]], v[c]);
+                } else {
+                    float old[VEC];
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) old[c] = arow[at[c]];
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) arow[at[c]] = old[c] + v[c];
+                }
+                wave_lds_sync();
+            }
+        }
+    };
+    Piece b0[kBatch], b1[kBatch];
+    if (steps > 0) request(0, b0);
+    for (int t = 0; t < steps; t += 2) {
+        if (t + 1 < steps) request(t + 1, b1);
+        apply(t, b0);
+        if (t + 2 < steps) request(t + 2, b0);
+        if (t + 1 < steps) apply(t + 1, b1);
+    }
+}
+
+// Decompress-and-update half (transmitted indices, DCT domain) on full tiles of 64 chunks, W
+// wavefronts per workgroup; NARROW as in compress_split.
 //
 // Scatter-add: wavefront w owns the rows [64w/W, 64(w+1)/W) of the tile, so no two wavefronts
 // ever add into the same accumulator and, inside a wavefront, LDS operations complete in program
-// order: replica after replica, deterministic.  k a multiple of 4: 16-byte loads of four
-// consecutive entries of one chunk per lane, a batch of four replicas requested at a time and
-// the next batch before the current one is applied (two batches in flight per wavefront: the
-// wavefronts of a workgroup are in this phase together, so what each keeps in flight decides
-// how busy the memory is); a plain read-add-write when the four indices of every lane and the
-// step from the previous lane ascend strictly (what compress emits), LDS atomics otherwise
-// (duplicates add).
-// Other k: one entry per lane, LDS atomics.  Then every class gathers its coefficients from
+// order: replica after replica, deterministic.  Two batches of four replicas are in flight per
+// wavefront (the wavefronts of a workgroup are in this phase together, so what each keeps in
+// flight decides how busy the memory is).  Then every class gathers its coefficients from
 // the rows, the inverse transform runs as in compress_split, and all wavefronts stream the
 // parameters (and the moments of Decoupled AdamW) through the update.
-template <int S, int W, bool PARAM_BF16>
+template <int S, int W, bool PARAM_BF16, bool NARROW = false>
 __global__ __launch_bounds__(kWave * W) void decompress_split(
-    KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const int32_t* __restrict__ idx,
-    int64_t idx_stride, const float* __restrict__ val, int64_t val_stride,
+    KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ idx,
+    int64_t idx_stride, const void* __restrict__ val, int64_t val_stride,
     void* __restrict__ params, AdamPtrs ad, float* __restrict__ presign_dbg) {
     using G = SplitGeom<S, W>;
     constexpr int Q = G::Q, kRow = G::kRow, kThreads = G::kThreads, kTile = G::kTile;
@@ -728,7 +941,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
     // where they are used)
     constexpr int kPieces = Q / 4;                // 4-element pieces of the tile per thread
     uint2 early[kPieces];
-    const bool params_early = PARAM_BF16 && !partial && !p.adam;
+    const bool params_early = PARAM_BF16 && !partial && !p.adam && p.use_dct;
     if constexpr (PARAM_BF16) {
         if (params_early) {
 #pragma unroll
@@ -748,141 +961,73 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
 
     // ---- scatter-add of this wavefront's rows, replica after replica
     {
-        const int64_t entry0 = (tile * kWave + w * kRowsPerWave) * static_cast<int64_t>(k);
+        const int64_t row0 = tile * kWave + w * kRowsPerWave;
         float* rows = &buf[w * kRowsPerWave * kRow];
         const uint32_t magic = entry_magic(k);
-        if (k % 4 == 0) {
-            const int quads = my_rows * k / 4;             // 16-byte pieces per replica
-            constexpr int kBatch = 4;                      // replicas per batch
-            // A step = one batch of replicas for one group of 64 pieces.  The loads of the
-            // next step are requested before the current one is applied: two batches in
-            // flight per wavefront.
-            const int n_batches = (p.R + kBatch - 1) / kBatch;
-            const int steps = ((quads + kWave - 1) / kWave) * n_batches;
-            auto piece = [&](int t, uint32_t& e, bool& in) {
-                const int q = (t / n_batches) * kWave + lane;
-                in = q < quads;
-                e = 4u * static_cast<uint32_t>(in ? q : 0);
-            };
-            auto request = [&](int t, int4 (&iv)[kBatch], float4 (&vv)[kBatch]) {
-                uint32_t e;
-                bool in;
-                piece(t, e, in);
-                const int r0 = (t % n_batches) * kBatch;
-#pragma unroll
-                for (int b = 0; b < kBatch; ++b) {
-                    if (r0 + b < p.R && in) {
-                        const uint4 x = ld_u4<true>(idx + (r0 + b) * idx_stride + entry0 + e);
-                        iv[b] = make_int4(static_cast<int>(x.x), static_cast<int>(x.y),
-                                          static_cast<int>(x.z), static_cast<int>(x.w));
-                        vv[b] = ld_f4<true>(val + (r0 + b) * val_stride + entry0 + e);
-                    } else {
-                        iv[b] = make_int4(-1, -1, -1, -1);
-                        vv[b] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    }
-                }
-            };
-            auto apply = [&](int t, const int4 (&iv)[kBatch], const float4 (&vv)[kBatch]) {
-                uint32_t e;
-                bool in;
-                piece(t, e, in);
-                const int r0 = (t % n_batches) * kBatch;
-                const uint32_t r = (k == 4) ? (e >> 2) : __umulhi(e, magic);   // row of the wavefront
-                const bool chunk_start = (e - r * static_cast<uint32_t>(k)) == 0u;
-                float* arow = rows + r * kRow;
-#pragma unroll
-                for (int b = 0; b < kBatch; ++b) {
-                    if (r0 + b < p.R) {
-                        const int at[4] = {iv[b].x, iv[b].y, iv[b].z, iv[b].w};
-                        const float v[4] = {vv[b].x, vv[b].y, vv[b].z, vv[b].w};
-                        const int prev = __shfl_up(at[3], 1);
-                        const bool asc = at[0] < at[1] && at[1] < at[2] && at[2] < at[3] &&
-                                         (lane == 0 || chunk_start || prev < at[0]);
-                        if (__any(in && !asc)) {
-#pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                if (static_cast<uint32_t>(at[c]) < static_cast<uint32_t>(S))
-                                    atomicAdd(&arow[at[c]], v[c]);
-                        } else {
-                            float old[4];
-#pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                old[c] = (static_cast<uint32_t>(at[c]) < static_cast<uint32_t>(S))
-                                             ? arow[at[c]] : 0.0f;
-#pragma unroll
-                            for (int c = 0; c < 4; ++c)
-                                if (static_cast<uint32_t>(at[c]) < static_cast<uint32_t>(S))
-                                    arow[at[c]] = old[c] + v[c];
-                        }
-                        wave_lds_sync();
-                    }
-                }
-            };
-            int4 iv0[kBatch], iv1[kBatch];
-            float4 vv0[kBatch], vv1[kBatch];
-            if (steps > 0) request(0, iv0, vv0);
-            for (int t = 0; t < steps; t += 2) {
-                if (t + 1 < steps) request(t + 1, iv1, vv1);
-                apply(t, iv0, vv0);
-                if (t + 2 < steps) request(t + 2, iv0, vv0);
-                if (t + 1 < steps) apply(t + 1, iv1, vv1);
-            }
+        // (the format is settled once, out here: a branch on it at every piece would cut the
+        // loads and the additions of a batch apart)
+        auto scatter = [&](auto val_tag, auto u8_tag) {
+            constexpr int VAL = decltype(val_tag)::value;
+            constexpr bool U8 = decltype(u8_tag)::value;
+            if (k % 4 == 0)
+                split_scatter<S, 4, VAL, U8>(p, lane, rows, my_rows, idx, idx_stride, val,
+                                             val_stride, row0 * k, row0, magic);
+            else
+                split_scatter<S, 1, VAL, U8>(p, lane, rows, my_rows, idx, idx_stride, val,
+                                             val_stride, row0 * k, row0, magic);
+        };
+        using std::integral_constant;
+        if constexpr (!NARROW) {
+            scatter(integral_constant<int, 0>{}, std::false_type{});
         } else {
-            // one entry per lane, LDS atomics; four groups of 64 entries requested together
-            const int entries = my_rows * k;
-            constexpr int kGroups = 4;
-            for (int r = 0; r < p.R; ++r) {
-                const int32_t* ir = idx + r * idx_stride + entry0;
-                const float* vr = val + r * val_stride + entry0;
-                for (int e0 = 0; e0 < entries; e0 += kGroups * kWave) {
-                    int at[kGroups];
-                    float v[kGroups];
-#pragma unroll
-                    for (int g = 0; g < kGroups; ++g) {
-                        const int e = e0 + g * kWave + lane;
-                        at[g] = -1;
-                        v[g] = 0.0f;
-                        if (e < entries) {
-                            at[g] = ir[e];
-                            v[g] = vr[e];
-                        }
-                    }
-#pragma unroll
-                    for (int g = 0; g < kGroups; ++g) {
-                        const int e = e0 + g * kWave + lane;
-                        const uint32_t rr = (k == 1) ? static_cast<uint32_t>(e)
-                                                     : __umulhi(static_cast<uint32_t>(e), magic);
-                        if (e < entries && static_cast<uint32_t>(at[g]) < static_cast<uint32_t>(S))
-                            atomicAdd(&rows[rr * kRow + at[g]], v[g]);
-                    }
-                }
-            }
+            auto by_value = [&](auto u8_tag) {
+                if (p.val_dtype == 1) scatter(integral_constant<int, 1>{}, u8_tag);
+                else if (p.val_dtype == 2) scatter(integral_constant<int, 2>{}, u8_tag);
+                else if (p.val_dtype == 3) scatter(integral_constant<int, 3>{}, u8_tag);
+                else scatter(integral_constant<int, 0>{}, u8_tag);
+            };
+            if (p.idx_u8) by_value(std::true_type{});
+            else by_value(std::false_type{});
         }
     }
     __syncthreads();
 
-    // ---- the lane's class of the averaged coefficients: a[W*m + off] * alpha_j / R
-    const int off = split_off<W>(w);
-    const float scale = p.alpha * p.inv_R;
-    float c[Q];
-    {
+    // ---- the lane's class of the averaged coefficients: a[W*m + off] * alpha_j / R, and back
+    // (raw domain: the rows hold the sums themselves)
+    if (p.use_dct) {
+        const int off = split_off<W>(w);
+        const float scale = p.alpha * p.inv_R;
+        float c[Q];
         const float* src = row + off;
 #pragma unroll
         for (int m = 0; m < Q; ++m) c[m] = src[W * m] * scale;
         if (w == 0) c[0] = row[0] * (p.alpha0 * p.inv_R);
+        __syncthreads();
+        split_inverse_to_rows<S, W>(row, w, c);
     }
-    __syncthreads();
-    split_inverse_to_rows<S, W>(row, w, c);
+    // (the domain is settled outside the update loops: a branch in every piece would cut their
+    // loads apart)
+    auto output4 = [&](int e4, auto raw_tag) -> float4 {
+        const int r = e4 / S, col = e4 - r * S;
+        if constexpr (decltype(raw_tag)::value) {
+            const float4 a = *reinterpret_cast<const float4*>(&buf[r * kRow + col]);
+            return make_float4(a.x * p.inv_R, a.y * p.inv_R, a.z * p.inv_R, a.w * p.inv_R);
+        } else {
+            return split_output<S, W>(&buf[r * kRow], col);
+        }
+    };
 
     // ---- y out of the rows, optional sign, parameter update, coalesced; the parameters (and
     // moments) of a batch of iterations are requested before the first is used
     {
         constexpr int kIt = Q / 4;                // 16-byte pieces per thread
-        constexpr int kBatch = (kIt % 8 == 0) ? 8 : 4;
+        // (fewer at a time where the LDS leaves room for more than two wavefronts per SIMD: eight
+        // pieces of parameters and moments would hold over 200 registers)
+        constexpr int kBatch = Q >= 64 ? 8 : (kIt % 4 == 0 ? 4 : (kIt % 3 == 0 ? 3 : 2));
         static_assert(kIt % kBatch == 0, "whole batches");
         // (full tiles run the code without the checks against the end of the shard: with them
         // the loads of a batch are no longer issued together)
-        auto update = [&](auto guarded_tag) {
+        auto update = [&](auto guarded_tag, auto raw_tag) {
         constexpr bool kGuarded = decltype(guarded_tag)::value;
 #pragma unroll 1
         for (int b0 = 0; b0 < kIt; b0 += kBatch) {
@@ -913,12 +1058,11 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const int e4 = 4 * (tid + kThreads * (b0 + j));
-                const int r = e4 / S, col = e4 - r * S;
                 const int64_t i = base + e4;
                 if (kGuarded && i + 3 >= n) {
                     // the piece that straddles the end of the shard: element by element
                     if (i < n) {
-                        const float4 y4 = split_output<S, W>(&buf[r * kRow], col);
+                        const float4 y4 = output4(e4, raw_tag);
                         const float yv[4] = {y4.x, y4.y, y4.z, y4.w};
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
@@ -944,7 +1088,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                     }
                     continue;
                 }
-                const float4 y4 = split_output<S, W>(&buf[r * kRow], col);
+                const float4 y4 = output4(e4, raw_tag);
                 if (presign_dbg) st_f4<false>(presign_dbg + i, y4);
                 const float y[4] = {y4.x, y4.y, y4.z, y4.w};
                 const float old[4] = {old4[j].x, old4[j].y, old4[j].z, old4[j].w};
@@ -968,7 +1112,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                     uint2 o;
                     o.x = pack_bf16x2(nw[0], nw[1]);
                     o.y = pack_bf16x2(nw[2], nw[3]);
-                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(params) + i) = o;
+                    st_u2<true>(static_cast<uint16_t*>(params) + i, o);
                 } else {
                     st_f4<true>(static_cast<float*>(params) + i,
                                 make_float4(nw[0], nw[1], nw[2], nw[3]));
@@ -980,9 +1124,8 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
 #pragma unroll
             for (int it = 0; it < kPieces; ++it) {
                 const int e4 = 4 * (tid + kThreads * it);
-                const int r = e4 / S, col = e4 - r * S;
                 const int64_t i = base + e4;
-                const float4 y4 = split_output<S, W>(&buf[r * kRow], col);
+                const float4 y4 = output4(e4, std::false_type{});
                 if (presign_dbg) st_f4<false>(presign_dbg + i, y4);
                 const float y[4] = {y4.x, y4.y, y4.z, y4.w};
                 const float old[4] = {__uint_as_float(early[it].x << 16),
@@ -996,12 +1139,14 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 uint2 o;
                 o.x = pack_bf16x2(nw[0], nw[1]);
                 o.y = pack_bf16x2(nw[2], nw[3]);
-                *reinterpret_cast<uint2*>(static_cast<uint16_t*>(params) + i) = o;
+                st_u2<true>(static_cast<uint16_t*>(params) + i, o);
             }
+        } else if (!p.use_dct) {
+            update(std::true_type{}, std::true_type{});
         } else if (partial) {
-            update(std::true_type{});
+            update(std::true_type{}, std::false_type{});
         } else {
-            update(std::false_type{});
+            update(std::false_type{}, std::false_type{});
         }
     }
 }

@@ -1,8 +1,7 @@
-// Decompress with Decoupled AdamW as the underlying optimizer for the narrow payloads (byte
-// indices with bf16 / fp16 values or two-bit signs; or no indices at all under Striding /
-// Random).  Chunk size 32 at the rates 1/2 ... 1/32 -- the paper's experiments synchronise only
-// signs at chunk size 32 ("Overall Setup") and run Decoupled AdamW on top -- and chunk size 64
-// at rates 1/2 and 1/4.
+// Decompress with Decoupled AdamW as the underlying optimizer for the narrow payloads without
+// transmitted indices (Striding / Random; bf16 / fp16 values or two-bit signs).  Chunk size 32
+// at the rates 1/2 ... 1/32 -- the paper's experiments synchronise only signs at chunk size 32
+// ("Overall Setup") and run Decoupled AdamW on top -- and chunk size 64 at rates 1/2 and 1/4.
 #include "tiled_kernels.hip.h"
 #include "tiled_launch.h"
 
@@ -17,20 +16,6 @@ namespace deto {
 namespace {
 
 template <int S, int K, int V>
-void indexed(const DecompressLaunch& a) {
-    const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
-    const TailRange tail{a.n, a.n_chunks};
-    if (a.param_bf16)
-        decompress_tiled<S, K, true, V, true><<<grid, kWave, 0, a.stream>>>(
-            a.p, a.tiles, tail, a.idx, a.idx_stride, a.val, a.val_stride, a.params, a.adam,
-            a.presign_dbg);
-    else
-        decompress_tiled<S, K, false, V, true><<<grid, kWave, 0, a.stream>>>(
-            a.p, a.tiles, tail, a.idx, a.idx_stride, a.val, a.val_stride, a.params, a.adam,
-            a.presign_dbg);
-}
-
-template <int S, int K, int V>
 void values_only(const DecompressLaunch& a) {
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
@@ -43,22 +28,15 @@ void values_only(const DecompressLaunch& a) {
             a.p, mw, a.tiles, tail, a.val, a.val_stride, a.params, a.adam, a.presign_dbg);
 }
 
-template <int S, int K, int V>
-void one(const DecompressLaunch& a) {
-    if (a.idx) indexed<S, K, V>(a);
-    else values_only<S, K, V>(a);
-}
-
 }  // namespace
 
 bool launch_decompress_adamw_narrow(const DecompressLaunch& a) {
-    if (!a.p.adam || a.p.val_dtype < 1 || a.p.val_dtype > 3 || (a.idx && !a.p.idx_u8))
-        return false;
+    if (!a.p.adam || a.idx || a.p.val_dtype < 1 || a.p.val_dtype > 3) return false;
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \
-        if (a.p.val_dtype == 1) one<S, K, 1>(a);                                                \
-        else if (a.p.val_dtype == 2) one<S, K, 2>(a);                                           \
-        else one<S, K, 3>(a);                                                                   \
+        if (a.p.val_dtype == 1) values_only<S, K, 1>(a);                                        \
+        else if (a.p.val_dtype == 2) values_only<S, K, 2>(a);                                   \
+        else values_only<S, K, 3>(a);                                                           \
         return true;                                                                            \
     }
     DETO_ADAMW_NARROW_LIST(X)

@@ -894,7 +894,7 @@ __device__ __forceinline__ float decode_entry(uint32_t raw, int j) {
 // caller passes indices).  Several replicas' payloads (two to eight, by k) are in flight while
 // one is scattered into LDS; LDS operations of one wavefront complete in order, so the additions
 // into one accumulator happen replica after replica and the result does not depend on timing.
-template <int S, int K, bool PARAM_BF16, int VAL = 0, bool ADAM = false>
+template <int S, int K, bool PARAM_BF16, int VAL = 0>
 __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_tiled(
     KParams p, int64_t n_tiles, TailRange tail, const void* __restrict__ idx_v,
     int64_t idx_stride, const void* __restrict__ val_v, int64_t val_stride,
@@ -1002,8 +1002,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
     row_to_regs<S>(row, y);
     finish_chunk<S>(p, y, row, presign_dbg, ebase, lane);
     wave_lds_sync();
-    if constexpr (ADAM) update_params_adamw_from_tile<S, PARAM_BF16>(p, tile, th, params, ad, ebase, lane);
-    else update_params_from_tile<S, PARAM_BF16>(p, tile, th, params, ebase, lane);
+    update_params_from_tile<S, PARAM_BF16>(p, tile, th, params, ebase, lane);
 }
 
 // Decompress-and-update half for Striding and Random without transmitted indices: every

@@ -78,9 +78,9 @@ bool launch_compress_topk_packed_s32(const CompressLaunch& a);
 bool launch_decompress_idx_packed_s32(const DecompressLaunch& a);
 bool launch_compress_topk_ternary(const CompressLaunch& a);    // byte indices + two-bit signs
 bool launch_decompress_idx_ternary(const DecompressLaunch& a);
-bool launch_decompress_adamw(const DecompressLaunch& a);       // Decoupled AdamW update
-bool launch_decompress_adamw_narrow(const DecompressLaunch& a);   // ... narrow payloads, with or without indices
-bool launch_decompress_scheme_adamw(const DecompressLaunch& a);   // ... without transmitted indices
+// Decoupled AdamW without transmitted indices (with them: launch_decompress_split)
+bool launch_decompress_scheme_adamw(const DecompressLaunch& a);
+bool launch_decompress_adamw_narrow(const DecompressLaunch& a);   // ... narrow payloads
 bool launch_compress_scheme_narrow_s32(const CompressLaunch& a);   // Striding / Random, narrow payload
 bool launch_decompress_scheme_narrow_s32(const DecompressLaunch& a);
 bool launch_compress_scheme_narrow_s64(const CompressLaunch& a);
@@ -92,10 +92,14 @@ bool launch_decompress_scheme_small(const DecompressLaunch& a);
 
 // Matrix-core kernels: tiles of 32 complete chunks, persistent single-wavefront workgroups.
 // A launcher returns the number of leading chunks it has taken (0: no kernel for this request).
+// NB = chunk size / 32.  What nothing else takes: compress at 160, 224, and at 32, 64 with
+// k > s/2; decompress at 160, 224.
 #ifdef DETO_TILED_ONLY_64_32
-#define DETO_MFMA_NB_LIST(X) X(4)
+#define DETO_MFMA_COMPRESS_LIST(X) X(2)
+#define DETO_MFMA_DECOMPRESS_LIST(X) X(5)
 #else
-#define DETO_MFMA_NB_LIST(X) X(1) X(2) X(3) X(4) X(5) X(7)   // 6 and 8: two-lanes-per-chunk kernels
+#define DETO_MFMA_COMPRESS_LIST(X) X(1) X(2) X(5) X(7)
+#define DETO_MFMA_DECOMPRESS_LIST(X) X(5) X(7)
 #endif
 
 inline unsigned mfma_grid(int64_t tiles, size_t smem_bytes) {
@@ -109,11 +113,6 @@ int64_t launch_decompress_mfma(const DecompressLaunch& a);
 
 // Two-lanes-per-chunk kernels (register-resident fast DCT split between lanes t and t+32): the
 // chunk sizes that do not fit one lane.  Same tiles and return convention.
-#ifdef DETO_TILED_ONLY_64_32
-#define DETO_PAIR_S_LIST(X)
-#else
-#define DETO_PAIR_S_LIST(X) X(192) X(256)
-#endif
 int64_t launch_compress_pair_96(const CompressLaunch& a);    // one translation unit each:
 int64_t launch_compress_pair_128(const CompressLaunch& a);   // the longest compiles
 int64_t launch_compress_pair_192(const CompressLaunch& a);
@@ -124,22 +123,83 @@ inline int64_t launch_compress_pair(const CompressLaunch& a) {
     if (!c) c = launch_compress_pair_192(a);
     return c ? c : launch_compress_pair_256(a);
 }
-int64_t launch_decompress_pair(const DecompressLaunch& a);
 
 // Lane per chunk, wavefront per coefficient class (split_kernels.hip.h): tiles of 64 chunks,
-// fp32 + int32 payloads with k <= s/2.  Same return convention.
-int64_t launch_decompress_split(const DecompressLaunch& a);      // chunk 192, 256; 64, 96, 128 at other k
+// k <= s/2 in the compress half.  Same return convention.
+int64_t launch_decompress_split(const DecompressLaunch& a, int classes);        // fp32 + int32
+int64_t launch_decompress_split_narrow(const DecompressLaunch& a, int classes); // other formats
+// 16-bit values, or byte indices:
+int64_t launch_compress_split_narrow_96(const CompressLaunch& a);
+int64_t launch_compress_split_narrow_128(const CompressLaunch& a);
+int64_t launch_compress_split_narrow_192(const CompressLaunch& a);
+int64_t launch_compress_split_narrow_256(const CompressLaunch& a);
 // chunk 64 on a small shard only (see small_shard_tiles); tried before the lane-per-chunk kernel
 int64_t launch_compress_split_64(const CompressLaunch& a);
 int64_t launch_compress_split_96(const CompressLaunch& a);
 int64_t launch_compress_split_128(const CompressLaunch& a);
 int64_t launch_compress_split_192(const CompressLaunch& a);
 int64_t launch_compress_split_256(const CompressLaunch& a);
+
+// Which decompress kernel serves transmitted indices: the number of coefficient classes
+// (wavefronts per tile) of the wavefront-per-class kernels, or 0 for a lane per chunk; `lane`:
+// the latter may be chosen (it is instantiated for some (s, k, format) only, without AdamW).
+//
+// A lane per chunk needs the fewest instructions but holds a whole chunk in registers: two
+// wavefronts per SIMD at chunk 64, one at 96 and 128, each with little in flight.  Two classes
+// cost about a third more instructions at twice the wavefronts, four classes half more again
+// at up to seven per SIMD.  So what decides is whether a shape is bound by memory latency (many
+// bytes per element: AdamW's moments, fp32 parameters, fp32 + int32 payloads) or by
+// instructions (few bytes, or many entries per byte: two-bit signs).  Measured on MI355X, us,
+// buffers rotating, a lane per chunk / two / four classes; A: 147 M bf16 parameters, R = 4;
+// B: 28 M and C: 11 M fp32 parameters, R = 2; D: 28 M bf16 parameters, R = 2:
+//   chunk 64, k 32, fp32 + int32, SGD   A 521/513/510  B  79/ 75/ 73  C 34/33/32  D 59/64/58
+//             k 16                      A 300/296/282  B  60/ 57/ 56  C 26/26/25  D 40/46/43
+//             k 8                       A 194/187/223  B  52/ 49/ 49  C 23/23/23  D 30/35/41
+//             k 4                       A 141/159/208  B  49/ 46/ 47  C 22/22/22  D 26/34/40
+//             k 16, fp16 + byte         A 169/200/224  B  52/ 49/ 50  C 22/24/24  D 29/41/42
+//             k 16, signs, AdamW        A 601/552/515  B 145/129/123  C 61/54/51  D  - /108/100
+//   chunk 32, k 16, fp32 + int32, SGD   A 508/498/494  B  75/ 72/ 73  C 33/31/30  D 57/57/56
+//             k 4, signs, SGD           A 113/194/259  B  47/ 43/ 51  C 21/20/24
+//             k 16, signs, AdamW        A 625/544/535  B 141/122/120  C 60/52/50  D  - /102/ 99
+//   chunk 128, k 16, fp32 + int32, SGD  A 205/209/214  B  57/ 55/ 52  C 29/30/26  D 44/44/42
+//             k 64, fp16 + byte         A  - /373/328  B  - / 79/ 69  C  - /42/33  D  - /67/60
+// Two classes also stay ahead of four where there are many entries per chunk to scatter with
+// little else to move (AdamW, chunk 32, k 4, signs, R = 16: 142 against 152 us).
+constexpr int64_t kLargeShard = int64_t{1} << 25;   // elements: D's order turns between D and A
+inline int decompress_classes(const KParams& p, int64_t n, bool param_bf16, bool lane) {
+    const int64_t rk = static_cast<int64_t>(p.R) * p.k;    // entries per chunk to scatter
+    const bool plain = p.val_dtype == 0 && !p.idx_u8, quads = p.k % 4 == 0;
+    const bool large = n > kLargeShard;
+    if (p.s == 192 || p.s == 256) return 4;
+    if (p.s != 16 && p.s != 32 && p.s != 64 && p.s != 96 && p.s != 128) return 0;
+    if (p.s == 16) return (lane && !p.adam && param_bf16) ? 0 : 2;
+    if (p.adam) return (quads ? (plain || rk <= p.s) : 4 * rk <= p.s) ? 4 : 2;
+    if (p.s >= 96) {
+        if (!param_bf16) return 4;
+        if (p.s == 128 && (rk >= p.s || !large)) return 4;
+        return lane ? 0 : (large ? 2 : 4);
+    }
+    bool split = false, wide = false;
+    if (!param_bf16) {
+        split = plain ? !(p.k == 1 && 2 * rk >= p.s) : rk <= (quads ? 16 : 8);
+        wide = p.s == 64 && plain && 2 * rk >= p.s;
+    } else if (large && plain && quads && p.R >= 2) {
+        wide = rk >= p.s;
+        split = wide || (p.s == 64 && 2 * rk >= p.s);
+    }
+    if (split) return wide ? 4 : 2;
+    return lane ? 0 : 2;
+}
+
 inline int64_t launch_compress_split(const CompressLaunch& a) {
     int64_t c = launch_compress_split_96(a);
     if (!c) c = launch_compress_split_128(a);
     if (!c) c = launch_compress_split_192(a);
-    return c ? c : launch_compress_split_256(a);
+    if (!c) c = launch_compress_split_256(a);
+    if (!c) c = launch_compress_split_narrow_96(a);
+    if (!c) c = launch_compress_split_narrow_128(a);
+    if (!c) c = launch_compress_split_narrow_192(a);
+    return c ? c : launch_compress_split_narrow_256(a);
 }
 
 }  // namespace deto

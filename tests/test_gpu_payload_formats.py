@@ -1,0 +1,151 @@
+"""Every payload format (fp32, bf16, fp16 or two-bit signs; int32 or byte indices) at the chunk
+sizes and k values that share run-time kernels, both halves against the oracle: full tiles, a
+partial tile, a ragged last chunk, tied chunks, more replicas than one batch of loads."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import Config
+from tests import parity
+from tests.test_gpu_parity import H, make_inputs  # noqa: F401  (H: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+FORMATS = {"bf16+u8": (oracle.BF16, True), "f16+i32": (oracle.F16, False),
+           "signs+u8": (oracle.TERNARY, True), "signs+i32": (oracle.TERNARY, False),
+           "f32+u8": (oracle.F32, True)}
+
+
+def with_ties(g, m, s):
+    """Zero chunks, and chunks of equal magnitudes, among the ordinary ones."""
+    g, m = g.copy(), m.copy()
+    C = g.size // s
+    for c in range(0, C, 5):
+        g[c * s:(c + 1) * s] = 0
+        m[c * s:(c + 1) * s] = 0
+        if c % 2:
+            m[c * s + (7 * c) % s] = 1.0 + c
+    return g, m
+
+
+def device_payload(H, val, val_dtype, idx, idx_u8):
+    import torch
+    i = None
+    if idx is not None:
+        i = torch.from_numpy(np.ascontiguousarray(idx.astype(np.uint8 if idx_u8 else np.int32))).to(H.DEV)
+    if val_dtype == oracle.TERNARY:
+        return i, torch.from_numpy(np.ascontiguousarray(val).view(np.int32)).to(H.DEV)
+    if val_dtype == oracle.F32:
+        return i, torch.from_numpy(np.ascontiguousarray(val)).to(H.DEV)
+    return i, H.bits16_to_dev(np.ascontiguousarray(val), val_dtype)
+
+
+def compress_case(H, cfg, g, m, val_dtype, idx_u8):
+    import torch
+    from paper_2502_06728_amd import binding
+    n, s, k = m.size, cfg.chunk, cfg.topk
+    C = -(-n // s)
+    if val_dtype == oracle.TERNARY:
+        m_gpu, idx, words, coeff = H.gpu_compress_ternary(cfg, g, m, idx_u8)
+        kept = coeff.reshape(C, s)[np.arange(C)[:, None], idx.reshape(C, k)].reshape(-1)
+        parity.check_compress(cfg, g, m, m_gpu, idx, kept, coeff)
+        assert np.array_equal(words, oracle.encode_ternary(cfg, n, kept))
+    elif val_dtype == oracle.F32:
+        gm = H.to_dev(m)
+        idx = torch.zeros(C * k, dtype=torch.uint8 if idx_u8 else torch.int32, device=H.DEV)
+        val = torch.zeros(C * k, dtype=torch.float32, device=H.DEV)
+        coeff = torch.zeros(C * s, dtype=torch.float32, device=H.DEV)
+        binding.detonation_compress_packed(H.bcfg(cfg), H.to_dev(g), gm, idx, val, coeff)
+        torch.cuda.synchronize()
+        parity.check_compress(cfg, g, m, H.to_host(gm), idx.cpu().numpy().astype(np.int32),
+                              H.to_host(val), H.to_host(coeff))
+    else:
+        m_gpu, idx, vbits, coeff = H.gpu_compress_packed(cfg, g, m, val_dtype, idx_u8)
+        parity.check_compress_packed(cfg, g, m, m_gpu, idx, vbits, coeff, val_dtype)
+
+
+def oracle_payloads(cfg, n, val_dtype, R, seed):
+    """R replicas' (idx [R, C*k], val, the values the receivers decode)."""
+    f = {oracle.TERNARY: oracle.compress_t, oracle.F32: oracle.compress}.get(
+        val_dtype, lambda c, g, m: oracle.compress_q(c, g, m, val_dtype))
+    pays = [f(cfg, *make_inputs(n, seed=seed + r)[:2])[1:] for r in range(R)]
+    return np.stack([p[0] for p in pays]), np.stack([p[1] for p in pays])
+
+
+def check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=None):
+    """Decompress on the device and judge it by the oracle on the same payload bytes."""
+    import torch
+    from paper_2502_06728_amd import binding
+    n, s, R = th.size, cfg.chunk, val.shape[0]
+    send = cfg.scheme == oracle.SCHEME_TOPK
+    i, v = device_payload(H, val, val_dtype, idx if send else None, idx_u8)
+    p = H.to_dev(th)
+    y = torch.full((n,), float("nan"), dtype=torch.float32, device=H.DEV)
+    if adam is None:
+        binding.detonation_decompress_step_packed(H.bcfg(cfg), R, i, v, p, y)
+        torch.cuda.synchronize()
+        if val_dtype == oracle.TERNARY:
+            val = np.stack([oracle.decode_ternary(cfg, n, w) for w in val])
+        if val_dtype in (oracle.TERNARY, oracle.F32):
+            parity.check_decompress(cfg, idx, val, th, H.to_host(p), H.to_host(y))
+        else:
+            parity.check_decompress_packed(cfg, idx, val, val_dtype, th, H.to_host(p), H.to_host(y))
+        return
+    rng = np.random.default_rng(n)
+    m0 = rng.standard_normal(n).astype(np.float32)
+    v0 = (rng.random(n) + 0.1).astype(np.float32)
+    ma, va, vm = H.to_dev(m0), H.to_dev(v0), H.to_dev(v0)
+    opt = binding.AdamW(0.9, 0.95, 1e-8, adam, 3)
+    binding.detonation_decompress_adamw_step_packed(H.bcfg(cfg), opt, R, i, v, p, ma, va,
+                                                    vm if adam else None, y)
+    torch.cuda.synchronize()
+    # Q as the device computed it (its own test is the plain update above) drives the oracle
+    th_o, m_o, v_o, vm_o = oracle.adamw_update(cfg, oracle.AdamW(0.9, 0.95, 1e-8, adam, 3),
+                                               H.to_host(y), th, m0, v0, v0)
+    assert np.abs(H.to_host(ma) - m_o).max() <= 1e-5 * np.abs(m_o).max()
+    assert np.abs(H.to_host(va) - v_o).max() <= 1e-5 * np.abs(v_o).max()
+    if adam:
+        assert np.abs(H.to_host(vm) - vm_o).max() <= 1e-5 * np.abs(vm_o).max()
+    got, want, tol = H.to_host(p), th_o, parity.TOL_F32
+    if th.dtype == np.uint16:
+        from paper_2502_06728_amd import synth
+        got, want, tol = synth.from_bf16_bits(got), synth.from_bf16_bits(th_o), parity.TOL_BF16
+    got, want = got.astype(np.float64), want.astype(np.float64)
+    assert (np.abs(got - want) <= tol * np.abs(want) + tol * cfg.lr).all()
+
+
+TOPK_SHAPES = [(16, 1), (16, 2), (16, 3), (16, 8), (32, 1), (32, 3), (32, 12), (64, 1), (64, 2), (64, 5), (64, 20), (96, 3), (96, 20), (96, 48), (128, 7), (128, 16),
+               (128, 64), (192, 6), (192, 24), (192, 33), (192, 96), (256, 8), (256, 32), (256, 33),
+               (256, 128)]
+
+
+@pytest.mark.parametrize("fmt", list(FORMATS))
+@pytest.mark.parametrize("s,k", TOPK_SHAPES)
+def test_topk(H, s, k, fmt):
+    val_dtype, idx_u8 = FORMATS[fmt]
+    bf16 = k % 2 == 0
+    # two full tiles, then a partial one of 37 chunks and a ragged one
+    n = s * (64 * 2 + 37) + s // 3
+    cfg = Config(chunk=s, topk=k, sign=True, lr=1e-3, weight_decay=0.01)
+    g, m, th = make_inputs(n, seed=s + k, params_bf16=bf16)
+    compress_case(H, cfg, *with_ties(g, m, s), val_dtype, idx_u8)
+    idx, val = oracle_payloads(cfg, n, val_dtype, 6, 700)
+    check_update(H, cfg, idx, val, val_dtype, idx_u8, th)
+    check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=bool(k % 3 == 0))
+
+
+@pytest.mark.parametrize("fmt", ["bf16+u8", "signs+i32", "f32+u8"])
+@pytest.mark.parametrize("s,k", [(16, 4), (32, 5), (64, 5), (96, 12), (128, 3), (192, 24), (256, 10)])
+def test_unordered_payloads(H, s, k, fmt):
+    """Duplicates and disorder add like the scatter-add they are; indices past the chunk are skipped."""
+    val_dtype, idx_u8 = FORMATS[fmt]
+    n = s * (64 + 9)
+    C, R = n // s, 3
+    cfg = Config(chunk=s, topk=k, sign=False)
+    rng = np.random.default_rng(s * k)
+    top = min(s + 3, 256)
+    idx = np.stack([np.sort(rng.integers(0, s, size=(C, k)), axis=1).reshape(-1),     # repeats
+                    rng.integers(0, top, size=C * k),                                  # anything
+                    np.tile(np.arange(k), C)]).astype(np.int32)
+    val = oracle_payloads(cfg, n, val_dtype, R, 40)[1]
+    check_update(H, cfg, idx, val, val_dtype, idx_u8, make_inputs(n, 3)[2])
