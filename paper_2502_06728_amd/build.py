@@ -26,6 +26,7 @@ UNITS = [
     "split_narrow_256.hip", "split_narrow_192.hip", "split_narrow_128.hip",
     "split_compress_96.hip", "split_compress_64.hip", "split_narrow_96.hip",
     "split_decompress.hip", "split_decompress_narrow.hip",
+    "split_scheme_compress.hip", "split_scheme_decompress.hip",
     # two lanes per chunk (chunk 96, 128, 192, 256)
     "pair_compress_256.hip", "pair_compress_192.hip", "pair_compress_128.hip",
     "pair_compress_96.hip",
@@ -33,9 +34,9 @@ UNITS = [
     "tiled_topk_s96.hip", "tiled_topk_s128.hip",
     # matrix-core kernels (every other multiple of 32)
     "mfma_compress.hip", "mfma_decompress.hip",
-    # lane per chunk: narrow payloads, Decoupled AdamW, Striding / Random
+    # lane per chunk: narrow payloads, Striding / Random
     "tiled_topk_packed.hip", "tiled_topk_packed_s32.hip", "tiled_topk_ternary.hip",
-    "tiled_adamw.hip", "tiled_adamw_narrow.hip", "tiled_scheme.hip", "tiled_scheme_small.hip",
+    "tiled_scheme.hip", "tiled_scheme_small.hip",
     "tiled_scheme_narrow_s32.hip", "tiled_scheme_narrow_s64.hip",
     "tiled_topk_s64.hip", "tiled_topk_s32.hip", "tiled_topk_s16.hip",
     # validation, dispatch, general kernels

@@ -170,6 +170,10 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
         return launched();
     }
 
+    // Striding in the raw domain with the plain payload does not look at the values: a plain
+    // streaming kernel serves any chunk size and k without a lane-per-chunk kernel
+    const bool stride_stream = p.scheme == DETO_SCHEME_STRIDE && !p.use_dct &&
+                               val_dtype == DETO_F32 && idx_dtype == DETO_IDX_I32;
     // a tiled kernel if one exists (full 64-chunk tiles plus, in the same launch, the tail
     // chunks on the general code), else the general kernel for everything
     int64_t c0 = 0;
@@ -204,6 +208,7 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
             // per chunk (other formats), anything else on the matrix-core kernel, which takes
             // the leading multiple of 32 chunks
             c0 = deto::launch_compress_split(a);
+            if (c0 == 0 && !stride_stream) c0 = deto::launch_compress_split_scheme(a);
             if (c0 == 0) c0 = deto::launch_compress_pair(a);
             if (c0 == 0) c0 = deto::launch_compress_mfma(a);
             if (c0 > 0) {
@@ -212,10 +217,7 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
             }
         }
     }
-    // Striding in the raw domain at a shape without a lane-per-chunk kernel: it does not look
-    // at the values, so a plain streaming kernel serves any chunk size and k
-    if (c0 == 0 && p.scheme == DETO_SCHEME_STRIDE && !p.use_dct && val_dtype == DETO_F32 &&
-        idx_dtype == DETO_IDX_I32) {
+    if (c0 == 0 && stride_stream) {
         const deto::StrideGeom sg = deto::stride_geom(p.s, p.k, p.step);
         const int64_t padded = C * p.s;
         const int64_t wgs = (padded + deto::kStrideSpan - 1) / deto::kStrideSpan;
@@ -328,6 +330,10 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         return launched();
     }
 
+    // Striding in the raw domain without transmitted indices: a plain streaming kernel at any chunk
+    // size and k without a lane-per-chunk kernel
+    const bool stride_stream =
+        !idx && p.scheme == DETO_SCHEME_STRIDE && !p.use_dct && val_dtype == DETO_F32;
     int64_t c0 = 0;
     const int64_t tiles = (n / p.s) / deto::kWave;
     // every replica's array must keep the alignment of a lane's access (four entries when k is
@@ -350,8 +356,14 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
             const int64_t c = deto::launch_decompress_split(d, classes);
             return c ? c : deto::launch_decompress_split_narrow(d, classes);
         };
-        // transmitted indices: a lane per chunk or a wavefront per coefficient class
-        if (idx) c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, true));
+        auto split_scheme = [](const deto::DecompressLaunch& d, int classes) -> int64_t {
+            return classes ? deto::launch_decompress_split_scheme(d, classes) : 0;
+        };
+        // a lane per chunk or a wavefront per coefficient class
+        if (idx)
+            c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, true));
+        else if (!stride_stream)
+            c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, true));
         const bool done = (c0 > 0 || tiles == 0) ? false
                           : idx ? (deto::launch_decompress_idx_s64(a) ||
                                  deto::launch_decompress_idx_s32(a) ||
@@ -361,9 +373,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
                                  deto::launch_decompress_idx_packed(a) ||
                                  deto::launch_decompress_idx_packed_s32(a) ||
                                  deto::launch_decompress_idx_ternary(a))
-                              : (deto::launch_decompress_scheme_adamw(a) ||
-                                 deto::launch_decompress_adamw_narrow(a) ||
-                                 deto::launch_decompress_scheme(a) ||
+                              : (deto::launch_decompress_scheme(a) ||
                                  deto::launch_decompress_scheme_small(a) ||
                                  deto::launch_decompress_scheme_narrow_s32(a) ||
                                  deto::launch_decompress_scheme_narrow_s64(a));
@@ -375,6 +385,8 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
             // no lane-per-chunk kernel for this (s, k, format)
             if (c0 == 0 && idx)
                 c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, false));
+            if (c0 == 0 && !idx && !stride_stream)
+                c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, false));
             if (c0 == 0) c0 = deto::launch_decompress_mfma(a);
             if (c0 > 0) {
                 rc = launched();
@@ -382,8 +394,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
             }
         }
     }
-    // Striding in the raw domain without transmitted indices, any chunk size and k
-    if (c0 == 0 && !idx && p.scheme == DETO_SCHEME_STRIDE && !p.use_dct && val_dtype == DETO_F32) {
+    if (c0 == 0 && stride_stream) {
         const deto::StrideGeom sg = deto::stride_geom(p.s, p.k, p.step);
         const int64_t wgs = (n + deto::kStrideSpan - 1) / deto::kStrideSpan;
         if (wgs <= 0x7FFFFFFF) {

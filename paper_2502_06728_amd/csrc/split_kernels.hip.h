@@ -313,6 +313,47 @@ __device__ __forceinline__ float4 split_output(const float* __restrict__ row, in
     return make_float4(e.w - o.w, e.z - o.z, e.y - o.y, e.x - o.x);
 }
 
+// The Random scheme's kept places of one chunk: the first k steps of a Fisher-Yates shuffle of
+// 0 .. S-1 in `places` (S bytes of LDS private to the calling lane), each place handed to `take`
+// as it is drawn.  Only places[t] is written back: place j is never read again after step j.
+// What bounds it is the LDS latency of a step (its write needs what it has read, the next step
+// reads after it), so four steps read at once and settle among themselves in registers what an
+// earlier one of the four has moved.
+template <int S, class Take>
+__device__ __forceinline__ void shuffle_places(uint64_t seed, uint64_t step, uint64_t chunk, int k,
+                                               uint8_t* places, Take take) {
+#pragma unroll
+    for (int q = 0; q < S / 4; ++q)
+        reinterpret_cast<uint32_t*>(places)[q] = 0x03020100u + 0x04040404u * q;
+    const uint64_t key = chunk_key(seed, step, chunk);
+    constexpr int kBatch = 4;
+    for (int j = 0; j < k; j += kBatch) {
+        uint32_t t[kBatch], pj[kBatch], pt[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            // (steps past the last one stay inside 0 .. S-1 and are not carried out: k <= S/2)
+            t[i] = j + i + bounded(draw(key, j + i), S - j - i);
+            pj[i] = places[j + i];
+            pt[i] = places[t[i]];
+        }
+#pragma unroll
+        for (int i = 1; i < kBatch; ++i) {
+#pragma unroll
+            for (int l = 0; l < i; ++l) {
+                pj[i] = (t[l] == static_cast<uint32_t>(j + i)) ? pj[l] : pj[i];
+                pt[i] = (t[l] == t[i]) ? pj[l] : pt[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            if (j + i < k) {
+                places[t[i]] = static_cast<uint8_t>(pj[i]);
+                take(pt[i]);
+            }
+        }
+    }
+}
+
 // Compress half (top-k, DCT domain, k <= S/2) on full tiles of 64 chunks; the chunks past the
 // last full tile form one partial tile (one more workgroup).
 // TOP > 0: for launches with k <= TOP (see the selection step).
@@ -320,11 +361,15 @@ __device__ __forceinline__ float4 split_output(const float* __restrict__ row, in
 // two-bit signs, byte or int32 indices); otherwise fp32 values and int32 indices.  Only the
 // staging step (what a kept coefficient leaves behind) and the payload's way out look at the
 // format, each behind one uniform branch, so one kernel serves all of them.
+// SCHEME (with NARROW, TOP = 0): Striding or Random in either domain (p.scheme, p.use_dct)
+// instead of top-k: the kept sets do not depend on the values, so one wavefront shuffles all 64
+// chunks (Random) or every wavefront writes the same pattern (Striding), and in the raw domain
+// the transforms fall away.
 // Occupancy: the workgroups of a CU are each in one phase at a time (barriers), so the number
 // of workgroups per CU is what overlaps memory phases with arithmetic.  Chunk 192 with the
 // partial sort fits three (168 registers, 52 KB of LDS with the dump slots inside the rows);
 // chunk 256 two (a 64-row tile alone is 65 KB); chunk 96 / 128 four to six of two wavefronts.
-template <int S, int W, bool GRAD_BF16, int TOP = 0, bool NARROW = false>
+template <int S, int W, bool GRAD_BF16, int TOP = 0, bool NARROW = false, bool SCHEME = false>
 __global__ __launch_bounds__(kWave * W)
 __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ grad,
@@ -412,18 +457,61 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     // ---- the lane's coefficients c[m] = coefficient W*m + off of chunk `lane`
     const int off = split_off<W>(w);
     float c[Q];
-    split_forward_local<S, W>(row, w, c);
-    __syncthreads();                              // every class has read the chunk: rows free
-    if constexpr (W == 4) split_forward_exchange<S>(row, w, c);
-    c[0] *= (w == 0) ? p.alpha0 : p.alpha;
+    const bool dct = !SCHEME || p.use_dct;
+    const float alpha0 = dct ? p.alpha0 : 1.0f, alpha = dct ? p.alpha : 1.0f;
+    if (dct) {
+        split_forward_local<S, W>(row, w, c);
+        __syncthreads();                          // every class has read the chunk: rows free
+        if constexpr (W == 4) split_forward_exchange<S>(row, w, c);
+        c[0] *= (w == 0) ? p.alpha0 : p.alpha;
 #pragma unroll
-    for (int m = 1; m < Q; ++m) c[m] *= p.alpha;
+        for (int m = 1; m < Q; ++m) c[m] *= p.alpha;
+    } else {
+#pragma unroll
+        for (int m = 0; m < Q; ++m) c[m] = row[W * m + off];
+        __syncthreads();
+    }
     if (coeff_dbg && alive) {
         float* dbg = coeff_dbg + (chunk0 + lane) * S + off;
 #pragma unroll
         for (int m = 0; m < Q; ++m) dbg[W * m] = c[m];
     }
 
+    uint32_t own[NW];     // this class's kept set: bit m = coefficient W*m + off
+    int need = 0;         // entries equal to the threshold that a tied chunk still takes
+    if constexpr (SCHEME) {
+        if (p.scheme == 2) {
+            // one wavefront, a lane per chunk (which one alternates, to spread over the SIMDs);
+            // the chunk's free row holds the places that are being shuffled
+            if (w == static_cast<int>(tile) % W) {
+#pragma unroll
+                for (int j = 0; j < W; ++j)
+#pragma unroll
+                    for (int i = 0; i < NW; ++i) s_mask[lane][j][i] = 0u;
+                shuffle_places<S>(p.seed, p.step, static_cast<uint64_t>(chunk0 + lane), k,
+                                  reinterpret_cast<uint8_t*>(row), [&](uint32_t at) {
+                    atomicOr(&s_mask[lane][split_off<W>(at % W)][(at / W) / 32],
+                             1u << ((at / W) % 32));
+                });
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < NW; ++j) own[j] = s_mask[lane][w][j];
+        } else {
+            const int stride = S / k;
+            int at = static_cast<int>(p.step % static_cast<uint64_t>(stride));
+#pragma unroll
+            for (int j = 0; j < NW; ++j) own[j] = 0u;
+            for (int j = 0; j < k; ++j, at += stride) {
+                const uint32_t bit = (at % W == off) ? 1u << ((at / W) % 32) : 0u;
+#pragma unroll
+                for (int i = 0; i < NW; ++i) own[i] |= ((at / W) / 32 == i) ? bit : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < NW; ++j) s_mask[lane][w][j] = own[j];
+            __syncthreads();
+        }
+    } else {
     // ---- k-th largest magnitude T of the chunk
     uint32_t T;
     {
@@ -523,7 +611,6 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     // ---- kept sets: magnitude >= T, unless more than k magnitudes reach T (a tie at the
     // threshold): then only those above T, and the chunk goes through the whole-wavefront
     // pass that adds the lowest indices among the equals
-    uint32_t own[NW];
     auto mark = [&](uint32_t thr) -> int {
 #pragma unroll
         for (int j = 0; j < NW; ++j) own[j] = 0u;
@@ -545,7 +632,6 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         return total;
     };
     uint32_t thr_gt = T, thr_eq = 0xFFFFFFFFu;
-    int need = 0;
     {
         const int cnt = mark(T);
         const bool tie = alive && cnt != k;      // the idle rows of a partial tile are all zero
@@ -573,6 +659,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
             }
             __syncthreads();
         }
+    }
+
     }
 
     // ---- payload staging, remainder in (settled chunks).  The position of coefficient m of
@@ -631,7 +719,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 r = as_f16 ? f16_to_f32(f32_to_f16(c[m])) : r;
                 left = c[m] - r;
             }
-            c[m] = (keep ? left : c[m]) * ((m == 0 && w == 0) ? p.alpha0 : p.alpha);
+            c[m] = (keep ? left : c[m]) * ((m == 0 && w == 0) ? alpha0 : alpha);
         });
     }
     __syncthreads();
@@ -641,6 +729,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         const unsigned long long tie_chunks = s_tie;
         // entries e .. e+3 of the tile (k a multiple of 4: they belong to one chunk)
         auto store_index4 = [&](uint32_t e, const float* src) {
+            if (SCHEME && !idx_out) return;       // not transmitted
             const float4 iv = *reinterpret_cast<const float4*>(src + kIdx0);
             const int4 i4 = make_int4(__float_as_int(iv.x), __float_as_int(iv.y),
                                       __float_as_int(iv.z), __float_as_int(iv.w));
@@ -686,7 +775,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 if constexpr (NARROW) {
                     if (p.val_dtype != 3)
                         store_payload_value(val_out, chunk0 * k + e, p.val_dtype, src[0]);
-                    store_payload_index(idx_out, chunk0 * k + e, p.idx_u8, at);
+                    if (!SCHEME || idx_out)
+                        store_payload_index(idx_out, chunk0 * k + e, p.idx_u8, at);
                 } else {
                     static_cast<float*>(val_out)[chunk0 * k + e] = src[0];
                     static_cast<int32_t*>(idx_out)[chunk0 * k + e] = at;
@@ -721,15 +811,27 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     __syncthreads();
 
     // ---- new momentum = inverse transform of the remainder
-    split_inverse_to_rows<S, W>(row, w, c);
-    {
+    if (dct) {
+        split_inverse_to_rows<S, W>(row, w, c);
+    } else {
+#pragma unroll
+        for (int m = 0; m < Q; ++m) row[W * m + off] = c[m];
+        __syncthreads();
+    }
+    auto store_momentum = [&](auto raw_tag) {
+        auto output4 = [&](int r, int col) -> float4 {
+            if constexpr (decltype(raw_tag)::value)
+                return *reinterpret_cast<const float4*>(&buf[r * kRow + col]);
+            else
+                return split_output<S, W>(&buf[r * kRow], col);
+        };
         constexpr int kIt = Q / 4;
         if (!partial) {
 #pragma unroll 4
             for (int it = 0; it < kIt; ++it) {
                 const int e4 = 4 * (tid + kThreads * it);
                 const int r = e4 / S, col = e4 - r * S;
-                st_f4<false>(mom + base + e4, split_output<S, W>(&buf[r * kRow], col));
+                st_f4<false>(mom + base + e4, output4(r, col));
             }
         } else {
             for (int it = 0; it < kIt; ++it) {
@@ -737,9 +839,9 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 const int r = e4 / S, col = e4 - r * S;
                 const int64_t i0 = base + e4;
                 if (i0 + 3 < n) {
-                    st_f4<false>(mom + i0, split_output<S, W>(&buf[r * kRow], col));
+                    st_f4<false>(mom + i0, output4(r, col));
                 } else if (i0 < n) {
-                    const float4 y = split_output<S, W>(&buf[r * kRow], col);
+                    const float4 y = output4(r, col);
                     const float v[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
@@ -747,6 +849,12 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 }
             }
         }
+    };
+    if constexpr (SCHEME) {
+        if (dct) store_momentum(std::false_type{});
+        else store_momentum(std::true_type{});
+    } else {
+        store_momentum(std::false_type{});
     }
 }
 
@@ -777,6 +885,14 @@ struct SplitPiece {
                 const uint4 t = ld_u4<true>(static_cast<const int32_t*>(idx) + ie);
                 i[0] = t.x; i[1] = t.y; i[2] = t.z; i[3] = t.w;
             }
+        } else {
+            i[0] = U8 ? static_cast<uint32_t>(static_cast<const uint8_t*>(idx)[ie])
+                      : static_cast<const uint32_t*>(idx)[ie];
+        }
+        load_values(val, ve, word_byte);
+    }
+    __device__ __forceinline__ void load_values(const void* val, int64_t ve, int64_t word_byte) {
+        if constexpr (VEC == 4) {
             if constexpr (VAL == 0) {
                 const uint4 t = ld_u4<true>(static_cast<const float*>(val) + ve);
                 v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
@@ -787,8 +903,6 @@ struct SplitPiece {
                 v[0] = t.x; v[1] = t.y;
             }
         } else {
-            i[0] = U8 ? static_cast<uint32_t>(static_cast<const uint8_t*>(idx)[ie])
-                      : static_cast<const uint32_t*>(idx)[ie];
             if constexpr (VAL == 0) v[0] = static_cast<const uint32_t*>(val)[ve];
             else if constexpr (VAL == 3) v[0] = static_cast<const uint8_t*>(val)[word_byte];
             else v[0] = static_cast<const uint16_t*>(val)[ve];
@@ -797,8 +911,13 @@ struct SplitPiece {
     // indices and values; j: the first entry's place in its chunk
     __device__ __forceinline__ void get(uint32_t j, uint32_t (&at)[VEC], float (&x)[VEC]) const {
 #pragma unroll
-        for (int c = 0; c < VEC; ++c) {
+        for (int c = 0; c < VEC; ++c)
             at[c] = (U8 && VEC == 4) ? (i[0] >> (8 * c)) & 0xFFu : i[U8 ? 0 : c];
+        values(j, x);
+    }
+    __device__ __forceinline__ void values(uint32_t j, float (&x)[VEC]) const {
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
             if constexpr (VAL == 0) x[c] = __uint_as_float(v[c]);
             else if constexpr (VAL == 3) x[c] = ternary_decode(v[0], VEC == 4 ? c : (j & 3u));
             else x[c] = decode16<VAL>(static_cast<uint16_t>(v[VEC == 1 ? 0 : c / 2] >> (16 * (c & 1))));
@@ -900,8 +1019,55 @@ __device__ __forceinline__ void split_scatter(const KParams& p, int lane, float*
     }
 }
 
+// The same without transmitted indices (Striding, Random): every replica kept the same places, so
+// the R values of an entry are summed in registers, replica 0 first, and written to their
+// place once.  place(r, j): the place of entry j of the wavefront's row r.
+template <int S, int VEC, int VAL, class Place>
+__device__ __forceinline__ void split_place_sums(const KParams& p, int lane, float* rows,
+                                                 int my_rows, const void* __restrict__ val,
+                                                 int64_t val_stride, int64_t entry0,
+                                                 int64_t chunk0, uint32_t magic, Place place) {
+    constexpr int kRow = S + 4;
+    constexpr int kBatch = 8;                              // replicas requested at a time
+    using Piece = SplitPiece<VEC, VAL, true>;
+    const int k = p.k;
+    const int pieces = my_rows * k / VEC;
+    const int chunk_bytes = 4 * ternary_words_per_chunk(k);
+    for (int q = lane; q < pieces; q += kWave) {
+        const uint32_t e = VEC * static_cast<uint32_t>(q);
+        const uint32_t r = (k == 1) ? e : __umulhi(e, magic);
+        const uint32_t j = e - r * static_cast<uint32_t>(k);
+        const int64_t word_byte = (chunk0 + r) * chunk_bytes + j / 4;
+        float sum[VEC];
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) sum[c] = 0.0f;
+        for (int r0 = 0; r0 < p.R; r0 += kBatch) {
+            Piece b[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                b[i].clear();
+                const int64_t rep = r0 + i;
+                if (rep < p.R)
+                    b[i].load_values(val, rep * val_stride + entry0 + e,
+                                     rep * val_stride * 4 + word_byte);
+            }
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                float x[VEC];
+                b[i].values(j, x);
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) sum[c] += x[c];   // (zero past the last replica)
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) rows[r * kRow + place(r, j + c)] = sum[c];
+    }
+}
+
 // Decompress-and-update half (transmitted indices, DCT domain) on full tiles of 64 chunks, W
-// wavefronts per workgroup; NARROW as in compress_split.
+// wavefronts per workgroup; NARROW as in compress_split.  SCHEME (with NARROW): Striding or Random
+// without transmitted indices, in either domain; one wavefront shuffles all 64 chunks of the tile
+// and lists their places in ascending order.
 //
 // Scatter-add: wavefront w owns the rows [64w/W, 64(w+1)/W) of the tile, so no two wavefronts
 // ever add into the same accumulator and, inside a wavefront, LDS operations complete in program
@@ -910,7 +1076,7 @@ __device__ __forceinline__ void split_scatter(const KParams& p, int lane, float*
 // flight decides how busy the memory is).  Then every class gathers its coefficients from
 // the rows, the inverse transform runs as in compress_split, and all wavefronts stream the
 // parameters (and the moments of Decoupled AdamW) through the update.
-template <int S, int W, bool PARAM_BF16, bool NARROW = false>
+template <int S, int W, bool PARAM_BF16, bool NARROW = false, bool SCHEME = false>
 __global__ __launch_bounds__(kWave * W) void decompress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ idx,
     int64_t idx_stride, const void* __restrict__ val, int64_t val_stride,
@@ -941,13 +1107,39 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
     // where they are used)
     constexpr int kPieces = Q / 4;                // 4-element pieces of the tile per thread
     uint2 early[kPieces];
-    const bool params_early = PARAM_BF16 && !partial && !p.adam && p.use_dct;
+    const bool params_early = PARAM_BF16 && !partial && !p.adam && (SCHEME || p.use_dct);
     if constexpr (PARAM_BF16) {
         if (params_early) {
 #pragma unroll
             for (int it = 0; it < kPieces; ++it)
                 early[it] = ld_u2<true>(static_cast<const uint16_t*>(params) + base +
                                         4 * (tid + kThreads * it));
+        }
+    }
+
+    // ---- Random: the places of every chunk, ascending, as bytes (entry e of the tile at byte e)
+    __shared__ __attribute__((aligned(16))) uint8_t s_places[SCHEME ? kWave * S / 2 : 4];
+    __shared__ uint32_t s_bits[SCHEME ? kWave * (S / 32 > 0 ? S / 32 : 1) : 1];
+    if constexpr (SCHEME) {
+        if (p.scheme == 2) {
+            if (w == static_cast<int>(tile) % W) {
+                constexpr int kWords = S / 32 > 0 ? S / 32 : 1;
+                uint32_t* bits = &s_bits[lane * kWords];
+#pragma unroll
+                for (int i = 0; i < kWords; ++i) bits[i] = 0u;
+                shuffle_places<S>(p.seed, p.step, static_cast<uint64_t>(tile * kWave + lane), k,
+                                  reinterpret_cast<uint8_t*>(row),
+                                  [&](uint32_t at) { atomicOr(&bits[at / 32], 1u << (at % 32)); });
+                uint8_t* out = &s_places[lane * k];
+                for (int i = 0; i < kWords; ++i) {
+                    uint32_t left = bits[i];
+                    while (left) {
+                        *out++ = static_cast<uint8_t>(32 * i + __ffs(left) - 1);
+                        left &= left - 1u;
+                    }
+                }
+            }
+            __syncthreads();
         }
     }
 
@@ -976,8 +1168,30 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 split_scatter<S, 1, VAL, U8>(p, lane, rows, my_rows, idx, idx_stride, val,
                                              val_stride, row0 * k, row0, magic);
         };
+        // Striding / Random without transmitted indices
+        [[maybe_unused]] auto place_sums = [&](auto val_tag) {
+            constexpr int VAL = decltype(val_tag)::value;
+            const int stride = S / k;
+            const int first = static_cast<int>(p.step % static_cast<uint64_t>(stride));
+            const uint8_t* listed = &s_places[SCHEME ? w * kRowsPerWave * k : 0];
+            auto place = [&](uint32_t r, uint32_t j) -> int {
+                return p.scheme == 2 ? static_cast<int>(listed[r * k + j])
+                                     : first + static_cast<int>(j) * stride;
+            };
+            if (k % 4 == 0)
+                split_place_sums<S, 4, VAL>(p, lane, rows, my_rows, val, val_stride, row0 * k, row0,
+                                            magic, place);
+            else
+                split_place_sums<S, 1, VAL>(p, lane, rows, my_rows, val, val_stride, row0 * k, row0,
+                                            magic, place);
+        };
         using std::integral_constant;
-        if constexpr (!NARROW) {
+        if constexpr (SCHEME) {
+            if (p.val_dtype == 1) place_sums(integral_constant<int, 1>{});
+            else if (p.val_dtype == 2) place_sums(integral_constant<int, 2>{});
+            else if (p.val_dtype == 3) place_sums(integral_constant<int, 3>{});
+            else place_sums(integral_constant<int, 0>{});
+        } else if constexpr (!NARROW) {
             scatter(integral_constant<int, 0>{}, std::false_type{});
         } else {
             auto by_value = [&](auto u8_tag) {
@@ -1120,12 +1334,12 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
             }
         }
         };
-        if (params_early) {
+        auto update_early = [&](auto raw_tag) {
 #pragma unroll
             for (int it = 0; it < kPieces; ++it) {
                 const int e4 = 4 * (tid + kThreads * it);
                 const int64_t i = base + e4;
-                const float4 y4 = output4(e4, std::false_type{});
+                const float4 y4 = output4(e4, raw_tag);
                 if (presign_dbg) st_f4<false>(presign_dbg + i, y4);
                 const float y[4] = {y4.x, y4.y, y4.z, y4.w};
                 const float old[4] = {__uint_as_float(early[it].x << 16),
@@ -1141,8 +1355,18 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 o.y = pack_bf16x2(nw[2], nw[3]);
                 st_u2<true>(static_cast<uint16_t*>(params) + i, o);
             }
+        };
+        if (params_early) {
+            if constexpr (SCHEME) {
+                if (p.use_dct) update_early(std::false_type{});
+                else update_early(std::true_type{});
+            } else {
+                update_early(std::false_type{});
+            }
         } else if (!p.use_dct) {
-            update(std::true_type{}, std::true_type{});
+            // (transmitted indices in the raw domain: rare, one copy of the loop with the checks)
+            if (SCHEME && !partial) update(std::integral_constant<bool, !SCHEME>{}, std::true_type{});
+            else update(std::true_type{}, std::true_type{});
         } else if (partial) {
             update(std::true_type{}, std::false_type{});
         } else {

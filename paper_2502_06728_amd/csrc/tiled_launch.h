@@ -78,9 +78,6 @@ bool launch_compress_topk_packed_s32(const CompressLaunch& a);
 bool launch_decompress_idx_packed_s32(const DecompressLaunch& a);
 bool launch_compress_topk_ternary(const CompressLaunch& a);    // byte indices + two-bit signs
 bool launch_decompress_idx_ternary(const DecompressLaunch& a);
-// Decoupled AdamW without transmitted indices (with them: launch_decompress_split)
-bool launch_decompress_scheme_adamw(const DecompressLaunch& a);
-bool launch_decompress_adamw_narrow(const DecompressLaunch& a);   // ... narrow payloads
 bool launch_compress_scheme_narrow_s32(const CompressLaunch& a);   // Striding / Random, narrow payload
 bool launch_decompress_scheme_narrow_s32(const DecompressLaunch& a);
 bool launch_compress_scheme_narrow_s64(const CompressLaunch& a);
@@ -128,6 +125,8 @@ inline int64_t launch_compress_pair(const CompressLaunch& a) {
 // k <= s/2 in the compress half.  Same return convention.
 int64_t launch_decompress_split(const DecompressLaunch& a, int classes);        // fp32 + int32
 int64_t launch_decompress_split_narrow(const DecompressLaunch& a, int classes); // other formats
+int64_t launch_compress_split_scheme(const CompressLaunch& a);                   // Striding / Random
+int64_t launch_decompress_split_scheme(const DecompressLaunch& a, int classes);  // ... no indices
 // 16-bit values, or byte indices:
 int64_t launch_compress_split_narrow_96(const CompressLaunch& a);
 int64_t launch_compress_split_narrow_128(const CompressLaunch& a);
@@ -175,6 +174,8 @@ inline int decompress_classes(const KParams& p, int64_t n, bool param_bf16, bool
     if (p.s == 16) return (lane && !p.adam && param_bf16) ? 0 : 2;
     if (p.adam) return (quads ? (plain || rk <= p.s) : 4 * rk <= p.s) ? 4 : 2;
     if (p.s >= 96) {
+        // (many entries per chunk to scatter: chunk 96, k 24, R = 22: 51 against 53 us a step)
+        if (lane && plain && rk >= 4 * p.s) return 0;
         if (!param_bf16) return 4;
         if (p.s == 128 && (rk >= p.s || !large)) return 4;
         return lane ? 0 : (large ? 2 : 4);
@@ -189,6 +190,30 @@ inline int decompress_classes(const KParams& p, int64_t n, bool param_bf16, bool
     }
     if (split) return wide ? 4 : 2;
     return lane ? 0 : 2;
+}
+
+// The same for Striding and Random without transmitted indices (0: a lane per chunk).  The sums
+// over the replicas are formed in registers, so large groups cost little; a shuffle costs one of
+// the wavefronts k steps, which is what the high rates lose.  us, a lane per chunk / two / four
+// classes, the shards A, B, D of decompress_classes:
+//   chunk 64, k 32, signs, AdamW, Random   A 597/525/540  B 147/132/121  D 123/111/113
+//             k 8, fp32, AdamW             A 628/579/557  B 147/130/122  D 121/110/104
+//             k 8, fp32, SGD               A 143/138/201  B  51/ 47/ 47  D  29/ 30/ 41
+//             k 32, fp32, SGD              A 307/288/364  B  64/ 66/ 78  D  43/ 54/ 71
+//   chunk 32, k 4, signs, coefficients     A 114/209/290  B  46/ 48/ 62  D  26/ 43/ 59
+//             k 1, signs                   A  99/135/168  B  45/ 40/ 42  D  23/ 30/ 35
+inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lane) {
+    const bool plain = p.val_dtype == 0;
+    const int64_t rk = static_cast<int64_t>(p.R) * p.k;
+    if (p.adam || !lane || (p.s != 32 && p.s != 64)) {
+        const int c = decompress_classes(p, n, param_bf16, false);
+        return (p.s >= 96 && c) ? 4 : c;
+    }
+    if (!param_bf16) return (16 * p.k <= p.s || (8 * p.k <= p.s && (p.s == 64 || plain))) ? 2 : 0;
+    // (Random on coefficients stays with a lane per chunk: 861 M, chunk 64: 3,666 against 3,709 us
+    // a step)
+    const bool large = n > kLargeShard && !(p.use_dct && p.scheme == 2);
+    return (large && plain && rk >= 2 * p.s) ? 2 : 0;
 }
 
 inline int64_t launch_compress_split(const CompressLaunch& a) {

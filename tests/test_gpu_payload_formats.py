@@ -149,3 +149,42 @@ def test_unordered_payloads(H, s, k, fmt):
                     np.tile(np.arange(k), C)]).astype(np.int32)
     val = oracle_payloads(cfg, n, val_dtype, R, 40)[1]
     check_update(H, cfg, idx, val, val_dtype, idx_u8, make_inputs(n, 3)[2])
+
+
+SCHEME_SHAPES = [(16, 3), (16, 8), (32, 3), (64, 2), (64, 7), (96, 12), (128, 4), (128, 16), (128, 64),
+                 (192, 5), (256, 32), (256, 127)]
+
+
+@pytest.mark.parametrize("fmt", ["f32+i32", "bf16+u8", "f16+i32", "signs+u8"])
+@pytest.mark.parametrize("scheme", [oracle.SCHEME_STRIDE, oracle.SCHEME_RANDOM])
+@pytest.mark.parametrize("dct", [False, True])
+@pytest.mark.parametrize("s,k", SCHEME_SHAPES)
+def test_striding_and_random(H, s, k, dct, scheme, fmt):
+    val_dtype, idx_u8 = FORMATS.get(fmt, (oracle.F32, False))
+    n = s * (64 + 37) + s // 3        # a full tile, 37 chunks and a ragged one
+    cfg = Config(chunk=s, topk=k, scheme=scheme, dct=dct, sign=True, lr=1e-3, seed=11, step=5)
+    g, m, th = make_inputs(n, seed=s + k, params_bf16=k % 2 == 0)
+    compress_case(H, cfg, g, m, val_dtype, idx_u8)
+    idx, val = oracle_payloads(cfg, n, val_dtype, 9 if k < 16 else 3, 300)
+    check_update(H, cfg, idx, val, val_dtype, idx_u8, th)
+    check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=bool(k % 3 == 0))
+
+
+@pytest.mark.parametrize("s,k", [(128, 16), (64, 5), (256, 40)])
+def test_random_without_index_output(H, s, k):
+    """No index array at all, and a caller that passes indices in the raw domain."""
+    import torch
+    from paper_2502_06728_amd import binding
+    n = s * (64 + 5) + 3
+    cfg = Config(chunk=s, topk=k, scheme=oracle.SCHEME_RANDOM, seed=2, step=9, sign=False)
+    g, m, th = make_inputs(n, seed=k)
+    m_gpu, _, words, _ = H.gpu_compress_ternary(cfg, g, m, False, want_idx=False)
+    m_o, idx_o, words_o = oracle.compress_t(cfg, g, m)
+    assert np.array_equal(words, words_o) and np.array_equal(m_gpu, m_o)
+    signs = oracle.decode_ternary(cfg, n, words_o)[None, :]
+    p, y = H.to_dev(th), torch.empty(n, dtype=torch.float32, device=H.DEV)
+    binding.detonation_decompress_step_packed(
+        H.bcfg(cfg), 1, torch.from_numpy(idx_o.astype(np.uint8)).to(H.DEV),
+        torch.from_numpy(words_o.view(np.int32)).to(H.DEV), p, y)
+    torch.cuda.synchronize()
+    parity.check_decompress(cfg, idx_o[None, :], signs, th, H.to_host(p), H.to_host(y))
