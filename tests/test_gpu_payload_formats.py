@@ -12,8 +12,7 @@ from tests.test_gpu_parity import H, make_inputs  # noqa: F401  (H: the fixture)
 pytestmark = pytest.mark.gpu
 
 FORMATS = {"bf16+u8": (oracle.BF16, True), "f16+i32": (oracle.F16, False),
-           "signs+u8": (oracle.TERNARY, True), "signs+i32": (oracle.TERNARY, False),
-           "f32+u8": (oracle.F32, True)}
+           "signs+u8": (oracle.TERNARY, True), "f32+u8": (oracle.F32, True)}
 
 
 def with_ties(g, m, s):
@@ -134,7 +133,7 @@ def test_topk(H, s, k, fmt):
     check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=bool(k % 3 == 0))
 
 
-@pytest.mark.parametrize("fmt", ["bf16+u8", "signs+i32", "f32+u8"])
+@pytest.mark.parametrize("fmt", ["f16+i32", "signs+u8", "f32+u8"])
 @pytest.mark.parametrize("s,k", [(16, 4), (32, 5), (64, 5), (96, 12), (128, 3), (192, 24), (256, 10)])
 def test_unordered_payloads(H, s, k, fmt):
     """Duplicates and disorder add like the scatter-add they are; indices past the chunk are skipped."""
@@ -151,11 +150,10 @@ def test_unordered_payloads(H, s, k, fmt):
     check_update(H, cfg, idx, val, val_dtype, idx_u8, make_inputs(n, 3)[2])
 
 
-SCHEME_SHAPES = [(16, 3), (16, 8), (32, 3), (64, 2), (64, 7), (96, 12), (128, 4), (128, 16), (128, 64),
-                 (192, 5), (256, 32), (256, 127)]
+SCHEME_SHAPES = [(16, 3), (32, 3), (64, 2), (96, 12), (128, 16), (128, 64), (192, 5), (256, 127)]
 
 
-@pytest.mark.parametrize("fmt", ["f32+i32", "bf16+u8", "f16+i32", "signs+u8"])
+@pytest.mark.parametrize("fmt", ["f32+i32", "f16+i32", "signs+u8"])
 @pytest.mark.parametrize("scheme", [oracle.SCHEME_STRIDE, oracle.SCHEME_RANDOM])
 @pytest.mark.parametrize("dct", [False, True])
 @pytest.mark.parametrize("s,k", SCHEME_SHAPES)
