@@ -2,7 +2,9 @@
 
 Argument marshalling only: device tensors in, raw pointers out; every step of the path
 runs in the HIP kernels.  There is no CPU fallback — if the library has not been built
-the first call raises.
+the first call raises.  The calls of a step hand their arguments to csrc/marshal.c first, which
+checks and converts what a program usually passes without ctypes; what it does not take goes
+through the checks below, which name what is wrong.
 """
 from __future__ import annotations
 
@@ -79,6 +81,7 @@ class DetonationError(RuntimeError):
 
 
 _lib = None
+_marshal = None     # csrc/marshal.c, set up by load()
 
 
 def load() -> ctypes.CDLL:
@@ -118,8 +121,35 @@ def load() -> ctypes.CDLL:
         lib.detonation_status_string.argtypes = [ctypes.c_int]
         lib.detonation_status_string.restype = ctypes.c_char_p
         lib.detonation_version.restype = ctypes.c_int
+        _load_marshal(lib)
         _lib = lib
     return _lib
+
+
+def _load_marshal(lib) -> None:
+    global _marshal
+    import importlib.machinery
+    import importlib.util
+
+    import torch
+    path = os.path.join(_HERE, "_marshal.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} is missing: run `python -m paper_2502_06728_amd.build`")
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+    spec = importlib.util.spec_from_file_location("_marshal", path, loader=loader)
+    m = importlib.util.module_from_spec(spec)
+    loader.exec_module(m)
+    m.setup(*(ctypes.cast(f, ctypes.c_void_p).value
+              for f in (lib.detonation_compress_packed, lib.detonation_decompress_step_packed,
+                        lib.detonation_decompress_adamw_step_packed)),
+            torch.float32, torch.bfloat16, torch.float16, torch.int32, torch.uint8,
+            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    _marshal = m
+
+
+def _marshalling():
+    load()
+    return _marshal
 
 
 def status_string(status: int) -> str:
@@ -166,6 +196,13 @@ def _idx_dtype(t) -> int:
     if t.dtype == torch.uint8:
         return IDX_U8
     raise TypeError(f"unsupported index dtype {t.dtype}")
+
+
+def _handle(stream):
+    """A given stream's handle; None stays None (the current stream)."""
+    if stream is None:
+        return None
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _stream(stream):
@@ -243,6 +280,13 @@ def detonation_compress(cfg: Config, grad, momentum, idx_out, val_out, coeff_dbg
                         stream=None, n: int | None = None) -> None:
     """Enqueue the compress half on `stream`.  momentum, idx_out, val_out (and coeff_dbg)
     are written in place by the kernels."""
+    if coeff_dbg is None:
+        rc = (_marshal or _marshalling()).compress(cfg, n, grad, momentum, idx_out, val_out, False,
+                                                   _handle(stream))
+        if rc == 0:
+            return
+        if rc > 0:
+            raise DetonationError(rc)
     _check(grad, momentum, idx_out, val_out, coeff_dbg)
     n = momentum.numel() if n is None else n
     _check_compress(cfg, n, grad, momentum, idx_out, val_out, coeff_dbg, packed=False)
@@ -259,6 +303,13 @@ def detonation_decompress_step(cfg: Config, R: int, idx, val, params, presign_db
                                val_replica_stride: int | None = None) -> None:
     """Enqueue the decompress-and-update half on `stream`.  idx/val hold R payloads
     (replica r at offset r*stride); params is updated in place."""
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+        rc = (_marshal or _marshalling()).decompress(
+            cfg, n, R, idx, val, params, False, _handle(stream))
+        if rc == 0:
+            return
+        if rc > 0:
+            raise DetonationError(rc)
     _check(idx, val, params, presign_dbg)
     n = params.numel() if n is None else n
     entries = payload_entries(cfg, n)
@@ -290,6 +341,13 @@ def detonation_compress_packed(cfg: Config, grad, momentum, idx_out, val_out, co
                                stream=None, n: int | None = None) -> None:
     """Compress half with the payload format given by the output tensors' dtypes: indices
     int32 or uint8, values float32, bfloat16, float16, or int32 words of the ternary payload."""
+    if coeff_dbg is None:
+        rc = (_marshal or _marshalling()).compress(cfg, n, grad, momentum, idx_out, val_out, True,
+                                                   _handle(stream))
+        if rc == 0:
+            return
+        if rc > 0:
+            raise DetonationError(rc)
     _check(grad, momentum, idx_out, val_out, coeff_dbg)
     n = momentum.numel() if n is None else n
     _check_compress(cfg, n, grad, momentum, idx_out, val_out, coeff_dbg, packed=True)
@@ -306,6 +364,13 @@ def detonation_decompress_step_packed(cfg: Config, R: int, idx, val, params, pre
                                       idx_replica_stride: int | None = None,
                                       val_replica_stride: int | None = None) -> None:
     """Decompress-and-update half for payloads in the format given by the tensors' dtypes."""
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+        rc = (_marshal or _marshalling()).decompress(
+            cfg, n, R, idx, val, params, True, _handle(stream))
+        if rc == 0:
+            return
+        if rc > 0:
+            raise DetonationError(rc)
     _check(idx, val, params, presign_dbg)
     n = params.numel() if n is None else n
     entries = payload_entries(cfg, n)
@@ -330,6 +395,14 @@ def detonation_decompress_adamw_step(cfg: Config, opt: AdamW, R: int, idx, val, 
                                      val_replica_stride: int | None = None) -> None:
     """Decompress half with Decoupled AdamW as the underlying optimizer; params and the moment
     tensors are updated in place."""
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+        rc = (_marshal or _marshalling()).decompress(
+            cfg, n, R, idx, val, params, False, _handle(stream),
+            opt, exp_avg, exp_avg_sq, max_exp_avg_sq)
+        if rc == 0:
+            return
+        if rc > 0:
+            raise DetonationError(rc)
     _check(idx, val, params, exp_avg, exp_avg_sq, max_exp_avg_sq, presign_dbg)
     n = params.numel() if n is None else n
     entries = payload_entries(cfg, n)
@@ -353,6 +426,14 @@ def detonation_decompress_adamw_step_packed(cfg: Config, opt: AdamW, R: int, idx
                                             idx_replica_stride: int | None = None,
                                             val_replica_stride: int | None = None) -> None:
     """Decoupled AdamW on payloads in the format given by the tensors' dtypes."""
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+        rc = (_marshal or _marshalling()).decompress(
+            cfg, n, R, idx, val, params, True, _handle(stream),
+            opt, exp_avg, exp_avg_sq, max_exp_avg_sq)
+        if rc == 0:
+            return
+        if rc > 0:
+            raise DetonationError(rc)
     _check(idx, val, params, exp_avg, exp_avg_sq, max_exp_avg_sq, presign_dbg)
     n = params.numel() if n is None else n
     entries = payload_entries(cfg, n)

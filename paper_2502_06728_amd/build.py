@@ -10,6 +10,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OBJ = os.path.join(_HERE, "_build")
 LIB = os.path.join(_HERE, "libdetonation.so")
+MARSHAL = os.path.join(_HERE, "_marshal.so")
 MEMBENCH = os.path.join(_HERE, "membench")
 
 HIPCC_FLAGS = [
@@ -43,6 +44,13 @@ UNITS = [
     # validation, dispatch, general kernels
     "detonation.hip",
 ]
+
+
+def _build_marshal(verbose: bool) -> None:
+    """The binding's argument marshalling (host code, CPython's C API)."""
+    import sysconfig
+    _run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
+          "-o", MARSHAL, os.path.join(CSRC, "marshal.c")], verbose)
 
 
 def _run(cmd: list[str], verbose: bool) -> None:
@@ -92,6 +100,7 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=max(1, min(len(jobs), 8))) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs], verbose)
+    _build_marshal(verbose)
     # the streaming micro-benchmark (HBM ceiling, counter calibration)
     if lib == LIB:
         _run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Wno-unused-result", "-o",
