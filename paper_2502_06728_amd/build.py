@@ -26,7 +26,6 @@ UNITS = [
     "split_compress_256.hip", "split_compress_192.hip", "split_compress_128.hip",
     "split_narrow_256.hip", "split_narrow_192.hip", "split_narrow_128.hip",
     "split_compress_96.hip", "split_compress_64.hip", "split_narrow_96.hip",
-    "split_narrow_64.hip", "split_narrow_32.hip", "split_narrow_16.hip",
     "split_decompress.hip", "split_decompress_narrow.hip",
     "split_scheme_compress.hip", "split_scheme_decompress.hip",
     # two lanes per chunk (chunk 96, 128, 192, 256)

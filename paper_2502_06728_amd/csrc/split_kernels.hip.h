@@ -313,67 +313,6 @@ __device__ __forceinline__ float4 split_output(const float* __restrict__ row, in
     return make_float4(e.w - o.w, e.z - o.z, e.y - o.y, e.x - o.x);
 }
 
-// The kept sets of the chunks in `near` (a bit per row of the tile) from the coefficients as the
-// general kernels sum them (same products in the same order), ranked like there: larger magnitude
-// first, then the lower index.  Every wavefront takes its share; called by the whole workgroup with
-// the tile's rows free (they hold the cosine table and the chunks at work).
-template <int S, int W, bool GRAD_BF16, int NW>
-__device__ __forceinline__ void settle_near_ties(const KParams& p, float* buf,
-                                                 unsigned long long near, int tid, int64_t base,
-                                                 int64_t n, const void* __restrict__ grad,
-                                                 const float* __restrict__ mom,
-                                                 uint32_t (*mask)[W][NW]) {
-    static_assert(4 * S + 2 * S * W <= kWave * (S + 4), "scratch in the tile");
-    const int lane = tid & (kWave - 1), w = tid >> 6;
-    float* tab = buf;
-    float* x = buf + 4 * S + 2 * S * w;
-    float* cf = x + S;
-    if (w == 0) build_cos_table(tab, S, lane);
-    __syncthreads();
-    int turn = 0;
-    while (near) {
-        const int r = __ffsll(near) - 1;
-        near &= near - 1ull;
-        if (turn++ % W != w) continue;
-        for (int e = lane; e < S; e += kWave) {
-            const int64_t i = base + r * S + e;
-            float v = 0.0f;
-            if (i < n) {
-                const float g = GRAD_BF16 ? bf16_to_f32(static_cast<const uint16_t*>(grad)[i])
-                                          : static_cast<const float*>(grad)[i];
-                v = fmaf(p.beta, mom[i], g);
-            }
-            x[e] = v;
-        }
-        if (lane < W * NW) mask[r][lane / NW][lane % NW] = 0u;
-        wave_lds_sync();
-        for (int e = lane; e < S; e += kWave) {
-            float acc = 0.0f;
-            int ph = e;
-#pragma unroll 8
-            for (int t = 0; t < S; ++t) {
-                acc = fmaf(x[t], tab[ph], acc);
-                ph += 2 * e;
-                if (ph >= 4 * S) ph -= 4 * S;
-            }
-            cf[e] = acc * ((e == 0) ? p.alpha0 : p.alpha);
-        }
-        wave_lds_sync();
-        for (int e = lane; e < S; e += kWave) {
-            const uint32_t me = __float_as_uint(cf[e]) & 0x7FFFFFFFu;
-            int rank = 0;
-#pragma unroll 8
-            for (int t = 0; t < S; ++t) {
-                const uint32_t o = __float_as_uint(cf[t]) & 0x7FFFFFFFu;
-                rank += (o > me || (o == me && t < e)) ? 1 : 0;
-            }
-            if (rank < p.k)
-                atomicOr(&mask[r][split_off<W>(e % W)][(e / W) / 32], 1u << ((e / W) % 32));
-        }
-        wave_lds_sync();
-    }
-}
-
 // The Random scheme's kept places of one chunk: the first k steps of a Fisher-Yates shuffle of
 // 0 .. S-1 in `places` (S bytes of LDS private to the calling lane), each place handed to `take`
 // as it is drawn.  Only places[t] is written back: place j is never read again after step j.
@@ -432,8 +371,7 @@ __device__ __forceinline__ void shuffle_places(uint64_t seed, uint64_t step, uin
 // chunk 256 two (a 64-row tile alone is 65 KB); chunk 96 / 128 four to six of two wavefronts.
 template <int S, int W, bool GRAD_BF16, int TOP = 0, bool NARROW = false, bool SCHEME = false>
 __global__ __launch_bounds__(kWave * W)
-__attribute__((amdgpu_waves_per_eu(
-    (S == 192 && TOP > 0) ? 3 : ((S == 128 && W == 4) ? 4 : 2)))) void compress_split(
+__attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ grad,
     float* __restrict__ mom, void* __restrict__ idx_out, void* __restrict__ val_out,
     float* __restrict__ coeff_dbg) {
@@ -574,9 +512,8 @@ __attribute__((amdgpu_waves_per_eu(
             __syncthreads();
         }
     } else {
-    // ---- k-th largest magnitude T of the chunk (and the largest: near ties, below)
+    // ---- k-th largest magnitude T of the chunk
     uint32_t T;
-    [[maybe_unused]] uint32_t largest = 0u;
     {
         // (the magnitudes are formed again when the kept sets are marked: keeping these
         // copies alive across the sort would cost Q registers)
@@ -669,7 +606,6 @@ __attribute__((amdgpu_waves_per_eu(
         } else {
             T = kth_of_two_lists<Q>(lists, lists + Q, k);
         }
-        if constexpr (NARROW) largest = max(lists[0], lists[(W / 2) * Q]);
     }
 
     // ---- kept sets: magnitude >= T, unless more than k magnitudes reach T (a tie at the
@@ -697,46 +633,14 @@ __attribute__((amdgpu_waves_per_eu(
     };
     uint32_t thr_gt = T, thr_eq = 0xFFFFFFFFu;
     {
-        bool near = false;
-        uint32_t settled[NW];
-        if constexpr (NARROW) {
-            // Near ties.  Where the k-th and the next magnitude are closer than the rounding of
-            // the transform, the kept set is settled on the directly summed coefficients of the
-            // general kernels, so that a chunk keeps the same places whichever of the two
-            // serves the call (unaligned buffers, fewer than 64 chunks).  Only for the formats
-            // that have no other kernel beside these two.  2^-18 of the largest magnitude: the
-            // two sums differ by up to 2^-20 of it (chunk 256).
-            if (p.val_dtype == 3 || S == 16) {
-                const float at = __uint_as_float(T) - 0x1p-18f * __uint_as_float(largest);
-                const uint32_t low = at > 0.0f ? __float_as_uint(at) : 0u;
-                near = mark(low) != k && alive && largest != 0u;
-                if (__syncthreads_or(near ? 1 : 0)) {
-                    mark(T);
-                    settle_near_ties<S, W, GRAD_BF16>(p, buf, __ballot(near), tid, base, n, grad, mom,
-                                                      s_mask);
-                    __syncthreads();
-#pragma unroll
-                    for (int j = 0; j < NW; ++j) settled[j] = s_mask[lane][w][j];
-                    __syncthreads();
-                }
-            }
-        }
-        auto keep_settled = [&]() {
-            if (near) {
-#pragma unroll
-                for (int j = 0; j < NW; ++j) s_mask[lane][w][j] = own[j] = settled[j];
-            }
-        };
         const int cnt = mark(T);
-        keep_settled();
-        const bool tie = alive && !near && cnt != k;   // (idle rows of a partial tile are zero)
+        const bool tie = alive && cnt != k;      // the idle rows of a partial tile are all zero
         if (__syncthreads_or(tie ? 1 : 0)) {
             if (tie) {
                 thr_gt = T + 1u;     // <= 0x80000000: no magnitude reaches that
                 thr_eq = T;
             }
             const int above = mark(thr_gt);
-            keep_settled();
             if (tie) need = k - above;
             // the tied chunks' coefficients in natural order in their rows, for wavefront 0
 #pragma unroll

@@ -1,6 +1,6 @@
 // Shared body of the split_narrow_*.hip units: the wavefront-per-coefficient-class compress
-// kernels of chunk size DETO_S with DETO_W classes for every payload format but fp32 values +
-// int32 indices (chunk 32, 64: two-bit signs), any k <= DETO_S / 2.  Defines the launcher DETO_SPLIT_NARROW_FN.
+// kernels of chunk size DETO_S with DETO_W classes for 16-bit values (byte or int32 indices)
+// and fp32 values with byte indices, any k <= DETO_S / 2.  Defines the launcher DETO_SPLIT_NARROW_FN.
 // DETO_TOP(X): the partial-sort lengths, ascending; a launch takes the first that holds its k.
 #include "split_kernels.hip.h"
 #include "tiled_launch.h"
@@ -13,11 +13,7 @@ int64_t DETO_SPLIT_NARROW_FN(const CompressLaunch& a) {
     return 0;
 #else
     if (p.s != DETO_S || p.scheme != 0 || !p.use_dct || 2 * p.k > DETO_S) return 0;
-    if (p.val_dtype == 0 && !p.idx_u8) return 0;
-    // (at chunk 32 and 64 the other formats' k without a lane-per-chunk kernel stay on the
-    // matrix-core kernels: their coefficients round differently, which at a near tie changes
-    // what a chunk keeps)
-    if ((DETO_S == 32 || DETO_S == 64) && p.val_dtype != 3) return 0;
+    if (p.val_dtype == 3 || (p.val_dtype == 0 && !p.idx_u8)) return 0;
     const int64_t tiles = (a.n / p.s) / kWave;
     // one workgroup per full tile and one for the chunks left over (a partial tile)
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);

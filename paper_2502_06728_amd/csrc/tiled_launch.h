@@ -127,10 +127,7 @@ int64_t launch_decompress_split(const DecompressLaunch& a, int classes);        
 int64_t launch_decompress_split_narrow(const DecompressLaunch& a, int classes); // other formats
 int64_t launch_compress_split_scheme(const CompressLaunch& a);                   // Striding / Random
 int64_t launch_decompress_split_scheme(const DecompressLaunch& a, int classes);  // ... no indices
-// all but fp32 + int32 payloads:
-int64_t launch_compress_split_narrow_16(const CompressLaunch& a);
-int64_t launch_compress_split_narrow_32(const CompressLaunch& a);
-int64_t launch_compress_split_narrow_64(const CompressLaunch& a);
+// 16-bit values, or byte indices:
 int64_t launch_compress_split_narrow_96(const CompressLaunch& a);
 int64_t launch_compress_split_narrow_128(const CompressLaunch& a);
 int64_t launch_compress_split_narrow_192(const CompressLaunch& a);
@@ -224,9 +221,6 @@ inline int64_t launch_compress_split(const CompressLaunch& a) {
     if (!c) c = launch_compress_split_128(a);
     if (!c) c = launch_compress_split_192(a);
     if (!c) c = launch_compress_split_256(a);
-    if (!c) c = launch_compress_split_narrow_16(a);
-    if (!c) c = launch_compress_split_narrow_32(a);
-    if (!c) c = launch_compress_split_narrow_64(a);
     if (!c) c = launch_compress_split_narrow_96(a);
     if (!c) c = launch_compress_split_narrow_128(a);
     if (!c) c = launch_compress_split_narrow_192(a);
