@@ -102,6 +102,62 @@ struct FastDct {
         }
     }
 
+    // What dct2_open (dct4_open) leaves to do at output i: the constant of the multiplication that
+    // output ends with, 1 if it does not end with one.
+    static constexpr float dct2_factor(int i) {
+        if constexpr (N == 1) return 1.0f;
+        else if constexpr (N == 3) return i == 1 ? kCosPi6 : 1.0f;
+        else return i % 2 ? FastDct<H>::dct4_factor(i / 2) : FastDct<H>::dct2_factor(i / 2);
+    }
+    static constexpr float dct4_factor(int i) {
+        if constexpr (N == 1) return kCosPi4;
+        else if constexpr (N == 3) return i == 1 ? kCosPi4 : 1.0f;
+        else return 1.0f;
+    }
+
+    // dct2 without those last multiplications: where an output is then added to another one, the
+    // two can round once, as they do inside dct4
+    static __device__ __forceinline__ void dct2_open(float (&x)[N]) {
+        if constexpr (N == 1) {
+            return;
+        } else if constexpr (N == 3) {
+            const float a = x[0], b = x[1], d = x[2];
+            x[0] = a + b + d;
+            x[1] = a - d;
+            x[2] = fmaf(0.5f, a + d, -b);
+        } else {
+            float u[H], v[H];
+            static_for<0, H>([&](auto i) {
+                u[i] = x[i] + x[N - 1 - i];
+                v[i] = x[i] - x[N - 1 - i];
+            });
+            FastDct<H>::dct2_open(u);
+            FastDct<H>::dct4_open(v);
+            static_for<0, H>([&](auto i) {
+                x[2 * i] = u[i];
+                x[2 * i + 1] = v[i];
+            });
+        }
+    }
+    static __device__ __forceinline__ void dct4_open(float (&x)[N]) {
+        if constexpr (N == 1) {
+            return;
+        } else if constexpr (N == 3) {
+            const float a = x[0], b = x[1], d = x[2];
+            x[0] = fmaf(kCosPi12, a, fmaf(kCosPi4, b, kCos5Pi12 * d));
+            x[1] = a - b - d;
+            x[2] = fmaf(kCos5Pi12, a, fmaf(-kCosPi4, b, kCosPi12 * d));
+        } else {
+            dct4(x);
+        }
+    }
+    static __device__ __forceinline__ void dct2_close(float (&x)[N]) {
+        static_for<0, N>([&](auto i) {
+            constexpr float f = dct2_factor(i);
+            if constexpr (f != 1.0f) x[i] *= f;
+        });
+    }
+
     static __device__ __forceinline__ void dct4(float (&x)[N]) {
         if constexpr (N == 1) {
             x[0] *= kCosPi4;

@@ -129,8 +129,35 @@ __device__ __forceinline__ void lds_to_regs_reversed(const float* src, float (&v
     }
 }
 
+// The sums A_i + B_j and differences A_i - B_j that end (and, in the inverse, begin) the split of
+// the DCT-IV over classes 2 and 3.  FUSED: a and b come from dct2_open, and where one of them still
+// lacks its last multiplication, that and the addition round once.  This is how the compiler
+// rounds them inside FastDct::dct4, hence in the two-lanes-per-chunk kernels, which hold both
+// operands in one lane; the narrow payload formats keep their results by it (rounded twice,
+// values differ in the last bit, and from a chunk's second call on so do near ties: chunk 128,
+// 192, 256 with 16-bit values, 12 M parameters, fourth call: up to 4 chunks).
+template <int Q, bool FUSED, int I, int J>
+__device__ __forceinline__ float class_sum(float a, float b) {
+    constexpr float fa = FUSED ? FastDct<Q>::dct2_factor(I) : 1.0f;
+    constexpr float fb = FUSED ? FastDct<Q>::dct2_factor(J) : 1.0f;
+    if constexpr (fa != 1.0f && fb != 1.0f) return fmaf(a, fa, b * fb);
+    else if constexpr (fa != 1.0f) return fmaf(a, fa, b);
+    else if constexpr (fb != 1.0f) return fmaf(b, fb, a);
+    else return a + b;
+}
+template <int Q, bool FUSED, int I, int J>
+__device__ __forceinline__ float class_difference(float a, float b) {
+    constexpr float fa = FUSED ? FastDct<Q>::dct2_factor(I) : 1.0f;
+    constexpr float fb = FUSED ? FastDct<Q>::dct2_factor(J) : 1.0f;
+    if constexpr (fa != 1.0f && fb != 1.0f) return fmaf(a, fa, -(b * fb));
+    else if constexpr (fa != 1.0f) return fmaf(a, fa, -b);
+    else if constexpr (fb != 1.0f) return fmaf(b, -fb, a);
+    else return a - b;
+}
+
 // ---- forward: the lane's class of coefficients (unscaled) from the chunk's row
-template <int S, int W>
+// (FUSED: classes 2 and 3 without the multiplications that class_sum does)
+template <int S, int W, bool FUSED = false>
 __device__ __forceinline__ void split_forward_local(const float* __restrict__ row, int w,
                                                     float (&c)[S / W]) {
     constexpr int Q = S / W;
@@ -174,15 +201,21 @@ __device__ __forceinline__ void split_forward_local(const float* __restrict__ ro
                 }
             });
         });
-        if (w == 1) FastDct<Q>::dct4(c);
-        else FastDct<Q>::dct2(c);
+        if (w == 1) {
+            FastDct<Q>::dct4(c);
+        } else if constexpr (FUSED) {
+            FastDct<Q>::dct2_open(c);
+            if (w == 0) FastDct<Q>::dct2_close(c);
+        } else {
+            FastDct<Q>::dct2(c);
+        }
     }
 }
 
 // W = 4: classes 2 and 3 hold A and B; after this class 2 holds the coefficients 4m+1 and
 // class 3 the coefficients 4m+3.  The tile rows must be free; contains workgroup barriers,
 // every wavefront calls it.
-template <int S>
+template <int S, bool FUSED = false>
 __device__ __forceinline__ void split_forward_exchange(float* __restrict__ row, int w,
                                                        float (&c)[S / 4]) {
     constexpr int Q = S / 4;
@@ -192,12 +225,14 @@ __device__ __forceinline__ void split_forward_exchange(float* __restrict__ row, 
         // c[l] = A[l] + B[Q-l] for l >= 1
         float br[Q];
         lds_to_regs_reversed<Q>(row + Q, br);        // br[i] = B[Q-1-i]
-        static_for<1, Q>([&](auto l) { c[l] += br[l - 1]; });
+        static_for<1, Q>([&](auto l) { c[l] = class_sum<Q, FUSED, l, Q - l>(c[l], br[l - 1]); });
     } else if (w == 3) {
         // c[l] = A[l+1] - B[Q-1-l] for l < Q-1, c[Q-1] = -B[0]
         float a[Q], d[Q];
         lds_to_regs<Q>(row, a);
-        static_for<0, Q - 1>([&](auto l) { d[l] = a[l + 1] - c[Q - 1 - l]; });
+        static_for<0, Q - 1>([&](auto l) {
+            d[l] = class_difference<Q, FUSED, l + 1, Q - 1 - l>(a[l + 1], c[Q - 1 - l]);
+        });
         d[Q - 1] = -c[0];
 #pragma unroll
         for (int l = 0; l < Q; ++l) c[l] = d[l];
@@ -208,7 +243,7 @@ __device__ __forceinline__ void split_forward_exchange(float* __restrict__ row, 
 // ---- inverse: the classes' scaled coefficients back into the rows as [E | O] (W = 2) or
 // [E (128) | O even (64) | O odd (64)] (W = 4), ready for split_output.  Contains workgroup
 // barriers; the rows must be free on entry.
-template <int S, int W>
+template <int S, int W, bool FUSED = false>
 __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, int w,
                                                       float (&c)[S / W]) {
     constexpr int Q = S / W;
@@ -256,7 +291,8 @@ __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, i
                     r[j] = (w == 2) ? av : ((j % 2) ? -bv : bv);
                 });
             });
-            FastDct<Q>::dct2(r);
+            if constexpr (FUSED) FastDct<Q>::dct2_open(r);
+            else FastDct<Q>::dct2(r);
 #pragma unroll
             for (int j = 0; j < Q; ++j) c[j] = r[j];
         }
@@ -280,11 +316,15 @@ __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, i
             float br[Q];
             lds_to_regs_reversed<Q>(row + 3 * Q, br);                    // br[i] = B[63-i]
             f[0] = c[0];
-            static_for<1, Q>([&](auto l) { f[l] = c[l] + br[l - 1]; });   // O[2l]
+            static_for<1, Q>([&](auto l) {                                // O[2l]
+                f[l] = class_sum<Q, FUSED, l, Q - l>(c[l], br[l - 1]);
+            });
         } else {
             float a[Q];
             lds_to_regs<Q>(row + 2 * Q, a);
-            static_for<0, Q - 1>([&](auto l) { f[l] = a[l + 1] - c[Q - 1 - l]; });   // O[2l+1]
+            static_for<0, Q - 1>([&](auto l) {                            // O[2l+1]
+                f[l] = class_difference<Q, FUSED, l + 1, Q - 1 - l>(a[l + 1], c[Q - 1 - l]);
+            });
             f[Q - 1] = -c[0];
         }
         __syncthreads();
@@ -378,6 +418,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     using G = SplitGeom<S, W>;
     constexpr int Q = G::Q, kRow = G::kRow, NW = G::NW, kThreads = G::kThreads;
     constexpr int kIdx0 = G::kIdx0, kTile = G::kTile;
+    constexpr bool kFused = W == 4 && NARROW && !SCHEME;   // (class_sum)
     // a launch with the partial sort has k <= TOP: the dump slots fit into the rows
     constexpr bool kRowDumps = TOP > 0 && TOP <= G::kRowDumpMaxK;
     __shared__ __attribute__((aligned(16))) float buf[kRowDumps ? G::kTile : G::kBufFloats];
@@ -460,9 +501,9 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     const bool dct = !SCHEME || p.use_dct;
     const float alpha0 = dct ? p.alpha0 : 1.0f, alpha = dct ? p.alpha : 1.0f;
     if (dct) {
-        split_forward_local<S, W>(row, w, c);
+        split_forward_local<S, W, kFused>(row, w, c);
         __syncthreads();                          // every class has read the chunk: rows free
-        if constexpr (W == 4) split_forward_exchange<S>(row, w, c);
+        if constexpr (W == 4) split_forward_exchange<S, kFused>(row, w, c);
         c[0] *= (w == 0) ? p.alpha0 : p.alpha;
 #pragma unroll
         for (int m = 1; m < Q; ++m) c[m] *= p.alpha;
@@ -812,7 +853,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
 
     // ---- new momentum = inverse transform of the remainder
     if (dct) {
-        split_inverse_to_rows<S, W>(row, w, c);
+        split_inverse_to_rows<S, W, kFused>(row, w, c);
     } else {
 #pragma unroll
         for (int m = 0; m < Q; ++m) row[W * m + off] = c[m];

@@ -223,3 +223,30 @@ def test_results_do_not_depend_on_alignment(H, s, k, fmt):
     torch.cuda.synchronize()
     for a, b in zip(*results):
         assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))
+
+
+@pytest.mark.parametrize("fmt", ["bf16+u8", "f16+i32", "f32+u8"])
+@pytest.mark.parametrize("s,k", [(96, 12), (128, 4), (128, 64), (192, 24), (192, 96), (256, 8), (256, 128)])
+def test_both_kernels_sum_alike(H, s, k, fmt):
+    """Narrow payloads above chunk 64 run with a wavefront per coefficient class up to k = s/2 and with
+    two lanes per chunk beyond: the same coefficients bit for bit, so that a kernel's choice does
+    not move near ties."""
+    val_dtype, idx_u8 = FORMATS[fmt]
+    n = s * 64 * 4
+    g, m, _ = make_inputs(n, seed=s + k)
+    coeffs = []
+    for kk in (k, s // 2 + 1):
+        cfg = Config(chunk=s, topk=kk, sign=True)
+        if val_dtype == oracle.F32:
+            import torch
+            from paper_2502_06728_amd import binding
+            C = n // s
+            coeff = torch.zeros(n, dtype=torch.float32, device=H.DEV)
+            binding.detonation_compress_packed(
+                H.bcfg(cfg), H.to_dev(g), H.to_dev(m), torch.zeros(C * kk, dtype=torch.uint8, device=H.DEV),
+                torch.zeros(C * kk, dtype=torch.float32, device=H.DEV), coeff)
+            torch.cuda.synchronize()
+            coeffs.append(H.to_host(coeff))
+        else:
+            coeffs.append(H.gpu_compress_packed(cfg, g, m, val_dtype, idx_u8)[3])
+    assert np.array_equal(coeffs[0].view(np.uint32), coeffs[1].view(np.uint32))
