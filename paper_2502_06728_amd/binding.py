@@ -4,17 +4,22 @@ Argument marshalling only: device tensors in, raw pointers out; every step of th
 runs in the HIP kernels.  There is no CPU fallback — if the library has not been built
 the first call raises.  The calls of a step hand their arguments to csrc/marshal.c first, which
 checks and converts what a program usually passes without ctypes; what it does not take goes
-through the checks below, which name what is wrong.
+through the checks below, which name what is wrong, and so does every call where it cannot be used
+(not built for this interpreter, a torch without the functions that it asks for the stream).
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import sysconfig
 from dataclasses import dataclass
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # DETONATION_LIB points the binding at another build of the same library
 LIB_PATH = os.environ.get("DETONATION_LIB", os.path.join(_HERE, "libdetonation.so"))
+# (named after the interpreter that it was compiled for: another one does not find it)
+MARSHAL_PATH = os.path.join(_HERE, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 SCHEME_TOPK, SCHEME_STRIDE, SCHEME_RANDOM = 0, 1, 2
 F32, BF16, F16, TERNARY = 0, 1, 2, 3
@@ -81,7 +86,17 @@ class DetonationError(RuntimeError):
 
 
 _lib = None
-_marshal = None     # csrc/marshal.c, set up by load()
+_marshal = None     # csrc/marshal.c, or _NoMarshal; set by load() or by the first call of a step
+
+
+class _NoMarshal:
+    """Leaves every call to the checks of this module."""
+
+    @staticmethod
+    def compress(*args) -> int:
+        return -1
+
+    decompress = compress
 
 
 def load() -> ctypes.CDLL:
@@ -121,22 +136,30 @@ def load() -> ctypes.CDLL:
         lib.detonation_status_string.argtypes = [ctypes.c_int]
         lib.detonation_status_string.restype = ctypes.c_char_p
         lib.detonation_version.restype = ctypes.c_int
-        _load_marshal(lib)
         _lib = lib
+        if "torch" in sys.modules:
+            _marshalling()
     return _lib
 
 
-def _load_marshal(lib) -> None:
+def _marshalling():
     global _marshal
+    lib = load()
+    if _marshal is None:
+        try:
+            _marshal = _load_marshal(lib)
+        except (ImportError, OSError, AttributeError):
+            _marshal = _NoMarshal
+    return _marshal
+
+
+def _load_marshal(lib):
     import importlib.machinery
     import importlib.util
 
     import torch
-    path = os.path.join(_HERE, "_marshal.so")
-    if not os.path.exists(path):
-        raise RuntimeError(f"{path} is missing: run `python -m paper_2502_06728_amd.build`")
-    loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
-    spec = importlib.util.spec_from_file_location("_marshal", path, loader=loader)
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL_PATH)
+    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH, loader=loader)
     m = importlib.util.module_from_spec(spec)
     loader.exec_module(m)
     m.setup(*(ctypes.cast(f, ctypes.c_void_p).value
@@ -144,12 +167,7 @@ def _load_marshal(lib) -> None:
                         lib.detonation_decompress_adamw_step_packed)),
             torch.float32, torch.bfloat16, torch.float16, torch.int32, torch.uint8,
             torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
-    _marshal = m
-
-
-def _marshalling():
-    load()
-    return _marshal
+    return m
 
 
 def status_string(status: int) -> str:

@@ -2,15 +2,18 @@
 from __future__ import annotations
 
 import os
+import shlex
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OBJ = os.path.join(_HERE, "_build")
 LIB = os.path.join(_HERE, "libdetonation.so")
-MARSHAL = os.path.join(_HERE, "_marshal.so")
+# (the interpreter's own suffix: binding.MARSHAL_PATH)
+MARSHAL = os.path.join(_HERE, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 MEMBENCH = os.path.join(_HERE, "membench")
 
 HIPCC_FLAGS = [
@@ -46,10 +49,16 @@ UNITS = [
 
 
 def _build_marshal(verbose: bool) -> None:
-    """The binding's argument marshalling (host code, CPython's C API)."""
-    import sysconfig
-    _run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
-          "-o", MARSHAL, os.path.join(CSRC, "marshal.c")], verbose)
+    """The binding's argument marshalling (host code, CPython's C API).  Without a C compiler or
+    Python.h the binding does all of it in Python, so that is no error."""
+    if os.path.exists(MARSHAL):
+        os.remove(MARSHAL)
+    try:
+        _run([*shlex.split(os.environ.get("CC", "cc")), "-O2", "-Wall", "-shared", "-fPIC",
+              "-I" + sysconfig.get_paths()["include"], "-o", MARSHAL,
+              os.path.join(CSRC, "marshal.c")], verbose)
+    except (OSError, RuntimeError) as e:
+        print(f"marshal.c is not compiled, the binding goes without it: {e}", file=sys.stderr)
 
 
 def _run(cmd: list[str], verbose: bool) -> None:
@@ -57,7 +66,7 @@ def _run(cmd: list[str], verbose: bool) -> None:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed:\n{res.stderr}")
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n{res.stderr}")
     # the host pass warns that it does not know the packed-fp32 feature: harmless
     err = "\n".join(l for l in res.stderr.splitlines()
                     if "packed-fp32-ops" not in l and "loop not unrolled" not in l)

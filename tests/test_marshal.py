@@ -1,6 +1,9 @@
 """The native argument marshalling of the binding (csrc/marshal.c) without a GPU: what it hands to the
 library for ordinary calls, and that it leaves everything else to the binding's own checks."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -137,3 +140,59 @@ def test_everything_else_is_left_to_the_checks(calls):
         binding.detonation_compress(cfg, torch.zeros(N), torch.zeros(N), idx.t, val.t)
     with pytest.raises(ValueError, match="at least"):
         binding.detonation_compress(cfg, on(N), on(N), idx, on(3))
+
+
+@pytest.fixture
+def unloaded(monkeypatch):
+    """The binding as it is before its first call."""
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_marshal", None)
+    return monkeypatch
+
+
+def goes_through_the_checks():
+    cfg = binding.Config(chunk=S, topk=K)
+    assert binding.version() >= 1007 and binding.payload_entries(cfg, N) == C * K
+    idx, val = torch.zeros(C * K, dtype=torch.int32), torch.zeros(C * K)
+    for f in (binding.detonation_compress, binding.detonation_compress_packed):
+        with pytest.raises(ValueError, match="contiguous device tensors"):
+            f(cfg, torch.zeros(N), torch.zeros(N), idx, val)
+        with pytest.raises(ValueError, match="at least"):
+            f(cfg, on(N), on(N), on(C * K, torch.int32), on(3))
+    for f in (binding.detonation_decompress_step, binding.detonation_decompress_step_packed):
+        with pytest.raises(ValueError, match="at least"):
+            f(cfg, 2, on(C * K, torch.int32), on(C * K), on(N))
+
+
+def test_works_without_the_compiled_marshalling(unloaded, tmp_path):
+    """Not compiled for this interpreter, or not loadable by it."""
+    unloaded.setattr(binding, "MARSHAL_PATH", str(tmp_path / "absent.so"))
+    goes_through_the_checks()
+    assert not hasattr(binding._marshal, "setup")
+    (tmp_path / "broken.so").write_bytes(b"no library")
+    unloaded.setattr(binding, "MARSHAL_PATH", str(tmp_path / "broken.so"))
+    unloaded.setattr(binding, "_marshal", None)
+    goes_through_the_checks()
+
+
+def test_works_without_torch_stream_functions(unloaded):
+    unloaded.delattr(torch._C, "_cuda_getCurrentRawStream")
+    goes_through_the_checks()
+
+
+def test_loading_the_library_needs_no_torch():
+    code = ("import sys; from paper_2502_06728_amd import binding as b; "
+            "assert b.version() >= 1007 and b.payload_entries(b.Config(), 100) == 16; "
+            "assert 'torch' not in sys.modules; import torch; assert hasattr(b._marshalling(), 'setup')")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=os.path.dirname(os.path.dirname(__file__)))
+
+
+def test_building_needs_no_c_compiler(monkeypatch, tmp_path, capsys):
+    from paper_2502_06728_amd import build
+    target = tmp_path / "m.so"
+    monkeypatch.setattr(build, "MARSHAL", str(target))
+    for cc in ("false", "no-such-compiler"):
+        target.write_bytes(b"of an earlier build")
+        monkeypatch.setenv("CC", cc)
+        build._build_marshal(False)
+        assert not target.exists() and "not compiled" in capsys.readouterr().err
