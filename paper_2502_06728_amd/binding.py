@@ -142,6 +142,8 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
+# (the fast calls take Config and AdamW themselves: a class of the caller's may say something else in
+# its c(), which only the ctypes calls ask)
 def _marshalling():
     global _marshal
     lib = load()
@@ -298,7 +300,7 @@ def detonation_compress(cfg: Config, grad, momentum, idx_out, val_out, coeff_dbg
                         stream=None, n: int | None = None) -> None:
     """Enqueue the compress half on `stream`.  momentum, idx_out, val_out (and coeff_dbg)
     are written in place by the kernels."""
-    if coeff_dbg is None:
+    if coeff_dbg is None and type(cfg) is Config:
         rc = (_marshal or _marshalling()).compress(cfg, n, grad, momentum, idx_out, val_out, False,
                                                    _handle(stream))
         if rc == 0:
@@ -321,7 +323,8 @@ def detonation_decompress_step(cfg: Config, R: int, idx, val, params, presign_db
                                val_replica_stride: int | None = None) -> None:
     """Enqueue the decompress-and-update half on `stream`.  idx/val hold R payloads
     (replica r at offset r*stride); params is updated in place."""
-    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None and \
+            type(cfg) is Config:
         rc = (_marshal or _marshalling()).decompress(
             cfg, n, R, idx, val, params, False, _handle(stream))
         if rc == 0:
@@ -359,7 +362,7 @@ def detonation_compress_packed(cfg: Config, grad, momentum, idx_out, val_out, co
                                stream=None, n: int | None = None) -> None:
     """Compress half with the payload format given by the output tensors' dtypes: indices
     int32 or uint8, values float32, bfloat16, float16, or int32 words of the ternary payload."""
-    if coeff_dbg is None:
+    if coeff_dbg is None and type(cfg) is Config:
         rc = (_marshal or _marshalling()).compress(cfg, n, grad, momentum, idx_out, val_out, True,
                                                    _handle(stream))
         if rc == 0:
@@ -382,7 +385,8 @@ def detonation_decompress_step_packed(cfg: Config, R: int, idx, val, params, pre
                                       idx_replica_stride: int | None = None,
                                       val_replica_stride: int | None = None) -> None:
     """Decompress-and-update half for payloads in the format given by the tensors' dtypes."""
-    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None and \
+            type(cfg) is Config:
         rc = (_marshal or _marshalling()).decompress(
             cfg, n, R, idx, val, params, True, _handle(stream))
         if rc == 0:
@@ -413,7 +417,8 @@ def detonation_decompress_adamw_step(cfg: Config, opt: AdamW, R: int, idx, val, 
                                      val_replica_stride: int | None = None) -> None:
     """Decompress half with Decoupled AdamW as the underlying optimizer; params and the moment
     tensors are updated in place."""
-    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None and \
+            type(cfg) is Config and type(opt) is AdamW:
         rc = (_marshal or _marshalling()).decompress(
             cfg, n, R, idx, val, params, False, _handle(stream),
             opt, exp_avg, exp_avg_sq, max_exp_avg_sq)
@@ -444,7 +449,8 @@ def detonation_decompress_adamw_step_packed(cfg: Config, opt: AdamW, R: int, idx
                                             idx_replica_stride: int | None = None,
                                             val_replica_stride: int | None = None) -> None:
     """Decoupled AdamW on payloads in the format given by the tensors' dtypes."""
-    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None:
+    if presign_dbg is None and idx_replica_stride is None and val_replica_stride is None and \
+            type(cfg) is Config and type(opt) is AdamW:
         rc = (_marshal or _marshalling()).decompress(
             cfg, n, R, idx, val, params, True, _handle(stream),
             opt, exp_avg, exp_avg_sq, max_exp_avg_sq)

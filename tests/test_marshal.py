@@ -196,3 +196,44 @@ def test_building_needs_no_c_compiler(monkeypatch, tmp_path, capsys):
         monkeypatch.setenv("CC", cc)
         build._build_marshal(False)
         assert not target.exists() and "not compiled" in capsys.readouterr().err
+
+
+def test_a_class_with_its_own_c_is_asked(monkeypatch):
+    """A Config or AdamW of the caller's that computes what it passes on (a schedule, say)."""
+    class Halved(binding.Config):
+        def c(self):
+            c = super().c()
+            c.lr *= 0.5
+            return c
+
+    class Later(binding.AdamW):
+        def c(self):
+            o = super().c()
+            o.step += 1
+            return o
+
+    seen = []
+
+    class Lib:
+        def __getattr__(self, name):
+            def f(*args):
+                seen.append((name, [a._obj for a in args if hasattr(a, "_obj")]))
+                return 0
+            return f
+
+    binding.load()
+    monkeypatch.setattr(binding, "load", lambda: Lib())
+    monkeypatch.setattr(binding, "payload_entries", lambda cfg, n: C * K)
+    idx, val = on(C * K, torch.int32), on(C * K)
+    cfg, opt = Halved(chunk=S, topk=K, lr=1.0), Later(step=4)
+    plain = binding.Config(chunk=S, topk=K)
+    for pk in ("", "_packed"):
+        getattr(binding, "detonation_compress" + pk)(cfg, on(N), on(N), idx, val, stream=7)
+        getattr(binding, "detonation_decompress_step" + pk)(cfg, 1, idx, val, on(N), stream=7)
+        ada = getattr(binding, "detonation_decompress_adamw_step" + pk)
+        ada(cfg, binding.AdamW(), 1, idx, val, on(N), on(N), on(N), stream=7)
+        assert [c[0].lr for _, c in seen] == [0.5] * 3
+        seen.clear()
+        ada(plain, opt, 1, idx, val, on(N), on(N), on(N), stream=7)
+        assert [c[1].step for _, c in seen] == [5]
+        seen.clear()
