@@ -72,6 +72,24 @@ def oracle_payloads(cfg, n, val_dtype, R, seed):
     return np.stack([p[0] for p in pays]), np.stack([p[1] for p in pays])
 
 
+def check_presign(cfg, n, idx, val, val_dtype, y):
+    """The averaged update before the sign against the oracle's, on the scale of the chunk's result and
+    of its largest payload value (the sum over replicas can cancel)."""
+    s, k, C = cfg.chunk, cfg.topk, -(-n // cfg.chunk)
+    if val_dtype == oracle.TERNARY:
+        want, decoded = oracle.presign_t(cfg, n, idx, val), np.ones((1, C, k))
+    elif val_dtype == oracle.F32:
+        want, decoded = oracle.presign(cfg, n, idx, val), val
+    else:
+        want = oracle.presign_q(cfg, n, idx, val, val_dtype)
+        decoded = ((val.astype(np.uint32) << 16).view(np.float32) if val_dtype == oracle.BF16
+                   else val.view(np.float16).astype(np.float32))
+    largest = np.abs(decoded.astype(np.float64).reshape(-1, C, k)).max(axis=(0, 2))
+    scale = np.maximum(np.repeat(largest, s)[:n], parity.parity_chunk_max(want, s))
+    err = parity.rel_chunk_err(y, want, s, scale=scale)
+    assert err <= parity.TOL_F32, f"pre-sign update differs: {err:.3e}"
+
+
 def check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=None):
     """Decompress on the device and judge it by the oracle on the same payload bytes."""
     import torch
@@ -99,7 +117,9 @@ def check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=None):
     binding.detonation_decompress_adamw_step_packed(H.bcfg(cfg), opt, R, i, v, p, ma, va,
                                                     vm if adam else None, y)
     torch.cuda.synchronize()
-    # Q as the device computed it (its own test is the plain update above) drives the oracle
+    # (AdamW may run on other kernels than the plain update: its pre-sign update has its own check)
+    check_presign(cfg, n, idx, val, val_dtype, H.to_host(y))
+    # Q as the device computed it drives the oracle
     th_o, m_o, v_o, vm_o = oracle.adamw_update(cfg, oracle.AdamW(0.9, 0.95, 1e-8, adam, 3),
                                                H.to_host(y), th, m0, v0, v0)
     assert np.abs(H.to_host(ma) - m_o).max() <= 1e-5 * np.abs(m_o).max()
