@@ -208,7 +208,8 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
             // per chunk (other formats), anything else on the matrix-core kernel, which takes
             // the leading multiple of 32 chunks
             c0 = deto::launch_compress_split(a);
-            if (c0 == 0 && !stride_stream) c0 = deto::launch_compress_split_scheme(a);
+            if (c0 == 0 && !stride_stream && !deto::few_chunks(p, C))
+                c0 = deto::launch_compress_split_scheme(a);
             if (c0 == 0) c0 = deto::launch_compress_pair(a);
             if (c0 == 0) c0 = deto::launch_compress_mfma(a);
             if (c0 > 0) {
@@ -351,13 +352,14 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
                                  val_replica_stride, params, param_dtype == DETO_BF16, presign_dbg,
                                  {0, 0, 0, 0}, st, adam};
         stride_pattern(p, a.stride_mask);
-        auto split = [](const deto::DecompressLaunch& d, int classes) -> int64_t {
-            if (classes == 0) return 0;
+        const bool few = deto::few_chunks_decompress(p, C, idx != nullptr);
+        auto split = [few](const deto::DecompressLaunch& d, int classes) -> int64_t {
+            if (few || classes == 0) return 0;
             const int64_t c = deto::launch_decompress_split(d, classes);
             return c ? c : deto::launch_decompress_split_narrow(d, classes);
         };
-        auto split_scheme = [](const deto::DecompressLaunch& d, int classes) -> int64_t {
-            return classes ? deto::launch_decompress_split_scheme(d, classes) : 0;
+        auto split_scheme = [few](const deto::DecompressLaunch& d, int classes) -> int64_t {
+            return (classes && !few) ? deto::launch_decompress_split_scheme(d, classes) : 0;
         };
         // a lane per chunk or a wavefront per coefficient class
         if (idx)

@@ -216,6 +216,30 @@ inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lan
     return (large && plain && rk >= 2 * p.s) ? 2 : 0;
 }
 
+// Few chunks: a launch of the wavefront-per-class kernels is then a handful of workgroups whose own
+// duration counts, while the general kernels spread the same chunks over the whole chip, a wavefront
+// each.  Those are 8 - 10 KB of LDS a workgroup, 16 - 20 per CU: some 5,000 chunks are one occupancy
+// round.  So they serve less than a tile (20 chunks of 64, k 21, R = 16, signs: 10 against 28 us;
+// 20 of 256, Random, k 128, R = 2: 16 against 30), and up to about a round what gives them little
+// to do per chunk: no transform (Striding and Random on the momentum itself), and two-bit signs of
+// many replicas, whose scatter the few wavefronts would do one step after the other.  us, general / wavefront per class, 0.3 M parameters (1,172 chunks of 256 ... 4,688 of 64),
+// signs: compress Striding 64/2 7 / 8, 96/48 6 / 10, 128/64 6 / 12, 256/128 7 / 18, Random 128/16
+// 8 / 10, 128/64 15 / 15, 256/128 22 / 26; decompress Random 128/16 R = 2 9 / 10, 256/128 23 / 32,
+// 256/8 R = 16 14 / 11; AdamW 128/64 R = 2 18 / 21, R = 16 33 / 24; top-k R = 16 128/42 30 / 53,
+// 256/85 50 / 102, 96/32 28 / 25.  1 M: compress 128/16 12 / 10, 256/32 10 / 14; AdamW 128/16
+// 17 / 11, 256/32 R = 2 14 / 16; top-k R = 16 128/42 77 / 59.
+inline bool few_chunks(const KParams& p, int64_t chunks) {   // compress (Striding, Random)
+    if (chunks < kWave) return true;
+    // (a shuffle of more than a quarter of the chunk is a long serial chain in the general kernel)
+    return !p.use_dct && chunks <= ((p.scheme == 2 && 4 * p.k > p.s) ? 2048 : 5120);
+}
+inline bool few_chunks_decompress(const KParams& p, int64_t chunks, bool idx) {
+    if (chunks < kWave) return true;
+    if (idx)
+        return p.val_dtype == 3 && chunks <= 2560 && static_cast<int64_t>(p.R) * p.k >= 4 * p.s;
+    return !p.use_dct && p.s >= 96 && p.R < 8 && chunks <= (p.adam ? 4096 : 2560);
+}
+
 inline int64_t launch_compress_split(const CompressLaunch& a) {
     int64_t c = launch_compress_split_96(a);
     if (!c) c = launch_compress_split_128(a);

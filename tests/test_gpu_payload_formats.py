@@ -190,6 +190,21 @@ def test_striding_and_random(H, s, k, dct, scheme, fmt):
     check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=bool(k % 3 == 0))
 
 
+@pytest.mark.parametrize("fmt", ["f32+i32", "bf16+u8", "signs+u8"])
+@pytest.mark.parametrize("scheme", [oracle.SCHEME_STRIDE, oracle.SCHEME_RANDOM])
+@pytest.mark.parametrize("s,k", [(64, 2), (96, 12), (128, 16), (128, 64), (192, 5), (256, 127)])
+def test_striding_and_random_on_many_chunks(H, s, k, scheme, fmt):
+    """In the raw domain up to 5,120 chunks stay on the general kernels: more than that."""
+    val_dtype, idx_u8 = FORMATS.get(fmt, (oracle.F32, False))
+    n = s * (64 * 81 + 37) + s // 3
+    cfg = Config(chunk=s, topk=k, scheme=scheme, sign=True, lr=1e-3, seed=11, step=5)
+    g, m, th = make_inputs(n, seed=s + k, params_bf16=k % 2 == 0)
+    compress_case(H, cfg, g, m, val_dtype, idx_u8)
+    idx, val = oracle_payloads(cfg, n, val_dtype, 3, 300)
+    check_update(H, cfg, idx, val, val_dtype, idx_u8, th)
+    check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=bool(k % 3 == 0))
+
+
 @pytest.mark.parametrize("s,k", [(128, 16), (64, 5), (256, 40)])
 def test_random_without_index_output(H, s, k):
     """No index array at all, and a caller that passes indices in the raw domain."""
