@@ -335,6 +335,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
     // size and k without a lane-per-chunk kernel
     const bool stride_stream =
         !idx && p.scheme == DETO_SCHEME_STRIDE && !p.use_dct && val_dtype == DETO_F32;
+    const bool stream_first = stride_stream && deto::stream_before_classes(p);
     int64_t c0 = 0;
     const int64_t tiles = (n / p.s) / deto::kWave;
     // every replica's array must keep the alignment of a lane's access (four entries when k is
@@ -364,7 +365,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         // a lane per chunk or a wavefront per coefficient class
         if (idx)
             c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, true));
-        else if (!stride_stream)
+        else if (!stream_first)
             c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, true));
         const bool done = (c0 > 0 || tiles == 0) ? false
                           : idx ? (deto::launch_decompress_idx_s64(a) ||
@@ -387,7 +388,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
             // no lane-per-chunk kernel for this (s, k, format)
             if (c0 == 0 && idx)
                 c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, false));
-            if (c0 == 0 && !idx && !stride_stream)
+            if (c0 == 0 && !idx && !stream_first)
                 c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, false));
             if (c0 == 0) c0 = deto::launch_decompress_mfma(a);
             if (c0 > 0) {

@@ -216,6 +216,14 @@ inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lan
     return (large && plain && rk >= 2 * p.s) ? 2 : 0;
 }
 
+// Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the
+// wavefront-per-class kernels?  Not for AdamW at chunk sizes up to 64: those have the sums over the
+// replicas in registers, four values a load, where the stream gathers them element by element.
+// us, stream / wavefront per class: 64/8, bf16 parameters, R = 2 1 M 14.6 / 7.8, 30 M 144 / 110,
+// R = 16 361 / 142; fp32 R = 2 30 M 137 / 133.  At larger chunks the stream is ahead with fp32
+// parameters and few replicas: 128/4 R = 2 30 M 130 / 141, 256/32 1 M 12.8 / 15.5.
+inline bool stream_before_classes(const KParams& p) { return !(p.adam && p.s <= 64); }
+
 // Few chunks: a launch of the wavefront-per-class kernels is then a handful of workgroups whose own
 // duration counts, while the general kernels spread the same chunks over the whole chip, a wavefront
 // each.  Those are 8 - 10 KB of LDS a workgroup, 16 - 20 per CU: some 5,000 chunks are one occupancy

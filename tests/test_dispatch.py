@@ -23,6 +23,7 @@ extern "C" int few(const int* a, int64_t chunks) { return deto::few_chunks(param
 extern "C" int few_decompress(const int* a, int64_t chunks) {
     return deto::few_chunks_decompress(params(a), chunks, a[4] == 0);
 }
+extern "C" int stream_first(const int* a, int64_t) { return deto::stream_before_classes(params(a)); }
 """
 
 
@@ -70,3 +71,8 @@ def test_a_round_of_chunks_without_a_transform_goes_to_the_general_kernels(rules
     assert not rules("few_decompress", 128, 42, 2561, 16, SIGNS)
     assert not rules("few_decompress", 128, 42, 2560, 2, SIGNS)
     assert not rules("few_decompress", 128, 42, 2560, 16, F16)
+
+
+def test_adamw_striding_streams_at_the_larger_chunks_only(rules):
+    for s, adam, stream in ((64, 0, True), (32, 1, False), (64, 1, False), (96, 1, True), (192, 1, True)):
+        assert bool(rules("stream_first", s, s // 8, 0, 2, F32, STRIDE, False, adam)) == stream
