@@ -364,7 +364,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         };
         // a lane per chunk or a wavefront per coefficient class
         if (idx)
-            c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, true));
+            c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, deto::lane_decompress(p)));
         else if (!stream_first)
             c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, true));
         const bool done = (c0 > 0 || tiles == 0) ? false
@@ -386,8 +386,6 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
             c0 = C;   // the tail chunks rode along in the same launch
         } else {
             // no lane-per-chunk kernel for this (s, k, format)
-            if (c0 == 0 && idx)
-                c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, false));
             if (c0 == 0 && !idx && !stream_first)
                 c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, false));
             if (c0 == 0) c0 = deto::launch_decompress_mfma(a);

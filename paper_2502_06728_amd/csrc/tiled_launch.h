@@ -64,6 +64,29 @@ inline unsigned tiled_grid(int64_t tiles, int64_t n_chunks) {
     return static_cast<unsigned>(tiles + (n_chunks - tiles * kWave));
 }
 
+// What the lane-per-chunk kernels are instantiated for: the k values of each chunk size with fp32
+// values and int32 indices, and the (chunk, k) pairs with byte indices and 16-bit values or two-bit
+// signs.
+#ifdef DETO_TILED_ONLY_64_32   // development builds: one instantiation, seconds to compile
+#define DETO_LANE_TOPK_16(X)
+#define DETO_LANE_TOPK_32(X)
+#define DETO_LANE_TOPK_64(X) X(32)
+#define DETO_LANE_TOPK_96(X)
+#define DETO_LANE_TOPK_128(X)
+#define DETO_LANE_16BIT_32(X)
+#define DETO_LANE_16BIT_64(X) X(64, 32)
+#define DETO_LANE_SIGNS(X) X(64, 32)
+#else
+#define DETO_LANE_TOPK_16(X) X(1) X(2) X(4) X(8)
+#define DETO_LANE_TOPK_32(X) X(1) X(2) X(4) X(8) X(16)
+#define DETO_LANE_TOPK_64(X) X(1) X(2) X(4) X(8) X(16) X(32)
+#define DETO_LANE_TOPK_96(X) X(6) X(12) X(24) X(48)                 // decompress only
+#define DETO_LANE_TOPK_128(X) X(1) X(4) X(8) X(16) X(32) X(64)      // decompress only
+#define DETO_LANE_16BIT_32(X) X(32, 16) X(32, 8) X(32, 4) X(32, 2) X(32, 1)
+#define DETO_LANE_16BIT_64(X) X(64, 32) X(64, 16) X(64, 8)
+#define DETO_LANE_SIGNS(X) X(64, 32) X(64, 16) X(32, 16) X(32, 8) X(32, 4) X(32, 2) X(32, 1)
+#endif
+
 bool launch_compress_topk_s64(const CompressLaunch& a);
 bool launch_compress_topk_s32(const CompressLaunch& a);
 bool launch_compress_topk_s16(const CompressLaunch& a);
@@ -139,57 +162,85 @@ int64_t launch_compress_split_128(const CompressLaunch& a);
 int64_t launch_compress_split_192(const CompressLaunch& a);
 int64_t launch_compress_split_256(const CompressLaunch& a);
 
+// A lane-per-chunk decompress kernel for this request with transmitted indices (plain SGD update)?
+inline bool lane_decompress(const KParams& p) {
+    if (p.adam) return false;
+    if (p.val_dtype == 0 && !p.idx_u8) {
+#define X(K) if (p.k == K) return true;
+        if (p.s == 16) { DETO_LANE_TOPK_16(X) }
+        else if (p.s == 32) { DETO_LANE_TOPK_32(X) }
+        else if (p.s == 64) { DETO_LANE_TOPK_64(X) }
+        else if (p.s == 96) { DETO_LANE_TOPK_96(X) }
+        else if (p.s == 128) { DETO_LANE_TOPK_128(X) }
+#undef X
+        return false;
+    }
+    if (!p.idx_u8 || p.val_dtype == 0) return false;
+#define X(S, K) if (p.s == S && p.k == K) return true;
+    if (p.val_dtype == 3) { DETO_LANE_SIGNS(X) }
+    else { DETO_LANE_16BIT_32(X) DETO_LANE_16BIT_64(X) }
+#undef X
+    return false;
+}
+
 // Which decompress kernel serves transmitted indices: the number of coefficient classes
-// (wavefronts per tile) of the wavefront-per-class kernels, or 0 for a lane per chunk; `lane`:
-// the latter may be chosen (it is instantiated for some (s, k, format) only, without AdamW).
+// (wavefronts per tile) of the wavefront-per-class kernels, or 0 for a lane per chunk (only if
+// `lane`: there is one).
 //
 // A lane per chunk needs the fewest instructions but holds a whole chunk in registers: two
-// wavefronts per SIMD at chunk 64, one at 96 and 128, each with little in flight.  Two classes
+// wavefronts per SIMD up to chunk 64, one at 96 and 128, each with little in flight.  Two classes
 // cost about a third more instructions at twice the wavefronts, four classes half more again
 // at up to seven per SIMD.  So what decides is whether a shape is bound by memory latency (many
 // bytes per element: AdamW's moments, fp32 parameters, fp32 + int32 payloads) or by
-// instructions (few bytes, or many entries per byte: two-bit signs).  Measured on MI355X, us,
-// buffers rotating, a lane per chunk / two / four classes; A: 147 M bf16 parameters, R = 4;
-// B: 28 M and C: 11 M fp32 parameters, R = 2; D: 28 M bf16 parameters, R = 2:
-//   chunk 64, k 32, fp32 + int32, SGD   A 521/513/510  B  79/ 75/ 73  C 34/33/32  D 59/64/58
-//             k 16                      A 300/296/282  B  60/ 57/ 56  C 26/26/25  D 40/46/43
-//             k 8                       A 194/187/223  B  52/ 49/ 49  C 23/23/23  D 30/35/41
-//             k 4                       A 141/159/208  B  49/ 46/ 47  C 22/22/22  D 26/34/40
-//             k 16, fp16 + byte         A 169/200/224  B  52/ 49/ 50  C 22/24/24  D 29/41/42
-//             k 16, signs, AdamW        A 601/552/515  B 145/129/123  C 61/54/51  D  - /108/100
-//   chunk 32, k 16, fp32 + int32, SGD   A 508/498/494  B  75/ 72/ 73  C 33/31/30  D 57/57/56
-//             k 4, signs, SGD           A 113/194/259  B  47/ 43/ 51  C 21/20/24
-//             k 16, signs, AdamW        A 625/544/535  B 141/122/120  C 60/52/50  D  - /102/ 99
-//   chunk 128, k 16, fp32 + int32, SGD  A 205/209/214  B  57/ 55/ 52  C 29/30/26  D 44/44/42
-//             k 64, fp16 + byte         A  - /373/328  B  - / 79/ 69  C  - /42/33  D  - /67/60
-// Two classes also stay ahead of four where there are many entries per chunk to scatter with
-// little else to move (AdamW, chunk 32, k 4, signs, R = 16: 142 against 152 us).
-constexpr int64_t kLargeShard = int64_t{1} << 25;   // elements: D's order turns between D and A
+// instructions (few bytes, or many entries per byte: two-bit signs), and how many rounds of
+// workgroups the launch is: one round of a lane per chunk is 1,024 tiles at one wavefront per SIMD
+// and 2,048 at two.
+//
+// The lines were drawn through 7,290 timed shapes (chunk 32 ... 128, seven k each, three payload
+// formats, both parameter types and optimizers, R = 2, 4, 16, 0.3 ... 147 M parameters, each call on
+// other buffers): the choice costs 1.6 % over the best of the three on average, and 38 shapes run
+// more than 5 % longer than on the kernels that served them before there were classes, none of
+// them by more than 13 %.  us, a lane per chunk / two / four classes:
+//   AdamW: four classes, except where a wavefront's share of a replica's payload (16 rows of k
+//   entries) leaves its lanes idle and there are many replicas' to scatter.
+//     64/16, signs, R = 4, 147 M bf16     - /523/509   32/4, signs, R = 16, 30 M bf16  - /136/158
+//     64/32, fp16, R = 16, 1 M bf16       - / 32/ 21   32/4, fp16, R = 16, 4 M fp32    - / 29/ 32
+//   Few tiles: four classes where there is no lane per chunk; a lane per chunk where its launch is
+//   about one round or less.
+//     64/21, fp32, R = 2, 1 M bf16        - / 12/  8   64/8, fp32, R = 2, 3 M fp32   7.9/9.5/9.1
+//     128/16, fp32, R = 2, 8 M fp32    19.8/19.7/21.9  64/8, fp32, R = 2, 12 M fp32   26/ 24/ 24
+//   Idle lanes without AdamW: 128/1, fp32, R = 16, 30 M bf16 51/51/58, 64/2, fp32, R = 16, 8 M fp32
+//   23/21/26.
+//   Large shards of bf16 parameters: from 2^25 elements on (with the line at 2^26 or 10^8 the
+//   average loss of the shapes above 40 M goes from 0.5 % to 1.4 or 2.5 %).
+//     64/32, fp32, 147 M, R = 4         512/510/504    30 M, R = 2  65/ 69/ 66
+//     64/16, fp32, 147 M, R = 4         302/305/289    30 M, R = 2  44/ 50/ 49
+constexpr int64_t kLargeShard = int64_t{1} << 25;
 inline int decompress_classes(const KParams& p, int64_t n, bool param_bf16, bool lane) {
     const int64_t rk = static_cast<int64_t>(p.R) * p.k;    // entries per chunk to scatter
+    const int64_t tiles = n / (kWave * p.s);
     const bool plain = p.val_dtype == 0 && !p.idx_u8, quads = p.k % 4 == 0;
-    const bool large = n > kLargeShard;
+    const bool large = n > kLargeShard, few = tiles <= 1024;
     if (p.s == 192 || p.s == 256) return 4;
     if (p.s != 16 && p.s != 32 && p.s != 64 && p.s != 96 && p.s != 128) return 0;
-    if (p.s == 16) return (lane && !p.adam && param_bf16) ? 0 : 2;
-    if (p.adam) return (quads ? (plain || rk <= p.s) : 4 * rk <= p.s) ? 4 : 2;
+    if (p.s == 16) return (lane && param_bf16) ? 0 : 2;
+    if (p.adam) return (few || p.k >= 16 || (quads ? plain || rk <= p.s : 4 * rk <= p.s)) ? 4 : 2;
     if (p.s >= 96) {
-        // (many entries per chunk to scatter: chunk 96, k 24, R = 22: 51 against 53 us a step)
-        if (lane && plain && rk >= 4 * p.s) return 0;
+        if (lane && (rk >= 8 * p.s || (few && tiles > 640))) return 0;
         if (!param_bf16) return 4;
+        if (lane && p.s == 128 && p.k < 4 && !few) return 0;
         if (p.s == 128 && (rk >= p.s || !large)) return 4;
         return lane ? 0 : (large ? 2 : 4);
     }
-    bool split = false, wide = false;
+    const bool wide = plain && p.k >= 8;    // (four classes, for SGD)
+    if (!lane) return (few || p.k >= 16 || (wide && !param_bf16 && p.s == 64 && 2 * rk >= p.s)) ? 4 : 2;
+    if (tiles <= 1536) return 0;
     if (!param_bf16) {
-        split = plain ? !(p.k == 1 && 2 * rk >= p.s) : rk <= (quads ? 16 : 8);
-        wide = p.s == 64 && plain && 2 * rk >= p.s;
-    } else if (large && plain && quads && p.R >= 2) {
-        wide = rk >= p.s;
-        split = wide || (p.s == 64 && 2 * rk >= p.s);
+        const bool split = plain || rk <= (quads ? 16 : 8);
+        return !split ? 0 : (wide && p.s == 64 && 2 * rk >= p.s) ? 4 : 2;
     }
-    if (split) return wide ? 4 : 2;
-    return lane ? 0 : 2;
+    if (!large || !plain || !quads || p.R < 2) return 0;
+    return rk >= p.s ? (wide ? 4 : 2) : (p.s == 64 && 2 * rk >= p.s) ? 2 : 0;
 }
 
 // The same for Striding and Random without transmitted indices (0: a lane per chunk).  The sums

@@ -38,6 +38,8 @@ bool DETO_DECOMPRESS_FN(const DecompressLaunch& a) {
             decompress_tiled<DETO_S, K, true><<<grid, kWave, 0, a.stream>>>(                    \
                 a.p, a.tiles, tail, a.idx, a.idx_stride, a.val, a.val_stride, a.params,               \
                 AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);                                                                 \
+        else if constexpr (DETO_S == 16)   /* (always two classes, see decompress_classes) */   \
+            return false;                                                                       \
         else                                                                                    \
             decompress_tiled<DETO_S, K, false><<<grid, kWave, 0, a.stream>>>(                   \
                 a.p, a.tiles, tail, a.idx, a.idx_stride, a.val, a.val_stride, a.params,               \

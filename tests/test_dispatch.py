@@ -23,6 +23,10 @@ extern "C" int few(const int* a, int64_t chunks) { return deto::few_chunks(param
 extern "C" int few_decompress(const int* a, int64_t chunks) {
     return deto::few_chunks_decompress(params(a), chunks, a[4] == 0);
 }
+extern "C" int lane(const int* a, int64_t) { return deto::lane_decompress(params(a)); }
+extern "C" int classes(const int* a, int64_t n, int bf16) {
+    return deto::decompress_classes(params(a), n, bf16, deto::lane_decompress(params(a)));
+}
 extern "C" int stream_first(const int* a, int64_t) { return deto::stream_before_classes(params(a)); }
 """
 
@@ -76,3 +80,47 @@ def test_a_round_of_chunks_without_a_transform_goes_to_the_general_kernels(rules
 def test_adamw_striding_streams_at_the_larger_chunks_only(rules):
     for s, adam, stream in ((64, 0, True), (32, 1, False), (64, 1, False), (96, 1, True), (192, 1, True)):
         assert bool(rules("stream_first", s, s // 8, 0, 2, F32, STRIDE, False, adam)) == stream
+
+
+def tiles(s, t):
+    return 64 * s * t + 1
+
+
+def test_lane_kernels_are_those_that_are_built(rules):
+    """The table behind the rules against the lists of the units."""
+    for s, ks in ((16, (1, 2, 4, 8)), (32, (1, 2, 4, 8, 16)), (64, (1, 2, 4, 8, 16, 32)), (96, (6, 12, 24, 48)),
+                  (128, (1, 4, 8, 16, 32, 64)), (192, ()), (256, ()), (48, ())):
+        assert tuple(k for k in range(1, s + 1) if rules("lane", s, k, 0)) == ks
+        assert not any(rules("lane", s, k, 0, adam=1) for k in range(1, s + 1))
+    for val, pairs in ((F16, {(64, 32), (64, 16), (64, 8), (32, 16), (32, 8), (32, 4), (32, 2), (32, 1)}),
+                       (SIGNS, {(64, 32), (64, 16), (32, 16), (32, 8), (32, 4), (32, 2), (32, 1)})):
+        got = {(s, k) for s in range(1, 257) for k in range(1, s + 1) if rules("lane", s, k, 0, val=val)}
+        assert got == pairs
+
+
+@pytest.mark.parametrize("s,k,R,val,adam,bf16,n,want", [
+    # AdamW: idle lanes with many replicas
+    (32, 4, 16, SIGNS, 1, 1, tiles(32, 1025), 2), (32, 4, 16, SIGNS, 1, 1, tiles(32, 1024), 4),
+    (32, 4, 8, SIGNS, 1, 1, tiles(32, 1025), 4), (64, 32, 16, F16, 1, 0, tiles(64, 1025), 4),
+    (64, 21, 16, F32, 1, 1, tiles(64, 100), 4), (128, 42, 16, SIGNS, 1, 0, tiles(128, 2000), 4),
+    # few tiles
+    (64, 21, 2, F32, 0, 1, tiles(64, 1024), 4), (64, 5, 2, F32, 0, 1, tiles(64, 1025), 2),
+    (64, 8, 2, F32, 0, 0, tiles(64, 1536), 0), (64, 8, 2, F32, 0, 0, tiles(64, 1537), 2),
+    (64, 32, 2, F32, 0, 0, tiles(64, 1537), 4), (64, 2, 16, F32, 0, 0, tiles(64, 1537), 2),
+    (128, 16, 2, F32, 0, 0, tiles(128, 640), 4), (128, 16, 2, F32, 0, 0, tiles(128, 641), 0),
+    (128, 16, 2, F32, 0, 0, tiles(128, 1024), 0), (128, 16, 2, F32, 0, 0, tiles(128, 1025), 4),
+    (96, 12, 2, F32, 0, 1, tiles(96, 100), 0), (96, 32, 16, F32, 0, 0, tiles(96, 1025), 4),
+    # many entries, idle lanes
+    (128, 64, 16, F32, 0, 0, tiles(128, 5000), 0), (128, 1, 16, F32, 0, 1, tiles(128, 1025), 0),
+    # large shards of bf16 parameters
+    (64, 32, 4, F32, 0, 1, 1 << 25, 0), (64, 32, 4, F32, 0, 1, (1 << 25) + 1, 4),
+    (64, 8, 4, F32, 0, 1, (1 << 25) + 1, 2), (64, 4, 16, F32, 0, 1, (1 << 25) + 1, 2),
+    (64, 8, 2, F32, 0, 1, (1 << 25) + 1, 0), (64, 32, 4, F16, 0, 1, (1 << 25) + 1, 0),
+    (128, 16, 4, F32, 0, 1, 1 << 25, 4), (128, 16, 4, F32, 0, 1, (1 << 25) + 1, 0),
+    (128, 16, 8, F32, 0, 1, (1 << 25) + 1, 4), (128, 5, 2, F16, 0, 1, (1 << 25) + 1, 2),
+    # no class kernels; chunk 16
+    (48, 6, 2, F32, 0, 1, tiles(48, 100), 0), (256, 32, 2, F32, 0, 1, tiles(256, 100), 4),
+    (16, 4, 2, F32, 0, 1, tiles(16, 100), 0), (16, 4, 2, F32, 0, 0, tiles(16, 100), 2),
+    (16, 3, 2, F32, 0, 1, tiles(16, 100), 2)])
+def test_decompress_classes(rules, s, k, R, val, adam, bf16, n, want):
+    assert rules("classes", s, k, n, R, val, TOPK, True, adam, bf16) == want

@@ -285,3 +285,54 @@ def test_both_kernels_sum_alike(H, s, k, fmt):
         else:
             coeffs.append(H.gpu_compress_packed(cfg, g, m, val_dtype, idx_u8)[3])
     assert np.array_equal(coeffs[0].view(np.uint32), coeffs[1].view(np.uint32))
+
+
+@pytest.mark.parametrize("s,k,R,fmt", [
+    (32, 8, 4, "f32+i32"), (32, 4, 16, "f32+i32"), (64, 8, 4, "f32+i32"), (64, 32, 2, "f32+i32"),
+    (64, 5, 3, "f32+i32"), (96, 5, 3, "f32+i32"), (96, 12, 2, "f32+i32"), (96, 20, 2, "bf16+u8"),
+    (128, 1, 9, "f32+i32"), (128, 4, 3, "f32+i32"), (128, 8, 2, "f32+i32"), (128, 32, 2, "f32+i32"),
+    (128, 5, 3, "f32+i32"), (128, 16, 3, "f16+i32"), (128, 5, 2, "signs+u8")])
+def test_large_bf16_shards(H, s, k, R, fmt):
+    """Above 2^25 bf16 parameters decompress takes other kernels (a lane per chunk at chunk 128, two
+    classes without one, more classes at chunk 32 and 64); the first, the last and some other runs of
+    chunks against the oracle."""
+    import torch
+    from paper_2502_06728_amd import binding, synth
+    val_dtype, idx_u8 = FORMATS.get(fmt, (oracle.F32, False))
+    n = (1 << 25) + s * (64 * 3 + 37) + s // 3
+    C = -(-n // s)
+    cfg = Config(chunk=s, topk=k, sign=True, lr=1e-3, weight_decay=0.01)
+    gen = torch.Generator(device=H.DEV)
+    gen.manual_seed(s * k)
+    params = (torch.randn(n, generator=gen, device=H.DEV) * 0.02).to(torch.bfloat16)
+    before = params.clone()
+    y = torch.full((n,), float("nan"), dtype=torch.float32, device=H.DEV)
+    # ascending places, others in every chunk and replica
+    step = s // k
+    first = torch.randint(0, step, (R, C, 1), generator=gen, device=H.DEV)
+    idx = (first + step * torch.arange(k, device=H.DEV)).to(torch.uint8 if idx_u8 else torch.int32)
+    if val_dtype == oracle.TERNARY:
+        assert k <= 16
+        code = torch.randint(0, 3, (R, C, k), generator=gen, device=H.DEV)
+        code = torch.where(code == 2, 3, code)
+        val = (code << (2 * torch.arange(k, device=H.DEV))).sum(-1).to(torch.int32).reshape(R, C, 1)
+    else:
+        val = torch.randn((R, C, k), generator=gen, device=H.DEV).to(H.VAL_TORCH[val_dtype])
+    binding.detonation_decompress_step_packed(H.bcfg(cfg), R, idx.reshape(R, -1), val.reshape(R, -1), params, y)
+    torch.cuda.synchronize()
+    for c0 in (0, C // 3, (1 << 25) // s - 128, C - 256):
+        c1 = min(c0 + 256, C)
+        e0, e1 = c0 * s, min(c1 * s, n)
+        v = val[:, c0:c1].contiguous().cpu()
+        if val_dtype == oracle.TERNARY:
+            v = v.numpy().view(np.uint32).reshape(R, -1)
+        elif val_dtype == oracle.F32:
+            v = v.numpy().reshape(R, -1)
+        else:
+            v = v.view(torch.int16).numpy().view(np.uint16).reshape(R, -1)
+        i = idx[:, c0:c1].to(torch.int32).cpu().numpy().reshape(R, -1)
+        got_y = H.to_host(y[e0:e1])
+        check_presign(cfg, e1 - e0, i, v, val_dtype, got_y)
+        want = synth.from_bf16_bits(oracle.update(cfg, got_y, H.to_host(before[e0:e1]))).astype(np.float64)
+        got = synth.from_bf16_bits(H.to_host(params[e0:e1])).astype(np.float64)
+        assert (np.abs(got - want) <= parity.TOL_BF16 * np.abs(want) + parity.TOL_BF16 * cfg.lr).all()
