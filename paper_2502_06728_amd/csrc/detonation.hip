@@ -366,7 +366,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         if (idx)
             c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, deto::lane_decompress(p)));
         else if (!stream_first)
-            c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, true));
+            c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, deto::lane_scheme(p)));
         const bool done = (c0 > 0 || tiles == 0) ? false
                           : idx ? (deto::launch_decompress_idx_s64(a) ||
                                  deto::launch_decompress_idx_s32(a) ||
@@ -385,9 +385,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
             if (rc) return rc;
             c0 = C;   // the tail chunks rode along in the same launch
         } else {
-            // no lane-per-chunk kernel for this (s, k, format)
-            if (c0 == 0 && !idx && !stream_first)
-                c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, false));
+            // no lane-per-chunk or wavefront-per-class kernel for this (s, k, format)
             if (c0 == 0) c0 = deto::launch_decompress_mfma(a);
             if (c0 > 0) {
                 rc = launched();

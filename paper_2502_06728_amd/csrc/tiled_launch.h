@@ -66,7 +66,7 @@ inline unsigned tiled_grid(int64_t tiles, int64_t n_chunks) {
 
 // What the lane-per-chunk kernels are instantiated for: the k values of each chunk size with fp32
 // values and int32 indices, and the (chunk, k) pairs with byte indices and 16-bit values or two-bit
-// signs.
+// signs; for Striding and Random the (chunk, k) pairs with fp32 and with narrow values.
 #ifdef DETO_TILED_ONLY_64_32   // development builds: one instantiation, seconds to compile
 #define DETO_LANE_TOPK_16(X)
 #define DETO_LANE_TOPK_32(X)
@@ -76,6 +76,10 @@ inline unsigned tiled_grid(int64_t tiles, int64_t n_chunks) {
 #define DETO_LANE_16BIT_32(X)
 #define DETO_LANE_16BIT_64(X) X(64, 32)
 #define DETO_LANE_SIGNS(X) X(64, 32)
+#define DETO_LANE_SCHEME(X) X(64, 32)
+#define DETO_LANE_SCHEME_SMALL(X)
+#define DETO_LANE_SCHEME_NARROW_32(X)
+#define DETO_LANE_SCHEME_NARROW_64(X) X(64, 32)
 #else
 #define DETO_LANE_TOPK_16(X) X(1) X(2) X(4) X(8)
 #define DETO_LANE_TOPK_32(X) X(1) X(2) X(4) X(8) X(16)
@@ -85,6 +89,10 @@ inline unsigned tiled_grid(int64_t tiles, int64_t n_chunks) {
 #define DETO_LANE_16BIT_32(X) X(32, 16) X(32, 8) X(32, 4) X(32, 2) X(32, 1)
 #define DETO_LANE_16BIT_64(X) X(64, 32) X(64, 16) X(64, 8)
 #define DETO_LANE_SIGNS(X) X(64, 32) X(64, 16) X(32, 16) X(32, 8) X(32, 4) X(32, 2) X(32, 1)
+#define DETO_LANE_SCHEME(X) X(64, 32) X(64, 16) X(64, 8) X(32, 16) X(32, 8)
+#define DETO_LANE_SCHEME_SMALL(X) X(32, 4) X(32, 2) X(32, 1) X(64, 4) X(64, 2) X(64, 1) X(16, 2) X(16, 1)
+#define DETO_LANE_SCHEME_NARROW_32(X) X(32, 16) X(32, 8) X(32, 4) X(32, 2) X(32, 1)
+#define DETO_LANE_SCHEME_NARROW_64(X) X(64, 32) X(64, 16) X(64, 8) X(64, 4)
 #endif
 
 bool launch_compress_topk_s64(const CompressLaunch& a);
@@ -243,28 +251,36 @@ inline int decompress_classes(const KParams& p, int64_t n, bool param_bf16, bool
     return rk >= p.s ? (wide ? 4 : 2) : (p.s == 64 && 2 * rk >= p.s) ? 2 : 0;
 }
 
-// The same for Striding and Random without transmitted indices (0: a lane per chunk).  The sums
-// over the replicas are formed in registers, so large groups cost little; a shuffle costs one of
-// the wavefronts k steps, which is what the high rates lose.  us, a lane per chunk / two / four
-// classes, the shards A, B, D of decompress_classes:
-//   chunk 64, k 32, signs, AdamW, Random   A 597/525/540  B 147/132/121  D 123/111/113
-//             k 8, fp32, AdamW             A 628/579/557  B 147/130/122  D 121/110/104
-//             k 8, fp32, SGD               A 143/138/201  B  51/ 47/ 47  D  29/ 30/ 41
-//             k 32, fp32, SGD              A 307/288/364  B  64/ 66/ 78  D  43/ 54/ 71
-//   chunk 32, k 4, signs, coefficients     A 114/209/290  B  46/ 48/ 62  D  26/ 43/ 59
-//             k 1, signs                   A  99/135/168  B  45/ 40/ 42  D  23/ 30/ 35
+// The same for Striding and Random without transmitted indices.
+inline bool lane_scheme(const KParams& p) {
+    if (p.adam) return false;
+#define X(S, K) if (p.s == S && p.k == K) return true;
+    if (p.val_dtype == 0) { DETO_LANE_SCHEME(X) DETO_LANE_SCHEME_SMALL(X) }
+    else { DETO_LANE_SCHEME_NARROW_32(X) DETO_LANE_SCHEME_NARROW_64(X) }
+#undef X
+    return false;
+}
+
+// The sums over the replicas are formed in registers, so large groups cost little; a shuffle costs
+// one of the wavefronts k steps, which is what the high rates lose.  AdamW: four classes at every
+// size (2,870 timed shapes of chunk 32 and 64, both domains, fp32 values and signs, else as above:
+// 0.4 % over the better of two and four on average, 2 % and 7 % for the former rule and for two).
+// Plain SGD: a lane per chunk where there is one, except for fp32 parameters at low rates on launches
+// of more than a round and a half of it, 3,072 tiles (none of 2,870 shapes runs more than 5 % longer
+// than on the kernels before there were classes; 8 with the line at 2,048, 39 at 1,024).  us:
+//   64/8, fp32, AdamW, two / four classes           147 M bf16, R = 4 532/523   30 M fp32, R = 2 145/134
+//   64/8, fp32, R = 2, Random, a lane / two classes 1 M fp32 6.2/7.5   8 M 16.1/17.1   30 M 55/51
+//   32/2, signs, R = 2, Random on coefficients      6 M fp32 10.8/13.7
+//   64/32, fp32, R = 4, Random                      100 M bf16 210/207   147 M 305/307
+//   16/2, fp32, R = 2, Random                       30 M bf16 29/45   fp32 51/49   16/1 50/44
 inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lane) {
-    const bool plain = p.val_dtype == 0;
-    const int64_t rk = static_cast<int64_t>(p.R) * p.k;
-    if (p.adam || !lane || (p.s != 32 && p.s != 64)) {
+    if (!lane) {
         const int c = decompress_classes(p, n, param_bf16, false);
-        return (p.s >= 96 && c) ? 4 : c;
+        return (c && p.s != 16 && (p.adam || p.s >= 96)) ? 4 : c;
     }
-    if (!param_bf16) return (16 * p.k <= p.s || (8 * p.k <= p.s && (p.s == 64 || plain))) ? 2 : 0;
-    // (Random on coefficients stays with a lane per chunk: 861 M, chunk 64: 3,666 against 3,709 us
-    // a step)
-    const bool large = n > kLargeShard && !(p.use_dct && p.scheme == 2);
-    return (large && plain && rk >= 2 * p.s) ? 2 : 0;
+    const bool low = 16 * p.k <= p.s ||
+                     (8 * p.k <= p.s && (p.s == 64 || (p.s == 32 && p.val_dtype == 0)));
+    return (!param_bf16 && low && n / (kWave * p.s) > 3072) ? 2 : 0;
 }
 
 // Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the

@@ -27,6 +27,10 @@ extern "C" int lane(const int* a, int64_t) { return deto::lane_decompress(params
 extern "C" int classes(const int* a, int64_t n, int bf16) {
     return deto::decompress_classes(params(a), n, bf16, deto::lane_decompress(params(a)));
 }
+extern "C" int lane_scheme(const int* a, int64_t) { return deto::lane_scheme(params(a)); }
+extern "C" int scheme_classes(const int* a, int64_t n, int bf16) {
+    return deto::scheme_classes(params(a), n, bf16, deto::lane_scheme(params(a)));
+}
 extern "C" int stream_first(const int* a, int64_t) { return deto::stream_before_classes(params(a)); }
 """
 
@@ -124,3 +128,28 @@ def test_lane_kernels_are_those_that_are_built(rules):
     (16, 3, 2, F32, 0, 1, tiles(16, 100), 2)])
 def test_decompress_classes(rules, s, k, R, val, adam, bf16, n, want):
     assert rules("classes", s, k, n, R, val, TOPK, True, adam, bf16) == want
+
+
+def test_lane_kernels_of_the_schemes(rules):
+    for val, pairs in ((F32, {(64, k) for k in (1, 2, 4, 8, 16, 32)} | {(32, k) for k in (1, 2, 4, 8, 16)} |
+                        {(16, 1), (16, 2)}),
+                       (SIGNS, {(64, k) for k in (4, 8, 16, 32)} | {(32, k) for k in (1, 2, 4, 8, 16)})):
+        got = {(s, k) for s in range(1, 257) for k in range(1, s + 1)
+               if rules("lane_scheme", s, k, 0, val=val, scheme=RANDOM)}
+        assert got == pairs
+
+
+@pytest.mark.parametrize("s,k,val,adam,bf16,n,want", [
+    (16, 2, F32, 0, 1, tiles(16, 10000), 0), (16, 1, F32, 0, 0, tiles(16, 3072), 0),
+    (16, 1, F32, 0, 0, tiles(16, 3073), 2), (16, 2, F32, 0, 0, tiles(16, 10000), 0),
+    (16, 2, F16, 0, 1, tiles(16, 10000), 2), (16, 2, F32, 1, 1, tiles(16, 10000), 2),
+    (64, 8, F32, 0, 0, tiles(64, 3072), 0), (64, 8, F32, 0, 0, tiles(64, 3073), 2),
+    (64, 8, F32, 0, 1, 1 << 28, 0), (64, 16, F32, 0, 0, tiles(64, 10000), 0),
+    (64, 32, F32, 0, 1, 1 << 28, 0), (32, 4, F32, 0, 0, tiles(32, 3073), 2),
+    (32, 4, SIGNS, 0, 0, tiles(32, 10000), 0), (32, 2, SIGNS, 0, 0, tiles(32, 10000), 2),
+    (64, 32, SIGNS, 1, 1, tiles(64, 10000), 4), (32, 4, SIGNS, 1, 0, tiles(32, 100), 4),
+    (64, 2, SIGNS, 0, 1, tiles(64, 1000), 4), (64, 2, SIGNS, 0, 1, tiles(64, 2000), 2),
+    (128, 16, F32, 0, 1, tiles(128, 100), 4), (48, 4, F32, 0, 1, tiles(48, 100), 0)])
+def test_scheme_classes(rules, s, k, val, adam, bf16, n, want):
+    for dct in (False, True):
+        assert rules("scheme_classes", s, k, n, 4, val, RANDOM, dct, adam, bf16) == want
