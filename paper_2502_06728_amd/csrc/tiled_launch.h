@@ -120,8 +120,9 @@ bool launch_decompress_scheme_small(const DecompressLaunch& a);
 
 // Matrix-core kernels: tiles of 32 complete chunks, persistent single-wavefront workgroups.
 // A launcher returns the number of leading chunks it has taken (0: no kernel for this request).
-// NB = chunk size / 32.  What nothing else takes: compress at 160, 224, and at 32, 64 with
-// k > s/2; decompress at 160, 224.
+// NB = chunk size / 32.  What nothing else takes: both halves at 160 and 224; compress at 32 and 64
+// with k > s/2, and with narrow values (at 32 also fp32 + int32) at a k without a lane-per-chunk
+// kernel.
 #ifdef DETO_TILED_ONLY_64_32
 #define DETO_MFMA_COMPRESS_LIST(X) X(2)
 #define DETO_MFMA_DECOMPRESS_LIST(X) X(5)
@@ -206,7 +207,7 @@ inline bool lane_decompress(const KParams& p) {
 //
 // The lines were drawn through 7,290 timed shapes (chunk 32 ... 128, seven k each, three payload
 // formats, both parameter types and optimizers, R = 2, 4, 16, 0.3 ... 147 M parameters, each call on
-// other buffers): the choice costs 1.6 % over the best of the three on average, and 38 shapes run
+// other buffers): the choice costs 1.6 % over the best of the three on average, and 35 shapes run
 // more than 5 % longer than on the kernels that served them before there were classes, none of
 // them by more than 13 %.  us, a lane per chunk / two / four classes:
 //   AdamW: four classes, except where a wavefront's share of a replica's payload (16 rows of k
@@ -217,6 +218,8 @@ inline bool lane_decompress(const KParams& p) {
 //   about one round or less.
 //     64/21, fp32, R = 2, 1 M bf16        - / 12/  8   64/8, fp32, R = 2, 3 M fp32   7.9/9.5/9.1
 //     128/16, fp32, R = 2, 8 M fp32    19.8/19.7/21.9  64/8, fp32, R = 2, 12 M fp32   26/ 24/ 24
+//   Eight or more entries per element, R*k >= 8 s: the instructions of the scatter are what is left.
+//     32/16, fp32, R = 16, 8 M fp32    101/106/105   30 M 380/399/388
 //   Idle lanes without AdamW: 128/1, fp32, R = 16, 30 M bf16 51/51/58, 64/2, fp32, R = 16, 8 M fp32
 //   23/21/26.
 //   Large shards of bf16 parameters: from 2^25 elements on (with the line at 2^26 or 10^8 the
@@ -233,8 +236,9 @@ inline int decompress_classes(const KParams& p, int64_t n, bool param_bf16, bool
     if (p.s != 16 && p.s != 32 && p.s != 64 && p.s != 96 && p.s != 128) return 0;
     if (p.s == 16) return (lane && param_bf16) ? 0 : 2;
     if (p.adam) return (few || p.k >= 16 || (quads ? plain || rk <= p.s : 4 * rk <= p.s)) ? 4 : 2;
+    if (lane && rk >= 8 * p.s) return 0;
     if (p.s >= 96) {
-        if (lane && (rk >= 8 * p.s || (few && tiles > 640))) return 0;
+        if (lane && few && tiles > 640) return 0;
         if (!param_bf16) return 4;
         if (lane && p.s == 128 && p.k < 4 && !few) return 0;
         if (p.s == 128 && (rk >= p.s || !large)) return 4;
@@ -267,7 +271,8 @@ inline bool lane_scheme(const KParams& p) {
 // 0.4 % over the better of two and four on average, 2 % and 7 % for the former rule and for two).
 // Plain SGD: a lane per chunk where there is one, except for fp32 parameters at low rates on launches
 // of more than a round and a half of it, 3,072 tiles (none of 2,870 shapes runs more than 5 % longer
-// than on the kernels before there were classes; 8 with the line at 2,048, 39 at 1,024).  us:
+// than on the kernels before there were classes; 8 with the line at 2,048, 39 at 1,024); twice that
+// at chunk 16 (16/1, fp32, Random on coefficients: 4 M 8.1/9.7, 8 M 15.5/15.5).  us:
 //   64/8, fp32, AdamW, two / four classes           147 M bf16, R = 4 532/523   30 M fp32, R = 2 145/134
 //   64/8, fp32, R = 2, Random, a lane / two classes 1 M fp32 6.2/7.5   8 M 16.1/17.1   30 M 55/51
 //   32/2, signs, R = 2, Random on coefficients      6 M fp32 10.8/13.7
@@ -280,7 +285,7 @@ inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lan
     }
     const bool low = 16 * p.k <= p.s ||
                      (8 * p.k <= p.s && (p.s == 64 || (p.s == 32 && p.val_dtype == 0)));
-    return (!param_bf16 && low && n / (kWave * p.s) > 3072) ? 2 : 0;
+    return (!param_bf16 && low && n / (kWave * p.s) > (p.s == 16 ? 6144 : 3072)) ? 2 : 0;
 }
 
 // Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the

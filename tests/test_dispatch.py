@@ -115,6 +115,7 @@ def test_lane_kernels_are_those_that_are_built(rules):
     (128, 16, 2, F32, 0, 0, tiles(128, 1024), 0), (128, 16, 2, F32, 0, 0, tiles(128, 1025), 4),
     (96, 12, 2, F32, 0, 1, tiles(96, 100), 0), (96, 32, 16, F32, 0, 0, tiles(96, 1025), 4),
     # many entries, idle lanes
+    (32, 16, 16, F32, 0, 0, tiles(32, 5000), 0), (32, 16, 15, F32, 0, 0, tiles(32, 5000), 2),
     (128, 64, 16, F32, 0, 0, tiles(128, 5000), 0), (128, 1, 16, F32, 0, 1, tiles(128, 1025), 0),
     # large shards of bf16 parameters
     (64, 32, 4, F32, 0, 1, 1 << 25, 0), (64, 32, 4, F32, 0, 1, (1 << 25) + 1, 4),
@@ -140,8 +141,8 @@ def test_lane_kernels_of_the_schemes(rules):
 
 
 @pytest.mark.parametrize("s,k,val,adam,bf16,n,want", [
-    (16, 2, F32, 0, 1, tiles(16, 10000), 0), (16, 1, F32, 0, 0, tiles(16, 3072), 0),
-    (16, 1, F32, 0, 0, tiles(16, 3073), 2), (16, 2, F32, 0, 0, tiles(16, 10000), 0),
+    (16, 2, F32, 0, 1, tiles(16, 10000), 0), (16, 1, F32, 0, 0, tiles(16, 6144), 0),
+    (16, 1, F32, 0, 0, tiles(16, 6145), 2), (16, 2, F32, 0, 0, tiles(16, 10000), 0),
     (16, 2, F16, 0, 1, tiles(16, 10000), 2), (16, 2, F32, 1, 1, tiles(16, 10000), 2),
     (64, 8, F32, 0, 0, tiles(64, 3072), 0), (64, 8, F32, 0, 0, tiles(64, 3073), 2),
     (64, 8, F32, 0, 1, 1 << 28, 0), (64, 16, F32, 0, 0, tiles(64, 10000), 0),
