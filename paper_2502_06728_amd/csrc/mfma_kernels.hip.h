@@ -315,20 +315,16 @@ __device__ __forceinline__ void store_tile_rows(const float* __restrict__ buf, i
 // the whole wavefront; their LDS rows hold the coefficients (ROWS rows; lane tt of the calling
 // wavefront carries chunk tt's need and thresholds).  Everything above thr_eq is kept
 // and, of the entries equal to it, the `need` lowest indices.  The payload goes out and the
-// row is left holding alpha_j * remainder.  TERNARY: the payload may be two-bit signs, which are
-// collected in `words` (LDS, ceil(k/16) words) before they leave.
-template <int S, int ROWS = kMfmaChunks, bool TERNARY = false>
+// row is left holding alpha_j * remainder.
+template <int S, int ROWS = kMfmaChunks>
 __device__ __forceinline__ void emit_tied_chunks(float* __restrict__ buf, const KParams& p,
                                                  int lane, int need, uint32_t thr_gt,
                                                  uint32_t thr_eq, int64_t chunk0,
                                                  void* __restrict__ idx_out,
                                                  void* __restrict__ val_out,
-                                                 float* __restrict__ coeff_dbg,
-                                                 uint32_t* words = nullptr) {
+                                                 float* __restrict__ coeff_dbg) {
     constexpr int kRow = S + 4;
     const int k = p.k;
-    const int n_words = ternary_words_per_chunk(k);
-    const bool ternary = TERNARY && p.val_dtype == 3;
     if (!__any(need != 0)) return;
     for (int tt = 0; tt < ROWS; ++tt) {
         const int c_need = __builtin_amdgcn_readlane(need, tt);
@@ -337,10 +333,6 @@ __device__ __forceinline__ void emit_tied_chunks(float* __restrict__ buf, const 
         const uint32_t c_eq = __builtin_amdgcn_readlane(thr_eq, tt);
         const int64_t chunk = chunk0 + tt;
         int kept_before = 0, eq_before = 0;
-        if (ternary) {
-            if (lane < n_words) words[lane] = 0u;
-            wave_lds_sync();
-        }
 #pragma unroll
         for (int e0 = 0; e0 < S; e0 += kWave) {
             const int e = e0 + lane;
@@ -356,8 +348,7 @@ __device__ __forceinline__ void emit_tied_chunks(float* __restrict__ buf, const 
             float rem = c;
             if (keep && pos < k) {
                 store_payload_index(idx_out, chunk * k + pos, p.idx_u8, e);
-                if (ternary) atomicOr(&words[pos >> 4], ternary_code(c) << (2 * (pos & 15)));
-                else store_payload_value(val_out, chunk * k + pos, p.val_dtype, c);
+                store_payload_value(val_out, chunk * k + pos, p.val_dtype, c);
                 rem = c - payload_roundtrip(p.val_dtype, c);
             }
             if (in) {
@@ -366,12 +357,6 @@ __device__ __forceinline__ void emit_tied_chunks(float* __restrict__ buf, const 
             }
             kept_before += __popcll(km);
             eq_before += __popcll(eqm);
-        }
-        if (ternary) {
-            wave_lds_sync();
-            if (lane < n_words)
-                static_cast<uint32_t*>(val_out)[chunk * n_words + lane] = words[lane];
-            wave_lds_sync();
         }
     }
 }

@@ -1,4 +1,5 @@
-// Lane per chunk, wavefront per coefficient class: the compress half for chunk sizes above 64.
+// Lane per chunk, wavefront per coefficient class: compress from chunk 96 on (on small shards from 64,
+// without top-k from 16), decompress at chunk 16 ... 256 by the rules in tiled_launch.h.
 //
 // A chunk of more than 64 elements does not fit one lane's registers at two wavefronts per
 // SIMD.  Splitting it between two lanes of ONE wavefront makes the lanes run different
@@ -8,10 +9,10 @@
 // of the chunk's coefficients, S/W of them, in its lanes' registers.  Every wavefront runs
 // straight-line code with no divergence, and the classes meet in LDS at workgroup barriers.
 //
-//   W = 2 (chunk 96, 128), first level of the DCT-II recursion of fast_dct.hip.h:
+//   W = 2, first level of the DCT-II recursion of fast_dct.hip.h:
 //     class 0: u_n = x_n + x_{S-1-n}, coefficients 2m   = dct2_{S/2}(u)
 //     class 1: w_n = x_n - x_{S-1-n}, coefficients 2m+1 = dct4_{S/2}(w)
-//   W = 4 (chunk 192, 256), two levels, Q = S/4:
+//   W = 4, two levels, Q = S/4:
 //     class 0: coefficients 4m   = dct2_Q(u_n + u_{S/2-1-n})
 //     class 1: coefficients 4m+2 = dct4_Q(u_n - u_{S/2-1-n})
 //     class 2, 3: the DCT-IV of w (length S/2) by plane rotations into two DCT-IIs of length
@@ -425,7 +426,6 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     __shared__ uint32_t s_mask[kWave][W][NW];    // kept sets: chunk, class, word
     __shared__ uint8_t s_cnt[kWave][W];          // kept per class (at most Q <= 64)
     __shared__ unsigned long long s_tie;         // chunks of the tile that took the tie pass
-    __shared__ uint32_t s_words[NARROW ? (S / 2 + 15) / 16 : 1];   // tie pass: one chunk's signs
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -690,8 +690,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
             if (w == 0) {
                 const unsigned long long tl = __ballot(need != 0);
                 if (lane == 0) s_tie = tl;
-                emit_tied_chunks<S, kWave, NARROW>(buf, p, lane, need, thr_gt, thr_eq, chunk0,
-                                                        idx_out, val_out, nullptr, s_words);
+                emit_tied_chunks<S, kWave>(buf, p, lane, need, thr_gt, thr_eq, chunk0, idx_out,
+                                           val_out, nullptr);
             }
             __syncthreads();
             if (need != 0) {
@@ -824,7 +824,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 }
             }
         }
-        if (NARROW && p.val_dtype == 3) {
+        if (SCHEME && p.val_dtype == 3) {
             // two-bit signs: a thread builds one 16-entry word from the staged values (the
             // tile's words are contiguous)
             const uint32_t nw = static_cast<uint32_t>(ternary_words_per_chunk(k));
@@ -868,8 +868,9 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         };
         constexpr int kIt = Q / 4;
         if (!partial) {
-            // (non-temporal: nothing reads the new momentum before the next step.  ViT shard,
-            // chunk 64 / 128 steps: 58 -> 55 and 66 -> 64 us; no change at chunk 256.  The
+            // (non-temporal: a program reads the new momentum only a step later.  Whole steps on
+            // rotating buffers, without -> with: 11 M fp32 64/16 62.2 -> 60.7 us, 28 M 130.7 ->
+            // 128.4, 16 M bf16 256/32 114.7 -> 113.1; 1 M, all of it in the caches, the same.  The
             // lane-per-chunk kernels lose by the same hint: 376 -> 405 us at 147 M parameters)
 #pragma unroll 8
             for (int it = 0; it < kIt; ++it) {
