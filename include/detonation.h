@@ -34,8 +34,8 @@
  *     The bandwidth kernels additionally need 16-byte aligned grad, momentum, params, optimizer
  *     state and debug arrays, and payload arrays aligned to one lane's access: when k is a
  *     multiple of 4, four consecutive entries (16 bytes of fp32 values or int32 indices,
- *     8 bytes of 16-bit values, 4 bytes of byte indices; 8 bytes of two-bit signs when k > 16,
- *     else 4), otherwise one element.  This holds for the base of idx / val and for every
+ *     8 bytes of 16-bit values, 4 bytes of byte indices), otherwise one element; two-bit signs
+ *     8 bytes when k is 17 ... 32, else 4.  This holds for the base of idx / val and for every
  *     replica offset r*stride, so the contiguous [R][C*k] buffer an all_gather returns always
  *     qualifies for fp32 + int32 payloads.  Buffers that do not meet this are still processed
  *     correctly, by general kernels that are more than ten times slower.

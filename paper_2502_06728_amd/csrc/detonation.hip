@@ -92,8 +92,8 @@ unsigned stream_grid(int64_t items) {
 
 bool aligned16(const void* p) { return aligned(p, 16); }
 
-// Width in bytes of one lane's access to a payload array in the lane-per-chunk, two-lane and
-// matrix-core kernels: four consecutive entries when k is a multiple of 4 (16 bytes of fp32 or
+// Width in bytes of one lane's access to a payload array in all but the general and streaming
+// kernels: four consecutive entries when k is a multiple of 4 (16 bytes of fp32 or
 // int32, 8 bytes of 16-bit values, 4 bytes of byte indices; a chunk's one or two words of two-bit
 // signs), a single element otherwise.  The array's base and every replica's offset from it
 // must be multiples of this for those kernels to be used.
@@ -203,10 +203,11 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
             if (rc) return rc;
             c0 = C;   // the tail chunks rode along in the same launch
         } else {
-            // no lane-per-chunk kernel for this (s, k): chunk 96, 128, 192 and 256 run with a
-            // wavefront per coefficient class (fp32 + int32 payloads, k <= s/2) or two lanes
-            // per chunk (other formats), anything else on the matrix-core kernel, which takes
-            // the leading multiple of 32 chunks
+            // no lane-per-chunk kernel for this (s, k, format): a wavefront per coefficient
+            // class (k <= s/2; top-k from chunk 96 on, not for two-bit signs; Striding and Random
+            // from chunk 16 on unless there are few chunks), two lanes per chunk (top-k at chunk
+            // 96, 128, 192, 256, k > s/2), the matrix-core kernel (top-k at other multiples of
+            // 32), which takes the leading multiple of 32 chunks
             c0 = deto::launch_compress_split(a);
             if (c0 == 0 && !stride_stream && !deto::few_chunks(p, C))
                 c0 = deto::launch_compress_split_scheme(a);

@@ -1,4 +1,5 @@
-// Matrix-core compress kernels (chunk sizes 160, 224, and 32, 64 with k > s/2; top-k selection).
+// Matrix-core compress kernels (chunk sizes 160, 224, and at 32 and 64 what has no lane-per-chunk or
+// wavefront-per-class kernel: k > s/2, other k with narrow values; top-k selection).
 #include "mfma_kernels.hip.h"
 #include "tiled_launch.h"
 

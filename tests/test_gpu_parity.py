@@ -990,7 +990,7 @@ def test_decoupled_adamw_narrow_payloads(H, s, k, params_bf16, val_dtype, scheme
     """Decoupled AdamW on what the paper's experiments put on the wire (signs only at chunk
     size 32, "Overall Setup") and on 16-bit values: byte indices under top-k, no indices under
     Random; two steps with local moments.  336 chunks, so the replicas' arrays start 16-byte
-    aligned (lane-per-chunk kernels; chunk 96 runs on the general ones)."""
+    aligned (wavefront-per-class kernels)."""
     import torch
     from paper_2502_06728_amd import binding
     n, R, amsgrad = s * 335 + 5, 3, True
