@@ -287,30 +287,24 @@ def test_both_kernels_sum_alike(H, s, k, fmt):
     assert np.array_equal(coeffs[0].view(np.uint32), coeffs[1].view(np.uint32))
 
 
-@pytest.mark.parametrize("s,k,R,fmt", [
-    (32, 8, 4, "f32+i32"), (32, 4, 16, "f32+i32"), (64, 8, 4, "f32+i32"), (64, 32, 2, "f32+i32"),
-    (64, 5, 3, "f32+i32"), (96, 5, 3, "f32+i32"), (96, 12, 2, "f32+i32"), (96, 20, 2, "bf16+u8"),
-    (128, 1, 9, "f32+i32"), (128, 4, 3, "f32+i32"), (128, 8, 2, "f32+i32"), (128, 32, 2, "f32+i32"),
-    (128, 5, 3, "f32+i32"), (128, 16, 3, "f16+i32"), (128, 5, 2, "signs+u8")])
-def test_large_bf16_shards(H, s, k, R, fmt):
-    """Above 2^25 bf16 parameters decompress takes other kernels (a lane per chunk at chunk 128, two
-    classes without one, more classes at chunk 32 and 64); the first, the last and some other runs of
-    chunks against the oracle."""
+def update_on_samples(H, cfg, n, R, fmt, bf16, at=()):
+    """Decompress of n parameters from payloads drawn on the device; the first, the last and some other
+    runs of chunks against the oracle."""
     import torch
     from paper_2502_06728_amd import binding, synth
     val_dtype, idx_u8 = FORMATS.get(fmt, (oracle.F32, False))
-    n = (1 << 25) + s * (64 * 3 + 37) + s // 3
+    s, k, send = cfg.chunk, cfg.topk, cfg.scheme == oracle.SCHEME_TOPK
     C = -(-n // s)
-    cfg = Config(chunk=s, topk=k, sign=True, lr=1e-3, weight_decay=0.01)
     gen = torch.Generator(device=H.DEV)
     gen.manual_seed(s * k)
-    params = (torch.randn(n, generator=gen, device=H.DEV) * 0.02).to(torch.bfloat16)
+    params = (torch.randn(n, generator=gen, device=H.DEV) * 0.02).to(torch.bfloat16 if bf16 else torch.float32)
     before = params.clone()
     y = torch.full((n,), float("nan"), dtype=torch.float32, device=H.DEV)
-    # ascending places, others in every chunk and replica
-    step = s // k
-    first = torch.randint(0, step, (R, C, 1), generator=gen, device=H.DEV)
-    idx = (first + step * torch.arange(k, device=H.DEV)).to(torch.uint8 if idx_u8 else torch.int32)
+    idx = None
+    if send:     # ascending places, others in every chunk and replica
+        step = s // k
+        first = torch.randint(0, step, (R, C, 1), generator=gen, device=H.DEV)
+        idx = (first + step * torch.arange(k, device=H.DEV)).to(torch.uint8 if idx_u8 else torch.int32)
     if val_dtype == oracle.TERNARY:
         assert k <= 16
         code = torch.randint(0, 3, (R, C, k), generator=gen, device=H.DEV)
@@ -318,9 +312,11 @@ def test_large_bf16_shards(H, s, k, R, fmt):
         val = (code << (2 * torch.arange(k, device=H.DEV))).sum(-1).to(torch.int32).reshape(R, C, 1)
     else:
         val = torch.randn((R, C, k), generator=gen, device=H.DEV).to(H.VAL_TORCH[val_dtype])
-    binding.detonation_decompress_step_packed(H.bcfg(cfg), R, idx.reshape(R, -1), val.reshape(R, -1), params, y)
+    binding.detonation_decompress_step_packed(H.bcfg(cfg), R, None if idx is None else idx.reshape(R, -1),
+                                              val.reshape(R, -1), params, y)
     torch.cuda.synchronize()
-    for c0 in (0, C // 3, (1 << 25) // s - 128, C - 256):
+    tol = parity.TOL_BF16 if bf16 else parity.TOL_F32
+    for c0 in (0, C // 3, *at, C - 256):
         c1 = min(c0 + 256, C)
         e0, e1 = c0 * s, min(c1 * s, n)
         v = val[:, c0:c1].contiguous().cpu()
@@ -330,9 +326,52 @@ def test_large_bf16_shards(H, s, k, R, fmt):
             v = v.numpy().reshape(R, -1)
         else:
             v = v.view(torch.int16).numpy().view(np.uint16).reshape(R, -1)
-        i = idx[:, c0:c1].to(torch.int32).cpu().numpy().reshape(R, -1)
+        if send:
+            i = idx[:, c0:c1].to(torch.int32).cpu().numpy().reshape(R, -1)
+        else:
+            kept = oracle.select(cfg, np.zeros((c1 - c0) * s, dtype=np.float32), chunk0=c0)
+            i = np.tile(kept.reshape(1, -1), (R, 1))
         got_y = H.to_host(y[e0:e1])
         check_presign(cfg, e1 - e0, i, v, val_dtype, got_y)
-        want = synth.from_bf16_bits(oracle.update(cfg, got_y, H.to_host(before[e0:e1]))).astype(np.float64)
-        got = synth.from_bf16_bits(H.to_host(params[e0:e1])).astype(np.float64)
-        assert (np.abs(got - want) <= parity.TOL_BF16 * np.abs(want) + parity.TOL_BF16 * cfg.lr).all()
+        got, want = H.to_host(params[e0:e1]), oracle.update(cfg, got_y, H.to_host(before[e0:e1]))
+        if bf16:
+            got, want = synth.from_bf16_bits(got), synth.from_bf16_bits(want)
+        got, want = got.astype(np.float64), want.astype(np.float64)
+        assert (np.abs(got - want) <= tol * np.abs(want) + tol * cfg.lr).all()
+
+
+@pytest.mark.parametrize("s,k,R,fmt", [
+    (32, 8, 4, "f32+i32"), (32, 4, 16, "f32+i32"), (64, 8, 4, "f32+i32"), (64, 32, 2, "f32+i32"),
+    (64, 5, 3, "f32+i32"), (96, 5, 3, "f32+i32"), (96, 12, 2, "f32+i32"), (96, 20, 2, "bf16+u8"),
+    (128, 1, 9, "f32+i32"), (128, 4, 3, "f32+i32"), (128, 8, 2, "f32+i32"), (128, 32, 2, "f32+i32"),
+    (128, 5, 3, "f32+i32"), (128, 16, 3, "f16+i32"), (128, 5, 2, "signs+u8")])
+def test_large_bf16_shards(H, s, k, R, fmt):
+    """Above 2^25 bf16 parameters decompress takes other kernels (a lane per chunk at chunk 128, two
+    classes without one, more classes at chunk 32 and 64)."""
+    cfg = Config(chunk=s, topk=k, sign=True, lr=1e-3, weight_decay=0.01)
+    update_on_samples(H, cfg, (1 << 25) + s * (64 * 3 + 37) + s // 3, R, fmt, True, at=((1 << 25) // s - 128,))
+
+
+@pytest.mark.parametrize("s,k,R,tiles,fmt,bf16", [
+    # a lane per chunk about one round long; many entries per element
+    (96, 6, 2, 700, "f32+i32", False), (96, 24, 2, 1020, "f32+i32", False), (128, 1, 3, 700, "f32+i32", False),
+    (128, 4, 2, 700, "f32+i32", False), (128, 16, 2, 700, "f32+i32", False), (128, 32, 2, 700, "f32+i32", True),
+    (96, 48, 16, 5, "f32+i32", False), (128, 64, 16, 5, "f32+i32", False), (32, 16, 16, 1600, "f32+i32", False),
+    (64, 32, 16, 5, "f32+i32", True),
+    # two classes on many tiles, four at more entries
+    (32, 3, 2, 1100, "f16+i32", False), (64, 5, 2, 1100, "signs+u8", False), (64, 2, 3, 1600, "f32+i32", False),
+    (64, 8, 2, 1600, "bf16+u8", False), (64, 16, 3, 1600, "f32+i32", False), (32, 8, 2, 1600, "f32+i32", False)])
+def test_launches_of_many_tiles(H, s, k, R, tiles, fmt, bf16):
+    cfg = Config(chunk=s, topk=k, sign=True, lr=1e-3, weight_decay=0.01)
+    update_on_samples(H, cfg, s * (64 * tiles + 37) + s // 3, R, fmt, bf16)
+
+
+@pytest.mark.parametrize("dct", [False, True])
+@pytest.mark.parametrize("scheme", [oracle.SCHEME_STRIDE, oracle.SCHEME_RANDOM])
+@pytest.mark.parametrize("s,k,tiles,fmt", [(64, 8, 3100, "f32+i32"), (64, 8, 3100, "signs+u8"),
+                                           (64, 4, 3100, "bf16+u8"), (32, 4, 3100, "f32+i32"),
+                                           (32, 2, 3100, "signs+u8"), (16, 1, 6200, "f32+i32"),
+                                           (64, 2, 1100, "signs+u8")])
+def test_low_rates_on_many_tiles(H, s, k, tiles, fmt, scheme, dct):
+    cfg = Config(chunk=s, topk=k, scheme=scheme, dct=dct, sign=True, lr=1e-3, seed=4, step=9)
+    update_on_samples(H, cfg, s * (64 * tiles + 37) + s // 3, 3, fmt, False)
