@@ -37,7 +37,7 @@ UNITS = [
     # lane per chunk, top-k with fp32 values and int32 indices, by chunk size
     "tiled_topk_s96.hip", "tiled_topk_s128.hip",
     # matrix-core kernels (every other multiple of 32)
-    "mfma_compress.hip", "mfma_decompress.hip",
+    "direct_compress.hip", "mfma_compress.hip", "mfma_decompress.hip",
     # lane per chunk: narrow payloads, Striding / Random
     "tiled_topk_packed.hip", "tiled_topk_packed_s32.hip", "tiled_topk_ternary.hip",
     "tiled_scheme.hip", "tiled_scheme_small.hip",

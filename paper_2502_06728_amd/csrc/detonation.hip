@@ -206,12 +206,14 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
             // no lane-per-chunk kernel for this (s, k, format): a wavefront per coefficient
             // class (k <= s/2; top-k from chunk 96 on, not for two-bit signs; Striding and Random
             // from chunk 16 on unless there are few chunks), two lanes per chunk (top-k at chunk
-            // 96, 128, 192, 256, k > s/2), the matrix-core kernel (top-k at other multiples of
-            // 32), which takes the leading multiple of 32 chunks
+            // 96, 128, 192, 256, k > s/2), direct sums on the matrix cores (top-k: two-bit signs,
+            // chunk 16), the matrix-core kernel (top-k at other multiples of 32), which takes the
+            // leading multiple of 32 chunks
             c0 = deto::launch_compress_split(a);
             if (c0 == 0 && !stride_stream && !deto::few_chunks(p, C))
                 c0 = deto::launch_compress_split_scheme(a);
             if (c0 == 0) c0 = deto::launch_compress_pair(a);
+            if (c0 == 0) c0 = deto::launch_compress_direct(a);
             if (c0 == 0) c0 = deto::launch_compress_mfma(a);
             if (c0 > 0) {
                 rc = launched();

@@ -171,6 +171,30 @@ int64_t launch_compress_split_128(const CompressLaunch& a);
 int64_t launch_compress_split_192(const CompressLaunch& a);
 int64_t launch_compress_split_256(const CompressLaunch& a);
 
+// Direct sums on the matrix cores (direct_kernels.hip.h): what compress_generic would serve, bit for
+// bit, at the chunk sizes of the list.  Takes all chunks or none.
+#ifdef DETO_TILED_ONLY_64_32
+#define DETO_DIRECT_COMPRESS_LIST(X) X(64)
+#else
+#define DETO_DIRECT_COMPRESS_LIST(X) X(16) X(32) X(64) X(96) X(128) X(160) X(192) X(224) X(256)
+#endif
+int64_t launch_compress_direct(const CompressLaunch& a);
+inline bool direct_compress(const KParams& p) {
+    if (p.scheme != 0 || (p.s != 16 && p.val_dtype != 3)) return false;
+#define X(S) if (p.s == S) return true;
+    DETO_DIRECT_COMPRESS_LIST(X)
+#undef X
+    return false;
+}
+
+// Few chunks stay on the general kernel, a wavefront each, up to about the round that fits the chip,
+// at the chunk sizes where its direct sums are short.  us, general / matrix cores, signs: 16/3 1,000
+// chunks 8.8 / 10.0, 4,000 9.4 / 9.9, 75,000 72 / 12; 64/8 1,000 9.8 / 11.5, 2,500 11.7 / 11.9, 4,000
+// 13.9 / 11.8; 96/12 1,000 17.0 / 12.9; 256/64 7 chunks 70 / 27.
+inline bool few_direct(const KParams& p, int64_t chunks) {
+    return p.k < p.s && chunks <= (p.s <= 32 ? 4096 : p.s == 64 ? 2048 : 0);
+}
+
 // A lane-per-chunk decompress kernel for this request with transmitted indices (plain SGD update)?
 inline bool lane_decompress(const KParams& p) {
     if (p.adam) return false;

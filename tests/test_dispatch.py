@@ -23,6 +23,9 @@ extern "C" int few(const int* a, int64_t chunks) { return deto::few_chunks(param
 extern "C" int few_decompress(const int* a, int64_t chunks) {
     return deto::few_chunks_decompress(params(a), chunks, a[4] == 0);
 }
+extern "C" int direct(const int* a, int64_t chunks) {
+    return deto::direct_compress(params(a)) && !deto::few_direct(params(a), chunks);
+}
 extern "C" int lane(const int* a, int64_t) { return deto::lane_decompress(params(a)); }
 extern "C" int classes(const int* a, int64_t n, int bf16) {
     return deto::decompress_classes(params(a), n, bf16, deto::lane_decompress(params(a)));
@@ -79,6 +82,16 @@ def test_a_round_of_chunks_without_a_transform_goes_to_the_general_kernels(rules
     assert not rules("few_decompress", 128, 42, 2561, 16, SIGNS)
     assert not rules("few_decompress", 128, 42, 2560, 2, SIGNS)
     assert not rules("few_decompress", 128, 42, 2560, 16, F16)
+
+
+@pytest.mark.parametrize("s,val,few", [(16, SIGNS, 4096), (16, F16, 4096), (32, SIGNS, 4096), (64, SIGNS, 2048),
+                                       (96, SIGNS, 0), (256, SIGNS, 0)])
+def test_direct_sums_where_there_are_more_than_a_few_chunks(rules, s, val, few):
+    assert not rules("direct", s, 3, few, 1, val) or few == 0
+    assert rules("direct", s, 3, few + 1, 1, val)
+    assert rules("direct", s, s, 1, 1, val)                 # (every entry kept: long sums)
+    assert not rules("direct", s, 3, 1 << 20, 1, val, STRIDE, True)
+    assert bool(rules("direct", s, 3, 1 << 20, 1, F16)) == (s == 16)
 
 
 def test_adamw_striding_streams_at_the_larger_chunks_only(rules):
