@@ -27,6 +27,7 @@ HIPCC_FLAGS = [
 UNITS = [
     # a wavefront per coefficient class (chunk 96, 128, 192, 256; 64 on small shards)
     "split_compress_256.hip", "split_compress_192.hip", "split_compress_128.hip",
+    "half_compress_256.hip",
     "split_narrow_256.hip", "split_narrow_192.hip", "split_narrow_128.hip",
     "split_compress_96.hip", "split_compress_64.hip", "split_narrow_96.hip",
     "split_decompress.hip", "split_decompress_narrow.hip",

@@ -169,7 +169,8 @@ int64_t launch_compress_split_64(const CompressLaunch& a);
 int64_t launch_compress_split_96(const CompressLaunch& a);
 int64_t launch_compress_split_128(const CompressLaunch& a);
 int64_t launch_compress_split_192(const CompressLaunch& a);
-int64_t launch_compress_split_256(const CompressLaunch& a);
+int64_t launch_compress_split_256(const CompressLaunch& a);      // k > 32
+int64_t launch_compress_halves_256(const CompressLaunch& a);     // k <= 32, any format but signs
 
 // Direct sums on the matrix cores (direct_kernels.hip.h): what compress_generic would serve, bit for
 // bit, at the chunk sizes of the list.  Takes all chunks or none.
@@ -345,7 +346,8 @@ inline bool few_chunks_decompress(const KParams& p, int64_t chunks, bool idx) {
 }
 
 inline int64_t launch_compress_split(const CompressLaunch& a) {
-    int64_t c = launch_compress_split_96(a);
+    int64_t c = launch_compress_halves_256(a);
+    if (!c) c = launch_compress_split_96(a);
     if (!c) c = launch_compress_split_128(a);
     if (!c) c = launch_compress_split_192(a);
     if (!c) c = launch_compress_split_256(a);
