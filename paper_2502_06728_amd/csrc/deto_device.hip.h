@@ -209,17 +209,23 @@ __device__ __forceinline__ float sign_or_self(float y, int use_sign) {
 
 // One Decoupled-AdamW step for one element: moments updated in place, returns the new
 // parameter value in fp32 (section "Decoupled AdamW"; q is the averaged update).
+template <bool AMSGRAD>
 __device__ __forceinline__ float adamw_step(const KParams& p, float theta, float q, float& m,
                                             float& v, float& vmax) {
     m = fmaf(p.b1, m, p.omb1 * q);
     v = fmaf(p.b2, v, p.omb2 * q * q);
     float vh = v;
-    if (p.amsgrad) {
+    if constexpr (AMSGRAD) {
         vmax = fmaxf(vmax, v);
         vh = vmax;
     }
     const float denom = fmaf(sqrtf(vh), p.inv_sqrt_bc2, p.eps);
     return fmaf(-p.step_size, m / denom, theta * p.wd_scale);
+}
+__device__ __forceinline__ float adamw_step(const KParams& p, float theta, float q, float& m,
+                                            float& v, float& vmax) {
+    return p.amsgrad ? adamw_step<true>(p, theta, q, m, v, vmax)
+                     : adamw_step<false>(p, theta, q, m, v, vmax);
 }
 
 // ---- Random scheme generator (paper, "Replication Schemes": indices are reproduced on

@@ -77,46 +77,6 @@ __device__ __forceinline__ uint32_t spread8(uint32_t x) {
     return (x | (x << 3)) & 0x11111111u;
 }
 
-// Ends one of several branches that do the same with different parts of a register array: merged into
-// one (by a chosen address) they would keep the array in scratch memory.
-#define DETO_KEEP_APART(text) asm volatile("; " text)
-
-// dst[i] = src[i] for i = B .. E-1 of a register array
-template <int B, int E, int Q>
-__device__ __forceinline__ void regs_range_to_lds(float* dst, const float (&v)[Q]) {
-    static_assert((E - B) % 4 == 0, "whole pieces");
-#pragma unroll
-    for (int i = B; i < E; i += 4)
-        *reinterpret_cast<float4*>(dst + i - B) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
-}
-// dst[i] = v[E-1-i] for i = 0 .. E-B-1
-template <int B, int E, int Q>
-__device__ __forceinline__ void reversed_range_to_lds(float* dst, const float (&v)[Q]) {
-    static_assert((E - B) % 4 == 0, "whole pieces");
-#pragma unroll
-    for (int i = 0; i < E - B; i += 4)
-        *reinterpret_cast<float4*>(dst + i) =
-            make_float4(v[E - 1 - i], v[E - 2 - i], v[E - 3 - i], v[E - 4 - i]);
-}
-template <int B, int E, int Q>
-__device__ __forceinline__ void lds_to_regs_range(const float* src, float (&v)[Q]) {
-#pragma unroll
-    for (int i = B; i < E; i += 4) {
-        const float4 t = *reinterpret_cast<const float4*>(src + i - B);
-        v[i] = t.x; v[i + 1] = t.y; v[i + 2] = t.z; v[i + 3] = t.w;
-    }
-}
-
-// f(class as a compile-time number): branches on the class inside an unrolled loop would cut it up, or
-// keep the operands of both sides live.
-template <class F>
-__device__ __forceinline__ void by_class(int w, F f) {
-    if (w == 0) f(std::integral_constant<int, 0>{});
-    else if (w == 1) f(std::integral_constant<int, 1>{});
-    else if (w == 2) f(std::integral_constant<int, 2>{});
-    else f(std::integral_constant<int, 3>{});
-}
-
 // Half P of class CLS's transform inputs, from a row that holds the pieces of half P (load_place): what
 // split_forward_local does for q in [P Q/8, (P+1) Q/8).
 template <int P, int CLS>
@@ -152,37 +112,6 @@ __device__ __forceinline__ void half_forward_inputs(const float* __restrict__ ro
     });
 }
 
-// Classes 2 and 3 of the inverse: the rotations of the pairs of odd coefficients (split_inverse_to_rows),
-// `other` being the other class's coefficients.  c[l] makes r[2l] and c[Q-1-l] makes r[2l+1].
-template <int CLS>
-__device__ __forceinline__ void half_inverse_rotations(const float* __restrict__ other,
-                                                       const float (&c)[HalfGeom::Q],
-                                                       float (&r)[HalfGeom::Q]) {
-    constexpr int Q = HalfGeom::Q, H = HalfGeom::H;
-    static_for<0, Q / 8>([&](auto q) {
-        const float4 fo = *reinterpret_cast<const float4*>(other + 4 * q);
-        const float4 ro = *reinterpret_cast<const float4*>(other + Q - 4 - 4 * q);
-        const float o[4] = {fo.x, fo.y, fo.z, fo.w};              // other[l]
-        const float orv[4] = {ro.w, ro.z, ro.y, ro.x};            // other[Q-1-l]
-        static_for<0, 8>([&](auto i) {
-            constexpr int j = 8 * q + i;
-            constexpr int l = j / 2, li = l - 4 * q;
-            constexpr float cs = Rot<H, j>::c, sn = Rot<H, j>::s;
-            // pair (v[j], v[H-1-j]): j even: (c2[l], c3[Q-1-l]); j odd: (c3[l], c2[Q-1-l])
-            if constexpr (CLS == 2) {
-                const float pj = (j % 2) ? o[li] : c[l];
-                const float qj = (j % 2) ? c[Q - 1 - l] : orv[li];
-                r[j] = fmaf(pj, cs, qj * sn);
-            } else {
-                const float pj = (j % 2) ? c[l] : o[li];
-                const float qj = (j % 2) ? orv[li] : c[Q - 1 - l];
-                const float bv = fmaf(qj, cs, -(pj * sn));
-                r[j] = (j % 2) ? -bv : bv;
-            }
-        });
-    });
-}
-
 // Where element column `col` of a chunk goes before the transform: its half and its place in the row.
 // half_forward_inputs reads four segments of L floats, ascending columns inside each: n, the ones
 // below S/2, those from S/2 on, and S-1-n; half 0 is the blocks 0, 3, 4 and 7 of L columns.
@@ -209,8 +138,8 @@ __device__ __forceinline__ void half_inverse(float* __restrict__ row, int w, flo
         FastDct<Q>::dct4(c);
     } else {
         float r[Q];
-        if (w == 2) half_inverse_rotations<2>(row + Q, c, r);
-        else half_inverse_rotations<3>(row, c, r);
+        if (w == 2) inverse_rotations<HalfGeom::S, 2>(row + Q, c, r);
+        else inverse_rotations<HalfGeom::S, 3>(row, c, r);
         if constexpr (FUSED) FastDct<Q>::dct2_open(r);
         else FastDct<Q>::dct2(r);
 #pragma unroll

@@ -130,6 +130,36 @@ __device__ __forceinline__ void lds_to_regs_reversed(const float* src, float (&v
     }
 }
 
+// Ends one of several branches that do the same with different parts of a register array: merged into
+// one (by a chosen address) they would keep the array in scratch memory.
+#define DETO_KEEP_APART(text) asm volatile("; " text)
+
+// dst[i] = src[i] for i = B .. E-1 of a register array
+template <int B, int E, int Q>
+__device__ __forceinline__ void regs_range_to_lds(float* dst, const float (&v)[Q]) {
+    static_assert((E - B) % 4 == 0, "whole pieces");
+#pragma unroll
+    for (int i = B; i < E; i += 4)
+        *reinterpret_cast<float4*>(dst + i - B) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+}
+// dst[i] = v[E-1-i] for i = 0 .. E-B-1
+template <int B, int E, int Q>
+__device__ __forceinline__ void reversed_range_to_lds(float* dst, const float (&v)[Q]) {
+    static_assert((E - B) % 4 == 0, "whole pieces");
+#pragma unroll
+    for (int i = 0; i < E - B; i += 4)
+        *reinterpret_cast<float4*>(dst + i) =
+            make_float4(v[E - 1 - i], v[E - 2 - i], v[E - 3 - i], v[E - 4 - i]);
+}
+template <int B, int E, int Q>
+__device__ __forceinline__ void lds_to_regs_range(const float* src, float (&v)[Q]) {
+#pragma unroll
+    for (int i = B; i < E; i += 4) {
+        const float4 t = *reinterpret_cast<const float4*>(src + i - B);
+        v[i] = t.x; v[i + 1] = t.y; v[i + 2] = t.z; v[i + 3] = t.w;
+    }
+}
+
 // The sums A_i + B_j and differences A_i - B_j that end (and, in the inverse, begin) the split of
 // the DCT-IV over classes 2 and 3.  FUSED: a and b come from dct2_open, and where one of them still
 // lacks its last multiplication, that and the addition round once.  This is how the compiler
@@ -156,8 +186,55 @@ __device__ __forceinline__ float class_difference(float a, float b) {
     else return a - b;
 }
 
-// ---- forward: the lane's class of coefficients (unscaled) from the chunk's row
-// (FUSED: classes 2 and 3 without the multiplications that class_sum does)
+// W = 4: f(class as a compile-time number).  Branches on the class inside an unrolled loop would cut it
+// up, or keep the operands of both sides live: with the inputs and the inverse's rotations by class,
+// compress alone, us, before and with it: 10.8 M fp32 128/16 fp16 36.3, 34.1; 60 M bf16 128/16 136,
+// 129, 192/24 158, 149, 256/64 209, 196.  (Two classes differ by a sign only: 96/12 130, 138.)
+template <class F>
+__device__ __forceinline__ void by_class(int w, F f) {
+    if (w == 0) f(std::integral_constant<int, 0>{});
+    else if (w == 1) f(std::integral_constant<int, 1>{});
+    else if (w == 2) f(std::integral_constant<int, 2>{});
+    else f(std::integral_constant<int, 3>{});
+}
+
+// W = 4: class CLS's inputs of the transform from the chunk's row
+template <int S, int CLS>
+__device__ __forceinline__ void split_forward_inputs(const float* __restrict__ row,
+                                                     float (&c)[S / 4]) {
+    constexpr int Q = S / 4, H = S / 2;
+    // four elements at a time: x[n], x[S-1-n], x[H-1-n], x[H+n] for n = 4q .. 4q+3
+    static_for<0, Q / 4>([&](auto q) {
+        const float4 f0 = *reinterpret_cast<const float4*>(row + 4 * q);
+        const float4 r1 = *reinterpret_cast<const float4*>(row + S - 4 - 4 * q);
+        const float4 r2 = *reinterpret_cast<const float4*>(row + H - 4 - 4 * q);
+        const float4 f3 = *reinterpret_cast<const float4*>(row + H + 4 * q);
+        const float x0[4] = {f0.x, f0.y, f0.z, f0.w};
+        const float x1[4] = {r1.w, r1.z, r1.y, r1.x};
+        const float x2[4] = {r2.w, r2.z, r2.y, r2.x};
+        const float x3[4] = {f3.x, f3.y, f3.z, f3.w};
+        static_for<0, 4>([&](auto i) {
+            constexpr int j = 4 * q + i;
+            if constexpr (CLS < 2) {
+                constexpr float sgn = CLS ? -1.0f : 1.0f;
+                c[j] = fmaf(sgn, x2[i] + x3[i], x0[i] + x1[i]);
+            } else {
+                // rotations of the DCT-IV of w (length H): pair (w_j, w_{H-1-j})
+                constexpr float cs = Rot<H, j>::c, sn = Rot<H, j>::s;
+                const float wj = x0[i] - x1[i], wr = x2[i] - x3[i];
+                if constexpr (CLS == 2) {
+                    c[j] = fmaf(wj, cs, wr * sn);
+                } else {
+                    const float bv = fmaf(wr, cs, -(wj * sn));
+                    c[j] = (j % 2) ? -bv : bv;
+                }
+            }
+        });
+    });
+}
+
+// The lane's class of coefficients (unscaled; FUSED: classes 2 and 3 without the multiplications that
+// class_sum does).
 template <int S, int W, bool FUSED = false>
 __device__ __forceinline__ void split_forward_local(const float* __restrict__ row, int w,
                                                     float (&c)[S / W]) {
@@ -176,32 +253,7 @@ __device__ __forceinline__ void split_forward_local(const float* __restrict__ ro
         if (w == 0) FastDct<Q>::dct2(c);
         else FastDct<Q>::dct4(c);
     } else {
-        constexpr int H = S / 2;
-        // four elements at a time: x[n], x[S-1-n], x[H-1-n], x[H+n] for n = 4q .. 4q+3
-        static_for<0, Q / 4>([&](auto q) {
-            const float4 f0 = *reinterpret_cast<const float4*>(row + 4 * q);
-            const float4 r1 = *reinterpret_cast<const float4*>(row + S - 4 - 4 * q);
-            const float4 r2 = *reinterpret_cast<const float4*>(row + H - 4 - 4 * q);
-            const float4 f3 = *reinterpret_cast<const float4*>(row + H + 4 * q);
-            const float x0[4] = {f0.x, f0.y, f0.z, f0.w};
-            const float x1[4] = {r1.w, r1.z, r1.y, r1.x};
-            const float x2[4] = {r2.w, r2.z, r2.y, r2.x};
-            const float x3[4] = {f3.x, f3.y, f3.z, f3.w};
-            static_for<0, 4>([&](auto i) {
-                constexpr int j = 4 * q + i;
-                if (w < 2) {
-                    const float sgn = w ? -1.0f : 1.0f;
-                    c[j] = fmaf(sgn, x2[i] + x3[i], x0[i] + x1[i]);
-                } else {
-                    // rotations of the DCT-IV of w (length H): pair (w_j, w_{H-1-j})
-                    constexpr float cs = Rot<H, j>::c, sn = Rot<H, j>::s;
-                    const float wj = x0[i] - x1[i], wr = x2[i] - x3[i];
-                    const float av = fmaf(wj, cs, wr * sn);
-                    const float bv = fmaf(wr, cs, -(wj * sn));
-                    c[j] = (w == 2) ? av : ((j % 2) ? -bv : bv);
-                }
-            });
-        });
+        by_class(w, [&](auto CLS) { split_forward_inputs<S, CLS>(row, c); });
         if (w == 1) {
             FastDct<Q>::dct4(c);
         } else if constexpr (FUSED) {
@@ -241,8 +293,40 @@ __device__ __forceinline__ void split_forward_exchange(float* __restrict__ row, 
     __syncthreads();
 }
 
+// Classes 2 and 3 (CLS) of the inverse of W = 4: the rotations of the pairs of odd coefficients, `other`
+// being the other class's coefficients.  v[j] = coefficient 2j+1 of the chunk, v[2l] = class 2's c[l],
+// v[2l+1] = class 3's c[l].  c[l] makes r[2l] and c[Q-1-l] makes r[2l+1].
+template <int S, int CLS>
+__device__ __forceinline__ void inverse_rotations(const float* __restrict__ other,
+                                                  const float (&c)[S / 4], float (&r)[S / 4]) {
+    constexpr int Q = S / 4, H = S / 2;
+    static_assert(Q % 8 == 0, "whole blocks of eight pairs");
+    static_for<0, Q / 8>([&](auto q) {
+        const float4 fo = *reinterpret_cast<const float4*>(other + 4 * q);
+        const float4 ro = *reinterpret_cast<const float4*>(other + Q - 4 - 4 * q);
+        const float o[4] = {fo.x, fo.y, fo.z, fo.w};              // other[l]
+        const float orv[4] = {ro.w, ro.z, ro.y, ro.x};            // other[Q-1-l]
+        static_for<0, 8>([&](auto i) {
+            constexpr int j = 8 * q + i;
+            constexpr int l = j / 2, li = l - 4 * q;
+            constexpr float cs = Rot<H, j>::c, sn = Rot<H, j>::s;
+            // pair (v[j], v[H-1-j]): j even: (c2[l], c3[Q-1-l]); j odd: (c3[l], c2[Q-1-l])
+            if constexpr (CLS == 2) {
+                const float pj = (j % 2) ? o[li] : c[l];
+                const float qj = (j % 2) ? c[Q - 1 - l] : orv[li];
+                r[j] = fmaf(pj, cs, qj * sn);
+            } else {
+                const float pj = (j % 2) ? c[l] : o[li];
+                const float qj = (j % 2) ? orv[li] : c[Q - 1 - l];
+                const float bv = fmaf(qj, cs, -(pj * sn));
+                r[j] = (j % 2) ? -bv : bv;
+            }
+        });
+    });
+}
+
 // ---- inverse: the classes' scaled coefficients back into the rows as [E | O] (W = 2) or
-// [E (128) | O even (64) | O odd (64)] (W = 4), ready for split_output.  Contains workgroup
+// [E (2Q) | O even (Q) | O odd (Q)] (W = 4), ready for split_output.  Contains workgroup
 // barriers; the rows must be free on entry.
 template <int S, int W, bool FUSED = false>
 __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, int w,
@@ -254,8 +338,7 @@ __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, i
         regs_to_lds<Q>(row + w * Q, c);
         __syncthreads();
     } else {
-        // classes 2 and 3 exchange their coefficients: v[j] = coefficient 2j+1 of the chunk,
-        // v[2l] = class 2's c[l], v[2l+1] = class 3's c[l]
+        // classes 2 and 3 exchange their coefficients
         constexpr int H = S / 2;
         if (w >= 2) regs_to_lds<Q>(row + H + (w - 2) * Q, c);
         __syncthreads();
@@ -264,72 +347,52 @@ __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, i
         } else if (w == 1) {
             FastDct<Q>::dct4(c);
         } else {
-            // the Q rotation pairs, eight at a time: four entries of the other class from the
-            // front and four from the back
-            static_assert(Q % 8 == 0, "whole blocks of eight pairs");
-            const float* other = row + H + (3 - w) * Q;
             float r[Q];
-            static_for<0, Q / 8>([&](auto q) {
-                const float4 fo = *reinterpret_cast<const float4*>(other + 4 * q);
-                const float4 ro = *reinterpret_cast<const float4*>(other + Q - 4 - 4 * q);
-                const float o[4] = {fo.x, fo.y, fo.z, fo.w};          // other[l]
-                const float orv[4] = {ro.w, ro.z, ro.y, ro.x};        // other[Q-1-l]
-                static_for<0, 8>([&](auto i) {
-                    constexpr int j = 8 * q + i;
-                    constexpr int l = j / 2, li = l - 4 * q;
-                    constexpr float cs = Rot<H, j>::c, sn = Rot<H, j>::s;
-                    // pair (v[j], v[H-1-j]): j even: (c2[l], c3[Q-1-l]); j odd: (c3[l], c2[Q-1-l])
-                    float pj, qj;
-                    if (w == 2) {
-                        pj = (j % 2) ? o[li] : c[l];
-                        qj = (j % 2) ? c[Q - 1 - l] : orv[li];
-                    } else {
-                        pj = (j % 2) ? c[l] : o[li];
-                        qj = (j % 2) ? orv[li] : c[Q - 1 - l];
-                    }
-                    const float av = fmaf(pj, cs, qj * sn);
-                    const float bv = fmaf(qj, cs, -(pj * sn));
-                    r[j] = (w == 2) ? av : ((j % 2) ? -bv : bv);
-                });
-            });
+            if (w == 2) inverse_rotations<S, 2>(row + H + Q, c, r);
+            else inverse_rotations<S, 3>(row + H, c, r);
             if constexpr (FUSED) FastDct<Q>::dct2_open(r);
             else FastDct<Q>::dct2(r);
 #pragma unroll
             for (int j = 0; j < Q; ++j) c[j] = r[j];
         }
         __syncthreads();
-        // EE | EO | A | B
+        // EE | EO | A | B.  The results take the places of what they are made of, so that no second
+        // array of Q is live: E[i] at c[i]; E[Q+m] at c[Q-1-m]; O[2l] at c[l]; O[2l+1] at c[Q-1-l]
+        // (but for the sign of the last one, which the store turns).
         regs_to_lds<Q>(row + w * Q, c);
         __syncthreads();
-        float f[Q];
+        float o[Q];
         if (w == 0) {
-            float eo[Q];
-            lds_to_regs<Q>(row + Q, eo);
+            lds_to_regs<Q>(row + Q, o);
 #pragma unroll
-            for (int i = 0; i < Q; ++i) f[i] = c[i] + eo[i];            // E[i]
+            for (int i = 0; i < Q; ++i) c[i] = c[i] + o[i];              // EE[i] + EO[i]
         } else if (w == 1) {
-            float ee[Q];
-            lds_to_regs_reversed<Q>(row, ee);                            // ee[m] = EE[63-m]
-            // E[64+m] = E[127-(63-m)] = EE[63-m] - EO[63-m]
+            lds_to_regs<Q>(row, o);
 #pragma unroll
-            for (int m = 0; m < Q; ++m) f[m] = ee[m] - c[Q - 1 - m];
+            for (int i = 0; i < Q; ++i) c[i] = o[i] - c[i];              // EE[i] - EO[i]
         } else if (w == 2) {
-            float br[Q];
-            lds_to_regs_reversed<Q>(row + 3 * Q, br);                    // br[i] = B[63-i]
-            f[0] = c[0];
-            static_for<1, Q>([&](auto l) {                                // O[2l]
-                f[l] = class_sum<Q, FUSED, l, Q - l>(c[l], br[l - 1]);
+            lds_to_regs_reversed<Q>(row + 3 * Q, o);                     // o[i] = B[Q-1-i]
+            static_for<1, Q>([&](auto l) {                               // A[l] + B[Q-l]
+                c[l] = class_sum<Q, FUSED, l, Q - l>(c[l], o[l - 1]);
             });
         } else {
-            float a[Q];
-            lds_to_regs<Q>(row + 2 * Q, a);
-            static_for<0, Q - 1>([&](auto l) {                            // O[2l+1]
-                f[l] = class_difference<Q, FUSED, l + 1, Q - 1 - l>(a[l + 1], c[Q - 1 - l]);
+            lds_to_regs<Q>(row + 2 * Q, o);
+            static_for<0, Q - 1>([&](auto l) {                           // A[l+1] - B[Q-1-l]
+                c[Q - 1 - l] = class_difference<Q, FUSED, l + 1, Q - 1 - l>(o[l + 1], c[Q - 1 - l]);
             });
-            f[Q - 1] = -c[0];
         }
         __syncthreads();
-        regs_to_lds<Q>(row + w * Q, f);
+        if (w == 1) {
+            reversed_range_to_lds<0, Q>(row + Q, c);
+            DETO_KEEP_APART("upper half of E");
+        } else if (w == 3) {
+            reversed_range_to_lds<0, Q>(row + 3 * Q, c);
+            row[4 * Q - 1] = -c[0];
+            DETO_KEEP_APART("odd entries of O");
+        } else {
+            regs_to_lds<Q>(row + w * Q, c);
+            DETO_KEEP_APART("lower half of E, even entries of O");
+        }
         __syncthreads();
     }
 }
@@ -1286,16 +1349,17 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
         static_assert(kIt % kBatch == 0, "whole batches");
         // (full tiles run the code without the checks against the end of the shard: with them
         // the loads of a batch are no longer issued together)
-        auto update = [&](auto guarded_tag, auto raw_tag) {
+        auto update_loop = [&](auto guarded_tag, auto raw_tag, auto amsgrad_tag) {
         constexpr bool kGuarded = decltype(guarded_tag)::value;
+        constexpr bool kAmsgrad = decltype(amsgrad_tag)::value;
 #pragma unroll 1
         for (int b0 = 0; b0 < kIt; b0 += kBatch) {
-            float4 old4[kBatch], m4[kBatch], v4[kBatch], x4[kBatch];
+            float4 old4[kBatch], m4[kBatch], v4[kBatch];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const int64_t i = base + 4 * (tid + kThreads * (b0 + j));
                 if constexpr (kGuarded) {
-                    old4[j] = m4[j] = v4[j] = x4[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    old4[j] = m4[j] = v4[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     if (i + 3 >= n) continue;   // the shard's end: handled below
                 }
                 if constexpr (PARAM_BF16) {
@@ -1307,11 +1371,9 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 } else {
                     old4[j] = ld_f4<true>(static_cast<const float*>(params) + i);
                 }
-                x4[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 if (p.adam) {
                     m4[j] = ld_f4<true>(ad.m + i);
                     v4[j] = ld_f4<true>(ad.v + i);
-                    if (p.amsgrad) x4[j] = ld_f4<true>(ad.vmax + i);
                 }
             }
 #pragma unroll
@@ -1333,9 +1395,9 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                                 : static_cast<const float*>(params)[i + e];
                             float nw;
                             if (p.adam) {
-                                float vm = p.amsgrad ? ad.vmax[i + e] : 0.0f;
-                                nw = adamw_step(p, th, q, ad.m[i + e], ad.v[i + e], vm);
-                                if (p.amsgrad) ad.vmax[i + e] = vm;
+                                float vm = kAmsgrad ? ad.vmax[i + e] : 0.0f;
+                                nw = adamw_step<kAmsgrad>(p, th, q, ad.m[i + e], ad.v[i + e], vm);
+                                if constexpr (kAmsgrad) ad.vmax[i + e] = vm;
                             } else {
                                 nw = fmaf(-p.lr, q, th * p.wd_scale);
                             }
@@ -1355,13 +1417,18 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 if (p.adam) {
                     float m[4] = {m4[j].x, m4[j].y, m4[j].z, m4[j].w};
                     float v[4] = {v4[j].x, v4[j].y, v4[j].z, v4[j].w};
-                    float x[4] = {x4[j].x, x4[j].y, x4[j].z, x4[j].w};
+                    // (amsgrad's maximum is not requested with the batch: its registers, 16 of them,
+                    // would be set aside in every launch)
+                    float4 x4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if constexpr (kAmsgrad) x4 = ld_f4<true>(ad.vmax + i);
+                    float x[4] = {x4.x, x4.y, x4.z, x4.w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        nw[e] = adamw_step(p, old[e], sign_or_self(y[e], p.use_sign), m[e], v[e], x[e]);
+                        nw[e] = adamw_step<kAmsgrad>(p, old[e], sign_or_self(y[e], p.use_sign), m[e],
+                                                     v[e], x[e]);
                     st_f4<true>(ad.m + i, make_float4(m[0], m[1], m[2], m[3]));
                     st_f4<true>(ad.v + i, make_float4(v[0], v[1], v[2], v[3]));
-                    if (p.amsgrad) st_f4<true>(ad.vmax + i, make_float4(x[0], x[1], x[2], x[3]));
+                    if constexpr (kAmsgrad) st_f4<true>(ad.vmax + i, make_float4(x[0], x[1], x[2], x[3]));
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -1378,6 +1445,10 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 }
             }
         }
+        };
+        auto update = [&](auto guarded_tag, auto raw_tag) {
+            if (p.adam && p.amsgrad) update_loop(guarded_tag, raw_tag, std::true_type{});
+            else update_loop(guarded_tag, raw_tag, std::false_type{});
         };
         auto update_early = [&](auto raw_tag) {
 #pragma unroll
