@@ -1349,7 +1349,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
         static_assert(kIt % kBatch == 0, "whole batches");
         // (full tiles run the code without the checks against the end of the shard: with them
         // the loads of a batch are no longer issued together)
-        auto update_loop = [&](auto guarded_tag, auto raw_tag, auto amsgrad_tag) {
+        auto update_loop = [&](auto guarded_tag, auto raw_tag, auto amsgrad_tag) __attribute__((always_inline)) {
         constexpr bool kGuarded = decltype(guarded_tag)::value;
         constexpr bool kAmsgrad = decltype(amsgrad_tag)::value;
 #pragma unroll 1
@@ -1446,8 +1446,10 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
             }
         }
         };
+        // (amsgrad, rare, has one copy of the loop, the one with the checks; a copy that two branches
+        // call has to be inlined into both, or its arrays live in scratch memory)
         auto update = [&](auto guarded_tag, auto raw_tag) {
-            if (p.adam && p.amsgrad) update_loop(guarded_tag, raw_tag, std::true_type{});
+            if (p.adam && p.amsgrad) update_loop(std::true_type{}, raw_tag, std::true_type{});
             else update_loop(guarded_tag, raw_tag, std::false_type{});
         };
         auto update_early = [&](auto raw_tag) {
