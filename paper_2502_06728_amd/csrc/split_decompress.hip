@@ -21,14 +21,15 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);
     if (grid64 > 0x7FFFFFFF) return 0;
     const unsigned grid = static_cast<unsigned>(grid64);
+    const unsigned spare = spare_lds(a);
 #define X(S, W)                                                                                 \
     if (p.s == S && classes == W) {                                                             \
         if (a.param_bf16)                                                                       \
-            decompress_split<S, W, true, DETO_SPLIT_NARROW><<<grid, W * kWave, 0, a.stream>>>(  \
+            decompress_split<S, W, true, DETO_SPLIT_NARROW><<<grid, W * kWave, spare, a.stream>>>(  \
                 p, tiles, a.n, a.n_chunks, a.idx, a.idx_stride, a.val, a.val_stride, a.params,  \
                 a.adam, a.presign_dbg);                                                         \
         else                                                                                    \
-            decompress_split<S, W, false, DETO_SPLIT_NARROW><<<grid, W * kWave, 0, a.stream>>>( \
+            decompress_split<S, W, false, DETO_SPLIT_NARROW><<<grid, W * kWave, spare, a.stream>>>( \
                 p, tiles, a.n, a.n_chunks, a.idx, a.idx_stride, a.val, a.val_stride, a.params,  \
                 a.adam, a.presign_dbg);                                                         \
         return a.n_chunks;   /* the tail chunks ride along */                                   \

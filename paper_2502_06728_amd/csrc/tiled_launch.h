@@ -313,6 +313,56 @@ inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lan
     return (!param_bf16 && low && n / (kWave * p.s) > (p.s == 16 ? 6144 : 3072)) ? 2 : 0;
 }
 
+// How many workgroups of a large launch share a CU (0: as many as fit).  Every tile in flight is a
+// window of its own in every array, and from some 150 KB in flight per CU on more windows no longer
+// hide latency but cost the memory its locality.  Where tiles are heavy and the kernel does not need
+// the wavefronts for its arithmetic, fewer are faster.  The lines were drawn through 830 timed shapes
+// at 30, 60 and 147 M parameters (chunk 16 ... 128, three rates, three formats, R = 2, 4, 8), each at
+// 3 ... 12 workgroups per CU; time at the chosen number over the time without a limit:
+//   compress, a lane per chunk, chunk 32: top-k and coefficients 10 (0.95 - 0.99; fewer lose where
+//   signs leave the transform as the bound: 32/16 30 M bf16 8 1.03), raw Striding / Random 8 (0.96 -
+//   0.98); chunk 16 10 (0.96 - 1.02), 64 raw 6 (0.95 - 0.99).
+constexpr int64_t kLimitedTiles = 10240;      // (40 tiles per CU)
+inline int compress_workgroups(const KParams& p, int64_t tiles) {
+    if (tiles <= kLimitedTiles) return 0;
+    const bool raw = p.scheme != 0 && !p.use_dct;
+    if (p.s == 64) return raw ? 6 : 0;
+    return p.s <= 32 ? (raw ? 8 : 10) : 0;
+}
+//   decompress, fp32 values, plain update, R*k >= s: with indices chunk 64 4 (147 M, 64/32 R = 2 0.93),
+//   from R*k = 2s on 3 (R = 4 0.94, R = 8 0.96; 30 M 1.00 - 1.05: from 2^26 elements on), chunk 32 5
+//   and 4 (0.93 - 0.98, from 2^25); without indices, R*k >= 2s, chunk 64 5 (0.95 - 1.00), chunk 32 6
+//   and from 4s on 4 (0.93 - 0.97).  AdamW gains nothing (0.97 - 1.02), and narrow payloads
+//   are bound by the scatter.
+inline int decompress_workgroups(const KParams& p, int64_t n, bool idx) {
+    const int64_t rk = static_cast<int64_t>(p.R) * p.k;
+    const bool large = n > (int64_t{1} << 26);
+    if (p.s != 32 && p.s != 64) return 0;
+    if (p.adam || p.val_dtype != 0 || p.idx_u8 || rk < p.s || rk >= 8 * p.s) return 0;
+    const bool twice = rk >= 2 * p.s;
+    if (idx) {
+        if (p.s == 64) return large ? (twice ? 3 : 4) : 0;
+        return twice ? (n > kLargeShard ? 4 : 0) : (large ? 5 : 0);
+    }
+    if (!large || !twice) return 0;
+    return p.s == 64 ? 5 : (rk >= 4 * p.s ? 4 : 6);
+}
+// Dynamic LDS for that: half way between what lets one workgroup more and one less onto a CU.
+// static_bytes: a tile's rows, (s + 4) floats a chunk (or, compress at small chunks, the working set of
+// the general code for the tail, 10 KB).
+inline unsigned spare_lds(int workgroups, int static_bytes) {
+    if (workgroups == 0) return 0;
+    const int total = 2 * 160 * 1024 / (2 * workgroups + 1);
+    return total > static_bytes ? static_cast<unsigned>(total - static_bytes) : 0u;
+}
+inline unsigned spare_lds(const CompressLaunch& a) {
+    const int rows = 4 * kWave * (a.p.s + 4);
+    return spare_lds(compress_workgroups(a.p, a.tiles), rows > 10240 ? rows : 10240);
+}
+inline unsigned spare_lds(const DecompressLaunch& a) {
+    return spare_lds(decompress_workgroups(a.p, a.n, a.idx != nullptr), 4 * kWave * (a.p.s + 4));
+}
+
 // Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the
 // wavefront-per-class kernels?  Not for AdamW at chunk sizes up to 64: those have the sums over the
 // replicas in registers, four values a load, where the stream gathers them element by element.

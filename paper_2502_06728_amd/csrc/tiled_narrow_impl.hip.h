@@ -21,7 +21,7 @@ bool DETO_COMPRESS_NARROW_FN(const CompressLaunch& a) {
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
 #define LAUNCH(S, K, G, V)                                                                      \
-    compress_tiled_topk<S, K, G, V><<<grid, kWave, 0, a.stream>>>(a.p, a.tiles, tail, a.grad,   \
+    compress_tiled_topk<S, K, G, V><<<grid, kWave, spare_lds(a), a.stream>>>(a.p, a.tiles, tail, a.grad,   \
                                                                   a.mom, a.idx, a.val, a.coeff_dbg)
 #ifdef DETO_NARROW_TERNARY
 #define X(S, K)                                                                                 \
@@ -51,7 +51,7 @@ bool DETO_DECOMPRESS_NARROW_FN(const DecompressLaunch& a) {
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
 #define LAUNCH(S, K, B, V)                                                                      \
-    decompress_tiled<S, K, B, V><<<grid, kWave, 0, a.stream>>>(                                 \
+    decompress_tiled<S, K, B, V><<<grid, kWave, spare_lds(a), a.stream>>>(                     \
         a.p, a.tiles, tail, a.idx, a.idx_stride, a.val, a.val_stride, a.params,                 \
         AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg)
 #ifdef DETO_NARROW_TERNARY

@@ -17,11 +17,11 @@ bool DETO_COMPRESS_SCHEME_FN(const CompressLaunch& a) {
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \
         if (a.grad_bf16)                                                                        \
-            compress_tiled_scheme<S, K, true><<<grid, kWave, 0, a.stream>>>(                    \
+            compress_tiled_scheme<S, K, true><<<grid, kWave, spare_lds(a), a.stream>>>(        \
                 a.p, words(a.stride_mask), a.tiles, tail, a.grad, a.mom, static_cast<int32_t*>(a.idx),        \
                 static_cast<float*>(a.val), a.coeff_dbg);         \
         else                                                                                    \
-            compress_tiled_scheme<S, K, false><<<grid, kWave, 0, a.stream>>>(                   \
+            compress_tiled_scheme<S, K, false><<<grid, kWave, spare_lds(a), a.stream>>>(       \
                 a.p, words(a.stride_mask), a.tiles, tail, a.grad, a.mom, static_cast<int32_t*>(a.idx),        \
                 static_cast<float*>(a.val), a.coeff_dbg);         \
         return true;                                                                            \
@@ -38,11 +38,11 @@ bool DETO_DECOMPRESS_SCHEME_FN(const DecompressLaunch& a) {
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \
         if (a.param_bf16)                                                                       \
-            decompress_tiled_scheme<S, K, true><<<grid, kWave, 0, a.stream>>>(                  \
+            decompress_tiled_scheme<S, K, true><<<grid, kWave, spare_lds(a), a.stream>>>(      \
                 a.p, words(a.stride_mask), a.tiles, tail, static_cast<const float*>(a.val), a.val_stride,     \
                 a.params, AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);     \
         else                                                                                    \
-            decompress_tiled_scheme<S, K, false><<<grid, kWave, 0, a.stream>>>(                 \
+            decompress_tiled_scheme<S, K, false><<<grid, kWave, spare_lds(a), a.stream>>>(     \
                 a.p, words(a.stride_mask), a.tiles, tail, static_cast<const float*>(a.val), a.val_stride,     \
                 a.params, AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);     \
         return true;                                                                            \

@@ -15,10 +15,10 @@ void compress_one(const CompressLaunch& a) {
     const TailRange tail{a.n, a.n_chunks};
     const MaskWords mw{{a.stride_mask[0], a.stride_mask[1], a.stride_mask[2], a.stride_mask[3]}};
     if (a.grad_bf16)
-        compress_tiled_scheme<S, K, true, V><<<grid, kWave, 0, a.stream>>>(
+        compress_tiled_scheme<S, K, true, V><<<grid, kWave, spare_lds(a), a.stream>>>(
             a.p, mw, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);
     else
-        compress_tiled_scheme<S, K, false, V><<<grid, kWave, 0, a.stream>>>(
+        compress_tiled_scheme<S, K, false, V><<<grid, kWave, spare_lds(a), a.stream>>>(
             a.p, mw, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);
 }
 
@@ -28,11 +28,11 @@ void decompress_one(const DecompressLaunch& a) {
     const TailRange tail{a.n, a.n_chunks};
     const MaskWords mw{{a.stride_mask[0], a.stride_mask[1], a.stride_mask[2], a.stride_mask[3]}};
     if (a.param_bf16)
-        decompress_tiled_scheme<S, K, true, V><<<grid, kWave, 0, a.stream>>>(
+        decompress_tiled_scheme<S, K, true, V><<<grid, kWave, spare_lds(a), a.stream>>>(
             a.p, mw, a.tiles, tail, a.val, a.val_stride, a.params,
             AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);
     else
-        decompress_tiled_scheme<S, K, false, V><<<grid, kWave, 0, a.stream>>>(
+        decompress_tiled_scheme<S, K, false, V><<<grid, kWave, spare_lds(a), a.stream>>>(
             a.p, mw, a.tiles, tail, a.val, a.val_stride, a.params,
             AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);
 }

@@ -15,10 +15,10 @@ bool DETO_COMPRESS_FN(const CompressLaunch& a) {
 #define X(K)                                                                                    \
     if (a.p.k == K) {                                                                           \
         if (a.grad_bf16)                                                                        \
-            compress_tiled_topk<DETO_S, K, true><<<grid, kWave, 0, a.stream>>>(                 \
+            compress_tiled_topk<DETO_S, K, true><<<grid, kWave, spare_lds(a), a.stream>>>(     \
                 a.p, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);                        \
         else                                                                                    \
-            compress_tiled_topk<DETO_S, K, false><<<grid, kWave, 0, a.stream>>>(                \
+            compress_tiled_topk<DETO_S, K, false><<<grid, kWave, spare_lds(a), a.stream>>>(    \
                 a.p, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);                        \
         return true;                                                                            \
     }
@@ -35,13 +35,13 @@ bool DETO_DECOMPRESS_FN(const DecompressLaunch& a) {
 #define X(K)                                                                                    \
     if (a.p.k == K) {                                                                           \
         if (a.param_bf16)                                                                       \
-            decompress_tiled<DETO_S, K, true><<<grid, kWave, 0, a.stream>>>(                    \
+            decompress_tiled<DETO_S, K, true><<<grid, kWave, spare_lds(a), a.stream>>>(        \
                 a.p, a.tiles, tail, a.idx, a.idx_stride, a.val, a.val_stride, a.params,               \
                 AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);                                                                 \
         else if constexpr (DETO_S == 16)   /* (always two classes, see decompress_classes) */   \
             return false;                                                                       \
         else                                                                                    \
-            decompress_tiled<DETO_S, K, false><<<grid, kWave, 0, a.stream>>>(                   \
+            decompress_tiled<DETO_S, K, false><<<grid, kWave, spare_lds(a), a.stream>>>(       \
                 a.p, a.tiles, tail, a.idx, a.idx_stride, a.val, a.val_stride, a.params,               \
                 AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);                                                                 \
         return true;                                                                            \

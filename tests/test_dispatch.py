@@ -26,6 +26,11 @@ extern "C" int few_decompress(const int* a, int64_t chunks) {
 extern "C" int direct(const int* a, int64_t chunks) {
     return deto::direct_compress(params(a)) && !deto::few_direct(params(a), chunks);
 }
+extern "C" int compress_wgs(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t); }
+extern "C" int decompress_wgs(const int* a, int64_t n) {
+    return deto::decompress_workgroups(params(a), n, a[4] == 0);
+}
+extern "C" int spare(const int* a, int64_t wgs) { return deto::spare_lds(static_cast<int>(wgs), a[0]); }
 extern "C" int lane(const int* a, int64_t) { return deto::lane_decompress(params(a)); }
 extern "C" int classes(const int* a, int64_t n, int bf16) {
     return deto::decompress_classes(params(a), n, bf16, deto::lane_decompress(params(a)));
@@ -92,6 +97,30 @@ def test_direct_sums_where_there_are_more_than_a_few_chunks(rules, s, val, few):
     assert rules("direct", s, s, 1, 1, val)                 # (every entry kept: long sums)
     assert not rules("direct", s, 3, 1 << 20, 1, val, STRIDE, True)
     assert bool(rules("direct", s, 3, 1 << 20, 1, F16)) == (s == 16)
+
+
+def test_workgroups_per_cu_of_large_launches(rules):
+    for s, scheme, dct, want in ((32, TOPK, True, 10), (32, RANDOM, True, 10), (32, STRIDE, False, 8),
+                                 (16, TOPK, True, 10), (64, RANDOM, False, 6), (64, TOPK, True, 0),
+                                 (128, TOPK, True, 0)):
+        assert rules("compress_wgs", s, 4, 10241, 1, F32, scheme, dct) == want
+        assert rules("compress_wgs", s, 4, 10240, 1, F32, scheme, dct) == 0
+    m26, m25 = 1 << 26, 1 << 25
+    for s, k, R, scheme, n, want in ((64, 32, 2, TOPK, m26, 4), (64, 32, 4, TOPK, m26, 3), (64, 16, 2, TOPK, m26, 0),
+                                     (64, 32, 16, TOPK, m26, 0), (32, 16, 2, TOPK, m26, 5), (32, 16, 4, TOPK, m25, 4),
+                                     (64, 32, 4, RANDOM, m26, 5), (64, 32, 2, RANDOM, m26, 0),
+                                     (32, 16, 4, RANDOM, m26, 6), (32, 16, 8, RANDOM, m26, 4)):
+        assert rules("decompress_wgs", s, k, n + 1, R, F32, scheme) == want
+        assert rules("decompress_wgs", s, k, n, R, F32, scheme) == 0
+        assert rules("decompress_wgs", s, k, n + 1, R, F16, scheme) == 0
+        assert rules("decompress_wgs", s, k, n + 1, R, F32, scheme, None, 1) == 0
+    # that many fit 160 KB, one more does not; within the 64 KB of a launch
+    for wgs in (3, 4, 5, 6, 8, 10):
+        for static in (9216, 10240, 17408):
+            total = rules("spare", static, 1, wgs) + static
+            assert total <= 65536 and (wgs + 1) * total > 163840
+            assert wgs * total <= 163840 or total == static
+    assert rules("spare", 9216, 1, 0) == 0
 
 
 def test_adamw_striding_streams_at_the_larger_chunks_only(rules):
