@@ -2,9 +2,9 @@
 // One 64-lane wavefront owns one chunk at a time (lane = element, element e + 64*r for
 // longer chunks) and walks the chunk range with a grid stride.  The DCT is the direct
 // O(s^2) sum over a cosine table held in LDS (direct_kernels.hip.h forms the same sums on the matrix
-// cores, bit for bit: a change of the order or rounding here has to be made there too).  These kernels cover what the tiled
-// kernels do not (odd chunk sizes, the tail of a shard, unaligned buffers); they follow
-// Algorithm 1 of the paper step by step.
+// cores, bit for bit: a change of the order or rounding here has to be made there too).  These
+// kernels cover what the tiled kernels do not (odd chunk sizes, the tail of a shard, unaligned
+// buffers); they follow Algorithm 1 of the paper step by step.
 #pragma once
 
 #include "deto_device.hip.h"

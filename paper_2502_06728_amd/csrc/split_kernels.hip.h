@@ -1,5 +1,5 @@
 // Lane per chunk, wavefront per coefficient class: compress from chunk 96 on (on small shards from 64,
-// without top-k from 16), decompress at chunk 16 ... 256 by the rules in tiled_launch.h.
+// without top-k from 16; top-k at 256 with k <= 32 in half_tile_kernels.hip.h), decompress at chunk 16 ... 256 by the rules in tiled_launch.h.
 //
 // A chunk of more than 64 elements does not fit one lane's registers at two wavefronts per
 // SIMD.  Splitting it between two lanes of ONE wavefront makes the lanes run different
@@ -358,7 +358,8 @@ __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, i
         __syncthreads();
         // EE | EO | A | B.  The results take the places of what they are made of, so that no second
         // array of Q is live: E[i] at c[i]; E[Q+m] at c[Q-1-m]; O[2l] at c[l]; O[2l+1] at c[Q-1-l]
-        // (but for the sign of the last one, which the store turns).
+        // (but for the sign of the last one, which the store turns: with ROCm 7.2 a sign turned in the branch,
+        // before the barrier, did not reach the store).
         regs_to_lds<Q>(row + w * Q, c);
         __syncthreads();
         float o[Q];
@@ -482,7 +483,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     using G = SplitGeom<S, W>;
     constexpr int Q = G::Q, kRow = G::kRow, NW = G::NW, kThreads = G::kThreads;
     constexpr int kIdx0 = G::kIdx0, kTile = G::kTile;
-    constexpr bool kFused = W == 4 && NARROW && !SCHEME;   // (class_sum)
+    // (class_sum; chunk 64: two classes and four round alike, so the shard's size does not matter)
+    constexpr bool kFused = W == 4 && (NARROW || S == 64) && !SCHEME;
     // a launch with the partial sort has k <= TOP: the dump slots fit into the rows
     constexpr bool kRowDumps = TOP > 0 && TOP <= G::kRowDumpMaxK;
     __shared__ __attribute__((aligned(16))) float buf[kRowDumps ? G::kTile : G::kBufFloats];

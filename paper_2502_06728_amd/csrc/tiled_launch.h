@@ -121,8 +121,8 @@ bool launch_decompress_scheme_small(const DecompressLaunch& a);
 // Matrix-core kernels: tiles of 32 complete chunks, persistent single-wavefront workgroups.
 // A launcher returns the number of leading chunks it has taken (0: no kernel for this request).
 // NB = chunk size / 32.  What nothing else takes: both halves at 160 and 224; compress at 32 and 64
-// with k > s/2, and with narrow values (at 32 also fp32 + int32) at a k without a lane-per-chunk
-// kernel.
+// with k > s/2, and with 16-bit values or byte indices (at 32 also fp32 + int32) at a k without a
+// lane-per-chunk kernel.
 #ifdef DETO_TILED_ONLY_64_32
 #define DETO_MFMA_COMPRESS_LIST(X) X(2)
 #define DETO_MFMA_DECOMPRESS_LIST(X) X(5)
