@@ -96,15 +96,6 @@ __device__ __forceinline__ uint32_t group_exclusive_sum(uint32_t own, int part) 
     return x - own;
 }
 
-// cnt + (mag >= cand): a compare into the carry and an add with carry
-__device__ __forceinline__ uint32_t add_if_at_least(uint32_t cnt, uint32_t mag, uint32_t cand) {
-    asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
-        : "+v"(cnt)
-        : "v"(mag), "v"(cand)
-        : "vcc");
-    return cnt;
-}
-
 // acc[b][cb] = the sums over u = 0 ... S-1, ascending, of cosine times row entry u, for the 16 block
 // rows and the 16 chunks of column block cb.  Lane (i, h) brings in block row i's cosines and chunk
 // i's entries for the terms u = h, h + 4, ...; cur[b] is the byte of the first of those cosines in
@@ -311,8 +302,8 @@ __global__ __launch_bounds__(DirectGeom<S>::kThreads) void compress_direct(
             uint32_t n0 = 0u, n1 = 0u;                     // (two chains)
 #pragma unroll
             for (int m = 0; m < Q; m += 2) {
-                n0 = add_if_at_least(n0, mag[m], cand);
-                n1 = add_if_at_least(n1, mag[m + 1], cand);
+                n0 += mag[m] >= cand ? 1u : 0u;
+                n1 += mag[m + 1] >= cand ? 1u : 0u;
             }
             return static_cast<int>(
                 group_reduce<L>(n0 + n1, [](uint32_t a, uint32_t b) { return a + b; }));

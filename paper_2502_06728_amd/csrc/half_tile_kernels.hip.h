@@ -42,11 +42,7 @@ struct HalfGeom {
 // 2*word + !(|x| < thr): for magnitudes this is mag >= thr as integers (a NaN counts as the largest);
 // a NaN threshold takes everything and shows as a tie
 __device__ __forceinline__ uint32_t push_unless_below(uint32_t word, float x, float thr) {
-    asm("v_cmp_nlt_f32_e64 vcc, |%1|, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
-        : "+v"(word)
-        : "v"(x), "v"(thr)
-        : "vcc");
-    return word;
+    return 2u * word + (!(fabsf(x) < thr) ? 1u : 0u);
 }
 
 // The TOP largest magnitudes (bit patterns) of a class, descending: sort_top_desc on magnitudes that

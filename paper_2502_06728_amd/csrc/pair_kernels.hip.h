@@ -92,13 +92,10 @@ __device__ __forceinline__ float4 combine_halves(const float* __restrict__ row, 
     return make_float4(e.w - o.w, e.z - o.z, e.y - o.y, e.x - o.x);
 }
 
-// 2*word + (mag >= thr): a compare into the carry and an add with carry
+// 2*word + (mag >= thr).  (The carry of a compare must not be read by the very next instructions: the
+// compiler sees to that, an asm statement would have to.)
 __device__ __forceinline__ uint32_t push_at_least(uint32_t word, uint32_t mag, uint32_t thr) {
-    asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
-        : "+v"(word)
-        : "v"(mag), "v"(thr)
-        : "vcc");
-    return word;
+    return 2u * word + (mag >= thr ? 1u : 0u);
 }
 
 // Compress half on full tiles of 32 chunks (top-k selection, DCT domain).
@@ -204,7 +201,6 @@ __global__ __launch_bounds__(kWave) void compress_pair(KParams p, int64_t tiles,
         for (int w = 0; w < NW; ++w) own[w] = 0u;
         static_for<0, H>([&](auto I) {
             constexpr int m = H - 1 - I;   // descending so that shifting lands bit m at m
-            // own = 2*own + (|c[m]| >= thr): a compare into the carry and an add with carry
             own[m / 32] = push_at_least(own[m / 32], __float_as_uint(c[m]) & 0x7FFFFFFFu, thr);
         });
         int cnt = 0;
