@@ -316,36 +316,60 @@ inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lan
 // How many workgroups of a large launch share a CU (0: as many as fit).  Every tile in flight is a
 // window of its own in every array, and from some 150 KB in flight per CU on more windows no longer
 // hide latency but cost the memory its locality.  Where tiles are heavy and the kernel does not need
-// the wavefronts for its arithmetic, fewer are faster.  The lines were drawn through 830 timed shapes
-// at 30, 60 and 147 M parameters (chunk 16 ... 128, three rates, three formats, R = 2, 4, 8), each at
-// 3 ... 12 workgroups per CU; time at the chosen number over the time without a limit:
-//   compress, a lane per chunk, chunk 32: top-k and coefficients 10 (0.95 - 0.99; fewer lose where
-//   signs leave the transform as the bound: 32/16 30 M bf16 8 1.03), raw Striding / Random 8 (0.96 -
-//   0.98); chunk 16 10 (0.96 - 1.02), 64 raw 6 (0.95 - 0.99).
+// the wavefronts for its arithmetic or its latencies, fewer are faster.  The lines come from timed
+// shapes on rotating buffers (11 ... 147 M parameters compress, 36 ... 147 M decompress; both element
+// types); in brackets the time at the chosen number over the time without a limit.
+//   compress, a lane per chunk: chunk 32, top-k (k 1, 8, 16, fp32, fp16, signs) and coefficients 10
+//   (0.95 - 0.99; fewer lose where signs leave the transform as the bound: 32/16 30 M bf16 8 1.03), raw
+//   Striding / Random 8 (0.94 - 0.98); chunk 16 10, raw 8 (0.95 - 1.01; with one or two entries of bf16
+//   gradients 11 M 1.01, 30 M 1.01 - 1.02, 45 M 0.99, hence the second line); chunk 64 raw 6 (0.96 -
+//   0.99).
 constexpr int64_t kLimitedTiles = 10240;      // (40 tiles per CU)
-inline int compress_workgroups(const KParams& p, int64_t tiles) {
+inline int compress_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) {
     if (tiles <= kLimitedTiles) return 0;
+    if (p.s == 16 && p.k <= 2 && grad_bf16 && tiles <= 32768) return 0;
     const bool raw = p.scheme != 0 && !p.use_dct;
     if (p.s == 64) return raw ? 6 : 0;
     return p.s <= 32 ? (raw ? 8 : 10) : 0;
 }
-//   decompress, fp32 values, plain update, R*k >= s: with indices chunk 64 4 (147 M, 64/32 R = 2 0.93),
-//   from R*k = 2s on 3 (R = 4 0.94, R = 8 0.96; 30 M 1.00 - 1.05: from 2^26 elements on), chunk 32 5
-//   and 4 (0.93 - 0.98, from 2^25); without indices, R*k >= 2s, chunk 64 5 (0.95 - 1.00), chunk 32 6
-//   and from 4s on 4 (0.93 - 0.97).  AdamW gains nothing (0.97 - 1.02), and narrow payloads
-//   are bound by the scatter.
-inline int decompress_workgroups(const KParams& p, int64_t n, bool idx) {
+//   decompress, fp32 values, plain update, s <= R*k < 8s (AdamW gains nothing, 0.97 - 1.02, and
+//   narrow payloads are bound by the scatter), from 2^26 elements on but where a line says otherwise.
+//   With indices (two or four wavefronts a workgroup) what has to be in flight is k entries a replica
+//   and chunk, in groups of four, so the fewer there are the more workgroups it takes, and entries one
+//   by one take all there are (147 M, bf16, at 3 or 4 a CU: 64/2 R = 64 2.08, 64/4 R = 32 1.59, 64/8
+//   R = 16 1.12, 64/30 R = 4 1.22, 32/4 R = 16 1.40, 32/15 R = 4 1.62).  Chunk 64: k from 16 on 4
+//   (0.98 - 1.01), from R*k = 2s on 3 (0.94 - 1.01); 8 and 12, fp32 parameters, 4 (0.96 - 1.01); 4 6
+//   (fp32 0.96 - 0.98, bf16 from 2s on 0.97 - 0.99).  Chunk 32: k from 16 on, from 2s on, 4
+//   (0.92 - 0.99, also from 2^25 on, 0.94 - 0.98), below 5 (0.93 - 0.99), but for 16 fp32 R = 2 and 20
+//   bf16 R = 2 6 (0.95 - 1.00; at 5 1.00 and 1.05 - 1.08); 8 and 12 5, fp32 from 2s on 4 (fp32 0.94 -
+//   1.01; bf16 0.95 - 0.97 from 2s on, 1.03 - 1.08 below); 4, fp32, 6, from 2^25 on (0.92 - 1.00; bf16
+//   1.01 - 1.12).
+//   Without indices (a lane per chunk), from R*k = 2s on and from k = 4 on (at these numbers 32/2 R = 64
+//   1.24, 32/1 R = 64 1.34, 64/2 R = 64 1.13): chunk 64 5 (0.94 - 1.02; not 32 from 4s on, 1.02 at
+//   70 M, nor 4 with the transform, 1.01 - 1.02), chunk 32 6, from 4s on 4, k = 4 5 (0.91 - 1.00).
+inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool param_bf16) {
     const int64_t rk = static_cast<int64_t>(p.R) * p.k;
     const bool large = n > (int64_t{1} << 26);
     if (p.s != 32 && p.s != 64) return 0;
     if (p.adam || p.val_dtype != 0 || p.idx_u8 || rk < p.s || rk >= 8 * p.s) return 0;
     const bool twice = rk >= 2 * p.s;
     if (idx) {
-        if (p.s == 64) return large ? (twice ? 3 : 4) : 0;
-        return twice ? (n > kLargeShard ? 4 : 0) : (large ? 5 : 0);
+        if (p.k % 4 != 0) return 0;
+        if (p.s == 32 && p.k >= 16 && twice) return n > kLargeShard ? 4 : 0;
+        if (p.s == 32 && p.k == 4 && !param_bf16) return n > kLargeShard ? 6 : 0;
+        if (!large) return 0;
+        if (p.s == 64) {
+            if (p.k >= 16) return twice ? 3 : 4;
+            if (p.k >= 8) return param_bf16 ? 0 : 4;
+            return (twice || !param_bf16) ? 6 : 0;
+        }
+        if (p.k >= 16) return (p.k == 16) == param_bf16 || 2 * rk >= 3 * p.s ? 5 : 6;
+        if (p.k >= 8) return !param_bf16 ? (twice ? 4 : 5) : (twice ? 5 : 0);
+        return 0;
     }
-    if (!large || !twice) return 0;
-    return p.s == 64 ? 5 : (rk >= 4 * p.s ? 4 : 6);
+    if (!large || !twice || p.k < 4) return 0;
+    if (p.s == 64) return (p.k == 32 && rk >= 4 * p.s) || (p.k == 4 && p.use_dct) ? 0 : 5;
+    return rk < 4 * p.s ? 6 : p.k == 4 ? 5 : 4;
 }
 // Dynamic LDS for that: half way between what lets one workgroup more and one less onto a CU.
 // static_bytes: a tile's rows, (s + 4) floats a chunk (or, compress at small chunks, the working set of
@@ -357,10 +381,11 @@ inline unsigned spare_lds(int workgroups, int static_bytes) {
 }
 inline unsigned spare_lds(const CompressLaunch& a) {
     const int rows = 4 * kWave * (a.p.s + 4);
-    return spare_lds(compress_workgroups(a.p, a.tiles), rows > 10240 ? rows : 10240);
+    return spare_lds(compress_workgroups(a.p, a.tiles, a.grad_bf16), rows > 10240 ? rows : 10240);
 }
 inline unsigned spare_lds(const DecompressLaunch& a) {
-    return spare_lds(decompress_workgroups(a.p, a.n, a.idx != nullptr), 4 * kWave * (a.p.s + 4));
+    return spare_lds(decompress_workgroups(a.p, a.n, a.idx != nullptr, a.param_bf16),
+                     4 * kWave * (a.p.s + 4));
 }
 
 // Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the

@@ -10,6 +10,7 @@ from paper_2502_06728_amd import build
 
 F32, F16, SIGNS = 0, 2, 3
 TOPK, STRIDE, RANDOM = 0, 1, 2
+RAW = (RANDOM, False)                                    # Random on the momentum itself
 
 DRIVER = r"""
 #include "tiled_launch.h"
@@ -26,9 +27,13 @@ extern "C" int few_decompress(const int* a, int64_t chunks) {
 extern "C" int direct(const int* a, int64_t chunks) {
     return deto::direct_compress(params(a)) && !deto::few_direct(params(a), chunks);
 }
-extern "C" int compress_wgs(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t); }
+extern "C" int compress_wgs(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t, false); }
+extern "C" int compress_wgs_bf16(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t, true); }
 extern "C" int decompress_wgs(const int* a, int64_t n) {
-    return deto::decompress_workgroups(params(a), n, a[4] == 0);
+    return deto::decompress_workgroups(params(a), n, a[4] == 0, true);
+}
+extern "C" int decompress_wgs_f32(const int* a, int64_t n) {
+    return deto::decompress_workgroups(params(a), n, a[4] == 0, false);
 }
 extern "C" int spare(const int* a, int64_t wgs) { return deto::spare_lds(static_cast<int>(wgs), a[0]); }
 extern "C" int lane(const int* a, int64_t) { return deto::lane_decompress(params(a)); }
@@ -121,6 +126,35 @@ def test_workgroups_per_cu_of_large_launches(rules):
             assert total <= 65536 and (wgs + 1) * total > 163840
             assert wgs * total <= 163840 or total == static
     assert rules("spare", 9216, 1, 0) == 0
+
+
+# (s, k, R, scheme, workgroups with bf16 and with fp32 parameters)
+@pytest.mark.parametrize("s,k,R,scheme,bf16,f32", [
+    # entries one by one, or few lanes of them: as many workgroups as fit
+    (64, 2, 64, TOPK, 0, 0), (64, 2, 32, TOPK, 0, 0), (64, 1, 64, TOPK, 0, 0), (64, 30, 4, TOPK, 0, 0),
+    (64, 18, 8, TOPK, 0, 0), (32, 1, 64, TOPK, 0, 0), (32, 2, 32, TOPK, 0, 0), (32, 15, 4, TOPK, 0, 0),
+    (32, 2, 64, RANDOM, 0, 0), (32, 1, 64, RANDOM, 0, 0), (64, 2, 64, RANDOM, 0, 0), (64, 32, 8, RANDOM, 0, 0),
+    # few entries a replica: more workgroups, or all
+    (64, 4, 32, TOPK, 6, 6), (64, 4, 16, TOPK, 0, 6), (64, 8, 16, TOPK, 0, 4), (64, 12, 16, TOPK, 0, 4),
+    (32, 4, 16, TOPK, 0, 6), (32, 8, 4, TOPK, 0, 5), (32, 12, 4, TOPK, 0, 5), (32, 8, 8, TOPK, 5, 4),
+    # the other lines
+    (64, 16, 16, TOPK, 3, 3), (64, 20, 4, TOPK, 4, 4), (32, 16, 2, TOPK, 5, 6), (32, 16, 3, TOPK, 5, 5),
+    (32, 20, 2, TOPK, 6, 5), (32, 24, 2, TOPK, 5, 5), (32, 24, 4, TOPK, 4, 4), (64, 4, 32, RANDOM, 0, 0), (64, 4, 32, RAW, 5, 5), (64, 16, 16, RANDOM, 5, 5),
+    (32, 4, 16, RANDOM, 6, 6), (32, 4, 32, RANDOM, 5, 5)])
+def test_workgroups_by_entries_and_parameters(rules, s, k, R, scheme, bf16, f32):
+    scheme, dct = scheme if scheme == RAW else (scheme, True)
+    for n in ((1 << 26) + 1, 147095552):
+        assert rules("decompress_wgs", s, k, n, R, F32, scheme, dct) == bf16
+        assert rules("decompress_wgs_f32", s, k, n, R, F32, scheme, dct) == f32
+        if rules("lane", s, k, n, R) and rules("classes", s, k, n, R, F32, TOPK, True, 0, 1) == 0:
+            assert rules("decompress_wgs", s, k, n, R) == 0   # (one wavefront a workgroup)
+
+
+def test_one_or_two_bf16_entries_of_16_are_limited_later(rules):
+    for name, k, tiles, want in (("compress_wgs_bf16", 1, 32768, 0), ("compress_wgs_bf16", 2, 32768, 0),
+                                 ("compress_wgs_bf16", 2, 32769, 10), ("compress_wgs_bf16", 4, 10241, 10),
+                                 ("compress_wgs", 1, 10241, 10)):
+        assert rules(name, 16, k, tiles) == want
 
 
 def test_adamw_striding_streams_at_the_larger_chunks_only(rules):
