@@ -32,6 +32,8 @@ UNITS = [
     "split_compress_96.hip", "split_compress_64.hip", "split_narrow_96.hip",
     "split_decompress.hip", "split_decompress_narrow.hip",
     "split_scheme_compress.hip", "split_scheme_decompress.hip",
+    "split_decompress_amsgrad.hip", "split_decompress_narrow_amsgrad.hip",
+    "split_scheme_decompress_amsgrad.hip",
     # two lanes per chunk (chunk 96, 128, 192, 256)
     "pair_compress_256.hip", "pair_compress_192.hip", "pair_compress_128.hip",
     "pair_compress_96.hip",

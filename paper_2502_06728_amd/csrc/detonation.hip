@@ -359,11 +359,15 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         const bool few = deto::few_chunks_decompress(p, C, idx != nullptr);
         auto split = [few](const deto::DecompressLaunch& d, int classes) -> int64_t {
             if (few || classes == 0) return 0;
-            const int64_t c = deto::launch_decompress_split(d, classes);
-            return c ? c : deto::launch_decompress_split_narrow(d, classes);
+            int64_t c = deto::launch_decompress_split(d, classes);
+            if (!c) c = deto::launch_decompress_split_narrow(d, classes);
+            if (!c) c = deto::launch_decompress_split_amsgrad(d, classes);
+            return c ? c : deto::launch_decompress_split_narrow_amsgrad(d, classes);
         };
         auto split_scheme = [few](const deto::DecompressLaunch& d, int classes) -> int64_t {
-            return (classes && !few) ? deto::launch_decompress_split_scheme(d, classes) : 0;
+            if (few || classes == 0) return 0;
+            const int64_t c = deto::launch_decompress_split_scheme(d, classes);
+            return c ? c : deto::launch_decompress_split_scheme_amsgrad(d, classes);
         };
         // a lane per chunk or a wavefront per coefficient class
         if (idx)

@@ -1,9 +1,12 @@
 // Decompress-and-update on the wavefront-per-coefficient-class kernels (transmitted indices; plain
 // SGD update or Decoupled AdamW; any k): launchers for fp32 values + int32 indices, and
-// (split_decompress_narrow.hip) for every other payload format.
+// (split_decompress_narrow.hip) for every other payload format; both again for amsgrad.
 #ifndef DETO_SPLIT_FN
 #define DETO_SPLIT_FN launch_decompress_split
 #define DETO_SPLIT_NARROW false
+#endif
+#ifndef DETO_SPLIT_AMSGRAD
+#define DETO_SPLIT_AMSGRAD false
 #endif
 #include "split_kernels.hip.h"
 #include "tiled_launch.h"
@@ -16,27 +19,28 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
     return 0;
 #else
     if (!a.idx || DETO_SPLIT_NARROW != (p.val_dtype != 0 || p.idx_u8)) return 0;
+    if (DETO_SPLIT_AMSGRAD != (p.adam && p.amsgrad)) return 0;
     const int64_t tiles = (a.n / p.s) / kWave;
     // one workgroup per full tile and one for the chunks left over (a partial tile)
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);
     if (grid64 > 0x7FFFFFFF) return 0;
     const unsigned grid = static_cast<unsigned>(grid64);
     const unsigned spare = spare_lds(a);
+#define LAUNCH(S, W, BF16)                                                                      \
+    decompress_split<S, W, BF16, DETO_SPLIT_NARROW, false, DETO_SPLIT_AMSGRAD>                  \
+        <<<grid, W * kWave, spare, a.stream>>>(p, tiles, a.n, a.n_chunks, a.idx, a.idx_stride,  \
+                                               a.val, a.val_stride, a.params, a.adam,           \
+                                               a.presign_dbg)
 #define X(S, W)                                                                                 \
     if (p.s == S && classes == W) {                                                             \
-        if (a.param_bf16)                                                                       \
-            decompress_split<S, W, true, DETO_SPLIT_NARROW><<<grid, W * kWave, spare, a.stream>>>(  \
-                p, tiles, a.n, a.n_chunks, a.idx, a.idx_stride, a.val, a.val_stride, a.params,  \
-                a.adam, a.presign_dbg);                                                         \
-        else                                                                                    \
-            decompress_split<S, W, false, DETO_SPLIT_NARROW><<<grid, W * kWave, spare, a.stream>>>( \
-                p, tiles, a.n, a.n_chunks, a.idx, a.idx_stride, a.val, a.val_stride, a.params,  \
-                a.adam, a.presign_dbg);                                                         \
+        if (a.param_bf16) LAUNCH(S, W, true);                                                   \
+        else LAUNCH(S, W, false);                                                               \
         return a.n_chunks;   /* the tail chunks ride along */                                   \
     }
     X(16, 2) X(32, 2) X(32, 4) X(64, 2) X(64, 4) X(96, 2) X(96, 4) X(128, 2) X(128, 4)
     X(192, 4) X(256, 4)
 #undef X
+#undef LAUNCH
     return 0;
 #endif
 }

@@ -1183,7 +1183,14 @@ __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, flo
 // flight decides how busy the memory is).  Then every class gathers its coefficients from
 // the rows, the inverse transform runs as in compress_split, and all wavefronts stream the
 // parameters (and the moments of Decoupled AdamW) through the update.
-template <int S, int W, bool PARAM_BF16, bool NARROW = false, bool SCHEME = false>
+//
+// AMSGRAD: Decoupled AdamW with the running maximum, in kernels of their own.  Its maximum is requested
+// with the rest of its batch; beside the plain update in one kernel that sets aside 16 registers in
+// every launch, and a copy of the loop without it nearly doubles the kernel.  us, as a copy with
+// checks in the same kernel and like this: amsgrad, signs, bf16, 256/32 10 M 92, 70, 128/16 10 M 66,
+// 57; fp32 64/8 2 M 17.7, 15.8; and the other launches: 64/20 signs 60 M SGD 122, 109, Random 32/5 60 M
+// 90, 71, 16/3 signs 30 M 61, 57.
+template <int S, int W, bool PARAM_BF16, bool NARROW = false, bool SCHEME = false, bool AMSGRAD = false>
 __global__ __launch_bounds__(kWave * W) void decompress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ idx,
     int64_t idx_stride, const void* __restrict__ val, int64_t val_stride,
@@ -1214,7 +1221,8 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
     // where they are used)
     constexpr int kPieces = Q / 4;                // 4-element pieces of the tile per thread
     uint2 early[kPieces];
-    const bool params_early = PARAM_BF16 && !partial && !p.adam && (SCHEME || p.use_dct);
+    const bool adam = AMSGRAD || p.adam;
+    const bool params_early = PARAM_BF16 && !partial && !adam && (SCHEME || p.use_dct);
     if constexpr (PARAM_BF16) {
         if (params_early) {
 #pragma unroll
@@ -1348,17 +1356,17 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
         static_assert(kIt % kBatch == 0, "whole batches");
         // (full tiles run the code without the checks against the end of the shard: with them
         // the loads of a batch are no longer issued together)
-        auto update_loop = [&](auto guarded_tag, auto raw_tag, auto amsgrad_tag) __attribute__((always_inline)) {
+        auto update = [&](auto guarded_tag, auto raw_tag) {
         constexpr bool kGuarded = decltype(guarded_tag)::value;
-        constexpr bool kAmsgrad = decltype(amsgrad_tag)::value;
 #pragma unroll 1
         for (int b0 = 0; b0 < kIt; b0 += kBatch) {
-            float4 old4[kBatch], m4[kBatch], v4[kBatch];
+            float4 old4[kBatch], m4[kBatch], v4[kBatch], x4[AMSGRAD ? kBatch : 1];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const int64_t i = base + 4 * (tid + kThreads * (b0 + j));
                 if constexpr (kGuarded) {
                     old4[j] = m4[j] = v4[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if constexpr (AMSGRAD) x4[j] = old4[j];
                     if (i + 3 >= n) continue;   // the shard's end: handled below
                 }
                 if constexpr (PARAM_BF16) {
@@ -1370,9 +1378,10 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 } else {
                     old4[j] = ld_f4<true>(static_cast<const float*>(params) + i);
                 }
-                if (p.adam) {
+                if (adam) {
                     m4[j] = ld_f4<true>(ad.m + i);
                     v4[j] = ld_f4<true>(ad.v + i);
+                    if constexpr (AMSGRAD) x4[j] = ld_f4<true>(ad.vmax + i);
                 }
             }
 #pragma unroll
@@ -1393,10 +1402,10 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                                 ? bf16_to_f32(static_cast<const uint16_t*>(params)[i + e])
                                 : static_cast<const float*>(params)[i + e];
                             float nw;
-                            if (p.adam) {
-                                float vm = kAmsgrad ? ad.vmax[i + e] : 0.0f;
-                                nw = adamw_step<kAmsgrad>(p, th, q, ad.m[i + e], ad.v[i + e], vm);
-                                if constexpr (kAmsgrad) ad.vmax[i + e] = vm;
+                            if (adam) {
+                                float vm = AMSGRAD ? ad.vmax[i + e] : 0.0f;
+                                nw = adamw_step<AMSGRAD>(p, th, q, ad.m[i + e], ad.v[i + e], vm);
+                                if constexpr (AMSGRAD) ad.vmax[i + e] = vm;
                             } else {
                                 nw = fmaf(-p.lr, q, th * p.wd_scale);
                             }
@@ -1413,21 +1422,19 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 const float y[4] = {y4.x, y4.y, y4.z, y4.w};
                 const float old[4] = {old4[j].x, old4[j].y, old4[j].z, old4[j].w};
                 float nw[4];
-                if (p.adam) {
+                if (adam) {
                     float m[4] = {m4[j].x, m4[j].y, m4[j].z, m4[j].w};
                     float v[4] = {v4[j].x, v4[j].y, v4[j].z, v4[j].w};
-                    // (amsgrad's maximum is not requested with the batch: its registers, 16 of them,
-                    // would be set aside in every launch)
-                    float4 x4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if constexpr (kAmsgrad) x4 = ld_f4<true>(ad.vmax + i);
-                    float x[4] = {x4.x, x4.y, x4.z, x4.w};
+                    float4 vm = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if constexpr (AMSGRAD) vm = x4[j];
+                    float x[4] = {vm.x, vm.y, vm.z, vm.w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        nw[e] = adamw_step<kAmsgrad>(p, old[e], sign_or_self(y[e], p.use_sign), m[e],
-                                                     v[e], x[e]);
+                        nw[e] = adamw_step<AMSGRAD>(p, old[e], sign_or_self(y[e], p.use_sign), m[e],
+                                                    v[e], x[e]);
                     st_f4<true>(ad.m + i, make_float4(m[0], m[1], m[2], m[3]));
                     st_f4<true>(ad.v + i, make_float4(v[0], v[1], v[2], v[3]));
-                    if constexpr (kAmsgrad) st_f4<true>(ad.vmax + i, make_float4(x[0], x[1], x[2], x[3]));
+                    if constexpr (AMSGRAD) st_f4<true>(ad.vmax + i, make_float4(x[0], x[1], x[2], x[3]));
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -1444,12 +1451,6 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 }
             }
         }
-        };
-        // (amsgrad, rare, has one copy of the loop, the one with the checks; a copy that two branches
-        // call has to be inlined into both, or its arrays live in scratch memory)
-        auto update = [&](auto guarded_tag, auto raw_tag) {
-            if (p.adam && p.amsgrad) update_loop(std::true_type{}, raw_tag, std::true_type{});
-            else update_loop(guarded_tag, raw_tag, std::false_type{});
         };
         auto update_early = [&](auto raw_tag) {
 #pragma unroll

@@ -159,6 +159,9 @@ int64_t launch_decompress_split(const DecompressLaunch& a, int classes);        
 int64_t launch_decompress_split_narrow(const DecompressLaunch& a, int classes); // other formats
 int64_t launch_compress_split_scheme(const CompressLaunch& a);                   // Striding / Random
 int64_t launch_decompress_split_scheme(const DecompressLaunch& a, int classes);  // ... no indices
+int64_t launch_decompress_split_amsgrad(const DecompressLaunch& a, int classes); // the same three,
+int64_t launch_decompress_split_narrow_amsgrad(const DecompressLaunch& a, int classes);   // AdamW
+int64_t launch_decompress_split_scheme_amsgrad(const DecompressLaunch& a, int classes);   // with amsgrad
 // 16-bit values, or byte indices:
 int64_t launch_compress_split_narrow_96(const CompressLaunch& a);
 int64_t launch_compress_split_narrow_128(const CompressLaunch& a);
