@@ -23,9 +23,10 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);
     if (grid64 > 0x7FFFFFFF) return 0;
     const unsigned grid = static_cast<unsigned>(grid64);
+    const unsigned spare = spare_lds(a, classes);
 #define LAUNCH(S, W, BF16)                                                                      \
     decompress_split<S, W, BF16, true, true, DETO_SPLIT_AMSGRAD>                                \
-        <<<grid, W * kWave, 0, a.stream>>>(p, tiles, a.n, a.n_chunks, nullptr, 0, a.val,        \
+        <<<grid, W * kWave, spare, a.stream>>>(p, tiles, a.n, a.n_chunks, nullptr, 0, a.val,        \
                                            a.val_stride, a.params, a.adam, a.presign_dbg)
 #define X(S, W)                                                                                 \
     if (p.s == S && classes == W) {                                                             \

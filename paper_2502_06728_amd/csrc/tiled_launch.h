@@ -335,26 +335,55 @@ inline int compress_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) 
     if (p.s == 64) return raw ? 6 : 0;
     return p.s <= 32 ? (raw ? 8 : 10) : 0;
 }
-//   decompress, fp32 values, plain update, s <= R*k < 8s (AdamW gains nothing, 0.97 - 1.02, and
-//   narrow payloads are bound by the scatter), from 2^26 elements on but where a line says otherwise.
-//   With indices (two or four wavefronts a workgroup) what has to be in flight is k entries a replica
-//   and chunk, in groups of four, so the fewer there are the more workgroups it takes, and entries one
-//   by one take all there are (147 M, bf16, at 3 or 4 a CU: 64/2 R = 64 2.08, 64/4 R = 32 1.59, 64/8
-//   R = 16 1.12, 64/30 R = 4 1.22, 32/4 R = 16 1.40, 32/15 R = 4 1.62).  Chunk 64: k from 16 on 4
-//   (0.98 - 1.01), from R*k = 2s on 3 (0.94 - 1.01); 8 and 12, fp32 parameters, 4 (0.96 - 1.01); 4 6
-//   (fp32 0.96 - 0.98, bf16 from 2s on 0.97 - 0.99).  Chunk 32: k from 16 on, from 2s on, 4
-//   (0.92 - 0.99, also from 2^25 on, 0.94 - 0.98), below 5 (0.93 - 0.99), but for 16 fp32 R = 2 and 20
-//   bf16 R = 2 6 (0.95 - 1.00; at 5 1.00 and 1.05 - 1.08); 8 and 12 5, fp32 from 2s on 4 (fp32 0.94 -
-//   1.01; bf16 0.95 - 0.97 from 2s on, 1.03 - 1.08 below); 4, fp32, 6, from 2^25 on (0.92 - 1.00; bf16
-//   1.01 - 1.12).
-//   Without indices (a lane per chunk), from R*k = 2s on and from k = 4 on (at these numbers 32/2 R = 64
-//   1.24, 32/1 R = 64 1.34, 64/2 R = 64 1.13): chunk 64 5 (0.94 - 1.02; not 32 from 4s on, 1.02 at
-//   70 M, nor 4 with the transform, 1.01 - 1.02), chunk 32 6, from 4s on 4, k = 4 5 (0.91 - 1.00).
-inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool param_bf16) {
+//   decompress (classes: wavefronts a workgroup; 0: a lane per chunk, one wavefront), fp32 values and
+//   plain update, from 2^26 elements on but where a line says otherwise (narrow payloads are bound by
+//   the scatter).  With indices what has to be in flight is k entries a replica and chunk, in groups of
+//   four: the fewer there are the more workgroups it takes, and entries one by one take all there are
+//   (147 M, bf16, at 3 or 4 a CU: 64/2 R = 64 2.08, 64/4 R = 32 1.59, 64/8 R = 16 1.12, 64/30 R = 4 1.22,
+//   32/4 R = 16 1.40, 32/15 R = 4 1.62).
+//     chunk 128, k >= 16, R*k >= s/2 with fp32 parameters, s with bf16: 3 (0.92 - 0.98; 36 M 1.01 - 1.05;
+//       R*k = s/4 1.03)
+//     chunk 96, fp32 parameters, R*k >= s/2: 4, from 2^25 on (0.97 - 1.00)
+//     chunk 64, R*k >= s: k >= 16 4 (0.98 - 1.01), from 2s on 3 (0.94 - 1.01); 8 and 12 on four classes 4
+//       (0.96 - 1.01); 4 6 (fp32 0.96 - 0.98, bf16 from 2s on 0.97 - 0.99)
+//     chunk 32, R*k >= s: k >= 16 5 (0.93 - 0.99), but 16 fp32 R = 2 and 20 bf16 R = 2 6 (0.95 - 1.00; at 5
+//       1.00 and 1.08), from 2s on 4, also from 2^25 on (0.92 - 0.99); 8 and 12 5 (fp32 0.94 - 1.01, from
+//       2s on 4; bf16 0.95 - 0.97 from 2s on, 1.03 - 1.08 below); 4, fp32, 6, from 2^25 on (0.92 - 1.00)
+//     chunk 32, bf16 parameters, two classes (4 and 12 entries), R*k >= 3s/4, 12 below 2s: 8 (0.95 - 0.97)
+//   Without indices (a lane per chunk), R*k >= 2s and k >= 4 (at these numbers 32/2 R = 64 1.24, 32/1
+//   R = 64 1.34, 64/2 R = 64 1.13):
+//     chunk 64 5 (0.94 - 1.02), not 32 from 4s on (1.02 at 70 M) nor 4 with the transform (1.02)
+//     chunk 32 6, from 4s on 4, k = 4 5 (0.91 - 1.00)
+//   AdamW, four classes, R*k <= s: the batches of parameters and moments are in flight.
+//     chunk 96: narrow or raw 4 from 2^23 on (0.98 - 1.00), the rest with bf16 parameters from 2^25 on
+//       (0.98 - 0.99; 20 M 1.04)
+//     chunk 64, bf16 parameters: narrow payloads, with indices or raw, 4 from 2^23 on (0.96 - 0.99), fp32
+//       values of the transform domain from 2^25 on (0.97 - 0.99); the others, and R*k = 4s, lose up to 1.07
+//     Random and Striding at chunk 32, fp32 values, bf16 parameters: 5 from 2^25 on (0.96 - 0.99)
+inline int adamw_workgroups(const KParams& p, int64_t n, bool idx, bool param_bf16, int classes) {
+    const int64_t rk = static_cast<int64_t>(p.R) * p.k;
+    const bool plain = p.val_dtype == 0 && !(idx && p.idx_u8);
+    // (amsgrad's kernels, with larger batches, gain nothing)
+    if (p.amsgrad || classes != 4 || rk > p.s || n <= (int64_t{1} << 23)) return 0;
+    const bool large = n > kLargeShard;
+    if (p.s == 96) return (idx ? !plain : !p.use_dct) || (large && param_bf16) ? 4 : 0;
+    if (!param_bf16) return 0;
+    if (p.s == 64) return plain ? (!idx && p.use_dct && large ? 4 : 0) : (idx || !p.use_dct ? 4 : 0);
+    return p.s == 32 && !idx && plain && large ? 5 : 0;
+}
+inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool param_bf16, int classes) {
+    if (p.adam) return adamw_workgroups(p, n, idx, param_bf16, classes);
     const int64_t rk = static_cast<int64_t>(p.R) * p.k;
     const bool large = n > (int64_t{1} << 26);
-    if (p.s != 32 && p.s != 64) return 0;
-    if (p.adam || p.val_dtype != 0 || p.idx_u8 || rk < p.s || rk >= 8 * p.s) return 0;
+    if (p.val_dtype != 0 || p.idx_u8 || rk >= 8 * p.s || idx != (classes != 0)) return 0;
+    if (idx && p.k % 4 == 0) {
+        if (p.s == 128)
+            return large && classes == 4 && p.k >= 16 && (param_bf16 ? rk : 2 * rk) >= p.s ? 3 : 0;
+        if (p.s == 96) return n > kLargeShard && !param_bf16 && 2 * rk >= p.s ? 4 : 0;
+        if (p.s == 32 && param_bf16 && classes == 2 && 4 * rk >= 3 * p.s && (p.k < 8 || rk < 2 * p.s))
+            return large ? 8 : 0;
+    }
+    if ((p.s != 32 && p.s != 64) || rk < p.s) return 0;
     const bool twice = rk >= 2 * p.s;
     if (idx) {
         if (p.k % 4 != 0) return 0;
@@ -363,7 +392,7 @@ inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool par
         if (!large) return 0;
         if (p.s == 64) {
             if (p.k >= 16) return twice ? 3 : 4;
-            if (p.k >= 8) return param_bf16 ? 0 : 4;
+            if (p.k >= 8) return classes == 4 ? 4 : 0;
             return (twice || !param_bf16) ? 6 : 0;
         }
         if (p.k >= 16) return (p.k == 16) == param_bf16 || 2 * rk >= 3 * p.s ? 5 : 6;
@@ -375,8 +404,9 @@ inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool par
     return rk < 4 * p.s ? 6 : p.k == 4 ? 5 : 4;
 }
 // Dynamic LDS for that: half way between what lets one workgroup more and one less onto a CU.
-// static_bytes: a tile's rows, (s + 4) floats a chunk (or, compress at small chunks, the working set of
-// the general code for the tail, 10 KB).
+// static_bytes: a tile's rows, (s + 4) floats a chunk (and, where the classes list the places
+// themselves, those; or, compress at small chunks, the working set of the general code for the tail,
+// 10 KB).
 inline unsigned spare_lds(int workgroups, int static_bytes) {
     if (workgroups == 0) return 0;
     const int total = 2 * 160 * 1024 / (2 * workgroups + 1);
@@ -386,9 +416,11 @@ inline unsigned spare_lds(const CompressLaunch& a) {
     const int rows = 4 * kWave * (a.p.s + 4);
     return spare_lds(compress_workgroups(a.p, a.tiles, a.grad_bf16), rows > 10240 ? rows : 10240);
 }
-inline unsigned spare_lds(const DecompressLaunch& a) {
-    return spare_lds(decompress_workgroups(a.p, a.n, a.idx != nullptr, a.param_bf16),
-                     4 * kWave * (a.p.s + 4));
+inline unsigned spare_lds(const DecompressLaunch& a, int classes = 0) {
+    const int s = a.p.s;
+    const int places = (!a.idx && classes) ? kWave * s / 2 + 8 * (s < 32 ? 32 : s) : 0;
+    return spare_lds(decompress_workgroups(a.p, a.n, a.idx != nullptr, a.param_bf16, classes),
+                     4 * kWave * (s + 4) + places);
 }
 
 // Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the

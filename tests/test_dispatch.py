@@ -29,12 +29,15 @@ extern "C" int direct(const int* a, int64_t chunks) {
 }
 extern "C" int compress_wgs(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t, false); }
 extern "C" int compress_wgs_bf16(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t, true); }
-extern "C" int decompress_wgs(const int* a, int64_t n) {
-    return deto::decompress_workgroups(params(a), n, a[4] == 0, true);
+static int decompress_wgs_of(const int* a, int64_t n, bool bf16) {
+    const deto::KParams p = params(a);
+    const bool idx = a[4] == 0;
+    const int classes = idx ? deto::decompress_classes(p, n, bf16, deto::lane_decompress(p))
+                            : deto::scheme_classes(p, n, bf16, deto::lane_scheme(p));
+    return deto::decompress_workgroups(p, n, idx, bf16, classes);
 }
-extern "C" int decompress_wgs_f32(const int* a, int64_t n) {
-    return deto::decompress_workgroups(params(a), n, a[4] == 0, false);
-}
+extern "C" int decompress_wgs(const int* a, int64_t n) { return decompress_wgs_of(a, n, true); }
+extern "C" int decompress_wgs_f32(const int* a, int64_t n) { return decompress_wgs_of(a, n, false); }
 extern "C" int spare(const int* a, int64_t wgs) { return deto::spare_lds(static_cast<int>(wgs), a[0]); }
 extern "C" int lane(const int* a, int64_t) { return deto::lane_decompress(params(a)); }
 extern "C" int classes(const int* a, int64_t n, int bf16) {
@@ -135,19 +138,39 @@ def test_workgroups_per_cu_of_large_launches(rules):
     (64, 18, 8, TOPK, 0, 0), (32, 1, 64, TOPK, 0, 0), (32, 2, 32, TOPK, 0, 0), (32, 15, 4, TOPK, 0, 0),
     (32, 2, 64, RANDOM, 0, 0), (32, 1, 64, RANDOM, 0, 0), (64, 2, 64, RANDOM, 0, 0), (64, 32, 8, RANDOM, 0, 0),
     # few entries a replica: more workgroups, or all
-    (64, 4, 32, TOPK, 6, 6), (64, 4, 16, TOPK, 0, 6), (64, 8, 16, TOPK, 0, 4), (64, 12, 16, TOPK, 0, 4),
-    (32, 4, 16, TOPK, 0, 6), (32, 8, 4, TOPK, 0, 5), (32, 12, 4, TOPK, 0, 5), (32, 8, 8, TOPK, 5, 4),
+    (64, 4, 32, TOPK, 6, 6), (64, 4, 16, TOPK, 0, 6), (64, 8, 16, TOPK, 4, 4), (64, 12, 16, TOPK, 0, 4),
+    (32, 4, 16, TOPK, 8, 6), (32, 8, 4, TOPK, 0, 5), (32, 12, 4, TOPK, 8, 5), (32, 8, 8, TOPK, 5, 4),
+    (32, 12, 8, TOPK, 5, 4),
     # the other lines
     (64, 16, 16, TOPK, 3, 3), (64, 20, 4, TOPK, 4, 4), (32, 16, 2, TOPK, 5, 6), (32, 16, 3, TOPK, 5, 5),
-    (32, 20, 2, TOPK, 6, 5), (32, 24, 2, TOPK, 5, 5), (32, 24, 4, TOPK, 4, 4), (64, 4, 32, RANDOM, 0, 0), (64, 4, 32, RAW, 5, 5), (64, 16, 16, RANDOM, 5, 5),
-    (32, 4, 16, RANDOM, 6, 6), (32, 4, 32, RANDOM, 5, 5)])
+    (32, 20, 2, TOPK, 6, 5), (32, 24, 2, TOPK, 5, 5), (32, 24, 4, TOPK, 4, 4), (64, 4, 32, RANDOM, 0, 0), (64, 4, 32, RAW, 5, 0), (64, 16, 16, RANDOM, 5, 5),
+    (32, 4, 16, RANDOM, 6, 0), (32, 4, 32, RANDOM, 5, 0),
+    # chunk 96 and 128 by classes; twelve entries on two classes
+    (128, 16, 4, TOPK, 0, 3), (128, 32, 4, TOPK, 3, 3), (128, 24, 4, TOPK, 0, 3), (128, 8, 8, TOPK, 0, 0),
+    (128, 16, 2, TOPK, 0, 0), (96, 12, 4, TOPK, 0, 4), (96, 24, 4, TOPK, 0, 4), (96, 12, 2, TOPK, 0, 0),
+    (32, 12, 2, TOPK, 8, 0), (32, 8, 3, TOPK, 0, 0), (32, 12, 1, TOPK, 0, 0)])
 def test_workgroups_by_entries_and_parameters(rules, s, k, R, scheme, bf16, f32):
     scheme, dct = scheme if scheme == RAW else (scheme, True)
     for n in ((1 << 26) + 1, 147095552):
         assert rules("decompress_wgs", s, k, n, R, F32, scheme, dct) == bf16
         assert rules("decompress_wgs_f32", s, k, n, R, F32, scheme, dct) == f32
-        if rules("lane", s, k, n, R) and rules("classes", s, k, n, R, F32, TOPK, True, 0, 1) == 0:
-            assert rules("decompress_wgs", s, k, n, R) == 0   # (one wavefront a workgroup)
+        if scheme == TOPK and rules("classes", s, k, n, R, F32, TOPK, True, 0, 1) == 0:
+            assert bf16 == 0                                  # (one wavefront a workgroup)
+
+
+# (s, k, R, values, scheme, elements from which on, workgroups with bf16 and with fp32 parameters)
+@pytest.mark.parametrize("s,k,R,val,scheme,line,bf16,f32", [
+    (64, 16, 4, SIGNS, TOPK, 23, 4, 0), (64, 32, 2, F16, TOPK, 23, 4, 0), (64, 32, 8, SIGNS, TOPK, 23, 0, 0),
+    (64, 16, 4, F32, TOPK, 25, 0, 0), (64, 5, 4, SIGNS, TOPK, 23, 0, 0), (64, 8, 2, SIGNS, RAW, 23, 4, 0),
+    (64, 16, 4, SIGNS, RANDOM, 25, 0, 0), (64, 16, 4, F32, RANDOM, 25, 4, 0), (64, 16, 4, F32, RAW, 25, 0, 0),
+    (96, 12, 4, F16, TOPK, 23, 4, 4), (96, 24, 4, F32, TOPK, 25, 4, 0), (96, 12, 4, F32, RAW, 23, 4, 4),
+    (96, 12, 4, F32, RANDOM, 25, 4, 0), (32, 8, 4, F32, RANDOM, 25, 5, 0), (32, 8, 4, F32, TOPK, 25, 0, 0),
+    (32, 4, 8, SIGNS, RANDOM, 25, 0, 0), (128, 16, 4, F32, TOPK, 25, 0, 0)])
+def test_workgroups_of_adamw(rules, s, k, R, val, scheme, line, bf16, f32):
+    scheme, dct = scheme if scheme == RAW else (scheme, True)
+    for n, on in ((1 << line, False), ((1 << line) + 1, True), (147095552, True)):
+        assert rules("decompress_wgs", s, k, n, R, val, scheme, dct, 1) == (bf16 if on else 0)
+        assert rules("decompress_wgs_f32", s, k, n, R, val, scheme, dct, 1) == (f32 if on else 0)
 
 
 def test_one_or_two_bf16_entries_of_16_are_limited_later(rules):
