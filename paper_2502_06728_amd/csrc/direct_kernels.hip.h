@@ -299,14 +299,12 @@ __global__ __launch_bounds__(DirectGeom<S>::kThreads) void compress_direct(
         }
         top = group_reduce<L>(top, [](uint32_t a, uint32_t b) { return max(a, b); });
         auto count_at_least = [&](uint32_t cand) -> int {
-            uint32_t n0 = 0u, n1 = 0u;                     // (two chains)
+            uint32_t cnt = 0u;
 #pragma unroll
-            for (int m = 0; m < Q; m += 2) {
-                n0 += mag[m] >= cand ? 1u : 0u;
-                n1 += mag[m + 1] >= cand ? 1u : 0u;
-            }
+            for (int m = 0; m < Q; m += 4)
+                cnt = add_if_at_least(cnt, mag[m], mag[m + 1], mag[m + 2], mag[m + 3], cand);
             return static_cast<int>(
-                group_reduce<L>(n0 + n1, [](uint32_t a, uint32_t b) { return a + b; }));
+                group_reduce<L>(cnt, [](uint32_t a, uint32_t b) { return a + b; }));
         };
         // lo: at least k magnitudes reach it; hi: fewer than k do.  First downwards from the
         // largest in growing steps (one octave, four, sixteen, ...), then by halves.  A candidate is

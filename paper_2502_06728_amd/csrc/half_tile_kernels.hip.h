@@ -39,12 +39,6 @@ struct HalfGeom {
     // wavefronts per SIMD: what the registers of Q coefficients allow (the LDS allows as many or more)
 };
 
-// 2*word + !(|x| < thr): for magnitudes this is mag >= thr as integers (a NaN counts as the largest);
-// a NaN threshold takes everything and shows as a tie
-__device__ __forceinline__ uint32_t push_unless_below(uint32_t word, float x, float thr) {
-    return 2u * word + (!(fabsf(x) < thr) ? 1u : 0u);
-}
-
 // The TOP largest magnitudes (bit patterns) of a class, descending: sort_top_desc on magnitudes that
 // are formed group by group, so that no more than 2 TOP keys are live beside c.
 template <int Q, int TOP>
@@ -383,9 +377,9 @@ compress_halves(
 #pragma unroll
         for (int j = 0; j < NW; ++j) own[j] = 0u;
         const float thr = __uint_as_float(T);
-        static_for<0, Q>([&](auto I) {
-            constexpr int m = Q - 1 - I;   // descending so that shifting lands bit m at m
-            own[m / 32] = push_unless_below(own[m / 32], c[m], thr);
+        static_for<0, Q / 2>([&](auto I) {
+            constexpr int m = Q - 2 - 2 * I;   // descending so that shifting lands bit m at m
+            own[m / 32] = push_unless_below(own[m / 32], c[m + 1], c[m], thr);
         });
         publish_bits(s_kept, own);
     }

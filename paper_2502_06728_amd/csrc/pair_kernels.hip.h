@@ -92,12 +92,6 @@ __device__ __forceinline__ float4 combine_halves(const float* __restrict__ row, 
     return make_float4(e.w - o.w, e.z - o.z, e.y - o.y, e.x - o.x);
 }
 
-// 2*word + (mag >= thr).  (The carry of a compare must not be read by the very next instructions: the
-// compiler sees to that, an asm statement would have to.)
-__device__ __forceinline__ uint32_t push_at_least(uint32_t word, uint32_t mag, uint32_t thr) {
-    return 2u * word + (mag >= thr ? 1u : 0u);
-}
-
 // Compress half on full tiles of 32 chunks (top-k selection, DCT domain).
 //
 // Selection.  Each lane sorts the magnitudes of its H coefficients in registers (sorting
@@ -199,9 +193,10 @@ __global__ __launch_bounds__(kWave) void compress_pair(KParams p, int64_t tiles,
     auto mark = [&](uint32_t thr) -> int {
 #pragma unroll
         for (int w = 0; w < NW; ++w) own[w] = 0u;
-        static_for<0, H>([&](auto I) {
-            constexpr int m = H - 1 - I;   // descending so that shifting lands bit m at m
-            own[m / 32] = push_at_least(own[m / 32], __float_as_uint(c[m]) & 0x7FFFFFFFu, thr);
+        auto mag = [&](int m) { return __float_as_uint(c[m]) & 0x7FFFFFFFu; };
+        static_for<0, H / 4>([&](auto I) {
+            constexpr int m = H - 4 - 4 * I;   // descending so that shifting lands bit m at m
+            own[m / 32] = push_if_at_least(own[m / 32], mag(m + 3), mag(m + 2), mag(m + 1), mag(m), thr);
         });
         int cnt = 0;
 #pragma unroll

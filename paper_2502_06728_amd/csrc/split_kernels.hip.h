@@ -94,12 +94,6 @@ __device__ __forceinline__ uint32_t kth_of_two_lists(const uint32_t* l0, const u
     return min(n0 > 0 ? t0 : 0xFFFFFFFFu, n1 > 0 ? t1 : 0xFFFFFFFFu);
 }
 
-// 2*word + (mag >= thr).  (The carry of a compare must not be read by the very next instructions: the
-// compiler sees to that, an asm statement would have to.)
-__device__ __forceinline__ uint32_t push_if_at_least(uint32_t word, uint32_t mag, uint32_t thr) {
-    return 2u * word + (mag >= thr ? 1u : 0u);
-}
-
 template <int Q>
 __device__ __forceinline__ void regs_to_lds(float* dst, const float (&v)[Q]) {
 #pragma unroll
@@ -717,9 +711,10 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     auto mark = [&](uint32_t thr) -> int {
 #pragma unroll
         for (int j = 0; j < NW; ++j) own[j] = 0u;
-        static_for<0, Q>([&](auto I) {
-            constexpr int m = Q - 1 - I;   // descending so that shifting lands bit m at m
-            own[m / 32] = push_if_at_least(own[m / 32], __float_as_uint(c[m]) & 0x7FFFFFFFu, thr);
+        auto mag = [&](int m) { return __float_as_uint(c[m]) & 0x7FFFFFFFu; };
+        static_for<0, Q / 4>([&](auto I) {
+            constexpr int m = Q - 4 - 4 * I;   // descending so that shifting lands bit m at m
+            own[m / 32] = push_if_at_least(own[m / 32], mag(m + 3), mag(m + 2), mag(m + 1), mag(m), thr);
         });
         int cnt = 0;
 #pragma unroll
