@@ -11,7 +11,9 @@ int64_t launch_compress_direct(const CompressLaunch& a) {
     if (p.s == S) {                                                                                \
         constexpr int NC = DirectGeom<S>::NC;                                                      \
         const int64_t tiles = (a.n / S) / NC;                                                      \
-        const unsigned grid = static_cast<unsigned>(tiles + (tiles * NC < a.n_chunks ? 1 : 0));    \
+        const int64_t grid64 = tiles + (tiles * NC < a.n_chunks ? 1 : 0);                          \
+        if (grid64 > 0x7FFFFFFF) return 0;                                                         \
+        const unsigned grid = static_cast<unsigned>(grid64);                                       \
         if (a.grad_bf16)                                                                           \
             compress_direct<S, true><<<grid, DirectGeom<S>::kThreads, 0, a.stream>>>(              \
                 p, tiles, a.n, a.n_chunks, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);              \

@@ -228,7 +228,7 @@ __global__ __launch_bounds__(DirectGeom<S>::kThreads) void compress_direct(
         const float c = kCosQuarter<S>.v[t];
         tab[t] = c;
         tab[2 * S - t] = -c;
-        if (2 * S + t < 4 * S) tab[2 * S + t] = -c;
+        tab[2 * S + t] = -c;
         if (t > 0) tab[4 * S - t] = c;
     }
     __syncthreads();
