@@ -1,13 +1,17 @@
 """The compress half at chunk size 64 and 128 picks its kernels by shard size (include/detonation.h,
-DETO_SMALL_SHARD_TILES): a small shard spreads every 64-chunk tile over more wavefronts (chunk 64:
-two coefficient classes instead of a lane per chunk; chunk 128: four classes instead of two).
+DETO_SMALL_SHARD_TILES): a small shard spreads every 64-chunk tile over more wavefronts (chunk 64: two
+coefficient classes instead of a lane per chunk, and four up to 512 tiles; chunk 128: four classes
+instead of two).  The shapes with a few tiles run four classes at chunk 64; two classes have tests of
+their own, above 512 tiles.
 Both choices against the oracle on the same inputs: every k family, bf16 and fp32 storage,
 partial tiles with a ragged last chunk, ties."""
 import numpy as np
 import pytest
 
 from oracle import Config
-from tests.test_gpu_parity import H, full_step, tie_case  # noqa: F401  (H: the fixture)
+from tests import parity
+from tests.test_gpu_parity import H, full_step, make_inputs, tie_case  # noqa: F401  (H: the fixture)
+from tests.test_gpu_payload_formats import with_ties
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +85,48 @@ def test_random_shapes(H, choice, s, k, n, R, bf16):
     cfg = Config(chunk=s, topk=k, sign=bool(k % 2))
     full_step(H, cfg, n, R=R, seed=n % 1000, grad_bf16=bf16, params_bf16=bf16,
               outliers=0.01 if bf16 else 0.0)
+
+
+def _two_class_inputs(n, seed, bf16):
+    """Chunk 64, ordinary values with tied chunks spread over all tiles."""
+    g, m, _ = make_inputs(n, seed=seed, grad_bf16=bf16)
+    return with_ties(g, m, 64)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("k", [1, 5, 16, 20, 32])
+def test_two_classes_above_512_tiles(H, monkeypatch, k, bf16):
+    """Chunk 64 with more than two tiles per CU runs with two classes: ties, a partial tile, a ragged last
+    chunk, both sort lengths."""
+    monkeypatch.delenv("DETO_SMALL_SHARD_TILES", raising=False)
+    n = 64 * (64 * 513 + 37) + 21
+    g, m = _two_class_inputs(n, k, bf16)
+    cfg = Config(chunk=64, topk=k)
+    parity.check_compress(cfg, g, m, *H.gpu_compress(cfg, g, m))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("k", [1, 5, 16, 20, 32])
+def test_two_and_four_classes_give_the_same_bits(H, monkeypatch, k, bf16):
+    """The first 512 tiles of a shard of 513 (two classes) and those tiles as a shard (four): four calls in
+    a row leave the same momentum and payload, so that a shard's length does not move near ties."""
+    import torch
+    from paper_2502_06728_amd import binding
+    monkeypatch.delenv("DETO_SMALL_SHARD_TILES", raising=False)
+    common = 64 * 64 * 512
+    g, m = _two_class_inputs(64 * (64 * 513 + 5) + 3, k, bf16)
+    cfg, results = Config(chunk=64, topk=k, decay=0.9), []
+    for n in (g.size, common):
+        grad, mom = H.to_dev(g[:n]), H.to_dev(m[:n])
+        entries = -(-n // 64) * k
+        idx = torch.zeros(entries, dtype=torch.int32, device=H.DEV)
+        val = torch.zeros(entries, device=H.DEV)
+        out = []
+        for _ in range(4):
+            binding.detonation_compress(H.bcfg(cfg), grad, mom, idx, val)
+            out += [mom[:common].clone().view(torch.int32), idx[:common // 64 * k].clone(),
+                    val[:common // 64 * k].clone().view(torch.int32)]
+        results.append(out)
+    torch.cuda.synchronize()
+    for a, b in zip(*results):
+        assert torch.equal(a, b), int((a != b).sum())
