@@ -26,9 +26,12 @@ def run(H, s, k, n, val, u8, bf16, aligned):
         m[c * s:(c + 1) * s] = 0
         if c % 2:
             m[c * s + (5 * c) % (min(n, (c + 1) * s) - c * s)] = 1e-3 * (c + 1)
-    m[s + 1] = 1e38                                          # products that overflow,
-    m[2 * s:3 * s] *= 1e-38                                  # and subnormal ones
+    m[2 * s:3 * s] *= 1e-38                                  # subnormal products,
     g[2 * s:3 * s] = 0
+    m[3 * s:4 * s] = 3e38                                    # sums that overflow,
+    m[4 * s + 1] = float("inf")                              # infinities and NaN in the input
+    m[5 * s - 1] = -float("inf")
+    m[s + s // 2] = float("nan")
     g = g.to(torch.bfloat16) if bf16 else g
     words = C * ((k + 15) // 16)
     idx = torch.zeros(C * k, dtype=torch.uint8 if u8 else torch.int32, device=H.DEV)
@@ -36,13 +39,17 @@ def run(H, s, k, n, val, u8, bf16, aligned):
                     dtype={F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16,
                            SIGNS: torch.int32}[val])
     cfg, out = binding.Config(chunk=s, topk=k, decay=0.9), []
+
+    def bits(t):
+        if t.is_floating_point():                            # (a NaN's sign and payload are free)
+            t = torch.where(t.isnan(), torch.full_like(t, float("nan")), t)
+        return t.clone() if t.element_size() == 1 else t.view(
+            torch.int16 if t.element_size() == 2 else torch.int32).clone()
+
     for call in range(3):
         coeff = torch.zeros(C * s, device=H.DEV)
         binding.detonation_compress_packed(cfg, g, m, idx, v, coeff)
-        for t in (m, idx, v, coeff):
-            t = t.clone()
-            out.append(t.view(torch.int16 if t.element_size() == 2 else torch.int32)
-                       if t.element_size() > 1 else t)
+        out += [bits(t) for t in (m, idx, v, coeff)]
     torch.cuda.synchronize()
     return out
 
