@@ -8,7 +8,7 @@ namespace deto {
 int64_t launch_compress_mfma(const CompressLaunch& a) {
     const KParams& p = a.p;
     if (p.scheme != 0 || !p.use_dct || p.s % 32 != 0 || p.s > 256) return 0;
-    if (p.val_dtype == 3) return 0;   // two-bit payload: general kernels
+    if (p.val_dtype == 3) return 0;   // two-bit payload: direct sums, or the general kernels on few chunks
     const int64_t tiles = (a.n / p.s) / kMfmaChunks;
     if (tiles <= 0) return 0;
 #define X(NB)                                                                                   \

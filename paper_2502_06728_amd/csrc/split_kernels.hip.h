@@ -1,5 +1,6 @@
 // Lane per chunk, wavefront per coefficient class: compress from chunk 96 on (on small shards from 64,
-// without top-k from 16; top-k at 256 with k <= 32 in half_tile_kernels.hip.h), decompress at chunk 16 ... 256 by the rules in tiled_launch.h.
+// without top-k from 16; top-k at 256 with k <= 32 in half_tile_kernels.hip.h), decompress at chunk
+// 16 ... 256 by the rules in tiled_launch.h.
 //
 // A chunk of more than 64 elements does not fit one lane's registers at two wavefronts per
 // SIMD.  Splitting it between two lanes of ONE wavefront makes the lanes run different
@@ -349,8 +350,10 @@ __device__ __forceinline__ void split_inverse_to_rows(float* __restrict__ row, i
         __syncthreads();
         // EE | EO | A | B.  The results take the places of what they are made of, so that no second
         // array of Q is live: E[i] at c[i]; E[Q+m] at c[Q-1-m]; O[2l] at c[l]; O[2l+1] at c[Q-1-l]
-        // (but for the sign of the last one, which the store turns: with ROCm 7.2 a sign turned in the branch,
-        // before the barrier, did not reach the store).
+        // (but for the sign of the last one, which the store turns.  Turned in the branch, by a bare
+        // negation of c[0] after which nothing else is done to it, it is in the compiler's intermediate code
+        // and missing in what ROCm 7.2 generates from it at chunk 192: structurising the branches it takes
+        // the negation out of the last one as free, and that branch then merges the unturned value.)
         regs_to_lds<Q>(row + w * Q, c);
         __syncthreads();
         float o[Q];
@@ -1480,8 +1483,10 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
             // (nothing is in flight here, but to the compiler the early parameters may be: without
             // this it waits between the loads of a batch that share registers with them.  vmcnt(0);
             // AdamW, bf16 parameters, us, without and with it: Random 256/32 30 M 140, 134; top-k 32/8
-            // 1 M 9.0, 8.2, 32/2 with 8 replicas 9.4, 8.3)
-            if constexpr (PARAM_BF16 && !AMSGRAD) __builtin_amdgcn_s_waitcnt(0x0F70);
+            // 1 M 9.0, 8.2, 32/2 with 8 replicas 9.4, 8.3.  Not below chunk 192 without indices: Random and
+            // Striding 32/16 80 M 258, 272, 32/4 147 M 519, 532)
+            if constexpr (PARAM_BF16 && !AMSGRAD && (!SCHEME || S >= 192))
+                __builtin_amdgcn_s_waitcnt(0x0F70);
             if (!p.use_dct) {
                 // (transmitted indices in the raw domain: rare, one copy of the loop with the checks)
                 if (SCHEME && !partial)

@@ -46,8 +46,8 @@ struct DecompressLaunch {
 // A shard of at most this many 64-chunk tiles counts as small: the launch is a few occupancy
 // rounds long, so what a tile takes from its first load to its last store decides the duration,
 // not the instructions per element.  The compress half then spreads a tile over more wavefronts
-// (chunk 64: two coefficient classes instead of a lane per chunk; chunk 128: four instead of
-// two).  Measured on MI355X: 4 - 13 % shorter launches at 1,300 - 8,000 tiles, 4 - 5 % longer
+// (chunk 64: two coefficient classes instead of a lane per chunk, and four up to 512 tiles; chunk 128:
+// four instead of two).  Measured on MI355X: 4 - 13 % shorter launches at 1,300 - 8,000 tiles, 4 - 5 % longer
 // ones at 36,000.  The environment variable DETO_SMALL_SHARD_TILES overrides the limit (0: never).
 inline int64_t small_shard_tiles() {
     const char* e = getenv("DETO_SMALL_SHARD_TILES");
@@ -360,12 +360,22 @@ inline int compress_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) 
 //     chunk 64, bf16 parameters: narrow payloads, with indices or raw, 4 from 2^23 on (0.96 - 0.99), fp32
 //       values of the transform domain from 2^25 on (0.97 - 0.99); the others, and R*k = 4s, lose up to 1.07
 //     Random and Striding at chunk 32, fp32 values, bf16 parameters: 5 from 2^25 on (0.96 - 0.99)
+//     chunk 32, narrow payloads of at most four replicas (more of them up to 1.30): with indices 5, fp32
+//       parameters from 2^23 on (0.96 - 1.01), bf16 from 2^26 on (0.96 - 1.00), but not 4 and 8 entries of four
+//       replicas (1.00 - 1.03); Random and Striding with fp32 parameters from 2^24 on 5 (0.95 - 1.00), signs
+//       of the transform domain 6 (0.96 - 1.00; at 5 1.06)
 inline int adamw_workgroups(const KParams& p, int64_t n, bool idx, bool param_bf16, int classes) {
     const int64_t rk = static_cast<int64_t>(p.R) * p.k;
     const bool plain = p.val_dtype == 0 && !(idx && p.idx_u8);
     // (amsgrad's kernels, with larger batches, gain nothing)
-    if (p.amsgrad || classes != 4 || rk > p.s || n <= (int64_t{1} << 23)) return 0;
+    if (p.amsgrad || classes != 4 || n <= (int64_t{1} << 23)) return 0;
     const bool large = n > kLargeShard;
+    if (p.s == 32 && p.R <= 4 && !plain) {
+        if (idx && !param_bf16) return 5;
+        if (idx) return n > (int64_t{1} << 26) && (p.R < 4 || p.k >= 16 || p.k % 4 != 0) ? 5 : 0;
+        if (!param_bf16) return n > (int64_t{1} << 24) ? (p.use_dct && p.val_dtype == 3 ? 6 : 5) : 0;
+    }
+    if (rk > p.s) return 0;
     if (p.s == 96) return (idx ? !plain : !p.use_dct) || (large && param_bf16) ? 4 : 0;
     if (!param_bf16) return 0;
     if (p.s == 64) return plain ? (!idx && p.use_dct && large ? 4 : 0) : (idx || !p.use_dct ? 4 : 0);
