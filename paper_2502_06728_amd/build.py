@@ -30,7 +30,8 @@ UNITS = [
     "half_compress_256.hip",
     "split_narrow_256.hip", "split_narrow_192.hip", "split_narrow_128.hip",
     "split_compress_96.hip", "split_compress_64.hip", "split_narrow_96.hip",
-    "split_decompress.hip", "split_decompress_narrow.hip",
+    "split_decompress.hip", "split_decompress_narrow.hip", "split_decompress_narrow_gang.hip",
+    "split_decompress_gang.hip",
     "split_scheme_compress.hip", "split_scheme_decompress.hip",
     "split_decompress_amsgrad.hip", "split_decompress_narrow_amsgrad.hip",
     "split_scheme_decompress_amsgrad.hip",

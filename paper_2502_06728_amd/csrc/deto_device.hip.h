@@ -37,7 +37,88 @@ struct KParams {
     float eps;
     float step_size;    // eta / (1 - beta1^t)
     float inv_sqrt_bc2; // 1 / sqrt(1 - beta2^t)
+    int run_lg;         // run_log2 of this call (6: no gangs)
 };
+
+// ---- Which 64 chunks a tile is made of.  Not 64 in a row: kGang consecutive tiles (a gang) share
+// kGang * 64 chunks and take them in turn, a run of 2^lg chunks each, so that the workgroups in flight walk
+// through every array side by side, in windows of a run each, instead of each through a window of its own.
+// Memory is faster that way.  The traffic alone, without arithmetic, 147 M parameters, us, tiles in a
+// row / in turn by 32: 24 KiB read and 32 KiB written a tile, 8 wavefronts a CU 393 / 348; eight streams of
+// 8 KiB read and one rewritten 513 / 440; AdamW's three rewritten 366 / 325.  Eight tiles in turn give half of
+// that, 64 no more than 32.  (Plain stores of an interleaved stream give it away: non-temporal ones
+// there.)  The chunks that do not fill a gang are tiles of 64 in a row (lg = 6: no gangs at all).
+//
+// A run is 512 elements or more (2 KiB of fp32: a wavefront's loads stay whole), and at least `run_bytes` of
+// every payload array, below which runs cost more lines than they save: decompress, plain update, us,
+// in a row / runs of that many bytes: 64/4, 32 replicas, fp32 parameters, 60 M 253 / 128 319, 64/16,
+// 8 replicas, 147 M bf16 487 / 512 472, 1,024 455, 128/32, 4 replicas 373 (fp32) / 512 380, 1,024 373.  More
+// than 16 chunks a run (32 at chunk 16) gain nothing: 32/16 signs 546 / 553.  Chunk 96 loses 3 - 6 %, chunk
+// 192 and 256 are bound by their arithmetic (256/32 decompress 246 / 262).
+constexpr int kGang = 32;
+constexpr int kRunElems = 512, kRunBytes = 128;
+constexpr bool in_gangs(int s) { return s == 16 || s == 32 || s == 64 || s == 128; }
+// idx_bytes: of one transmitted index, 0 without indices
+__host__ __device__ constexpr int run_log2(int s, int k, int val_dtype, int idx_bytes, int run_bytes) {
+    if (!in_gangs(s)) return 6;
+    int payload = val_dtype == 3 ? 4 * ((k + 15) / 16) : k * (val_dtype == 0 ? 4 : 2);
+    if (idx_bytes != 0 && k * idx_bytes < payload) payload = k * idx_bytes;
+    int lg = 0;
+    while (lg < 6 && ((s << lg) < kRunElems || (payload << lg) < run_bytes)) ++lg;
+    return lg <= (s == 16 ? 5 : 4) ? lg : 6;
+}
+// Decompress reads a payload per replica: the more of the traffic that is, the longer its runs (us, in a
+// row / runs of that many bytes.  AdamW, 64/4: 4 replicas 147 M 550 / 128 530, 32 replicas 60 M 388 / 128
+// 427.  Plain update, 4 replicas, fp32 parameters, 60 M: 64/8 116 / 256 113, 64/4 100 / 256 103, 32/4 147 M
+// 284 / 256 272).
+__host__ __device__ constexpr int decompress_run_bytes(int s, int k, int R, bool adam) {
+    if (adam) return R * k <= s ? 128 : 256;
+    return 2 * R * k <= s && (s <= 32 || k >= 8) ? 256 : 1024;
+}
+
+struct TileRows {
+    int64_t first;      // chunk of row 0
+    uint32_t skip;      // chunks between a run's end and the next one's start
+    int lg;
+    // row r's chunk, counted from `first`
+    __host__ __device__ __forceinline__ uint32_t chunk(uint32_t r) const { return r + (r >> lg) * skip; }
+    // item e (of row r) of the tile's, `unit` a chunk, counted from the first chunk's first item.  (Below
+    // 2^24: 24-bit products.)
+    __device__ __forceinline__ uint32_t item(uint32_t e, uint32_t r, uint32_t unit) const {
+        return e + __umul24(r >> lg, skip * unit);
+    }
+    // The accesses below are a uniform base and a 32-bit offset of the lane; what these functions give is
+    // added to the pointer one after the other, so that it stays that way.
+    // Elements e .. e + 4 * kWave - 1 that a wavefront takes at a time, S a chunk (a run is a multiple of
+    // that): where the first one is
+    template <int S>
+    __device__ __forceinline__ uint32_t quads(uint32_t e) const {
+        return e + ((e / S) >> lg) * (skip * S);
+    }
+    // item it * BLOCK + within (within < BLOCK), UNIT a chunk, LG = lg: the block's part and the lane's
+    template <int UNIT, int LG, int BLOCK>
+    __device__ __forceinline__ uint32_t block(int it) const {
+        constexpr int kRun = UNIT << LG;
+        if constexpr (LG >= 6 || (kRun % BLOCK != 0 && BLOCK % kRun != 0)) return 0u;
+        else return it * BLOCK + (it * BLOCK / kRun) * (skip * UNIT);
+    }
+    template <int UNIT, int LG, int BLOCK>
+    __device__ __forceinline__ uint32_t within_block(int it, uint32_t within) const {
+        constexpr int kRun = UNIT << LG;
+        if constexpr (LG >= 6) return it * BLOCK + within;
+        else if constexpr (kRun % BLOCK == 0) return within;
+        else if constexpr (BLOCK % kRun == 0) return within + __umul24(within / kRun, skip * UNIT);
+        else return it * BLOCK + within + __umul24((it * BLOCK + within) / kRun, skip * UNIT);
+    }
+};
+
+__host__ __device__ __forceinline__ TileRows tile_rows(int64_t tile, int64_t tiles, int lg) {
+    const int64_t gang = tile / kGang;
+    if (lg < 6 && (gang + 1) * kGang <= tiles)
+        return {gang * (kGang * kWave) + ((tile % kGang) << lg),
+                static_cast<uint32_t>(kGang - 1) << lg, lg};
+    return {tile * kWave, 0u, lg};
+}
 
 // AdamW moment arrays (device pointers; vmax only with amsgrad)
 struct AdamPtrs {
@@ -54,7 +135,8 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 // Per-site policy (measured on MI355X, OLMo-1B shard): the decompress kernel gains from
 // the hint on every access; the compress kernel, which rewrites the momentum it has just
-// read, does not.
+// read, on its stores where tiles are in gangs (LG < 6: 64/32 374 us without both, 372 with gangs alone,
+// 360 with both; without gangs the hint costs 4 %).
 #ifndef DETO_NT_COMPRESS_GRAD
 #define DETO_NT_COMPRESS_GRAD 0
 #endif
@@ -62,10 +144,10 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 #define DETO_NT_COMPRESS_MOM 0
 #endif
 #ifndef DETO_NT_COMPRESS_PAYLOAD
-#define DETO_NT_COMPRESS_PAYLOAD 0
+#define DETO_NT_COMPRESS_PAYLOAD (LG < 6)
 #endif
 #ifndef DETO_NT_COMPRESS_MOM_ST
-#define DETO_NT_COMPRESS_MOM_ST 0
+#define DETO_NT_COMPRESS_MOM_ST (LG < 6)
 #endif
 #ifndef DETO_NT_DECOMPRESS_LD
 #define DETO_NT_DECOMPRESS_LD 1

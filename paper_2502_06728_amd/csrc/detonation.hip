@@ -142,7 +142,9 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
         !aligned(coeff_dbg, 4))
         return DETO_ERR_ALIGN;
 
-    const KParams p = resolve(cfg, 1, val_dtype, idx_dtype);
+    KParams p = resolve(cfg, 1, val_dtype, idx_dtype);
+    p.run_lg = deto::run_log2(p.s, p.k, val_dtype, idx_out ? static_cast<int>(idx_size(idx_dtype)) : 0,
+                              deto::kRunBytes);
     const int64_t C = chunks_of(n, p.s);
     hipStream_t st = static_cast<hipStream_t>(stream);
     fresh_status();
@@ -290,6 +292,10 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         return DETO_ERR_ALIGN;
 
     KParams p = resolve(cfg, R, val_dtype, idx_dtype);
+    p.run_lg = n <= deto::kGangShard
+                   ? 6
+                   : deto::run_log2(p.s, p.k, val_dtype, idx ? static_cast<int>(idx_size(idx_dtype)) : 0,
+                                    deto::decompress_run_bytes(p.s, p.k, R, opt != nullptr));
     if (opt) {
         const double bc1 = 1.0 - std::pow(static_cast<double>(opt->beta1),
                                           static_cast<double>(opt->step));
@@ -359,7 +365,9 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         const bool few = deto::few_chunks_decompress(p, C, idx != nullptr);
         auto split = [few](const deto::DecompressLaunch& d, int classes) -> int64_t {
             if (few || classes == 0) return 0;
-            int64_t c = deto::launch_decompress_split(d, classes);
+            int64_t c = deto::launch_decompress_split_gang(d, classes);
+            if (!c) c = deto::launch_decompress_split_narrow_gang(d, classes);
+            if (!c) c = deto::launch_decompress_split(d, classes);
             if (!c) c = deto::launch_decompress_split_narrow(d, classes);
             if (!c) c = deto::launch_decompress_split_amsgrad(d, classes);
             return c ? c : deto::launch_decompress_split_narrow_amsgrad(d, classes);

@@ -319,7 +319,7 @@ __device__ __forceinline__ void store_tile_rows(const float* __restrict__ buf, i
 template <int S, int ROWS = kMfmaChunks>
 __device__ __forceinline__ void emit_tied_chunks(float* __restrict__ buf, const KParams& p,
                                                  int lane, int need, uint32_t thr_gt,
-                                                 uint32_t thr_eq, int64_t chunk0,
+                                                 uint32_t thr_eq, const TileRows& rows,
                                                  void* __restrict__ idx_out,
                                                  void* __restrict__ val_out,
                                                  float* __restrict__ coeff_dbg) {
@@ -331,7 +331,7 @@ __device__ __forceinline__ void emit_tied_chunks(float* __restrict__ buf, const 
         if (c_need == 0) continue;
         const uint32_t c_gt = __builtin_amdgcn_readlane(thr_gt, tt);
         const uint32_t c_eq = __builtin_amdgcn_readlane(thr_eq, tt);
-        const int64_t chunk = chunk0 + tt;
+        const int64_t chunk = rows.first + rows.chunk(tt);
         int kept_before = 0, eq_before = 0;
 #pragma unroll
         for (int e0 = 0; e0 < S; e0 += kWave) {
@@ -509,7 +509,8 @@ __attribute__((amdgpu_waves_per_eu(MfmaGeom<NB>::kWavesPerSimd))) void compress_
             }
         }
         wave_lds_sync();
-        emit_tied_chunks<G::S>(buf, p, lane, need, thr_gt, thr_eq, chunk0, idx_out, val_out, coeff_dbg);
+        emit_tied_chunks<G::S>(buf, p, lane, need, thr_gt, thr_eq, TileRows{chunk0, 0u, 6}, idx_out, val_out,
+                                coeff_dbg);
         wave_lds_sync();
 
         // ---- new momentum = inverse transform of the remainder

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kWave) void compress_pair(KParams p, int64_t tiles,
 #pragma unroll
         for (int m = 0; m < H; ++m) row[2 * m + h] = c[m];
         wave_lds_sync();
-        emit_tied_chunks<32 * NB>(buf, p, lane, need, thr_gt, thr_eq, chunk0, idx_out, val_out,
+        emit_tied_chunks<32 * NB>(buf, p, lane, need, thr_gt, thr_eq, TileRows{chunk0, 0u, 6}, idx_out, val_out,
                              nullptr);
         wave_lds_sync();
     }

@@ -33,7 +33,15 @@ int64_t launch_compress_split_128(const CompressLaunch& a) {
             if (a.grad_bf16) LAUNCH(4, true, 0);
             else LAUNCH(4, false, 0);
         }
-    } else if (p.k <= 16) {
+        return a.n_chunks;
+    }
+#undef LAUNCH
+    // tiles in gangs
+#define LAUNCH(W, BF16, TOP)                                                               \
+    compress_split<128, W, BF16, TOP, false, false, true>                                  \
+        <<<grid, SplitGeom<128, W>::kThreads, 0, a.stream>>>(                              \
+            p, tiles, a.n, a.n_chunks, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
+    if (p.k <= 16) {
         // a launch with k <= 16 sorts out only every lane's 16 largest magnitudes
         if (a.grad_bf16) LAUNCH(DETO_SPLIT_W, true, 16);
         else LAUNCH(DETO_SPLIT_W, false, 16);

@@ -8,6 +8,11 @@
 #ifndef DETO_SPLIT_AMSGRAD
 #define DETO_SPLIT_AMSGRAD false
 #endif
+#ifndef DETO_SPLIT_GANG
+#define DETO_SPLIT_GANG false
+#define DETO_SPLIT_SHAPES(X) \
+    X(16, 2) X(32, 2) X(32, 4) X(64, 2) X(64, 4) X(96, 2) X(96, 4) X(128, 2) X(128, 4) X(192, 4) X(256, 4)
+#endif
 #include "split_kernels.hip.h"
 #include "tiled_launch.h"
 
@@ -20,6 +25,7 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
 #else
     if (!a.idx || DETO_SPLIT_NARROW != (p.val_dtype != 0 || p.idx_u8)) return 0;
     if (DETO_SPLIT_AMSGRAD != (p.adam && p.amsgrad)) return 0;
+    if (DETO_SPLIT_GANG && !decompress_gangs(p, classes)) return 0;
     const int64_t tiles = (a.n / p.s) / kWave;
     // one workgroup per full tile and one for the chunks left over (a partial tile)
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);
@@ -27,7 +33,7 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
     const unsigned grid = static_cast<unsigned>(grid64);
     const unsigned spare = spare_lds(a, classes);
 #define LAUNCH(S, W, BF16)                                                                      \
-    decompress_split<S, W, BF16, DETO_SPLIT_NARROW, false, DETO_SPLIT_AMSGRAD>                  \
+    decompress_split<S, W, BF16, DETO_SPLIT_NARROW, false, DETO_SPLIT_AMSGRAD, DETO_SPLIT_GANG> \
         <<<grid, W * kWave, spare, a.stream>>>(p, tiles, a.n, a.n_chunks, a.idx, a.idx_stride,  \
                                                a.val, a.val_stride, a.params, a.adam,           \
                                                a.presign_dbg)
@@ -37,8 +43,7 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
         else LAUNCH(S, W, false);                                                               \
         return a.n_chunks;   /* the tail chunks ride along */                                   \
     }
-    X(16, 2) X(32, 2) X(32, 4) X(64, 2) X(64, 4) X(96, 2) X(96, 4) X(128, 2) X(128, 4)
-    X(192, 4) X(256, 4)
+    DETO_SPLIT_SHAPES(X)
 #undef X
 #undef LAUNCH
     return 0;

@@ -468,7 +468,9 @@ __device__ __forceinline__ void shuffle_places(uint64_t seed, uint64_t step, uin
 // of workgroups per CU is what overlaps memory phases with arithmetic.  Chunk 192 with the
 // partial sort fits three (168 registers, 52 KB of LDS with the dump slots inside the rows);
 // chunk 256 two (a 64-row tile alone is 65 KB); chunk 96 / 128 four to six of two wavefronts.
-template <int S, int W, bool GRAD_BF16, int TOP = 0, bool NARROW = false, bool SCHEME = false>
+// GANG: tiles in gangs (run_log2); fp32 values and int32 indices, top-k.
+template <int S, int W, bool GRAD_BF16, int TOP = 0, bool NARROW = false, bool SCHEME = false,
+          bool GANG = false>
 __global__ __launch_bounds__(kWave * W)
 __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ grad,
@@ -499,8 +501,15 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     const bool partial = tile >= tiles;    // (a partial tile can have 64 rows, the last ragged)
     const int live = partial ? static_cast<int>(n_chunks - tiles * kWave) : kWave;
     const bool alive = lane < live;
-    const int64_t base = tile * static_cast<int64_t>(kWave * S);
-    const int64_t chunk0 = tile * kWave;
+    static_assert(!GANG || (!NARROW && !SCHEME), "one payload format");
+    const TileRows rows = GANG ? tile_rows(tile, tiles, p.run_lg) : TileRows{tile * kWave, 0u, 6};
+    const int64_t chunk0 = rows.first;
+    const int64_t base = chunk0 * S;
+    // where the thread's piece `it` of the tile (element 4 * (tid + kThreads * it)) is in an array
+    auto piece = [&](auto* array, int it) {
+        if constexpr (GANG) return array + (base + rows.quads<S>(4 * kWave * (w + W * it))) + 4u * lane;
+        else return array + base + 4 * (tid + kThreads * it);
+    };
     float* row = &buf[lane * kRow];
     if (tid == 0) s_tie = 0ull;
 
@@ -508,16 +517,17 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     // rows past a partial tile's chunks become zero)
     {
         constexpr int kIt = Q / 4;               // 16-byte pieces per thread
-        auto fold_piece = [&](int e4) {
+        auto fold_piece = [&](int it) {
+            const int e4 = 4 * (tid + kThreads * it);
             const int r = e4 / S, col = e4 - r * S;
-            const float4 m = ld_f4<false>(mom + base + e4);
+            const float4 m = ld_f4<false>(piece(mom, it));
             float4 g;
             if constexpr (GRAD_BF16) {
-                const uint2 gb = ld_u2<false>(static_cast<const uint16_t*>(grad) + base + e4);
+                const uint2 gb = ld_u2<false>(piece(static_cast<const uint16_t*>(grad), it));
                 g = make_float4(__uint_as_float(gb.x << 16), __uint_as_float(gb.x & 0xFFFF0000u),
                                 __uint_as_float(gb.y << 16), __uint_as_float(gb.y & 0xFFFF0000u));
             } else {
-                g = ld_f4<false>(static_cast<const float*>(grad) + base + e4);
+                g = ld_f4<false>(piece(static_cast<const float*>(grad), it));
             }
             *reinterpret_cast<float4*>(&buf[r * kRow + col]) =
                 make_float4(fmaf(p.beta, m.x, g.x), fmaf(p.beta, m.y, g.y),
@@ -525,13 +535,13 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         };
         if (!partial) {
 #pragma unroll
-            for (int it = 0; it < kIt; ++it) fold_piece(4 * (tid + kThreads * it));
+            for (int it = 0; it < kIt; ++it) fold_piece(it);
         } else {
             for (int it = 0; it < kIt; ++it) {
                 const int e4 = 4 * (tid + kThreads * it);
                 const int64_t i0 = base + e4;
                 if (i0 + 3 < n) {
-                    fold_piece(e4);
+                    fold_piece(it);
                 } else {
                     // the piece that straddles the end of the shard, and everything past it
                     const int r = e4 / S, col = e4 - r * S;
@@ -572,7 +582,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         __syncthreads();
     }
     if (coeff_dbg && alive) {
-        float* dbg = coeff_dbg + (chunk0 + lane) * S + off;
+        float* dbg = coeff_dbg + (chunk0 + rows.chunk(lane)) * S + off;
 #pragma unroll
         for (int m = 0; m < Q; ++m) dbg[W * m] = c[m];
     }
@@ -750,7 +760,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
             if (w == 0) {
                 const unsigned long long tl = __ballot(need != 0);
                 if (lane == 0) s_tie = tl;
-                emit_tied_chunks<S, kWave>(buf, p, lane, need, thr_gt, thr_eq, chunk0, idx_out,
+                emit_tied_chunks<S, kWave>(buf, p, lane, need, thr_gt, thr_eq, rows, idx_out,
                                            val_out, nullptr);
             }
             __syncthreads();
@@ -829,6 +839,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         const uint32_t magic = entry_magic(k);
         const unsigned long long tie_chunks = s_tie;
         // entries e .. e+3 of the tile (k a multiple of 4: they belong to one chunk)
+        // (gangs: entry e of row r is this many entries further on)
+        auto further = [&](uint32_t r) -> uint32_t { return GANG ? rows.item(0u, r, k) : 0u; };
         auto store_index4 = [&](uint32_t e, const float* src) {
             if (SCHEME && !idx_out) return;       // not transmitted
             const float4 iv = *reinterpret_cast<const float4*>(src + kIdx0);
@@ -838,7 +850,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(idx_out) + chunk0 * k + e) =
                     static_cast<uint32_t>(i4.x | (i4.y << 8) | (i4.z << 16) | (i4.w << 24));
             else
-                *reinterpret_cast<int4*>(static_cast<int32_t*>(idx_out) + chunk0 * k + e) = i4;
+                st_u4<GANG>(static_cast<int32_t*>(idx_out) + chunk0 * k + e,
+                             make_uint4(i4.x, i4.y, i4.z, i4.w));
         };
         if (k % 4 == 0) {
             const int quads = live * k / 4;                // 16-byte pieces of the tile
@@ -848,9 +861,10 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 const uint32_t j = e - r * static_cast<uint32_t>(k);
                 if ((tie_chunks >> r) & 1ull) continue;    // written by the tie pass
                 const float* src = &buf[r * kRow + j];
+                const uint32_t to = e + further(r);
                 const float4 v = *reinterpret_cast<const float4*>(src);
                 if (!NARROW || p.val_dtype == 0) {
-                    st_f4<false>(static_cast<float*>(val_out) + chunk0 * k + e, v);
+                    st_f4<GANG>(static_cast<float*>(val_out) + chunk0 * k + to, v);
                 } else if (p.val_dtype != 3) {
                     uint2 h;
                     if (p.val_dtype == 1) {
@@ -860,9 +874,9 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                         h.x = f32_to_f16(v.x) | (static_cast<uint32_t>(f32_to_f16(v.y)) << 16);
                         h.y = f32_to_f16(v.z) | (static_cast<uint32_t>(f32_to_f16(v.w)) << 16);
                     }
-                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(val_out) + chunk0 * k + e) = h;
+                    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(val_out) + chunk0 * k + to) = h;
                 }
-                store_index4(e, src);
+                store_index4(to, src);
             }
         } else {
             // four entries of a lane could straddle two chunks (and the arrays need not be
@@ -879,8 +893,8 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                     if (!SCHEME || idx_out)
                         store_payload_index(idx_out, chunk0 * k + e, p.idx_u8, at);
                 } else {
-                    static_cast<float*>(val_out)[chunk0 * k + e] = src[0];
-                    static_cast<int32_t*>(idx_out)[chunk0 * k + e] = at;
+                    static_cast<float*>(val_out)[chunk0 * k + e + further(r)] = src[0];
+                    static_cast<int32_t*>(idx_out)[chunk0 * k + e + further(r)] = at;
                 }
             }
         }
@@ -936,7 +950,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
             for (int it = 0; it < kIt; ++it) {
                 const int e4 = 4 * (tid + kThreads * it);
                 const int r = e4 / S, col = e4 - r * S;
-                st_f4<true>(mom + base + e4, output4(r, col));
+                st_f4<true>(piece(mom, it), output4(r, col));
             }
         } else {
             for (int it = 0; it < kIt; ++it) {
@@ -996,6 +1010,13 @@ struct SplitPiece {
         }
         load_values(val, ve, word_byte);
     }
+    // The same from a uniform part u (and its byte uw) and a 32-bit one of the lane: a scalar base for
+    // the access.
+    __device__ __forceinline__ void load_from(const void* idx, int64_t iu, const void* val, int64_t vu,
+                                              uint32_t e, int64_t wu, uint32_t word_byte) {
+        load(static_cast<const char*>(idx) + iu * (U8 ? 1 : 4), e,
+             static_cast<const char*>(val) + (VAL == 3 ? wu : vu * (VAL == 0 ? 4 : 2)), e, word_byte);
+    }
     __device__ __forceinline__ void load_values(const void* val, int64_t ve, int64_t word_byte) {
         if constexpr (VEC == 4) {
             if constexpr (VAL == 0) {
@@ -1037,11 +1058,14 @@ struct SplitPiece {
 // Inside a group a replica's entries hit distinct accumulators when the indices of every lane,
 // and the step from the previous lane, ascend strictly (what compress emits): a plain
 // read-add-write then; LDS atomics otherwise (duplicates add; they cost about 3 cycles a lane).
-template <int S, int VEC, int VAL, bool U8>
+// GANG: `rows` are the tile's rows row0 .., whose chunks `gang` knows (entry0 and chunk0 are those of its
+// first one).
+template <int S, int VEC, int VAL, bool U8, bool GANG>
 __device__ __forceinline__ void split_scatter(const KParams& p, int lane, float* rows, int my_rows,
                                               const void* __restrict__ idx, int64_t idx_stride,
                                               const void* __restrict__ val, int64_t val_stride,
-                                              int64_t entry0, int64_t chunk0, uint32_t magic) {
+                                              int64_t entry0, int64_t chunk0, uint32_t magic,
+                                              const TileRows& gang, int row0) {
     constexpr int kRow = S + 4;
     constexpr int kBatch = 4;                              // replicas per batch
     using Piece = SplitPiece<VEC, VAL, U8>;
@@ -1065,12 +1089,18 @@ __device__ __forceinline__ void split_scatter(const KParams& p, int lane, float*
         locate(t, in, e, r, j);
         const int r0 = (t % n_batches) * kBatch;
         const int64_t word_byte = (chunk0 + r) * chunk_bytes + j / 4;
+        const uint32_t at = gang.item(row0 * k + e, row0 + r, k);
+        const uint32_t byte = gang.item((row0 + r) * chunk_bytes + j / 4, row0 + r, chunk_bytes);
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
             if (r0 + i < p.R && in) {
                 const int64_t rep = r0 + i;
-                b[i].load(idx, rep * idx_stride + entry0 + e, val,
-                          rep * val_stride + entry0 + e, rep * val_stride * 4 + word_byte);
+                if constexpr (GANG)
+                    b[i].load_from(idx, rep * idx_stride + entry0, val, rep * val_stride + entry0, at,
+                                   rep * val_stride * 4 + chunk0 * chunk_bytes, byte);
+                else
+                    b[i].load(idx, rep * idx_stride + entry0 + e, val,
+                              rep * val_stride + entry0 + e, rep * val_stride * 4 + word_byte);
             } else {
                 b[i].clear();
             }
@@ -1188,8 +1218,11 @@ __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, flo
 // checks in the same kernel and like this: amsgrad, signs, bf16, 256/32 10 M 92, 70, 128/16 10 M 66,
 // 57; fp32 64/8 2 M 17.7, 15.8; and the other launches: 64/20 signs 60 M SGD 122, 109, Random 32/5 60 M
 // 90, 71, 16/3 signs 30 M 61, 57.
-template <int S, int W, bool PARAM_BF16, bool NARROW = false, bool SCHEME = false, bool AMSGRAD = false>
-__global__ __launch_bounds__(kWave * W) void decompress_split(
+// GANG: tiles in gangs (run_log2), transmitted indices.  (80 registers are six wavefronts per SIMD, 81 five.)
+template <int S, int W, bool PARAM_BF16, bool NARROW = false, bool SCHEME = false, bool AMSGRAD = false,
+          bool GANG = false>
+__global__ __launch_bounds__(kWave * W)
+__attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ idx,
     int64_t idx_stride, const void* __restrict__ val, int64_t val_stride,
     void* __restrict__ params, AdamPtrs ad, float* __restrict__ presign_dbg) {
@@ -1210,7 +1243,16 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
     const int live = partial ? static_cast<int>(n_chunks - tiles * kWave) : kWave;
     // rows of this wavefront's share that are chunks
     const int my_rows = min(max(live - w * kRowsPerWave, 0), kRowsPerWave);
-    const int64_t base = tile * static_cast<int64_t>(kWave * S);
+    static_assert(!GANG || (!SCHEME && !AMSGRAD), "transmitted indices");
+    const TileRows gang = GANG ? tile_rows(tile, tiles, p.run_lg) : TileRows{tile * kWave, 0u, 6};
+    const int64_t base = gang.first * S;
+    // where the thread's piece `it` of the tile (element 4 * (tid + kThreads * it)) is, as a uniform part and
+    // the lane's
+    auto piece = [&](int it) -> int64_t {
+        if constexpr (GANG) return base + gang.quads<S>(4 * kWave * (w + W * it));
+        else return base + 4 * (tid + kThreads * it);
+    };
+    const uint32_t lane4 = GANG ? 4u * lane : 0u;
     float* row = &buf[lane * kRow];
 
     // ---- the tile's bf16 parameters, requested first: they are needed only after the
@@ -1225,8 +1267,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
         if (params_early) {
 #pragma unroll
             for (int it = 0; it < kPieces; ++it)
-                early[it] = ld_u2<true>(static_cast<const uint16_t*>(params) + base +
-                                        4 * (tid + kThreads * it));
+                early[it] = ld_u2<true>(static_cast<const uint16_t*>(params) + piece(it) + lane4);
         }
     }
 
@@ -1266,7 +1307,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
 
     // ---- scatter-add of this wavefront's rows, replica after replica
     {
-        const int64_t row0 = tile * kWave + w * kRowsPerWave;
+        const int64_t row0 = GANG ? gang.first : tile * kWave + w * kRowsPerWave;
         float* rows = &buf[w * kRowsPerWave * kRow];
         const uint32_t magic = entry_magic(k);
         // (the format is settled once, out here: a branch on it at every piece would cut the
@@ -1275,11 +1316,13 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
             constexpr int VAL = decltype(val_tag)::value;
             constexpr bool U8 = decltype(u8_tag)::value;
             if (k % 4 == 0)
-                split_scatter<S, 4, VAL, U8>(p, lane, rows, my_rows, idx, idx_stride, val,
-                                             val_stride, row0 * k, row0, magic);
+                split_scatter<S, 4, VAL, U8, GANG>(p, lane, rows, my_rows, idx, idx_stride, val,
+                                                   val_stride, row0 * k, row0, magic, gang,
+                                                   GANG ? w * kRowsPerWave : 0);
             else
-                split_scatter<S, 1, VAL, U8>(p, lane, rows, my_rows, idx, idx_stride, val,
-                                             val_stride, row0 * k, row0, magic);
+                split_scatter<S, 1, VAL, U8, GANG>(p, lane, rows, my_rows, idx, idx_stride, val,
+                                                   val_stride, row0 * k, row0, magic, gang,
+                                                   GANG ? w * kRowsPerWave : 0);
         };
         // Striding / Random without transmitted indices
         [[maybe_unused]] auto place_sums = [&](auto val_tag) {
@@ -1361,31 +1404,31 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
             float4 old4[kBatch], m4[kBatch], v4[kBatch], x4[AMSGRAD ? kBatch : 1];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
-                const int64_t i = base + 4 * (tid + kThreads * (b0 + j));
+                const int64_t u = piece(b0 + j), i = u + lane4;
                 if constexpr (kGuarded) {
                     old4[j] = m4[j] = v4[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     if constexpr (AMSGRAD) x4[j] = old4[j];
                     if (i + 3 >= n) continue;   // the shard's end: handled below
                 }
                 if constexpr (PARAM_BF16) {
-                    const uint2 pb = ld_u2<true>(static_cast<const uint16_t*>(params) + i);
+                    const uint2 pb = ld_u2<true>(static_cast<const uint16_t*>(params) + u + lane4);
                     old4[j] = make_float4(__uint_as_float(pb.x << 16),
                                           __uint_as_float(pb.x & 0xFFFF0000u),
                                           __uint_as_float(pb.y << 16),
                                           __uint_as_float(pb.y & 0xFFFF0000u));
                 } else {
-                    old4[j] = ld_f4<true>(static_cast<const float*>(params) + i);
+                    old4[j] = ld_f4<true>(static_cast<const float*>(params) + u + lane4);
                 }
                 if (adam) {
-                    m4[j] = ld_f4<true>(ad.m + i);
-                    v4[j] = ld_f4<true>(ad.v + i);
-                    if constexpr (AMSGRAD) x4[j] = ld_f4<true>(ad.vmax + i);
+                    m4[j] = ld_f4<true>(ad.m + u + lane4);
+                    v4[j] = ld_f4<true>(ad.v + u + lane4);
+                    if constexpr (AMSGRAD) x4[j] = ld_f4<true>(ad.vmax + u + lane4);
                 }
             }
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const int e4 = 4 * (tid + kThreads * (b0 + j));
-                const int64_t i = base + e4;
+                const int64_t u = piece(b0 + j), i = u + lane4;
                 if (kGuarded && i + 3 >= n) {
                     // the piece that straddles the end of the shard: element by element
                     if (i < n) {
@@ -1416,7 +1459,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                     continue;
                 }
                 const float4 y4 = output4(e4, raw_tag);
-                if (presign_dbg) st_f4<false>(presign_dbg + i, y4);
+                if (presign_dbg) st_f4<false>(presign_dbg + u + lane4, y4);
                 const float y[4] = {y4.x, y4.y, y4.z, y4.w};
                 const float old[4] = {old4[j].x, old4[j].y, old4[j].z, old4[j].w};
                 float nw[4];
@@ -1430,9 +1473,9 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                     for (int e = 0; e < 4; ++e)
                         nw[e] = adamw_step<AMSGRAD>(p, old[e], sign_or_self(y[e], p.use_sign), m[e],
                                                     v[e], x[e]);
-                    st_f4<true>(ad.m + i, make_float4(m[0], m[1], m[2], m[3]));
-                    st_f4<true>(ad.v + i, make_float4(v[0], v[1], v[2], v[3]));
-                    if constexpr (AMSGRAD) st_f4<true>(ad.vmax + i, make_float4(x[0], x[1], x[2], x[3]));
+                    st_f4<true>(ad.m + u + lane4, make_float4(m[0], m[1], m[2], m[3]));
+                    st_f4<true>(ad.v + u + lane4, make_float4(v[0], v[1], v[2], v[3]));
+                    if constexpr (AMSGRAD) st_f4<true>(ad.vmax + u + lane4, make_float4(x[0], x[1], x[2], x[3]));
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -1442,9 +1485,9 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                     uint2 o;
                     o.x = pack_bf16x2(nw[0], nw[1]);
                     o.y = pack_bf16x2(nw[2], nw[3]);
-                    st_u2<true>(static_cast<uint16_t*>(params) + i, o);
+                    st_u2<true>(static_cast<uint16_t*>(params) + u + lane4, o);
                 } else {
-                    st_f4<true>(static_cast<float*>(params) + i,
+                    st_f4<true>(static_cast<float*>(params) + u + lane4,
                                 make_float4(nw[0], nw[1], nw[2], nw[3]));
                 }
             }
@@ -1454,9 +1497,9 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
 #pragma unroll
             for (int it = 0; it < kPieces; ++it) {
                 const int e4 = 4 * (tid + kThreads * it);
-                const int64_t i = base + e4;
+                const int64_t u = piece(it);
                 const float4 y4 = output4(e4, raw_tag);
-                if (presign_dbg) st_f4<false>(presign_dbg + i, y4);
+                if (presign_dbg) st_f4<false>(presign_dbg + u + lane4, y4);
                 const float y[4] = {y4.x, y4.y, y4.z, y4.w};
                 const float old[4] = {__uint_as_float(early[it].x << 16),
                                       __uint_as_float(early[it].x & 0xFFFF0000u),
@@ -1469,7 +1512,7 @@ __global__ __launch_bounds__(kWave * W) void decompress_split(
                 uint2 o;
                 o.x = pack_bf16x2(nw[0], nw[1]);
                 o.y = pack_bf16x2(nw[2], nw[3]);
-                st_u2<true>(static_cast<uint16_t*>(params) + i, o);
+                st_u2<true>(static_cast<uint16_t*>(params) + u + lane4, o);
             }
         };
         if (params_early) {

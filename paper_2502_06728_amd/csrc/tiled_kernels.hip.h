@@ -98,20 +98,23 @@ __device__ __forceinline__ ChunkMask<S> mask_from_words(const MaskWords& m) {
 }
 
 // ---- phase 1 of compress: m1 = beta*m + g, coalesced, into the LDS tile
-template <int S, bool GRAD_BF16>
+template <int S, int LG, bool GRAD_BF16>
 __device__ __forceinline__ void fold_tile_to_lds(const KParams& p, const void* __restrict__ grad,
-                                                 const float* __restrict__ mom, int64_t ebase,
+                                                 const float* __restrict__ mom, const TileRows& rows,
                                                  float* tile, int lane) {
     using G = TileGeom<S>;
+    const int64_t ebase = rows.first * S;
 #pragma unroll
     for (int it = 0; it < S / 8; ++it) {
         const int pe = it * 512 + lane * 8;
-        const float4 ma = ld_f4<DETO_NT_COMPRESS_MOM>(mom + ebase + pe);
-        const float4 mb = ld_f4<DETO_NT_COMPRESS_MOM>(mom + ebase + pe + 4);
+        const int64_t ge = ebase + rows.block<S, LG, 512>(it);
+        const uint32_t at = rows.within_block<S, LG, 512>(it, lane * 8);
+        const float4 ma = ld_f4<DETO_NT_COMPRESS_MOM>(mom + ge + at);
+        const float4 mb = ld_f4<DETO_NT_COMPRESS_MOM>(mom + ge + at + 4);
         float g[8];
         if constexpr (GRAD_BF16) {
             const uint4 raw =
-                ld_u4<DETO_NT_COMPRESS_GRAD>(static_cast<const uint16_t*>(grad) + ebase + pe);
+                ld_u4<DETO_NT_COMPRESS_GRAD>(static_cast<const uint16_t*>(grad) + ge + at);
             g[0] = __uint_as_float(raw.x << 16);
             g[1] = __uint_as_float(raw.x & 0xFFFF0000u);
             g[2] = __uint_as_float(raw.y << 16);
@@ -122,9 +125,9 @@ __device__ __forceinline__ void fold_tile_to_lds(const KParams& p, const void* _
             g[7] = __uint_as_float(raw.w & 0xFFFF0000u);
         } else {
             const float4 ga =
-                ld_f4<DETO_NT_COMPRESS_GRAD>(static_cast<const float*>(grad) + ebase + pe);
+                ld_f4<DETO_NT_COMPRESS_GRAD>(static_cast<const float*>(grad) + ge + at);
             const float4 gb =
-                ld_f4<DETO_NT_COMPRESS_GRAD>(static_cast<const float*>(grad) + ebase + pe + 4);
+                ld_f4<DETO_NT_COMPRESS_GRAD>(static_cast<const float*>(grad) + ge + at + 4);
             g[0] = ga.x; g[1] = ga.y; g[2] = ga.z; g[3] = ga.w;
             g[4] = gb.x; g[5] = gb.y; g[6] = gb.z; g[7] = gb.w;
         }
@@ -186,14 +189,16 @@ constexpr int staging_row(int k) {
 // past kept ones, so a dropped element is overwritten by the next kept one.
 // VAL selects the payload format: 0 = fp32 values + int32 indices; 1 (bf16) / 2 (fp16) =
 // 16-bit values + byte indices (the values in c are then already rounded to that format).
-template <int S, int K, int VAL = 0>
+template <int S, int K, int VAL, int LG>
 __device__ __forceinline__ void compact_and_store_payload(const float (&c)[S],
                                                           const ChunkMask<S>& mk, float* tile,
                                                           int lane,
                                                           void* __restrict__ idx_out_v,
                                                           void* __restrict__ val_out_v,
-                                                          int64_t pbase) {
+                                                          const TileRows& rows) {
     using G = TileGeom<S>;
+    const int64_t pbase = rows.first * K;
+    const uint32_t own = rows.chunk(lane);
     constexpr int PR = staging_row(K);              // staging row, one spare slot + pad
     float* vrow = tile + lane * PR;
     uint8_t* ibytes = reinterpret_cast<uint8_t*>(tile + kWave * PR);   // indices as bytes
@@ -214,7 +219,7 @@ __device__ __forceinline__ void compact_and_store_payload(const float (&c)[S],
             // ternary: the lane packs the signs of its chunk's K staged values, two bits each
             // (0 = zero, 1 = +1, 3 = -1), into ceil(K/16) words
             constexpr int W = (K + 15) / 16;
-            uint32_t* words = static_cast<uint32_t*>(val_out_v) + (pbase / K) * W + lane * W;
+            uint32_t* words = static_cast<uint32_t*>(val_out_v) + (rows.first + own) * W;
             uint32_t wv[W];
 #pragma unroll
             for (int w = 0; w < W; ++w) wv[w] = 0u;
@@ -246,6 +251,8 @@ __device__ __forceinline__ void compact_and_store_payload(const float (&c)[S],
             for (int it = 0; it < K / 4; ++it) {
                 const int e = it * 256 + lane * 4;
                 const int r = e / K, col = e % K;
+                const int64_t ge = pbase + rows.block<K, LG, 256>(it);
+                const uint32_t at = rows.within_block<K, LG, 256>(it, lane * 4);
                 const float4 v = *reinterpret_cast<const float4*>(tile + r * PR + col);
                 uint2 packed;
                 if constexpr (VAL == 1) {
@@ -257,11 +264,11 @@ __device__ __forceinline__ void compact_and_store_payload(const float (&c)[S],
                     packed.y =
                         encode16<VAL>(v.z) | (static_cast<uint32_t>(encode16<VAL>(v.w)) << 16);
                 }
-                *reinterpret_cast<uint2*>(val16 + pbase + e) = packed;
+                *reinterpret_cast<uint2*>(val16 + ge + at) = packed;
             }
         } else {
             // k = 1, 2: the lane stores its own chunk's entries
-            uint16_t* val16 = static_cast<uint16_t*>(val_out_v) + pbase + lane * K;
+            uint16_t* val16 = static_cast<uint16_t*>(val_out_v) + pbase + own * K;
 #pragma unroll
             for (int j = 0; j < K; ++j) val16[j] = encode16<VAL>(vrow[j]);
         }
@@ -272,12 +279,13 @@ __device__ __forceinline__ void compact_and_store_payload(const float (&c)[S],
                 for (int it = 0; it < K / 4; ++it) {
                     const int e = it * 256 + lane * 4;
                     const int r = e / K, col = e % K;
-                    *reinterpret_cast<uint32_t*>(idx8 + pbase + e) =
+                    *reinterpret_cast<uint32_t*>(idx8 + pbase + rows.block<K, LG, 256>(it) +
+                                                 rows.within_block<K, LG, 256>(it, lane * 4)) =
                         *reinterpret_cast<const uint32_t*>(ibytes + r * PR + col);
                 }
             } else {
 #pragma unroll
-                for (int j = 0; j < K; ++j) idx8[pbase + lane * K + j] = irow[j];
+                for (int j = 0; j < K; ++j) idx8[pbase + own * K + j] = irow[j];
             }
         }
         wave_lds_sync();
@@ -290,37 +298,50 @@ __device__ __forceinline__ void compact_and_store_payload(const float (&c)[S],
         for (int it = 0; it < K / 4; ++it) {
             const int e = it * 256 + lane * 4;
             const int r = e / K, col = e % K;
-            st_f4<DETO_NT_COMPRESS_PAYLOAD>(val_out + pbase + e,
+            const int64_t ge = pbase + rows.block<K, LG, 256>(it);
+                const uint32_t at = rows.within_block<K, LG, 256>(it, lane * 4);
+            st_f4<DETO_NT_COMPRESS_PAYLOAD>(val_out + ge + at,
                                             *reinterpret_cast<const float4*>(tile + r * PR + col));
             if (idx_out) {
                 const uint32_t pk = *reinterpret_cast<const uint32_t*>(ibytes + r * PR + col);
                 st_u4<DETO_NT_COMPRESS_PAYLOAD>(
-                    idx_out + pbase + e,
+                    idx_out + ge + at,
                     make_uint4(pk & 0xFFu, (pk >> 8) & 0xFFu, (pk >> 16) & 0xFFu, pk >> 24));
             }
         }
     } else {
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            val_out[pbase + lane * K + j] = vrow[j];
-            if (idx_out) idx_out[pbase + lane * K + j] = irow[j];
+            val_out[pbase + own * K + j] = vrow[j];
+            if (idx_out) idx_out[pbase + own * K + j] = irow[j];
         }
     }
     wave_lds_sync();
 }
 
 // ---- phase 3b of compress: the tile (rows = residual momentum) out, coalesced
-template <int S>
+template <int S, int LG>
 __device__ __forceinline__ void store_tile_momentum(const float* tile, float* __restrict__ mom,
-                                                    int64_t ebase, int lane) {
+                                                    const TileRows& rows, int lane) {
     using G = TileGeom<S>;
+    const int64_t ebase = rows.first * S;
+    if constexpr (LG >= 6) {
 #pragma unroll
-    for (int it = 0; it < S / 8; ++it) {
-        const int pe = it * 512 + lane * 8;
+        for (int it = 0; it < S / 8; ++it) {
+            const int pe = it * 512 + lane * 8;
+            const float* src = tile + (pe / S) * G::kRow + (pe % S);
+            st_f4<false>(mom + ebase + pe, *reinterpret_cast<const float4*>(src));
+            st_f4<false>(mom + ebase + pe + 4, *reinterpret_cast<const float4*>(src + 4));
+        }
+        return;
+    }
+#pragma unroll
+    for (int it = 0; it < S / 4; ++it) {
+        const int pe = it * 256 + lane * 4;
         const float* src = tile + (pe / S) * G::kRow + (pe % S);
-        st_f4<DETO_NT_COMPRESS_MOM_ST>(mom + ebase + pe, *reinterpret_cast<const float4*>(src));
-        st_f4<DETO_NT_COMPRESS_MOM_ST>(mom + ebase + pe + 4,
-                                       *reinterpret_cast<const float4*>(src + 4));
+        st_f4<DETO_NT_COMPRESS_MOM_ST>(mom + ebase + rows.block<S, LG, 256>(it) +
+                                           rows.within_block<S, LG, 256>(it, lane * 4),
+                                       *reinterpret_cast<const float4*>(src));
     }
 }
 
@@ -372,9 +393,11 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
                                            idx_out, val_out, coeff_dbg);
         return;
     }
-    const int64_t ebase = t * G::kElems;
+    constexpr int kLg = run_log2(S, K, VAL, VAL ? 1 : 4, kRunBytes);
+    const TileRows rows = tile_rows(t, n_tiles, kLg);
+    const int64_t own = rows.first + rows.chunk(lane);     // the lane's chunk
 
-    fold_tile_to_lds<S, GRAD_BF16>(p, grad, mom, ebase, tile, lane);
+    fold_tile_to_lds<S, kLg, GRAD_BF16>(p, grad, mom, rows, tile, lane);
     wave_lds_sync();
 
     // ---- phase 2: lane = chunk
@@ -384,7 +407,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
     FastDct<S>::dct2(c);
     c[0] *= p.alpha0;
     static_for<1, S>([&](auto i) { c[i] *= p.alpha; });
-    if (coeff_dbg) regs_to_global<S>(coeff_dbg + ebase + static_cast<int64_t>(lane) * S, c);
+    if (coeff_dbg) regs_to_global<S>(coeff_dbg + own * S, c);
 
     // threshold: K-th largest magnitude
     static_assert(S <= 64, "a chunk and its sorted magnitudes live in one lane's registers");
@@ -440,7 +463,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
             c[i] = r;
         });
     }
-    compact_and_store_payload<S, K, VAL>(c, mk, tile, lane, idx_out, val_out, t * (kWave * K));
+    compact_and_store_payload<S, K, VAL, kLg>(c, mk, tile, lane, idx_out, val_out, rows);
 
     // ---- m <- m1 - q.  With q = D^T(kept coefficients) and m1 = D^T(all coefficients), the
     // residual is the inverse transform of the dropped ones.
@@ -449,7 +472,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
     FastDct<S>::dct3(u);
     regs_to_row<S>(row, u);
     wave_lds_sync();
-    store_tile_momentum<S>(tile, mom, ebase, lane);
+    store_tile_momentum<S, kLg>(tile, mom, rows, lane);
 }
 
 // Compress half for Striding and Random on full tiles, in the raw-momentum domain or (with
@@ -473,9 +496,11 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
                                            idx_out, val_out, coeff_dbg);
         return;
     }
-    const int64_t ebase = t * G::kElems;
+    constexpr int kLg = run_log2(S, K, VAL, 0, kRunBytes);
+    const TileRows rows = tile_rows(t, n_tiles, kLg);
+    const int64_t own = rows.first + rows.chunk(lane);     // the lane's chunk
 
-    fold_tile_to_lds<S, GRAD_BF16>(p, grad, mom, ebase, tile, lane);
+    fold_tile_to_lds<S, kLg, GRAD_BF16>(p, grad, mom, rows, tile, lane);
     wave_lds_sync();
 
     float* row = tile + lane * G::kRow;
@@ -486,12 +511,12 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
         c[0] *= p.alpha0;
         static_for<1, S>([&](auto i) { c[i] *= p.alpha; });
     }
-    if (coeff_dbg) regs_to_global<S>(coeff_dbg + ebase + static_cast<int64_t>(lane) * S, c);
+    if (coeff_dbg) regs_to_global<S>(coeff_dbg + own * S, c);
 
     ChunkMask<S> mk = mask_from_words<S>(stride_mask);
     if (p.scheme == 2) {
         wave_lds_sync();   // rows are in registers: the tile doubles as shuffle scratch
-        mk = random_mask<S, K>(p.seed, p.step, static_cast<uint64_t>(t) * kWave + lane,
+        mk = random_mask<S, K>(p.seed, p.step, static_cast<uint64_t>(own),
                                reinterpret_cast<uint8_t*>(tile) + lane * G::kPermStride);
         wave_lds_sync();
     }
@@ -505,12 +530,10 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
             u[i] = mk.bit(i) ? (c[i] - r) : c[i];
             c[i] = r;
         });
-        compact_and_store_payload<S, K, VAL>(c, mk, tile, lane, idx_out, val_out,
-                                             t * (kWave * K));
+        compact_and_store_payload<S, K, VAL, kLg>(c, mk, tile, lane, idx_out, val_out, rows);
         static_for<0, S>([&](auto i) { c[i] = u[i]; });
     } else {
-        compact_and_store_payload<S, K, VAL>(c, mk, tile, lane, idx_out, val_out,
-                                             t * (kWave * K));
+        compact_and_store_payload<S, K, VAL, kLg>(c, mk, tile, lane, idx_out, val_out, rows);
         static_for<0, S>([&](auto i) { c[i] = mk.bit(i) ? 0.0f : c[i]; });
     }
     if (p.use_dct) {
@@ -520,7 +543,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
     }
     regs_to_row<S>(row, c);
     wave_lds_sync();
-    store_tile_momentum<S>(tile, mom, ebase, lane);
+    store_tile_momentum<S, kLg>(tile, mom, rows, lane);
 }
 
 // One replica's payload entries of a tile, as each lane holds them after a coalesced load:
@@ -534,10 +557,12 @@ struct PayloadRegs<K, 0> {
     static constexpr int kVec = (K % 4 == 0) ? K / 4 : 1;
     int4 i[kVec];
     float4 v[kVec];
-    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, int e) {
-        const uint4 iv = ld_u4<DETO_NT_DECOMPRESS_LD>(static_cast<const int32_t*>(ir) + e);
+    // (entry u + e: a uniform part and the lane's)
+    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, uint32_t u,
+                                         uint32_t e) {
+        const uint4 iv = ld_u4<DETO_NT_DECOMPRESS_LD>(static_cast<const int32_t*>(ir) + u + e);
         i[it] = make_int4(iv.x, iv.y, iv.z, iv.w);
-        v[it] = ld_f4<DETO_NT_DECOMPRESS_LD>(static_cast<const float*>(vr) + e);
+        v[it] = ld_f4<DETO_NT_DECOMPRESS_LD>(static_cast<const float*>(vr) + u + e);
     }
     template <int C>
     __device__ __forceinline__ uint32_t idx(int it) const {
@@ -554,9 +579,10 @@ struct PayloadRegs {
     static constexpr int kVec = (K % 4 == 0) ? K / 4 : 1;
     uint32_t i[kVec];
     uint2 v[kVec];
-    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, int e) {
-        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + e);
-        v[it] = ld_u2<DETO_NT_DECOMPRESS_LD>(static_cast<const uint16_t*>(vr) + e);
+    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, uint32_t u,
+                                         uint32_t e) {
+        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + u + e);
+        v[it] = ld_u2<DETO_NT_DECOMPRESS_LD>(static_cast<const uint16_t*>(vr) + u + e);
     }
     template <int C>
     __device__ __forceinline__ uint32_t idx(int it) const {
@@ -578,9 +604,11 @@ struct PayloadRegs<K, 3> {
     static constexpr int kChunkBytes = 4 * ((K + 15) / 16);
     uint32_t i[kVec];
     uint32_t v[kVec];
-    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, int e) {
-        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + e);
-        v[it] = static_cast<const uint8_t*>(vr)[(e / K) * kChunkBytes + (e % K) / 4];
+    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, uint32_t u,
+                                         uint32_t e) {
+        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + u + e);
+        const uint32_t all = u + e;
+        v[it] = static_cast<const uint8_t*>(vr)[(all / K) * kChunkBytes + (all % K) / 4];
     }
     template <int C>
     __device__ __forceinline__ uint32_t idx(int it) const {
@@ -593,12 +621,14 @@ struct PayloadRegs<K, 3> {
     }
 };
 
-template <int K, int VAL>
+template <int K, int VAL, int LG>
 __device__ __forceinline__ void load_payload(PayloadRegs<K, VAL>& r, const void* __restrict__ ir,
-                                             const void* __restrict__ vr, int lane) {
+                                             const void* __restrict__ vr, const TileRows& rows,
+                                             int lane) {
     static_assert(K % 4 == 0, "vector path");
 #pragma unroll
-    for (int it = 0; it < K / 4; ++it) r.load(it, ir, vr, it * 256 + lane * 4);
+    for (int it = 0; it < K / 4; ++it) 
+        r.load(it, ir, vr, rows.block<K, LG, 256>(it), rows.within_block<K, LG, 256>(it, lane * 4));
 }
 
 // a[chunk][index] += value; an index outside [0,S) lands in the row's padding slot S.
@@ -685,18 +715,19 @@ struct ParamRegs {
     float4 f[PARAM_BF16 ? 1 : 2 * kIt];
 };
 
-template <int S, bool PARAM_BF16>
+template <int S, int LG, bool PARAM_BF16>
 __device__ __forceinline__ void load_params(ParamRegs<S, PARAM_BF16>& th,
-                                            const void* __restrict__ params, int64_t ebase,
+                                            const void* __restrict__ params, const TileRows& rows,
                                             int lane) {
 #pragma unroll
     for (int it = 0; it < S / 8; ++it) {
-        const int pe = it * 512 + lane * 8;
+        const int64_t ge = rows.first * S + rows.block<S, LG, 512>(it);
+        const uint32_t at = rows.within_block<S, LG, 512>(it, lane * 8);
         if constexpr (PARAM_BF16) {
             th.b[it] =
-                ld_u4<DETO_NT_DECOMPRESS_LD>(static_cast<const uint16_t*>(params) + ebase + pe);
+                ld_u4<DETO_NT_DECOMPRESS_LD>(static_cast<const uint16_t*>(params) + ge + at);
         } else {
-            const float* src = static_cast<const float*>(params) + ebase + pe;
+            const float* src = static_cast<const float*>(params) + ge + at;
             th.f[2 * it] = ld_f4<DETO_NT_DECOMPRESS_LD>(src);
             th.f[2 * it + 1] = ld_f4<DETO_NT_DECOMPRESS_LD>(src + 4);
         }
@@ -705,20 +736,22 @@ __device__ __forceinline__ void load_params(ParamRegs<S, PARAM_BF16>& th,
 
 // Last phase of decompress: the tile rows hold Q; theta <- theta*(1-eta*lambda) - eta*Q,
 // coalesced, rounded to the parameter dtype.
-template <int S, bool PARAM_BF16>
+template <int S, int LG, bool PARAM_BF16>
 __device__ __forceinline__ void update_params_from_tile(const KParams& p, const float* tile,
                                                         const ParamRegs<S, PARAM_BF16>& th,
-                                                        void* __restrict__ params, int64_t ebase,
+                                                        void* __restrict__ params, const TileRows& rows,
                                                         int lane) {
     using G = TileGeom<S>;
 #pragma unroll
     for (int it = 0; it < S / 8; ++it) {
         const int pe = it * 512 + lane * 8;
+        const int64_t ge = rows.first * S + rows.block<S, LG, 512>(it);
+        const uint32_t at = rows.within_block<S, LG, 512>(it, lane * 8);
         const float* src = tile + (pe / S) * G::kRow + (pe % S);
         const float4 qa = *reinterpret_cast<const float4*>(src);
         const float4 qb = *reinterpret_cast<const float4*>(src + 4);
         if constexpr (PARAM_BF16) {
-            uint16_t* dst = static_cast<uint16_t*>(params) + ebase + pe;
+            uint16_t* dst = static_cast<uint16_t*>(params) + ge + at;
             const uint4 raw = th.b[it];
             auto upd = [&](uint32_t w, float q0, float q1) -> uint32_t {
                 const float t0 = __uint_as_float(w << 16) * p.wd_scale;
@@ -732,7 +765,7 @@ __device__ __forceinline__ void update_params_from_tile(const KParams& p, const 
             out.w = upd(raw.w, qb.z, qb.w);
             st_u4<DETO_NT_DECOMPRESS_ST>(dst, out);
         } else {
-            float* dst = static_cast<float*>(params) + ebase + pe;
+            float* dst = static_cast<float*>(params) + ge + at;
             float4 ta = th.f[2 * it];
             float4 tb = th.f[2 * it + 1];
             ta.x = fmaf(-p.lr, qa.x, ta.x * p.wd_scale);
@@ -753,8 +786,7 @@ __device__ __forceinline__ void update_params_from_tile(const KParams& p, const 
 // domain), optional export, sign, back into the lane's LDS row.
 template <int S>
 __device__ __forceinline__ void finish_chunk(const KParams& p, float (&y)[S], float* row,
-                                             float* __restrict__ presign_dbg, int64_t ebase,
-                                             int lane) {
+                                             float* __restrict__ presign_dbg, int64_t own) {
     if (p.use_dct) {
         y[0] *= p.alpha0 * p.inv_R;
         const float ar = p.alpha * p.inv_R;
@@ -763,7 +795,7 @@ __device__ __forceinline__ void finish_chunk(const KParams& p, float (&y)[S], fl
     } else {
         static_for<0, S>([&](auto i) { y[i] *= p.inv_R; });
     }
-    if (presign_dbg) regs_to_global<S>(presign_dbg + ebase + static_cast<int64_t>(lane) * S, y);
+    if (presign_dbg) regs_to_global<S>(presign_dbg + own * S, y);
     static_for<0, S>([&](auto i) { y[i] = sign_or_self(y[i], p.use_sign); });
     regs_to_row<S>(row, y);
 }
@@ -832,15 +864,17 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
                                               presign_dbg);
         return;
     }
-    const int64_t ebase = t * G::kElems;
-    const int64_t pbase = t * (kWave * K);
+    constexpr int kLg = 6;      // (no gangs: what large launches gain by them runs on the classes)
+    const TileRows rows = tile_rows(t, n_tiles, kLg);
+    const uint32_t own = rows.chunk(lane);                 // the lane's chunk, from the first one
+    const int64_t pbase = rows.first * K;
     // replica r's entries of this tile, in bytes from the array bases
     // (ternary: ceil(K/16) words per chunk, replica stride in 32-bit words)
     constexpr int kIdxBytes = VAL ? 1 : 4, kValBytes = VAL ? 2 : 4;
     constexpr int kTernaryWords = (K + 15) / 16;
     const char* idx = static_cast<const char*>(idx_v) + pbase * kIdxBytes;
     const char* val = static_cast<const char*>(val_v) +
-                      (VAL == 3 ? t * (kWave * kTernaryWords * 4) : pbase * kValBytes);
+                      (VAL == 3 ? rows.first * (kTernaryWords * 4) : pbase * kValBytes);
     const int64_t idx_step = idx_stride * kIdxBytes;
     const int64_t val_step = val_stride * (VAL == 3 ? 4 : kValBytes);
 
@@ -856,7 +890,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
         constexpr int kBuf = K > 32 ? 2 : (K > 8 ? 3 : 8);
         PayloadRegs<K, VAL> b[kBuf];
         auto fetch = [&](PayloadRegs<K, VAL>& dst, int r) {
-            load_payload<K, VAL>(dst, idx + r * idx_step, val + r * val_step, lane);
+            load_payload<K, VAL, kLg>(dst, idx + r * idx_step, val + r * val_step, rows, lane);
         };
 #pragma unroll
         for (int i = 0; i < kBuf; ++i)
@@ -882,22 +916,22 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
             for (int i = 0; i < kBatch; ++i) {
                 if (r0 + i < p.R) {
                     const int r = r0 + i;
-                    const char* ir = idx + r * idx_step + lane * K * kIdxBytes;
+                    const char* ir = idx + r * idx_step + own * K * kIdxBytes;
                     const char* vr = val + r * val_step;
                     if constexpr (VAL == 3) {
                         static_assert(K < 16, "one word per chunk");
-                        raw[i][0] = reinterpret_cast<const uint32_t*>(vr)[lane];
+                        raw[i][0] = reinterpret_cast<const uint32_t*>(vr)[own];
                     }
 #pragma unroll
                     for (int j = 0; j < K; ++j) {
                         if constexpr (VAL == 0) {
                             at[i][j] =
                                 static_cast<uint32_t>(reinterpret_cast<const int32_t*>(ir)[j]);
-                            raw[i][j] = reinterpret_cast<const uint32_t*>(vr)[lane * K + j];
+                            raw[i][j] = reinterpret_cast<const uint32_t*>(vr)[own * K + j];
                         } else {
                             at[i][j] = reinterpret_cast<const uint8_t*>(ir)[j];
                             if constexpr (VAL != 3)
-                                raw[i][j] = reinterpret_cast<const uint16_t*>(vr)[lane * K + j];
+                                raw[i][j] = reinterpret_cast<const uint16_t*>(vr)[own * K + j];
                         }
                     }
                 }
@@ -914,15 +948,15 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
         }
     }
     ParamRegs<S, PARAM_BF16> th;
-    load_params<S, PARAM_BF16>(th, params, ebase, lane);
+    load_params<S, kLg, PARAM_BF16>(th, params, rows, lane);
     wave_lds_sync();
 
     float* row = tile + lane * G::kRow;
     float y[S];
     row_to_regs<S>(row, y);
-    finish_chunk<S>(p, y, row, presign_dbg, ebase, lane);
+    finish_chunk<S>(p, y, row, presign_dbg, rows.first + own);
     wave_lds_sync();
-    update_params_from_tile<S, PARAM_BF16>(p, tile, th, params, ebase, lane);
+    update_params_from_tile<S, kLg, PARAM_BF16>(p, tile, th, params, rows, lane);
 }
 
 // Decompress-and-update half for Striding and Random without transmitted indices: every
@@ -947,31 +981,35 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
                                               presign_dbg);
         return;
     }
-    const int64_t ebase = t * G::kElems;
-    const int64_t pbase = t * (kWave * K);
+    // (R is not known here: runs as for many replicas.  fp32 parameters: 64/32, coefficients, 147 M 388, 394)
+    constexpr int kLg = PARAM_BF16 ? run_log2(S, K, VAL, 0, 1024) : 6;
+    const TileRows rows = tile_rows(t, n_tiles, kLg);
+    const uint32_t own = rows.chunk(lane);                 // the lane's chunk, from the first one
+    const int64_t pbase = rows.first * K;
     constexpr int PR = staging_row(K);
     static_assert(kWave * PR * 4 + kWave * G::kPermStride <= G::kFloats * 4, "LDS layout");
 
     ParamRegs<S, PARAM_BF16> th;
-    load_params<S, PARAM_BF16>(th, params, ebase, lane);
+    load_params<S, kLg, PARAM_BF16>(th, params, rows, lane);
 
     // sum over replicas, coalesced; staged as [chunk][k].  One replica's four consecutive
     // entries it*256 + 4*lane ... of this tile, as loaded (k a multiple of 4):
     [[maybe_unused]] auto load4 = [&](int r, int it) -> RawQuad<VAL> {
-        const int e = it * 256 + lane * 4;
+        const uint32_t u = rows.block<K, kLg, 256>(it);
+        const uint32_t e = rows.within_block<K, kLg, 256>(it, lane * 4);
         RawQuad<VAL> q;
         if constexpr (VAL == 0) {
             q.v = ld_f4<DETO_NT_DECOMPRESS_LD>(static_cast<const float*>(val_v) + r * val_stride +
-                                               pbase + e);
+                                               pbase + u + e);
         } else if constexpr (VAL == 3) {
             // two-bit signs: ceil(K/16) words per chunk, replica stride in words
             constexpr int kChunkBytes = 4 * ((K + 15) / 16);
             const uint8_t* bytes = static_cast<const uint8_t*>(val_v) + r * val_stride * 4 +
-                                   t * (kWave * kChunkBytes);
-            q.b = bytes[(e / K) * kChunkBytes + (e % K) / 4];
+                                   rows.first * kChunkBytes;
+            q.b = bytes[((u + e) / K) * kChunkBytes + ((u + e) % K) / 4];
         } else {
             q.w = ld_u2<DETO_NT_DECOMPRESS_LD>(static_cast<const uint16_t*>(val_v) +
-                                               r * val_stride + pbase + e);
+                                               r * val_stride + pbase + u + e);
         }
         return q;
     };
@@ -1024,17 +1062,17 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
                     if constexpr (VAL == 3) {
                         static_assert(K < 16, "one word per chunk");
                         x[i][0] =
-                            static_cast<const uint32_t*>(val_v)[r * val_stride + t * kWave + lane];
+                            static_cast<const uint32_t*>(val_v)[r * val_stride + rows.first + own];
                     } else if constexpr (VAL == 0) {
 #pragma unroll
                         for (int j = 0; j < K; ++j)
                             x[i][j] = static_cast<const uint32_t*>(
-                                val_v)[r * val_stride + pbase + lane * K + j];
+                                val_v)[r * val_stride + pbase + own * K + j];
                     } else {
 #pragma unroll
                         for (int j = 0; j < K; ++j)
                             x[i][j] = static_cast<const uint16_t*>(
-                                val_v)[r * val_stride + pbase + lane * K + j];
+                                val_v)[r * val_stride + pbase + own * K + j];
                     }
                 }
             }
@@ -1052,7 +1090,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
     }
     ChunkMask<S> mk = mask_from_words<S>(stride_mask);
     if (p.scheme == 2)
-        mk = random_mask<S, K>(p.seed, p.step, static_cast<uint64_t>(t) * kWave + lane,
+        mk = random_mask<S, K>(p.seed, p.step, static_cast<uint64_t>(rows.first + own),
                                reinterpret_cast<uint8_t*>(tile + kWave * PR) +
                                    lane * G::kPermStride);
     wave_lds_sync();
@@ -1071,9 +1109,9 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
     }
     wave_lds_sync();
     float* row = tile + lane * G::kRow;
-    finish_chunk<S>(p, y, row, presign_dbg, ebase, lane);
+    finish_chunk<S>(p, y, row, presign_dbg, rows.first + own);
     wave_lds_sync();
-    update_params_from_tile<S, PARAM_BF16>(p, tile, th, params, ebase, lane);
+    update_params_from_tile<S, kLg, PARAM_BF16>(p, tile, th, params, rows, lane);
 }
 
 }  // namespace deto

@@ -49,6 +49,7 @@ struct DecompressLaunch {
 // (chunk 64: two coefficient classes instead of a lane per chunk, and four up to 512 tiles; chunk 128:
 // four instead of two).  Measured on MI355X: 4 - 13 % shorter launches at 1,300 - 8,000 tiles, 4 - 5 % longer
 // ones at 36,000.  The environment variable DETO_SMALL_SHARD_TILES overrides the limit (0: never).
+constexpr int64_t kLargeShard = int64_t{1} << 25;   // elements
 inline int64_t small_shard_tiles() {
     const char* e = getenv("DETO_SMALL_SHARD_TILES");
     if (e && *e) {
@@ -162,6 +163,9 @@ int64_t launch_decompress_split_scheme(const DecompressLaunch& a, int classes); 
 int64_t launch_decompress_split_amsgrad(const DecompressLaunch& a, int classes); // the same three,
 int64_t launch_decompress_split_narrow_amsgrad(const DecompressLaunch& a, int classes);   // AdamW
 int64_t launch_decompress_split_scheme_amsgrad(const DecompressLaunch& a, int classes);   // with amsgrad
+// ... tiles in gangs (decompress_gangs says which):
+int64_t launch_decompress_split_gang(const DecompressLaunch& a, int classes);
+int64_t launch_decompress_split_narrow_gang(const DecompressLaunch& a, int classes);
 // 16-bit values, or byte indices:
 int64_t launch_compress_split_narrow_96(const CompressLaunch& a);
 int64_t launch_compress_split_narrow_128(const CompressLaunch& a);
@@ -254,7 +258,6 @@ inline bool lane_decompress(const KParams& p) {
 //   average loss of the shapes above 40 M goes from 0.5 % to 1.4 or 2.5 %).
 //     64/32, fp32, 147 M, R = 4         512/510/504    30 M, R = 2  65/ 69/ 66
 //     64/16, fp32, 147 M, R = 4         302/305/289    30 M, R = 2  44/ 50/ 49
-constexpr int64_t kLargeShard = int64_t{1} << 25;
 inline int decompress_classes(const KParams& p, int64_t n, bool param_bf16, bool lane) {
     const int64_t rk = static_cast<int64_t>(p.R) * p.k;    // entries per chunk to scatter
     const int64_t tiles = n / (kWave * p.s);
@@ -333,7 +336,33 @@ inline int compress_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) 
     if (p.s == 16 && p.k <= 2 && grad_bf16 && tiles <= 32768) return 0;
     const bool raw = p.scheme != 0 && !p.use_dct;
     if (p.s == 64) return raw ? 6 : 0;
+    // (signs, top-k, chunk 32, 7: 32/16 147 M bf16 277, 273; 32/4 28 M fp32 65.0, 64.0; fp32 gradients from 2^25
+    // elements on 5: 32/16 333, 321, 32/4 60 M 134, 128)
+    if (p.s == 32 && p.scheme == 0 && p.val_dtype == 3)
+        return !grad_bf16 && tiles * (kWave * p.s) > kLargeShard ? 5 : 7;
     return p.s <= 32 ? (raw ? 8 : 10) : 0;
+}
+// Tiles in gangs (run_log2): fewer of them are in flight at no loss.  us without a limit, or at the one above,
+// and at the chosen one (147 M; 60 M):
+//   chunk 32, from 2^25 elements on: fp32 values, bf16 gradients, k >= 8 5 (349, 327; 147, 139), fewer
+//     entries 6 (279, 262; 118, 112), fp32 gradients 5 (399, 386; 166, 159); 16-bit values 7 and 5
+//   chunk 16, from 2^25 on, 8 (291, 284; 121, 118)
+//   chunk 64, top-k, from 2^26 on: fp32 gradients 5 (428, 416; 100 M 286, 279); bf16 with 32 fp32 entries 5
+//     (358, 349; at 60 M 150, 154), 16-bit values 7 (301, 296), others none (64/16 60 M at 5 128, 136); Striding
+//     and Random on coefficients, bf16, from 2^27 on, 6 (308, 303; 861 M 1,763, 1,719; 80 M 168, 169)
+inline int compress_gang_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) {
+    const int64_t n = tiles * (kWave * p.s);
+    if (p.scheme != 0 && !p.use_dct) return compress_workgroups(p, tiles, grad_bf16);
+    if (p.s == 64) {
+        if (n <= (int64_t{1} << 26)) return 0;
+        if (p.scheme != 0) return grad_bf16 && n > (int64_t{1} << 27) ? 6 : 0;
+        if (!grad_bf16) return 5;
+        return p.k < 32 ? 0 : p.val_dtype == 0 ? 5 : 7;
+    }
+    if (n <= kLargeShard || p.s > 32) return compress_workgroups(p, tiles, grad_bf16);
+    if (p.s == 16) return 8;
+    if (!grad_bf16) return 5;
+    return p.val_dtype != 0 ? 7 : p.k >= 8 ? 5 : 6;
 }
 //   decompress (classes: wavefronts a workgroup; 0: a lane per chunk, one wavefront), fp32 values and
 //   plain update, from 2^26 elements on but where a line says otherwise (narrow payloads are bound by
@@ -413,6 +442,40 @@ inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool par
     if (p.s == 64) return (p.k == 32 && rk >= 4 * p.s) || (p.k == 4 && p.use_dct) ? 0 : 5;
     return rk < 4 * p.s ? 6 : p.k == 4 ? 5 : 4;
 }
+// The same for tiles in gangs (run_log2), from 2^25 elements on; us without a limit, or at the one above, and at the
+// chosen one (147 M; 60 M):
+//   indices, fp32 values, plain update: chunk 128, k >= 32, 3 (bf16 488, 480; 205, 203; 16 entries 276, 284: none);
+//     chunk 64, k >= 16, R*k >= 2s 3 (471, 449; 198, 190; fp32 565, 538), s 4 (276, 271; 117, 112); chunk 32, k >= 16,
+//     from 2s on 4 bf16 (447, 437), 5 fp32 (557, 542; 233, 226), from s on 5 (280, 273) and 6 (151, 148); 4 entries
+//     8 (278, 272; fp32 and bf16)
+//   AdamW, four classes: chunk 64, indices, fp32 values 3, from 2^24 on (bf16 859, 838; 350, 341; fp32 969, 936; with
+//     R*k = 2s and few entries 351, 354: k >= 16 there), narrow ones 4 bf16, 3 fp32 (643, 628); chunk 128, R*k <= s,
+//     3 (586, 577); chunk 32, fp32 values and parameters 5 (653, 645)
+// (The same kernels with the addresses of tiles in a row are up to 5 % faster where memory is not the bound:
+// shards of less than 2^23 elements (64/8 AdamW 7 M 34.8, 36.1; 64/16 11 M 23.6, 22.1), narrow payloads under the
+// plain update (128/16 fp16 11 M 23.6, 24.1), entries one by one (128/29 35 M 76, 79).)
+constexpr int64_t kGangShard = int64_t{1} << 23;
+inline bool decompress_gangs(const KParams& p, int classes) {      // transmitted indices
+    if (p.run_lg >= 6 || classes == 0 || p.k % 4 != 0 || (p.adam && p.amsgrad)) return false;
+    if (p.s != 32 && p.s != 64 && p.s != 128) return false;
+    return (p.val_dtype == 0 && !p.idx_u8) || (p.adam && classes == 4);
+}
+inline int decompress_gang_workgroups(const KParams& p, int64_t n, bool param_bf16, int classes) {
+    const int64_t rk = static_cast<int64_t>(p.R) * p.k;
+    if (n <= (int64_t{1} << (p.adam && p.s == 64 ? 24 : 25))) return 0;
+    const bool plain = p.val_dtype == 0 && !p.idx_u8;
+    if (p.adam) {
+        if (classes != 4) return 0;
+        if (p.s == 64) return plain ? (rk <= p.s || p.k >= 16 ? 3 : 0) : param_bf16 ? 4 : 3;
+        if (p.s == 128) return rk <= p.s ? 3 : 0;
+        return p.s == 32 && plain && !param_bf16 ? 5 : 0;
+    }
+    if (p.s == 128) return p.k >= 32 ? 3 : 0;
+    if (p.s == 64) return p.k < 16 ? 0 : rk >= 2 * p.s ? 3 : rk >= p.s ? 4 : 0;
+    if (p.s != 32) return 0;
+    if (p.k < 16) return p.k == 4 ? 8 : 0;
+    return rk >= 2 * p.s ? (param_bf16 ? 4 : 5) : rk >= p.s ? (param_bf16 ? 5 : 6) : 0;
+}
 // Dynamic LDS for that: half way between what lets one workgroup more and one less onto a CU.
 // static_bytes: a tile's rows, (s + 4) floats a chunk (and, where the classes list the places
 // themselves, those; or, compress at small chunks, the working set of the general code for the tail,
@@ -424,13 +487,17 @@ inline unsigned spare_lds(int workgroups, int static_bytes) {
 }
 inline unsigned spare_lds(const CompressLaunch& a) {
     const int rows = 4 * kWave * (a.p.s + 4);
-    return spare_lds(compress_workgroups(a.p, a.tiles, a.grad_bf16), rows > 10240 ? rows : 10240);
+    const int wgs = a.p.run_lg < 6 ? compress_gang_workgroups(a.p, a.tiles, a.grad_bf16)
+                                   : compress_workgroups(a.p, a.tiles, a.grad_bf16);
+    return spare_lds(wgs, rows > 10240 ? rows : 10240);
 }
 inline unsigned spare_lds(const DecompressLaunch& a, int classes = 0) {
     const int s = a.p.s;
     const int places = (!a.idx && classes) ? kWave * s / 2 + 8 * (s < 32 ? 32 : s) : 0;
-    return spare_lds(decompress_workgroups(a.p, a.n, a.idx != nullptr, a.param_bf16, classes),
-                     4 * kWave * (s + 4) + places);
+    const int wgs = a.idx && decompress_gangs(a.p, classes)
+                        ? decompress_gang_workgroups(a.p, a.n, a.param_bf16, classes)
+                          : decompress_workgroups(a.p, a.n, a.idx != nullptr, a.param_bf16, classes);
+    return spare_lds(wgs, 4 * kWave * (s + 4) + places);
 }
 
 // Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the
