@@ -47,6 +47,8 @@ UNITS = [
     "tiled_scheme.hip", "tiled_scheme_small.hip",
     "tiled_scheme_narrow_s32.hip", "tiled_scheme_narrow_s64.hip",
     "tiled_topk_s64.hip", "tiled_topk_s32.hip", "tiled_topk_s16.hip",
+    # Striding / Random on the momentum itself
+    "raw_decompress.hip", "raw_compress.hip",
     # validation, dispatch, general kernels
     "detonation.hip",
 ]

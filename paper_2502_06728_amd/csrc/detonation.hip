@@ -186,6 +186,8 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
         deto::CompressLaunch a{p, tiles, n, C, grad, grad_dtype == DETO_BF16, momentum, idx_out,
                                val_out, coeff_dbg, {0, 0, 0, 0}, st};
         stride_pattern(p, a.stride_mask);
+        // Striding and Random on the momentum itself stream at any size
+        if (deto::launch_compress_raw(a)) return launched();
         // (chunk 64 on a small shard: two wavefronts per tile, see small_shard_tiles)
         const bool done = tiles == 0 ? false
                           : (p.scheme == DETO_SCHEME_TOPK)
@@ -362,6 +364,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
                                  val_replica_stride, params, param_dtype == DETO_BF16, presign_dbg,
                                  {0, 0, 0, 0}, st, adam};
         stride_pattern(p, a.stride_mask);
+        if (deto::launch_decompress_raw(a)) return launched();
         const bool few = deto::few_chunks_decompress(p, C, idx != nullptr);
         auto split = [few](const deto::DecompressLaunch& d, int classes) -> int64_t {
             if (few || classes == 0) return 0;

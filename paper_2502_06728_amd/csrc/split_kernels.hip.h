@@ -460,10 +460,9 @@ __device__ __forceinline__ void shuffle_places(uint64_t seed, uint64_t step, uin
 // two-bit signs, byte or int32 indices); otherwise fp32 values and int32 indices.  Only the
 // staging step (what a kept coefficient leaves behind) and the payload's way out look at the
 // format, each behind one uniform branch, so one kernel serves all of them.
-// SCHEME (with NARROW, TOP = 0): Striding or Random in either domain (p.scheme, p.use_dct)
-// instead of top-k: the kept sets do not depend on the values, so one wavefront shuffles all 64
-// chunks (Random) or every wavefront writes the same pattern (Striding), and in the raw domain
-// the transforms fall away.
+// SCHEME (with NARROW, TOP = 0): Striding or Random on the coefficients (p.scheme) instead of
+// top-k: the kept sets do not depend on the values, so one wavefront shuffles all 64 chunks
+// (Random) or every wavefront writes the same pattern (Striding).
 // Occupancy: the workgroups of a CU are each in one phase at a time (barriers), so the number
 // of workgroups per CU is what overlaps memory phases with arithmetic.  Chunk 192 with the
 // partial sort fits three (168 registers, 52 KB of LDS with the dump slots inside the rows);
@@ -567,20 +566,12 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     // ---- the lane's coefficients c[m] = coefficient W*m + off of chunk `lane`
     const int off = split_off<W>(w);
     float c[Q];
-    const bool dct = !SCHEME || p.use_dct;
-    const float alpha0 = dct ? p.alpha0 : 1.0f, alpha = dct ? p.alpha : 1.0f;
-    if (dct) {
-        split_forward_local<S, W, kFused>(row, w, c);
-        __syncthreads();                          // every class has read the chunk: rows free
-        if constexpr (W == 4) split_forward_exchange<S, kFused>(row, w, c);
-        c[0] *= (w == 0) ? p.alpha0 : p.alpha;
+    split_forward_local<S, W, kFused>(row, w, c);
+    __syncthreads();                              // every class has read the chunk: rows free
+    if constexpr (W == 4) split_forward_exchange<S, kFused>(row, w, c);
+    c[0] *= (w == 0) ? p.alpha0 : p.alpha;
 #pragma unroll
-        for (int m = 1; m < Q; ++m) c[m] *= p.alpha;
-    } else {
-#pragma unroll
-        for (int m = 0; m < Q; ++m) c[m] = row[W * m + off];
-        __syncthreads();
-    }
+    for (int m = 1; m < Q; ++m) c[m] *= p.alpha;
     if (coeff_dbg && alive) {
         float* dbg = coeff_dbg + (chunk0 + rows.chunk(lane)) * S + off;
 #pragma unroll
@@ -830,7 +821,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 r = as_f16 ? f16_to_f32(f32_to_f16(c[m])) : r;
                 left = c[m] - r;
             }
-            c[m] = (keep ? left : c[m]) * ((m == 0 && w == 0) ? alpha0 : alpha);
+            c[m] = (keep ? left : c[m]) * ((m == 0 && w == 0) ? p.alpha0 : p.alpha);
         });
     }
     __syncthreads();
@@ -926,19 +917,10 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     __syncthreads();
 
     // ---- new momentum = inverse transform of the remainder
-    if (dct) {
-        split_inverse_to_rows<S, W, kFused>(row, w, c);
-    } else {
-#pragma unroll
-        for (int m = 0; m < Q; ++m) row[W * m + off] = c[m];
-        __syncthreads();
-    }
-    auto store_momentum = [&](auto raw_tag) {
+    split_inverse_to_rows<S, W, kFused>(row, w, c);
+    {
         auto output4 = [&](int r, int col) -> float4 {
-            if constexpr (decltype(raw_tag)::value)
-                return *reinterpret_cast<const float4*>(&buf[r * kRow + col]);
-            else
-                return split_output<S, W>(&buf[r * kRow], col);
+            return split_output<S, W>(&buf[r * kRow], col);
         };
         constexpr int kIt = Q / 4;
         if (!partial) {
@@ -968,12 +950,6 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 }
             }
         }
-    };
-    if constexpr (SCHEME) {
-        if (dct) store_momentum(std::false_type{});
-        else store_momentum(std::true_type{});
-    } else {
-        store_momentum(std::false_type{});
     }
 }
 

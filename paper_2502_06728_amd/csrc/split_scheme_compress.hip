@@ -1,4 +1,4 @@
-// Striding / Random compress on the wavefront-per-coefficient-class kernels: either domain, every
+// Striding / Random compress on the wavefront-per-coefficient-class kernels: on coefficients, every
 // payload format, any k <= S/2, for what the lane-per-chunk kernels are not instantiated for
 // (chunk sizes above 64, low rates with narrow payloads).
 #include "split_kernels.hip.h"
@@ -11,7 +11,7 @@ int64_t launch_compress_split_scheme(const CompressLaunch& a) {
 #ifdef DETO_TILED_ONLY_64_32
     return 0;
 #else
-    if (p.scheme == 0 || 2 * p.k > p.s) return 0;
+    if (p.scheme == 0 || !p.use_dct || 2 * p.k > p.s) return 0;
     const int64_t tiles = (a.n / p.s) / kWave;
     // one workgroup per full tile and one for the chunks left over (a partial tile)
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);

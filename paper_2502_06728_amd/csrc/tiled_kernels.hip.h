@@ -475,9 +475,8 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
     store_tile_momentum<S, kLg>(tile, mom, rows, lane);
 }
 
-// Compress half for Striding and Random on full tiles, in the raw-momentum domain or (with
-// p.use_dct) on DCT coefficients.  Same three phases; the kept set is a bit pattern that does
-// not depend on the data: `stride_mask` for Striding, a per-chunk shuffle for Random.
+// Compress half for Striding and Random on DCT coefficients, full tiles (on the momentum itself:
+// raw_kernels.hip.h).  Same three phases; the kept set is a bit pattern that does not depend on the data: `stride_mask` for Striding, a per-chunk shuffle for Random.
 // VAL as in compact_and_store_payload (narrow formats: byte indices, if any are asked for).
 template <int S, int K, bool GRAD_BF16, int VAL = 0>
 __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_tiled_scheme(
@@ -506,11 +505,9 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
     float* row = tile + lane * G::kRow;
     float c[S];
     row_to_regs<S>(row, c);
-    if (p.use_dct) {
-        FastDct<S>::dct2(c);
-        c[0] *= p.alpha0;
-        static_for<1, S>([&](auto i) { c[i] *= p.alpha; });
-    }
+    FastDct<S>::dct2(c);
+    c[0] *= p.alpha0;
+    static_for<1, S>([&](auto i) { c[i] *= p.alpha; });
     if (coeff_dbg) regs_to_global<S>(coeff_dbg + own * S, c);
 
     ChunkMask<S> mk = mask_from_words<S>(stride_mask);
@@ -536,11 +533,9 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
         compact_and_store_payload<S, K, VAL, kLg>(c, mk, tile, lane, idx_out, val_out, rows);
         static_for<0, S>([&](auto i) { c[i] = mk.bit(i) ? 0.0f : c[i]; });
     }
-    if (p.use_dct) {
-        c[0] *= p.alpha0;
-        static_for<1, S>([&](auto i) { c[i] *= p.alpha; });
-        FastDct<S>::dct3(c);
-    }
+    c[0] *= p.alpha0;
+    static_for<1, S>([&](auto i) { c[i] *= p.alpha; });
+    FastDct<S>::dct3(c);
     regs_to_row<S>(row, c);
     wave_lds_sync();
     store_tile_momentum<S, kLg>(tile, mom, rows, lane);

@@ -163,6 +163,14 @@ int64_t launch_decompress_split_scheme(const DecompressLaunch& a, int classes); 
 int64_t launch_decompress_split_amsgrad(const DecompressLaunch& a, int classes); // the same three,
 int64_t launch_decompress_split_narrow_amsgrad(const DecompressLaunch& a, int classes);   // AdamW
 int64_t launch_decompress_split_scheme_amsgrad(const DecompressLaunch& a, int classes);   // with amsgrad
+// Striding / Random on the momentum itself (raw_kernels.hip.h): (chunk size, pieces of four elements a
+// thread)
+#define DETO_RAW_COMPRESS_LIST(X) X(16, 2) X(32, 2) X(64, 2) X(96, 3) X(128, 2) X(128, 4) X(192, 3) X(256, 4)
+#define DETO_RAW_DECOMPRESS_LIST(X) \
+    X(16, 2) X(16, 4) X(32, 2) X(32, 4) X(32, 8) X(64, 2) X(64, 4) X(64, 8) X(96, 3) X(96, 6) X(128, 2) \
+    X(128, 4) X(128, 8) X(192, 3) X(192, 6) X(256, 4) X(256, 8)
+int64_t launch_compress_raw(const CompressLaunch& a);
+int64_t launch_decompress_raw(const DecompressLaunch& a);
 // ... tiles in gangs (decompress_gangs says which):
 int64_t launch_decompress_split_gang(const DecompressLaunch& a, int classes);
 int64_t launch_decompress_split_narrow_gang(const DecompressLaunch& a, int classes);
@@ -530,6 +538,54 @@ inline bool few_chunks_decompress(const KParams& p, int64_t chunks, bool idx) {
     if (idx)
         return p.val_dtype == 3 && chunks <= 2560 && static_cast<int64_t>(p.R) * p.k >= 4 * p.s;
     return !p.use_dct && p.s >= 96 && p.R < 8 && chunks <= (p.adam ? 4096 : 2560);
+}
+
+// ---- Striding and Random on the momentum itself (raw_kernels.hip.h).  Against the kernels before them (general
+// ones, a lane per chunk, classes, the stream), geometric mean over random shapes of chunk 16 ... 256, formats,
+// optimizers and replicas: 0.74 of their time at 0.05 - 1 M elements, 0.70 at 1 - 10 M, 0.91 at 10 - 150 M.
+// Pieces of four elements a thread: few while a launch's own latency counts (1.5 M, 128/4 compress, 2 / 4 / 8
+// pieces 5.0 / 5.8 / 6.7 us; AdamW 64/8 2.6 M 9.4 / 11.4 / 14.9), more where a replica's entries of a workgroup
+// would be a short run (128/16, 49 replicas, signs, 18 M 43.5 / 36.1 / 36.4; 256/64 bf16 60 M, 4 replicas 174 /
+// 106 / 81) and for compress where the shuffle is long (128/32 7 M 19.6 / 18.9; 256/64 60 M 144 / 127 / 129).
+// Workgroups per CU of large launches, without a limit / with it (147 M): compress 128/16 fp32 328 / 4 313, bf16
+// 278 / 5 263, 32/1 signs bf16 265 / 252; decompress, fp32 parameters, 128/16 206 / 5 204; AdamW, 2 pieces, 60 M
+// 64/8 bf16 205 / 3 198, fp32 258 / 251.
+constexpr int64_t kRawLimited = int64_t{1} << 24;
+inline int raw_compress_quads(const KParams& p) {
+    if (p.s == 96 || p.s == 192) return 3;
+    return p.s == 256 || (p.s == 128 && p.k >= 32 && p.scheme == 2) ? 4 : 2;
+}
+inline int raw_compress_workgroups(int64_t n, bool grad_bf16) {
+    return n > kRawLimited ? (grad_bf16 ? 5 : 4) : 0;
+}
+inline int raw_decompress_quads(const KParams& p, int64_t n) {
+    const bool few = p.adam ? n <= (int64_t{1} << 26) : n <= (int64_t{1} << 22) && p.R < 16;
+    const bool many = !p.adam && n > (int64_t{1} << 23) && p.R * p.k >= p.s;
+    if (p.s == 96) return few ? 3 : 6;
+    if (p.s == 192) return few && n <= (int64_t{1} << 23) ? 3 : 6;
+    if (p.s == 256) return p.adam || few || p.R * p.k < p.s ? 4 : 8;
+    return few ? 2 : many && p.s != 16 ? 8 : 4;
+}
+// Not on large launches with entries one by one (two or four bytes a load; 32/13, 4 replicas, bf16 103 M 197, 239), or
+// where a lane per chunk does for bf16 parameters what is left to do (narrow values 32/1 139 M 93, 127; 32/16
+// 17 M 23.7, 26.0; 64/32, 4 replicas, 147 M 287, 294, but 64/8 30 M 35, 32), nor on launches of a few
+// wavefronts there (0.06 M 3.2, 3.7).
+inline bool raw_decompress(const KParams& p, int64_t n, bool param_bf16) {
+    const bool lane = lane_scheme(p);
+    if (n <= (int64_t{1} << 17)) return !lane;
+    if (n <= (int64_t{1} << 23)) return true;
+    if (p.k % 4 != 0) return false;
+    return !(param_bf16 && lane && (p.val_dtype != 0 || p.s <= 32 || n > (int64_t{1} << 26)));
+}
+inline int raw_decompress_workgroups(const KParams& p, int64_t n, bool param_bf16) {
+    if (n <= kLargeShard) return 0;
+    if (p.adam) return n <= (int64_t{1} << 26) && p.val_dtype == 0 ? 3 : 0;
+    return param_bf16 ? 0 : 5;
+}
+// dynamic LDS of a launch that takes `bytes` and is to have that many workgroups per CU
+inline unsigned raw_lds(int bytes, int workgroups) {
+    const int want = workgroups == 0 ? 0 : 2 * 160 * 1024 / (2 * workgroups + 1);
+    return static_cast<unsigned>(want > bytes ? want : bytes);
 }
 
 inline int64_t launch_compress_split(const CompressLaunch& a) {

@@ -1,5 +1,5 @@
 // Shared body of tiled_scheme.hip / tiled_scheme_small.hip: instantiates the Striding / Random
-// kernels (raw-momentum or coefficient domain) for the (chunk, k) pairs in DETO_SCHEME_LIST(X)
+// kernels (decompress: raw-momentum or coefficient domain) for the (chunk, k) pairs in DETO_SCHEME_LIST(X)
 // and defines the two launchers named by DETO_COMPRESS_SCHEME_FN / DETO_DECOMPRESS_SCHEME_FN.
 #include "tiled_kernels.hip.h"
 #include "tiled_launch.h"
@@ -11,7 +11,7 @@ MaskWords words(const uint32_t (&w)[4]) { return MaskWords{{w[0], w[1], w[2], w[
 }  // namespace
 
 bool DETO_COMPRESS_SCHEME_FN(const CompressLaunch& a) {
-    if (a.p.val_dtype != 0 || a.p.idx_u8) return false;   // fp32 values, int32 indices only
+    if (!a.p.use_dct || a.p.val_dtype != 0 || a.p.idx_u8) return false;   // fp32 values, int32 indices only
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
 #define X(S, K)                                                                                 \

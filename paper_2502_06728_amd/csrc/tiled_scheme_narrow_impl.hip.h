@@ -41,7 +41,7 @@ void decompress_one(const DecompressLaunch& a) {
 
 bool DETO_COMPRESS_SCHEME_NARROW_FN(const CompressLaunch& a) {
     // indices, if wanted, leave as bytes
-    if (a.p.scheme == 0 || a.p.val_dtype < 1 || a.p.val_dtype > 3 || (a.idx && !a.p.idx_u8))
+    if (a.p.scheme == 0 || !a.p.use_dct || a.p.val_dtype < 1 || a.p.val_dtype > 3 || (a.idx && !a.p.idx_u8))
         return false;
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \

@@ -1,0 +1,69 @@
+"""Striding and Random on the momentum itself, streamed: the edges of a workgroup's run of chunks, k = 1 ... s/2, all
+payload formats, index output, replicas beyond a batch of loads, both optimizers, and the large launches' rules,
+against the oracle (and the kept bits of the momentum exactly)."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import Config
+from tests import parity
+from tests.test_gpu_parity import H, make_inputs  # noqa: F401  (H: the fixture)
+from tests.test_gpu_payload_formats import FORMATS, check_update, compress_case, oracle_payloads, update_on_samples
+
+pytestmark = pytest.mark.gpu
+SCHEMES = [oracle.SCHEME_STRIDE, oracle.SCHEME_RANDOM]
+
+
+@pytest.mark.parametrize("scheme", SCHEMES)
+@pytest.mark.parametrize("s,k,elements", [
+    (16, 1, 2048), (16, 8, 2048 * 2 + 16), (32, 3, 2048 * 2 - 1), (32, 16, 2048 + 1), (64, 2, 2048 * 3 + 63),
+    (64, 32, 2048 * 2), (96, 5, 3072 + 95), (96, 48, 3072 * 2), (128, 16, 2048 * 2 + 128), (128, 32, 4096 * 2 - 127),
+    (128, 64, 4096 + 3), (192, 7, 3072 * 2 + 1), (192, 96, 3072 - 5), (256, 1, 4096), (256, 128, 4096 * 2 + 255)])
+def test_edges(H, s, k, elements, scheme):
+    formats = list({"f32+i32": (oracle.F32, False), **FORMATS}.items())
+    for i in {0, 1 + (s // 16 + k) % 5}:                   # (the other formats by turns)
+        val_dtype, idx_u8 = formats[i][1]
+        n = (1 << 17 if i == 0 and s <= 64 else 0) + elements   # (a lane per chunk serves smaller shards)
+        cfg = Config(chunk=s, topk=k, scheme=scheme, sign=i % 2 == 0, lr=1e-3, seed=11, step=5 + i, weight_decay=0.1)
+        g, m, th = make_inputs(n, seed=s + k + i, grad_bf16=i % 2 == 1, params_bf16=i % 3 == 0)
+        compress_case(H, cfg, g, m, val_dtype, idx_u8)
+        idx, val = oracle_payloads(cfg, n, val_dtype, (1, 9, 33, 2, 5, 17)[i], 300)
+        check_update(H, cfg, idx, val, val_dtype, idx_u8, th)
+        check_update(H, cfg, idx, val, val_dtype, idx_u8, th, adam=i % 2 == 0)
+
+
+@pytest.mark.parametrize("scheme", SCHEMES)
+def test_non_finite_values(H, scheme):
+    """What is kept is sent as it is; what is not stays as it is, and the rest of the chunk with it."""
+    s, k = 128, 16
+    n = s * (64 + 3)
+    cfg = Config(chunk=s, topk=k, scheme=scheme, seed=3, step=2)
+    g, m, _ = make_inputs(n, seed=1)
+    m[::97], m[1::97], m[2::97] = np.nan, np.inf, -np.inf
+    m_gpu, idx, val, coeff = H.gpu_compress(cfg, g, m)
+    kept = np.zeros(n, dtype=bool)
+    at = np.repeat(np.arange(n // s) * s, k) + idx
+    kept[at] = True
+    finite = np.isfinite(m)
+    assert np.array_equal(finite, np.isfinite(coeff[:n]))
+    assert np.array_equal(val.view(np.uint32), coeff[at].view(np.uint32))
+    assert np.array_equal(m_gpu[~kept].view(np.uint32), coeff[:n][~kept].view(np.uint32))
+    assert (m_gpu[kept & finite] == 0).all()
+
+
+@pytest.mark.parametrize("s,k,R,fmt,bf16", [(64, 8, 4, "f32+i32", True), (64, 32, 4, "f32+i32", False),
+                                            (128, 16, 9, "bf16+u8", True), (128, 8, 40, "signs+u8", False),
+                                            (96, 12, 8, "f32+i32", False), (192, 24, 3, "f16+i32", True),
+                                            (256, 64, 4, "f32+i32", True), (32, 8, 8, "f32+i32", False)])
+def test_large_launches(H, s, k, R, fmt, bf16):
+    cfg = Config(chunk=s, topk=k, scheme=oracle.SCHEME_RANDOM, seed=3, step=2)
+    update_on_samples(H, cfg, (1 << 23) + 8192 * 3 + 5 * s + 1, R, fmt, bf16)
+
+
+@pytest.mark.parametrize("s,k,bf16", [(32, 4, True), (128, 16, False)])
+def test_compress_with_fewer_workgroups(H, s, k, bf16):
+    n = (1 << 24) + 4096 + 7
+    g, m, _ = make_inputs(n, seed=k, grad_bf16=bf16)
+    cfg = Config(chunk=s, topk=k, scheme=oracle.SCHEME_RANDOM, seed=3, step=2)
+    m_gpu, idx, val, coeff = H.gpu_compress(cfg, g, m)
+    parity.check_compress(cfg, g, m, m_gpu, idx, val, coeff)
