@@ -53,14 +53,8 @@ struct SplitGeom {
     static constexpr int kThreads = kWave * W;
     static constexpr int NW = (Q + 31) / 32;        // mask words per lane
     // payload staging inside a chunk's row: values at row[pos], indices at row[kIdx0 + pos]
-    // (k <= S/2); what a lane drops goes to a dump slot of its own: past the tile in general,
-    // inside its row when k <= kRowDumpMaxK leaves room there (value at row[kRowDump + a], its
-    // index kIdx0 further on in the row's padding, row[S + a]; a = lane / 16 spreads the 64
-    // lanes of a wavefront over the 64 banks: the row stride is 4 banks.  The classes of a
-    // chunk share the slot: nobody reads it)
+    // (k <= S/2); what a lane drops goes to a dump slot of its own past the tile
     static constexpr int kIdx0 = S / 2 + 4;
-    static constexpr int kRowDump = S / 2 - 4;
-    static constexpr int kRowDumpMaxK = S / 2 - 4;
     static constexpr int kBufFloats = kTile + kThreads + kIdx0;
 };
 
@@ -465,7 +459,7 @@ __device__ __forceinline__ void shuffle_places(uint64_t seed, uint64_t step, uin
 // (Random) or every wavefront writes the same pattern (Striding).
 // Occupancy: the workgroups of a CU are each in one phase at a time (barriers), so the number
 // of workgroups per CU is what overlaps memory phases with arithmetic.  Chunk 192 with the
-// partial sort fits three (168 registers, 52 KB of LDS with the dump slots inside the rows);
+// partial sort fits three (168 registers, 52 KB of LDS with the lists of places in the mask words);
 // chunk 256 two (a 64-row tile alone is 65 KB); chunk 96 / 128 four to six of two wavefronts.
 // GANG: tiles in gangs (run_log2); fp32 values and int32 indices, top-k.
 template <int S, int W, bool GRAD_BF16, int TOP = 0, bool NARROW = false, bool SCHEME = false,
@@ -480,10 +474,20 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     constexpr int kIdx0 = G::kIdx0, kTile = G::kTile;
     // (class_sum; chunk 64: two classes and four round alike, so the shard's size does not matter)
     constexpr bool kFused = W == 4 && (NARROW || S == 64) && !SCHEME;
-    // a launch with the partial sort has k <= TOP: the dump slots fit into the rows
-    constexpr bool kRowDumps = TOP > 0 && TOP <= G::kRowDumpMaxK;
-    __shared__ __attribute__((aligned(16))) float buf[kRowDumps ? G::kTile : G::kBufFloats];
-    __shared__ uint32_t s_mask[kWave][W][NW];    // kept sets: chunk, class, word
+    // a launch with the partial sort keeps few: their places are listed (payload staging), up to 16 of
+    // a chunk in its row's padding, more in its mask words if these are as many bytes (chunk 192: 2 KB
+    // more would cost one of three workgroups per CU, 60 M parameters 156 -> 190 us)
+    constexpr bool kList = TOP > 0;
+    constexpr bool kOwnPlaces = TOP > 16 && TOP > 4 * W * NW, kMaskPlaces = TOP > 16 && !kOwnPlaces;
+    static_assert(!(kList && SCHEME), "the kept sets of top-k");
+    __shared__ __attribute__((aligned(16))) float buf[kList ? G::kTile : G::kBufFloats];
+    __shared__ __attribute__((aligned(16))) uint8_t s_places[kOwnPlaces ? kWave * TOP : 16];
+    __shared__ __attribute__((aligned(16))) uint32_t s_mask[kWave][W][NW];   // kept sets: chunk, class, word
+    auto places = [&](uint32_t r) -> uint8_t* {
+        if constexpr (kOwnPlaces) return &s_places[r * TOP];
+        else if constexpr (kMaskPlaces) return reinterpret_cast<uint8_t*>(s_mask[r]);
+        else return reinterpret_cast<uint8_t*>(&buf[r * kRow + S]);
+    };
     __shared__ uint8_t s_cnt[kWave][W];          // kept per class (at most Q <= 64)
     __shared__ unsigned long long s_tie;         // chunks of the tile that took the tie pass
 
@@ -769,7 +773,52 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     // this class is the number of kept coefficients of the chunk with a smaller index: the
     // class's own bits below m, and of another class w' its bits below m (+ 1 if that class's
     // offset is the smaller one).
-    if (need == 0 && alive) {
+    if constexpr (kList) {
+        // k <= TOP: the coefficients go into the row class by class, and a lane goes through its kept
+        // ones alone, writing down each one's index at its position.  The payload's threads take the values
+        // out of the rows and leave there what stays in the momentum.  (The walk below is a quarter of the
+        // kernel's vector instructions, 619 of 2,350 a wavefront at 128/16 with 16-bit values, and writes
+        // to a dump slot at seven of eight steps; here a lane takes the steps of the fullest class of 64
+        // chunks, about 9 there.  Compress, us, walk -> list: 10.8 M 128/16 fp16 34.9 -> 32.6, 128/4 33.8 ->
+        // 30.9; fp32 5 M 64/5 17.6 -> 16.6, 1 M 64/1 8.1 -> 7.6, 64/8 8.9 -> 8.7; 60 M 96/3 fp16 133 -> 117,
+        // 192/7 146 -> 135.  Large launches of 128 and two classes wait for memory either way.  A launch
+        // without the partial sort keeps too many: its lanes would take as many steps as the walk.)
+        regs_to_lds<Q>(row + w * Q, c);
+        uint32_t others[W - 1][NW];
+        uint32_t at = 0u;                             // (the classes' bits lined up as below)
+#pragma unroll
+        for (int o = 1; o < W; ++o) {
+            const int wo = (w + o) % W;
+            const uint32_t adj = split_off<W>(wo) < off ? 1u : 0u;
+            uint32_t ow[NW];
+#pragma unroll
+            for (int j = 0; j < NW; ++j) ow[j] = s_mask[lane][wo][j];
+            at += ow[0] & adj;
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+                others[o - 1][j] = __builtin_amdgcn_alignbit((j + 1 < NW) ? ow[j + 1] : 0u, ow[j], adj);
+        }
+        if constexpr (kMaskPlaces) __syncthreads();
+        if (need == 0 && alive) {
+            uint8_t* out = places(lane);
+#pragma unroll
+            for (int j = 0; j < NW; ++j) {
+                uint32_t left = own[j];
+                while (left != 0u) {
+                    const uint32_t m = __builtin_ctz(left);
+                    const uint32_t low = (1u << m) - 1u;
+                    uint32_t to = at;
+#pragma unroll
+                    for (int o = 0; o < W - 1; ++o) to += __popc(others[o][j] & low);
+                    out[to] = static_cast<uint8_t>(W * (32 * j + m) + off);
+                    ++at;
+                    left &= left - 1u;
+                }
+#pragma unroll
+                for (int o = 0; o < W - 1; ++o) at += __popc(others[o][j]);
+            }
+        }
+    } else if (need == 0 && alive) {
         // the other classes' bits lined up with this class's steps, and counted into the start
         uint32_t plane0[NW], plane1[NW];
         uint32_t start = 0u;
@@ -794,8 +843,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
             }
         }
         char* lds = reinterpret_cast<char*>(buf);
-        const uint32_t dump = static_cast<uint32_t>(sizeof(float)) *
-                              (kRowDumps ? lane * kRow + G::kRowDump + (lane >> 4) : kTile + tid);
+        const uint32_t dump = static_cast<uint32_t>(sizeof(float)) * (kTile + tid);
         uint32_t at = static_cast<uint32_t>(sizeof(float)) * (lane * kRow + start);
         const int idx0 = off;
         // what a kept coefficient leaves behind: the rounding error of a 16-bit format, nothing
@@ -832,17 +880,23 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         // entries e .. e+3 of the tile (k a multiple of 4: they belong to one chunk)
         // (gangs: entry e of row r is this many entries further on)
         auto further = [&](uint32_t r) -> uint32_t { return GANG ? rows.item(0u, r, k) : 0u; };
-        auto store_index4 = [&](uint32_t e, const float* src) {
+        auto store_index4 = [&](uint32_t e, const int4& i4) {
             if (SCHEME && !idx_out) return;       // not transmitted
-            const float4 iv = *reinterpret_cast<const float4*>(src + kIdx0);
-            const int4 i4 = make_int4(__float_as_int(iv.x), __float_as_int(iv.y),
-                                      __float_as_int(iv.z), __float_as_int(iv.w));
             if (NARROW && p.idx_u8)
                 *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(idx_out) + chunk0 * k + e) =
                     static_cast<uint32_t>(i4.x | (i4.y << 8) | (i4.z << 16) | (i4.w << 24));
             else
                 st_u4<GANG>(static_cast<int32_t*>(idx_out) + chunk0 * k + e,
                              make_uint4(i4.x, i4.y, i4.z, i4.w));
+        };
+        // takes coefficient i of row r out of the row: what a kept one leaves behind there is the
+        // rounding error of a 16-bit format, nothing otherwise
+        auto take = [&](uint32_t r, uint32_t i) -> float {
+            const uint32_t cls = W == 2 ? i & 1u : ((i & 1u) << 1) | ((i >> 1) & 1u);    // (split_off)
+            float* from = &buf[r * kRow + cls * Q + i / W];
+            const float v = *from;
+            *from = NARROW ? v - payload_roundtrip(p.val_dtype, v) : 0.0f;
+            return v;
         };
         if (k % 4 == 0) {
             const int quads = live * k / 4;                // 16-byte pieces of the tile
@@ -851,9 +905,20 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 const uint32_t r = __umulhi(e, magic);     // chunk of the tile, k >= 4
                 const uint32_t j = e - r * static_cast<uint32_t>(k);
                 if ((tie_chunks >> r) & 1ull) continue;    // written by the tie pass
-                const float* src = &buf[r * kRow + j];
                 const uint32_t to = e + further(r);
-                const float4 v = *reinterpret_cast<const float4*>(src);
+                float4 v;
+                int4 i4;
+                if constexpr (kList) {
+                    const uint32_t four = *reinterpret_cast<const uint32_t*>(places(r) + j);
+                    i4 = make_int4(four & 0xFFu, (four >> 8) & 0xFFu, (four >> 16) & 0xFFu, four >> 24);
+                    v = make_float4(take(r, i4.x), take(r, i4.y), take(r, i4.z), take(r, i4.w));
+                } else {
+                    const float* src = &buf[r * kRow + j];
+                    v = *reinterpret_cast<const float4*>(src);
+                    const float4 iv = *reinterpret_cast<const float4*>(src + kIdx0);
+                    i4 = make_int4(__float_as_int(iv.x), __float_as_int(iv.y), __float_as_int(iv.z),
+                                   __float_as_int(iv.w));
+                }
                 if (!NARROW || p.val_dtype == 0) {
                     st_f4<GANG>(static_cast<float*>(val_out) + chunk0 * k + to, v);
                 } else if (p.val_dtype != 3) {
@@ -867,7 +932,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                     }
                     *reinterpret_cast<uint2*>(static_cast<uint16_t*>(val_out) + chunk0 * k + to) = h;
                 }
-                store_index4(to, src);
+                store_index4(to, i4);
             }
         } else {
             // four entries of a lane could straddle two chunks (and the arrays need not be
@@ -877,14 +942,15 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
                 const uint32_t j = e - r * static_cast<uint32_t>(k);
                 if ((tie_chunks >> r) & 1ull) continue;
                 const float* src = &buf[r * kRow + j];
-                const int at = __float_as_int(src[kIdx0]);
+                const int at = kList ? places(r)[j] : __float_as_int(src[kIdx0]);
+                const float v = kList ? take(r, at) : src[0];
                 if constexpr (NARROW) {
                     if (p.val_dtype != 3)
-                        store_payload_value(val_out, chunk0 * k + e, p.val_dtype, src[0]);
+                        store_payload_value(val_out, chunk0 * k + e, p.val_dtype, v);
                     if (!SCHEME || idx_out)
                         store_payload_index(idx_out, chunk0 * k + e, p.idx_u8, at);
                 } else {
-                    static_cast<float*>(val_out)[chunk0 * k + e + further(r)] = src[0];
+                    static_cast<float*>(val_out)[chunk0 * k + e + further(r)] = v;
                     static_cast<int32_t*>(idx_out)[chunk0 * k + e + further(r)] = at;
                 }
             }
@@ -915,6 +981,14 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
         }
     }
     __syncthreads();
+    if constexpr (kList) {
+        lds_to_regs<Q>(row + w * Q, c);
+        if (need == 0) {                              // (a tied chunk's are scaled)
+            c[0] *= (w == 0) ? p.alpha0 : p.alpha;
+#pragma unroll
+            for (int m = 1; m < Q; ++m) c[m] *= p.alpha;
+        }
+    }
 
     // ---- new momentum = inverse transform of the remainder
     split_inverse_to_rows<S, W, kFused>(row, w, c);
