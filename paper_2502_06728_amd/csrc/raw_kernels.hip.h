@@ -299,16 +299,16 @@ __device__ __forceinline__ void raw_sign_sums(const KParams& p, int tid, int fir
     const int k = p.k, nw = ternary_words_per_chunk(k);
     for (int q = tid - first; q < live * nw; q += kRawThreads - first) {
         uint32_t ones[4] = {0u, 0u, 0u, 0u}, both[4] = {0u, 0u, 0u, 0u};   // byte b: field 4b + i
-        for (int r0 = 0; r0 < p.R; r0 += 30) {
-            uint32_t x[30];
+        for (int r0 = 0; r0 < p.R; r0 += 33) {          // (64 replicas: two batches)
+            uint32_t x[33];
 #pragma unroll
-            for (int i = 0; i < 30; ++i)
+            for (int i = 0; i < 33; ++i)
                 x[i] = r0 + i < p.R ? words[(r0 + i) * val_stride + q] : 0u;
 #pragma unroll
-            for (int f = 0; f < 30; f += 15) {
+            for (int f = 0; f < 33; f += 15) {
                 uint32_t o4[2] = {0u, 0u}, b4[2] = {0u, 0u};               // nibble b: field 2b + i
 #pragma unroll
-                for (int t = f; t < f + 15; t += 3) {
+                for (int t = f; t < f + 15 && t < 33; t += 3) {
                     uint32_t o2 = 0u, b2 = 0u;
 #pragma unroll
                     for (int i = t; i < t + 3; ++i) {

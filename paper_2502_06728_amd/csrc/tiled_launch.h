@@ -570,10 +570,31 @@ inline int raw_decompress_quads(const KParams& p, int64_t n) {
 // where a lane per chunk does for bf16 parameters what is left to do (narrow values 32/1 139 M 93, 127; 32/16
 // 17 M 23.7, 26.0; 64/32, 4 replicas, 147 M 287, 294, but 64/8 30 M 35, 32), nor on launches of a few
 // wavefronts there (0.06 M 3.2, 3.7).
+// Two-bit signs are words whatever k is, added 16 fields at a time here and one by one elsewhere, so large launches
+// of those come here but for a few short forms, us, before / here:
+//   bf16 parameters, a lane per chunk: from 16 replicas and 32 entries on (147 M 32/16 R = 16 252 / 194, R = 6
+//     152 / 190; 64/32 R = 64 1,040 / 315; 32/2 R = 64 339 / 303, R = 16 158 / 148; 32/1 R = 40 245 / 220, R = 16
+//     154 / 162); below 2^24 with one or two entries only from more than s on
+//   k no multiple of four, plain update: five and more (32/5 R = 64 147 M 950 / 297, R = 2 fp32 45 M 65 / 60;
+//     256/100 R = 16 fp32 147 M 704 / 284); fewer where R*k > s, R*k = s with 48 replicas or bf16 parameters from
+//     2^24 on (64/2 R = 32 100 M 122 / 104), or three with less than 16 (16/2 R = 9 147 M 245 / 184; 128/2 R = 64
+//     229 / 164; 64/3 R = 2 fp32 60 M 80.7 / 78.1; but 64/2 R = 32 fp32 60 M 97 / 106, 128/3 R = 24 fp32 60 M
+//     85 / 97: a replica's words of a workgroup are a short run)
+//   the same under AdamW: five and more (64/21 R = 64 100 M 1,036 / 490; 256/6 R = 2 100 M 373 / 338; 16/3 R = 4
+//     100 M 321 / 337), where 48 replicas and more keep an eighth of the chunk (192/7 R = 64 fp32 100 M 481 / 539)
 inline bool raw_decompress(const KParams& p, int64_t n, bool param_bf16) {
     const bool lane = lane_scheme(p);
     if (n <= (int64_t{1} << 17)) return !lane;
     if (n <= (int64_t{1} << 23)) return true;
+    if (p.val_dtype == 3) {
+        const int64_t rk = static_cast<int64_t>(p.R) * p.k;
+        if (lane && param_bf16)
+            return p.R >= 16 && rk >= 32 && (p.k >= 4 || rk > p.s || n > (int64_t{1} << 24));
+        if (p.k % 4 == 0) return true;
+        if (p.adam) return p.k >= 5 && (p.R < 48 || 8 * p.k >= p.s);
+        return p.k >= 5 || rk > p.s || (p.k == 3 && p.R < 16) ||
+               (rk == p.s && (p.R >= 48 || (param_bf16 && n > (int64_t{1} << 24))));
+    }
     if (p.k % 4 != 0) return false;
     return !(param_bf16 && lane && (p.val_dtype != 0 || p.s <= 32 || n > (int64_t{1} << 26)));
 }

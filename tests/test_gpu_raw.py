@@ -54,7 +54,11 @@ def test_non_finite_values(H, scheme):
 @pytest.mark.parametrize("s,k,R,fmt,bf16", [(64, 8, 4, "f32+i32", True), (64, 32, 4, "f32+i32", False),
                                             (128, 16, 9, "bf16+u8", True), (128, 8, 40, "signs+u8", False),
                                             (96, 12, 8, "f32+i32", False), (192, 24, 3, "f16+i32", True),
-                                            (256, 64, 4, "f32+i32", True), (32, 8, 8, "f32+i32", False)])
+                                            (256, 64, 4, "f32+i32", True), (32, 8, 8, "f32+i32", False),
+                                            # signs: batches of 33 replicas, words of one entry and of 16, odd k
+                                            (32, 1, 64, "signs+u8", True), (32, 16, 33, "signs+u8", True),
+                                            (64, 2, 34, "signs+u8", True), (16, 2, 16, "signs+u8", False),
+                                            (64, 3, 2, "signs+u8", False), (128, 13, 5, "signs+u8", True)])
 def test_large_launches(H, s, k, R, fmt, bf16):
     cfg = Config(chunk=s, topk=k, scheme=oracle.SCHEME_RANDOM, seed=3, step=2)
     update_on_samples(H, cfg, (1 << 23) + 8192 * 3 + 5 * s + 1, R, fmt, bf16)

@@ -17,6 +17,9 @@ static deto::KParams params(int s, int k, int R, int val, int adam) {
 extern "C" int takes(int s, int k, int val, int bf16, int64_t n) {
     return deto::raw_decompress(params(s, k, 2, val, 0), n, bf16 != 0);
 }
+extern "C" int takes_signs(int s, int k, int R, int bf16, int adam, int64_t n) {
+    return deto::raw_decompress(params(s, k, R, 3, adam), n, bf16 != 0);
+}
 extern "C" int compress_quads(int s, int k) { return deto::raw_compress_quads(params(s, k, 1, 0, 0)); }
 extern "C" int quads(int s, int k, int R, int adam, int64_t n) {
     return deto::raw_decompress_quads(params(s, k, R, 0, adam), n);
@@ -63,3 +66,15 @@ def test_every_choice_is_built(lib):
     (64, 8, 0, 0, 1 << 30, 1), (64, 8, 2, 1, (1 << 23) + 1, 0), (64, 8, 2, 0, (1 << 23) + 1, 1), (32, 8, 0, 1, (1 << 23) + 1, 0)])
 def test_decompress_rule(lib, s, k, val, bf16, n, want):
     assert lib.takes(s, k, val, bf16, ctypes.c_int64(n)) == want
+
+
+@pytest.mark.parametrize("s,k,R,bf16,adam,n,want", [
+    (32, 16, 15, 1, 0, 1 << 27, 0), (32, 16, 16, 1, 0, 1 << 27, 1), (32, 1, 31, 1, 0, 1 << 27, 0), (32, 1, 32, 1, 0, 1 << 27, 1),
+    (32, 2, 16, 1, 0, 1 << 24, 0), (32, 2, 17, 1, 0, 1 << 24, 1), (32, 2, 16, 1, 0, (1 << 24) + 1, 1), (64, 4, 16, 1, 0, 1 << 24, 1),
+    (64, 2, 32, 1, 0, 1 << 24, 0), (64, 2, 32, 1, 0, (1 << 24) + 1, 1),
+    (64, 5, 1, 0, 0, 1 << 24, 1), (64, 3, 15, 0, 0, 1 << 24, 1), (64, 3, 16, 0, 0, 1 << 24, 0), (64, 3, 22, 0, 0, 1 << 24, 1),
+    (32, 1, 32, 0, 0, 1 << 24, 0), (64, 1, 64, 0, 0, 1 << 24, 1), (64, 2, 32, 0, 0, 1 << 24, 0), (16, 1, 17, 0, 0, 1 << 24, 1),
+    (64, 3, 64, 1, 1, 1 << 24, 0), (64, 5, 47, 1, 1, 1 << 24, 1), (64, 7, 48, 0, 1, 1 << 24, 0), (32, 5, 48, 0, 1, 1 << 24, 1),
+    (64, 4, 64, 0, 1, 1 << 24, 1), (64, 3, 16, 0, 0, 1 << 23, 1)])
+def test_decompress_rule_of_signs(lib, s, k, R, bf16, adam, n, want):
+    assert lib.takes_signs(s, k, R, bf16, adam, ctypes.c_int64(n)) == want
