@@ -289,56 +289,20 @@ __device__ __forceinline__ void raw_entry_sums(const KParams& p, int tid, int fi
     }
 }
 
-// The same for two-bit signs, a word of 16 entries a thread.  A field is 0, 1 or 3 (2 counts as 0), so its sum
-// is (fields with bit 0) - 2 (fields with both bits): both are counted side by side, three replicas in
-// the two bits of a field, five times that in four bits, up to 64 in eight.
+// The same for two-bit signs, a word of 16 entries a thread.
 __device__ __forceinline__ void raw_sign_sums(const KParams& p, int tid, int first, int live,
                                               const uint32_t* __restrict__ words,
                                               int64_t val_stride, float* sums) {
     if (tid < first) return;
     const int k = p.k, nw = ternary_words_per_chunk(k);
     for (int q = tid - first; q < live * nw; q += kRawThreads - first) {
-        uint32_t ones[4] = {0u, 0u, 0u, 0u}, both[4] = {0u, 0u, 0u, 0u};   // byte b: field 4b + i
-        for (int r0 = 0; r0 < p.R; r0 += 33) {          // (64 replicas: two batches)
-            uint32_t x[33];
-#pragma unroll
-            for (int i = 0; i < 33; ++i)
-                x[i] = r0 + i < p.R ? words[(r0 + i) * val_stride + q] : 0u;
-#pragma unroll
-            for (int f = 0; f < 33; f += 15) {
-                uint32_t o4[2] = {0u, 0u}, b4[2] = {0u, 0u};               // nibble b: field 2b + i
-#pragma unroll
-                for (int t = f; t < f + 15 && t < 33; t += 3) {
-                    uint32_t o2 = 0u, b2 = 0u;
-#pragma unroll
-                    for (int i = t; i < t + 3; ++i) {
-                        const uint32_t one = x[i] & 0x55555555u;
-                        o2 += one;
-                        b2 += one & (x[i] >> 1);
-                    }
-                    o4[0] += o2 & 0x33333333u;
-                    o4[1] += (o2 >> 2) & 0x33333333u;
-                    b4[0] += b2 & 0x33333333u;
-                    b4[1] += (b2 >> 2) & 0x33333333u;
-                }
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    ones[i] += o4[i] & 0x0F0F0F0Fu;
-                    ones[i + 2] += (o4[i] >> 4) & 0x0F0F0F0Fu;
-                    both[i] += b4[i] & 0x0F0F0F0Fu;
-                    both[i + 2] += (b4[i] >> 4) & 0x0F0F0F0Fu;
-                }
-            }
-        }
+        const SignCounts counts(words + q, val_stride, p.R);
         const int r = q / nw, j0 = 16 * (q - r * nw);
         float* to = sums + r * k + j0;
         const int cnt = k - j0;
 #pragma unroll
-        for (int f = 0; f < 16; ++f) {
-            const int sum = static_cast<int>((ones[f % 4] >> (8 * (f / 4))) & 0xFFu) -
-                            2 * static_cast<int>((both[f % 4] >> (8 * (f / 4))) & 0xFFu);
-            if (f < cnt) to[f] = static_cast<float>(sum);
-        }
+        for (int f = 0; f < 16; ++f)
+            if (f < cnt) to[f] = counts.sum(f);
     }
 }
 

@@ -1218,6 +1218,20 @@ __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, flo
     const int k = p.k;
     const int pieces = my_rows * k / VEC;
     const int chunk_bytes = 4 * ternary_words_per_chunk(k);
+    if constexpr (VAL == 3) {
+        if (count_signs(p)) {
+            const int nw = chunk_bytes / 4;
+            const uint32_t* words = static_cast<const uint32_t*>(val) + chunk0 * nw;
+            for (int q = lane; q < my_rows * nw; q += kWave) {
+                const SignCounts counts(words + q, val_stride, p.R);
+                const int r = q / nw, j0 = 16 * (q - r * nw);
+#pragma unroll
+                for (int f = 0; f < 16; ++f)
+                    if (j0 + f < k) rows[r * kRow + place(r, j0 + f)] = counts.sum(f);
+            }
+            return;
+        }
+    }
     for (int q = lane; q < pieces; q += kWave) {
         const uint32_t e = VEC * static_cast<uint32_t>(q);
         const uint32_t r = (k == 1) ? e : __umulhi(e, magic);

@@ -1008,7 +1008,21 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
         }
         return q;
     };
-    if constexpr (K % 4 == 0) {
+    bool counted = false;
+    if constexpr (VAL == 3) {
+        counted = count_signs(p);
+        if (counted) {
+            constexpr int kWords = (K + 15) / 16;
+            static_for<0, kWords>([&](auto w) {
+                const SignCounts counts(static_cast<const uint32_t*>(val_v) + (rows.first + own) * kWords + w,
+                                        val_stride, p.R);
+                static_for<0, (K - 16 * w < 16 ? K - 16 * w : 16)>(
+                    [&](auto f) { tile[lane * PR + 16 * w + f] = counts.sum(f); });
+            });
+        }
+    }
+    if (counted) {
+    } else if constexpr (K % 4 == 0) {
         float4 acc[K / 4];
 #pragma unroll
         for (int it = 0; it < K / 4; ++it) acc[it] = load4(0, it).get();
