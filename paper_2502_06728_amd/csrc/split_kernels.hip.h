@@ -1206,7 +1206,8 @@ __device__ __forceinline__ void split_scatter(const KParams& p, int lane, float*
 
 // The same without transmitted indices (Striding, Random): every replica kept the same places, so
 // the R values of an entry are summed in registers, replica 0 first, and written to their
-// place once.  place(r, j): the place of entry j of the wavefront's row r.
+// place once.  place(r, j): the place of entry j of the wavefront's row r.  Two-bit signs of many replicas
+// (count_signs): a word of a chunk per lane.
 template <int S, int VEC, int VAL, class Place>
 __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, float* rows,
                                                  int my_rows, const void* __restrict__ val,

@@ -1008,6 +1008,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
         }
         return q;
     };
+    // two-bit signs of many replicas: the words of the lane's own chunk, 16 fields at a time
     bool counted = false;
     if constexpr (VAL == 3) {
         counted = count_signs(p);
