@@ -20,9 +20,12 @@ def test_counts(H, s, k, dct, R):
     n = s * 64 + 5 * s + 7
     cfg = Config(chunk=s, topk=k, scheme=scheme, dct=dct, sign=R != 33, lr=1e-3, seed=11, step=5, weight_decay=0.1)
     _, _, th = make_inputs(n, seed=s + k, params_bf16=R % 3 == 0)
-    idx, val = oracle_payloads(cfg, n, oracle.TERNARY, R, 300)
-    words = val.reshape(R, -1).view(np.uint32)
+    # (three replicas' payloads, moved by chunks, stand for R)
+    idx, val = oracle_payloads(cfg, n, oracle.TERNARY, 3, 300)
     nw = -(-k // 16)
+    idx = np.stack([idx[r % 3] for r in range(R)])
+    val = np.stack([np.roll(val[r % 3], r * nw, axis=0) for r in range(R)])
+    words = val.reshape(R, -1).view(np.uint32)
     for row, code in ((1, 0x55555555), (2, 0xFFFFFFFF), (3, 0xAAAAAAAA), (66, 0xE4E4E4E4)):
         words[:, row * nw:(row + 1) * nw] = code
     check_update(H, cfg, idx, val, oracle.TERNARY, True, th)
