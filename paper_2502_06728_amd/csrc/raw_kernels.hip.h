@@ -156,9 +156,9 @@ __global__ __launch_bounds__(kRawThreads) void compress_raw(
         lds_barrier();
         // (Random: the entries take the place of the shuffle, which is over)
 
-        // ---- m1 = beta*m + g; kept elements go to their entry, the rest stays.  sent(c): what the
-        // receivers decode
-        auto emit = [&](auto sent) {
+        // ---- m1 = beta*m + g; kept elements go to their entry, the rest stays.  left(c): what a kept one
+        // leaves behind
+        auto emit = [&](auto left) {
 #pragma unroll
             for (int j = 0; j < QUADS; ++j) {
                 const uint32_t i = o + 4u * kRawThreads * j;
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kRawThreads) void compress_raw(
                     const uint32_t bit = (bits >> e) & 1u;
                     if (bit) {
                         staged[entry] = c[e];
-                        c[e] -= sent(c[e]);
+                        c[e] = left(c[e]);
                     }
                     entry += bit;
                 }
@@ -201,12 +201,14 @@ __global__ __launch_bounds__(kRawThreads) void compress_raw(
                 }
             }
         };
+        // (fp32 values and signs: nothing, as a constant, so that an infinity or a NaN that was sent is gone
+        // from the momentum; c - c would keep it there as NaN)
         if (p.val_dtype == 1)
-            emit([](float c) { return __uint_as_float(pack_bf16x2(c, 0.0f) << 16); });
+            emit([](float c) { return c - __uint_as_float(pack_bf16x2(c, 0.0f) << 16); });
         else if (p.val_dtype == 2)
-            emit([](float c) { return f16_to_f32(f32_to_f16(c)); });
+            emit([](float c) { return c - f16_to_f32(f32_to_f16(c)); });
         else
-            emit([](float c) { return c; });
+            emit([](float) { return 0.0f; });
     };
     if (base + G::kElems <= n) body(std::false_type{});
     else body(std::true_type{});

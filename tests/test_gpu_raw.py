@@ -33,22 +33,31 @@ def test_edges(H, s, k, elements, scheme):
 
 
 @pytest.mark.parametrize("scheme", SCHEMES)
-def test_non_finite_values(H, scheme):
-    """What is kept is sent as it is; what is not stays as it is, and the rest of the chunk with it."""
-    s, k = 128, 16
-    n = s * (64 + 3)
+@pytest.mark.parametrize("s,k,signs", [(128, 16, False), (64, 8, False), (32, 4, False), (32, 8, True), (96, 12, True)])
+def test_non_finite_values(H, s, k, signs, scheme):
+    """What is kept is sent as it is and leaves nothing behind, an infinity or a NaN no more than a number; what is
+    not stays as it is, and the rest of the chunk with it."""
+    n = max(s * (64 + 3), (1 << 17) + s)                   # (a whole tile of chunks and some)
     cfg = Config(chunk=s, topk=k, scheme=scheme, seed=3, step=2)
     g, m, _ = make_inputs(n, seed=1)
     m[::97], m[1::97], m[2::97] = np.nan, np.inf, -np.inf
-    m_gpu, idx, val, coeff = H.gpu_compress(cfg, g, m)
-    kept = np.zeros(n, dtype=bool)
-    at = np.repeat(np.arange(n // s) * s, k) + idx
+    if signs:
+        m_gpu, idx, words, coeff = H.gpu_compress_ternary(cfg, g, m, True)
+    else:
+        m_gpu, idx, val, coeff = H.gpu_compress(cfg, g, m)
+    kept = np.zeros(coeff.size, dtype=bool)
+    at = np.repeat(np.arange(coeff.size // s) * s, k) + idx
     kept[at] = True
-    finite = np.isfinite(m)
-    assert np.array_equal(finite, np.isfinite(coeff[:n]))
-    assert np.array_equal(val.view(np.uint32), coeff[at].view(np.uint32))
+    assert (kept[:n] & ~np.isfinite(m)).any()
+    assert np.array_equal(np.isfinite(m), np.isfinite(coeff[:n]))
+    if signs:
+        number = ~np.isnan(coeff[at])                      # (a NaN is sent as either sign)
+        assert np.array_equal(oracle.decode_ternary(cfg, n, words)[number], np.sign(coeff[at][number]))
+    else:
+        assert np.array_equal(val.view(np.uint32), coeff[at].view(np.uint32))
+    kept = kept[:n]
     assert np.array_equal(m_gpu[~kept].view(np.uint32), coeff[:n][~kept].view(np.uint32))
-    assert (m_gpu[kept & finite] == 0).all()
+    assert not m_gpu[kept].view(np.uint32).any()
 
 
 @pytest.mark.parametrize("s,k,R,fmt,bf16", [(64, 8, 4, "f32+i32", True), (64, 32, 4, "f32+i32", False),
