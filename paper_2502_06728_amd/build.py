@@ -117,8 +117,8 @@ def build(verbose: bool = False) -> str:
     _build_marshal(verbose)
     # the streaming micro-benchmark (HBM ceiling, counter calibration)
     if lib == LIB:
-        _run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Wno-unused-result", "-o",
-              MEMBENCH, os.path.join(CSRC, "membench.hip")], verbose)
+        _run([hipcc, *HIPCC_FLAGS, "-Wno-unused-result", "-o", MEMBENCH, os.path.join(CSRC, "membench.hip")],
+             verbose)
     return lib
 
 

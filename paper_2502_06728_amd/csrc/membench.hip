@@ -9,12 +9,16 @@
 //                     8 KiB stream that is read and rewritten (the parameters);
 //   compress shape:   per tile 16 KiB + 8 KiB read (momentum, gradient), 16 KiB + 8 KiB + 8 KiB
 //                     written (momentum in place, values, indices).
-// Each with plain and with non-temporal accesses.  These are the ceilings the library's kernels
+//   AdamW shape:      per tile 8 KiB of payload read, 8 KiB of parameters and twice 16 KiB of moments read and
+//                     rewritten.
+// Each with plain and with non-temporal accesses, and with tiles in gangs (run_log2): 32 tiles side by side, in runs
+// of 512 elements.  These are the ceilings the library's kernels
 // are measured against: what the memory system gives this access pattern when compute is free.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 
 #define CHECK(x)                                                                  \
     do {                                                                          \
@@ -63,52 +67,98 @@ __device__ __forceinline__ void st16(f32x4* p, f32x4 v) {
     else *p = v;
 }
 
+// Access i (of ACCESSES, 64 x 16 bytes each) of tile t in a stream.  GANG: 32 tiles share their part of the stream
+// and take it in turn, RUN accesses each; the tiles that do not fill a gang lie in a row.
+constexpr size_t kGang = 32;
+template <bool GANG, int ACCESSES, int RUN>
+__device__ __forceinline__ size_t place(size_t t, size_t tiles, int i) {
+    const size_t gang = t / kGang;
+    if (GANG && (gang + 1) * kGang <= tiles)
+        return (gang * (kGang * ACCESSES) + (i / RUN) * (kGang * RUN) + (t % kGang) * RUN + i % RUN) * 64 + threadIdx.x;
+    return (t * ACCESSES + i) * 64 + threadIdx.x;
+}
+
 // decompress shape: NS read-only streams + one read-modify-write stream; a workgroup (one
 // wavefront) takes PIECE KiB of every stream (PIECE lane accesses of 16 bytes per stream; the
 // library's kernels: 8, a tile of 64 chunks); everything is requested before anything is used
-template <int NS, int PIECE, bool NTL, bool NTS>
+template <int NS, int PIECE, bool NTL, bool NTS, bool GANG = false>
 __global__ __launch_bounds__(64) void decompress_shape(const f32x4* __restrict__ payload,
                                                        size_t stream_stride16,
                                                        f32x4* __restrict__ params) {
-    const size_t base = static_cast<size_t>(blockIdx.x) * (64 * PIECE) + threadIdx.x;
     f32x4 v[NS][PIECE], th[PIECE];
+    auto at = [](int i) { return place<GANG, PIECE, 1>(blockIdx.x, gridDim.x, i); };
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
         for (int i = 0; i < PIECE; ++i)
-            v[s][i] = ld16<NTL>(payload + s * stream_stride16 + base + 64 * i);
+            v[s][i] = ld16<NTL>(payload + s * stream_stride16 + at(i));
 #pragma unroll
-    for (int i = 0; i < PIECE; ++i) th[i] = ld16<NTL>(params + base + 64 * i);
+    for (int i = 0; i < PIECE; ++i) th[i] = ld16<NTL>(params + at(i));
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
         for (int i = 0; i < PIECE; ++i) th[i] += v[s][i];
 #pragma unroll
-    for (int i = 0; i < PIECE; ++i) st16<NTS>(params + base + 64 * i, th[i]);
+    for (int i = 0; i < PIECE; ++i) st16<NTS>(params + at(i), th[i]);
 }
 
 // compress shape: momentum 16 KiB read and rewritten, gradient 8 KiB read, 8 KiB + 8 KiB written
-template <bool NTL, bool NTS>
+template <bool NTL, bool NTS, bool GANG = false>
 __global__ __launch_bounds__(64) void compress_shape(const f32x4* __restrict__ grad,
                                                      f32x4* __restrict__ mom,
                                                      f32x4* __restrict__ val,
                                                      f32x4* __restrict__ idx) {
-    const size_t t = blockIdx.x;
-    const int lane = threadIdx.x;
+    auto at16 = [](int i) { return place<GANG, 16, 2>(blockIdx.x, gridDim.x, i); };
+    auto at8 = [](int i) { return place<GANG, 8, 1>(blockIdx.x, gridDim.x, i); };
     f32x4 m[16], g[8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) m[i] = ld16<NTL>(mom + t * 1024 + 64 * i + lane);
+    for (int i = 0; i < 16; ++i) m[i] = ld16<NTL>(mom + at16(i));
 #pragma unroll
-    for (int i = 0; i < 8; ++i) g[i] = ld16<NTL>(grad + t * 512 + 64 * i + lane);
+    for (int i = 0; i < 8; ++i) g[i] = ld16<NTL>(grad + at8(i));
 #pragma unroll
     for (int i = 0; i < 16; ++i) m[i] = m[i] * 0.999f + g[i % 8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        st16<NTS>(val + t * 512 + 64 * i + lane, m[i]);
-        st16<NTS>(idx + t * 512 + 64 * i + lane, g[i]);
+        st16<NTS>(val + at8(i), m[i]);
+        st16<NTS>(idx + at8(i), g[i]);
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) st16<NTS>(mom + t * 1024 + 64 * i + lane, m[i]);
+    for (int i = 0; i < 16; ++i) st16<NTS>(mom + at16(i), m[i]);
+}
+
+// AdamW shape: 8 KiB of payload read, 8 KiB of parameters and 16 + 16 KiB of moments read and rewritten, all of it
+// non-temporal; four 1 KiB accesses of every stream at a time, as the update does it
+template <bool GANG>
+__global__ __launch_bounds__(256) void adamw_shape(const f32x4* __restrict__ payload, f32x4* __restrict__ params,
+                                                   f32x4* __restrict__ m, f32x4* __restrict__ v) {
+    const int w = threadIdx.x / 64;                   // wavefront w: accesses w, w + 4, ... of the tile
+    auto place4 = [&](auto accesses, auto run, int i) {
+        return place<GANG, decltype(accesses)::value, decltype(run)::value>(blockIdx.x, gridDim.x, i) - 64 * w;
+    };
+    std::integral_constant<int, 16> c16;
+    std::integral_constant<int, 8> c8;
+    std::integral_constant<int, 2> c2;
+    std::integral_constant<int, 1> c1;
+    f32x4 p[2], th[2], a[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        p[i] = ld16<true>(payload + place4(c8, c1, w + 4 * i));
+        th[i] = ld16<true>(params + place4(c8, c1, w + 4 * i));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        a[i] = ld16<true>(m + place4(c16, c2, w + 4 * i));
+        b[i] = ld16<true>(v + place4(c16, c2, w + 4 * i));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        a[i] = a[i] * 0.9f + p[i % 2];
+        b[i] = b[i] * 0.95f + p[i % 2];
+        st16<true>(m + place4(c16, c2, w + 4 * i), a[i]);
+        st16<true>(v + place4(c16, c2, w + 4 * i), b[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) st16<true>(params + place4(c8, c1, w + 4 * i), th[i] + a[i] + b[i]);
 }
 
 template <typename Launch>
@@ -171,6 +221,20 @@ static int traffic_shapes(int iters) {
     rc |= time_shape("compress shape, non-temporal loads and stores", cbytes, iters, [&] {
         compress_shape<true, true><<<grid, 64>>>(payload, mom, payload + stream16,
                                                  payload + 2 * stream16); });
+    rc |= time_shape("decompress shape in gangs, non-temporal loads and stores", dbytes, iters, [&] {
+        decompress_shape<8, 8, true, true, true><<<grid, 64>>>(payload, stream16, params); });
+    rc |= time_shape("compress shape in gangs, plain", cbytes, iters, [&] {
+        compress_shape<false, false, true><<<grid, 64>>>(payload, mom, payload + stream16,
+                                                         payload + 2 * stream16); });
+    rc |= time_shape("compress shape in gangs, non-temporal stores", cbytes, iters, [&] {
+        compress_shape<false, true, true><<<grid, 64>>>(payload, mom, payload + stream16,
+                                                        payload + 2 * stream16); });
+    // AdamW: the second moment = payload streams 2 and 3
+    const double abytes = static_cast<double>(tiles) * 1024.0 * (8.0 + 2.0 * 40.0);
+    rc |= time_shape("AdamW shape (48 KiB in, 40 KiB out per tile), non-temporal", abytes, iters, [&] {
+        adamw_shape<false><<<grid, 256>>>(payload, params, mom, payload + 2 * stream16); });
+    rc |= time_shape("AdamW shape in gangs, non-temporal", abytes, iters, [&] {
+        adamw_shape<true><<<grid, 256>>>(payload, params, mom, payload + 2 * stream16); });
     CHECK(hipFree(payload));
     CHECK(hipFree(params));
     CHECK(hipFree(mom));
