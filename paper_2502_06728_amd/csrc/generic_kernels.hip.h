@@ -79,11 +79,16 @@ __device__ __forceinline__ void compact_flags(int s, int lane, const int* flag, 
 // Payload access in whatever format the caller chose (runtime switch: these kernels are the
 // general path).  What the momentum gives up for a kept coefficient v: the value the receivers
 // decode for the 16-bit formats; v itself for fp32 and for the ternary payload (Algorithm 1:
-// the extracted components leave the momentum, whatever goes on the wire).
+// the extracted components leave the momentum, whatever goes on the wire).  What it keeps of v without a transform
+// is nothing then, also of an infinity or a NaN (v - v would be NaN).
 __device__ __forceinline__ float payload_roundtrip(int val_dtype, float v) {
     if (val_dtype == 1) return decode16<1>(encode16<1>(v));
     if (val_dtype == 2) return decode16<2>(encode16<2>(v));
     return v;
+}
+
+__device__ __forceinline__ float payload_remainder(int val_dtype, float v) {
+    return val_dtype == 1 || val_dtype == 2 ? v - payload_roundtrip(val_dtype, v) : 0.0f;
 }
 
 // ---- ternary payload: sign(v) in two bits (0 = zero, 1 = +1, 3 = -1), 16 entries per 32-bit
@@ -254,19 +259,18 @@ __device__ __forceinline__ void compress_generic_chunks(
         for (int e = lane; e < s; e += kWave) {
             const int64_t i = base + e;
             if (i >= n) continue;
-            float q;
             if (p.use_dct) {
-                q = 0.0f;
+                float q = 0.0f;
 #pragma unroll 4
                 for (int j = 0; j < k; ++j) {
                     const int r = sidx[j];
                     const float a = (r == 0) ? p.alpha0 : p.alpha;
                     q = fmaf(tab[((2 * e + 1) * r) % (4 * s)], a * sval[j], q);
                 }
+                mom[i] = x[e] - q;
             } else {
-                q = flag[e] ? payload_roundtrip(p.val_dtype, x[e]) : 0.0f;
+                mom[i] = flag[e] ? payload_remainder(p.val_dtype, x[e]) : x[e];
             }
-            mom[i] = x[e] - q;
         }
         __syncthreads();
     }

@@ -33,7 +33,8 @@ def test_edges(H, s, k, elements, scheme):
 
 
 @pytest.mark.parametrize("scheme", SCHEMES)
-@pytest.mark.parametrize("s,k,signs", [(128, 16, False), (64, 8, False), (32, 4, False), (32, 8, True), (96, 12, True)])
+@pytest.mark.parametrize("s,k,signs", [(128, 16, False), (64, 8, False), (32, 4, False), (32, 8, True), (96, 12, True),
+                                       (48, 6, False), (48, 6, True)])          # (48: the general kernels)
 def test_non_finite_values(H, s, k, signs, scheme):
     """What is kept is sent as it is and leaves nothing behind, an infinity or a NaN no more than a number; what is
     not stays as it is, and the rest of the chunk with it."""
