@@ -34,7 +34,8 @@ UNITS = [
     "split_decompress_gang.hip",
     "split_scheme_compress.hip", "split_scheme_decompress.hip",
     "split_decompress_amsgrad.hip", "split_decompress_narrow_amsgrad.hip",
-    "split_scheme_decompress_amsgrad.hip",
+    "split_scheme_decompress_amsgrad.hip", "split_scheme_decompress_counts.hip",
+    "split_scheme_decompress_counts_amsgrad.hip",
     # two lanes per chunk (chunk 96, 128, 192, 256)
     "pair_compress_256.hip", "pair_compress_192.hip", "pair_compress_128.hip",
     "pair_compress_96.hip",

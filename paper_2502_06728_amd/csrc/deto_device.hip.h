@@ -38,6 +38,7 @@ struct KParams {
     float step_size;    // eta / (1 - beta1^t)
     float inv_sqrt_bc2; // 1 / sqrt(1 - beta2^t)
     int run_lg;         // run_log2 of this call (6: no gangs)
+    int count_signs;    // this call's two-bit signs are counted a word at a time (count_signs)
 };
 
 // ---- Which 64 chunks a tile is made of.  Not 64 in a row: kGang consecutive tiles (a gang) share
@@ -387,42 +388,57 @@ __device__ __forceinline__ uint32_t bounded(uint32_t d, uint32_t b) {
     return __umulhi(d, b);
 }
 
-// The sums over R replicas of a word of 16 two-bit signs; replica r's word is at[r * stride].  A field is 0, 1
-// or 3 (2 counts as 0), so its sum is (fields with bit 0) - 2 (fields with both bits): both are counted side by
-// side, three replicas in the two bits of a field, five times that in four bits, up to 64 in eight.
+// The sums over R replicas of a word of 16 two-bit signs; replica r's word is words[r * stride + at], words uniform.
+// A field is 0, 1 or 3 (2 counts as 0), so its sum is (fields with bit 0) - 2 (fields with both bits): both are counted
+// side by side, three replicas in the two bits of a field, five times that in four bits, up to 64 in eight.  Batches of
+// 18 words, not of 33: the registers are worth a wavefront per SIMD more to a launch than a round trip less to 64
+// replicas (streaming kernels, geometric mean over 600 random shapes 0.93 of the time, none but 2 % of them longer).
 struct SignCounts {
     uint32_t ones[4] = {0u, 0u, 0u, 0u}, both[4] = {0u, 0u, 0u, 0u};      // byte b: field 4b + i
 
-    __device__ __forceinline__ SignCounts(const uint32_t* __restrict__ at, int64_t stride, int R) {
-        constexpr int kBatch = 33;                                         // (64 replicas: two batches)
-        for (int r0 = 0; r0 < R; r0 += kBatch) {
-            uint32_t x[kBatch];
+    // (a batch is counted whole, however few replicas are in it)
+    __device__ __forceinline__ SignCounts(const uint32_t* __restrict__ words, uint32_t at, int64_t stride,
+                                          int R) {
+        int r0 = 0;
+        for (; R - r0 > 18; r0 += 18) add<18>(words, at, stride, r0, R);
+        const int left = R - r0;
+        if (left <= 3) add<3>(words, at, stride, r0, R);
+        else if (left <= 9) add<9>(words, at, stride, r0, R);
+        else add<18>(words, at, stride, r0, R);
+    }
+    // the replicas r0 .. r0 + BATCH - 1 that there are.  Every load is unconditional (the last replica's again
+    // past it): behind a branch a load is masked, and so waited for, before the next one leaves.
+    template <int BATCH>
+    __device__ __forceinline__ void add(const uint32_t* __restrict__ words, uint32_t at, int64_t stride, int r0,
+                                        int R) {
+        uint32_t x[BATCH];
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) x[i] = r0 + i < R ? at[(r0 + i) * stride] : 0u;
+        for (int i = 0; i < BATCH; ++i) x[i] = (words + min(r0 + i, R - 1) * stride)[at];
 #pragma unroll
-            for (int f = 0; f < kBatch; f += 15) {
-                uint32_t o4[2] = {0u, 0u}, b4[2] = {0u, 0u};               // nibble b: field 2b + i
+        for (int i = 0; i < BATCH; ++i) x[i] = r0 + i < R ? x[i] : 0u;
 #pragma unroll
-                for (int t = f; t < f + 15 && t < kBatch; t += 3) {
-                    uint32_t o2 = 0u, b2 = 0u;
+        for (int f = 0; f < BATCH; f += 15) {
+            uint32_t o4[2] = {0u, 0u}, b4[2] = {0u, 0u};               // nibble b: field 2b + i
 #pragma unroll
-                    for (int i = t; i < t + 3; ++i) {
-                        const uint32_t one = x[i] & 0x55555555u;
-                        o2 += one;
-                        b2 += one & (x[i] >> 1);
-                    }
-                    o4[0] += o2 & 0x33333333u;
-                    o4[1] += (o2 >> 2) & 0x33333333u;
-                    b4[0] += b2 & 0x33333333u;
-                    b4[1] += (b2 >> 2) & 0x33333333u;
+            for (int t = f; t < f + 15 && t < BATCH; t += 3) {
+                uint32_t o2 = 0u, b2 = 0u;
+#pragma unroll
+                for (int i = t; i < t + 3; ++i) {
+                    const uint32_t one = x[i] & 0x55555555u;
+                    o2 += one;
+                    b2 += one & (x[i] >> 1);
                 }
+                o4[0] += o2 & 0x33333333u;
+                o4[1] += (o2 >> 2) & 0x33333333u;
+                b4[0] += b2 & 0x33333333u;
+                b4[1] += (b2 >> 2) & 0x33333333u;
+            }
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    ones[i] += o4[i] & 0x0F0F0F0Fu;
-                    ones[i + 2] += (o4[i] >> 4) & 0x0F0F0F0Fu;
-                    both[i] += b4[i] & 0x0F0F0F0Fu;
-                    both[i + 2] += (b4[i] >> 4) & 0x0F0F0F0Fu;
-                }
+            for (int i = 0; i < 2; ++i) {
+                ones[i] += o4[i] & 0x0F0F0F0Fu;
+                ones[i + 2] += (o4[i] >> 4) & 0x0F0F0F0Fu;
+                both[i] += b4[i] & 0x0F0F0F0Fu;
+                both[i + 2] += (b4[i] >> 4) & 0x0F0F0F0Fu;
             }
         }
     }
@@ -432,12 +448,5 @@ struct SignCounts {
                                   2 * static_cast<int>((both[f % 4] >> (8 * (f / 4))) & 0xFFu));
     }
 };
-// Counted, or decoded and added one by one?  Counting costs the same for one and for 33 replicas and for every k,
-// and where a wavefront has 16 chunks' words, most of its lanes idle.  Decompress, us, one by one / counted: 60 M
-// bf16 32/16 R = 64 311 / 153, 64/21 R = 20 260 / 167, 64/5 R = 33 150 / 87, fp32 64/32 R = 64 AdamW 417 / 322; but
-// 60 M bf16 128/16 R = 20 111 / 122, 64/2 R = 10 63 / 74, fp32 16/2 R = 8 98 / 137, 64/16 R = 10 AdamW 208 / 216.
-__device__ __forceinline__ bool count_signs(const KParams& p) {
-    return p.R >= 32 || (p.R >= 16 && p.k > 16);
-}
 
 }  // namespace deto

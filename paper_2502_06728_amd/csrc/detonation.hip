@@ -313,6 +313,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         p.step_size = static_cast<float>(static_cast<double>(cfg->lr) / bc1);
         p.inv_sqrt_bc2 = static_cast<float>(1.0 / std::sqrt(bc2));
     }
+    p.count_signs = !idx && deto::count_signs(p);
     const int64_t C = chunks_of(n, p.s);
     const int64_t entries = C * p.k;
     // a replica's values: one element per entry, or ceil(k/16) words per chunk (ternary)
@@ -377,8 +378,10 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         };
         auto split_scheme = [few](const deto::DecompressLaunch& d, int classes) -> int64_t {
             if (few || classes == 0) return 0;
-            const int64_t c = deto::launch_decompress_split_scheme(d, classes);
-            return c ? c : deto::launch_decompress_split_scheme_amsgrad(d, classes);
+            int64_t c = deto::launch_decompress_split_scheme(d, classes);
+            if (!c) c = deto::launch_decompress_split_scheme_counts(d, classes);
+            if (!c) c = deto::launch_decompress_split_scheme_amsgrad(d, classes);
+            return c ? c : deto::launch_decompress_split_scheme_counts_amsgrad(d, classes);
         };
         // a lane per chunk or a wavefront per coefficient class
         if (idx)

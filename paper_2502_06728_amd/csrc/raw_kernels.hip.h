@@ -298,7 +298,7 @@ __device__ __forceinline__ void raw_sign_sums(const KParams& p, int tid, int fir
     if (tid < first) return;
     const int k = p.k, nw = ternary_words_per_chunk(k);
     for (int q = tid - first; q < live * nw; q += kRawThreads - first) {
-        const SignCounts counts(words + q, val_stride, p.R);
+        const SignCounts counts(words, q, val_stride, p.R);
         const int r = q / nw, j0 = 16 * (q - r * nw);
         float* to = sums + r * k + j0;
         const int cnt = k - j0;

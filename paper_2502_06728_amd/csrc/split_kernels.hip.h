@@ -1206,8 +1206,7 @@ __device__ __forceinline__ void split_scatter(const KParams& p, int lane, float*
 
 // The same without transmitted indices (Striding, Random): every replica kept the same places, so
 // the R values of an entry are summed in registers, replica 0 first, and written to their
-// place once.  place(r, j): the place of entry j of the wavefront's row r.  Two-bit signs of many replicas
-// (count_signs): a word of a chunk per lane.
+// place once.  place(r, j): the place of entry j of the wavefront's row r.
 template <int S, int VEC, int VAL, class Place>
 __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, float* rows,
                                                  int my_rows, const void* __restrict__ val,
@@ -1219,20 +1218,6 @@ __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, flo
     const int k = p.k;
     const int pieces = my_rows * k / VEC;
     const int chunk_bytes = 4 * ternary_words_per_chunk(k);
-    if constexpr (VAL == 3) {
-        if (count_signs(p)) {
-            const int nw = chunk_bytes / 4;
-            const uint32_t* words = static_cast<const uint32_t*>(val) + chunk0 * nw;
-            for (int q = lane; q < my_rows * nw; q += kWave) {
-                const SignCounts counts(words + q, val_stride, p.R);
-                const int r = q / nw, j0 = 16 * (q - r * nw);
-#pragma unroll
-                for (int f = 0; f < 16; ++f)
-                    if (j0 + f < k) rows[r * kRow + place(r, j0 + f)] = counts.sum(f);
-            }
-            return;
-        }
-    }
     for (int q = lane; q < pieces; q += kWave) {
         const uint32_t e = VEC * static_cast<uint32_t>(q);
         const uint32_t r = (k == 1) ? e : __umulhi(e, magic);
@@ -1264,6 +1249,22 @@ __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, flo
     }
 }
 
+// The same for two-bit signs of many replicas: a word of 16 entries per lane.
+template <int S, class Place>
+__device__ __forceinline__ void split_count_sums(const KParams& p, int lane, float* rows, int my_rows,
+                                                 const void* __restrict__ val, int64_t val_stride,
+                                                 int64_t chunk0, Place place) {
+    const int k = p.k, nw = ternary_words_per_chunk(k);
+    const uint32_t* words = static_cast<const uint32_t*>(val) + chunk0 * nw;
+    for (int q = lane; q < my_rows * nw; q += kWave) {
+        const SignCounts counts(words, q, val_stride, p.R);
+        const int r = q / nw, j0 = 16 * (q - r * nw);
+#pragma unroll
+        for (int f = 0; f < 16; ++f)
+            if (j0 + f < k) rows[r * (S + 4) + place(r, j0 + f)] = counts.sum(f);
+    }
+}
+
 // Decompress-and-update half (transmitted indices, DCT domain) on full tiles of 64 chunks, W
 // wavefronts per workgroup; NARROW as in compress_split.  SCHEME (with NARROW): Striding or Random
 // without transmitted indices, in either domain; one wavefront shuffles all 64 chunks of the tile
@@ -1284,8 +1285,11 @@ __device__ __forceinline__ void split_place_sums(const KParams& p, int lane, flo
 // 57; fp32 64/8 2 M 17.7, 15.8; and the other launches: 64/20 signs 60 M SGD 122, 109, Random 32/5 60 M
 // 90, 71, 16/3 signs 30 M 61, 57.
 // GANG: tiles in gangs (run_log2), transmitted indices.  (80 registers are six wavefronts per SIMD, 81 five.)
+// COUNT (with SCHEME): two-bit signs of many replicas, counted a word at a time (count_signs), in kernels of their own:
+// in one kernel the words of a batch cost every other payload up to three wavefronts per SIMD (16/2: 50 registers, 71;
+// 16/1 R = 16 1.2 M 5.8 us, 6.6).
 template <int S, int W, bool PARAM_BF16, bool NARROW = false, bool SCHEME = false, bool AMSGRAD = false,
-          bool GANG = false>
+          bool GANG = false, bool COUNT = false>
 __global__ __launch_bounds__(kWave * W)
 __attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_split(
     KParams p, int64_t tiles, int64_t n, int64_t n_chunks, const void* __restrict__ idx,
@@ -1399,7 +1403,9 @@ __attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_sp
                 return p.scheme == 2 ? static_cast<int>(listed[r * k + j])
                                      : first + static_cast<int>(j) * stride;
             };
-            if (k % 4 == 0)
+            if constexpr (COUNT)
+                split_count_sums<S>(p, lane, rows, my_rows, val, val_stride, row0, place);
+            else if (k % 4 == 0)
                 split_place_sums<S, 4, VAL>(p, lane, rows, my_rows, val, val_stride, row0 * k, row0,
                                             magic, place);
             else
@@ -1407,7 +1413,10 @@ __attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_sp
                                             magic, place);
         };
         using std::integral_constant;
-        if constexpr (SCHEME) {
+        static_assert(!COUNT || SCHEME, "no transmitted indices");
+        if constexpr (COUNT) {
+            place_sums(integral_constant<int, 3>{});
+        } else if constexpr (SCHEME) {
             if (p.val_dtype == 1) place_sums(integral_constant<int, 1>{});
             else if (p.val_dtype == 2) place_sums(integral_constant<int, 2>{});
             else if (p.val_dtype == 3) place_sums(integral_constant<int, 3>{});

@@ -958,7 +958,9 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
 // replica kept the same positions, so the R value arrays are summed entry by entry while
 // they stream in, and each chunk's lane spreads the k sums over the positions of its bit
 // pattern.
-template <int S, int K, bool PARAM_BF16, int VAL = 0>
+// COUNT: two-bit signs of many replicas, counted a word at a time: kernels of
+// their own, since those of a few replicas lose registers to it (32/8 R = 4 11 M 13.4 us, 14.8 in one kernel).
+template <int S, int K, bool PARAM_BF16, int VAL = 0, bool COUNT = false>
 __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_tiled_scheme(
     KParams p, MaskWords stride_mask, int64_t n_tiles, TailRange tail,
     const void* __restrict__ val_v, int64_t val_stride, void* __restrict__ params, AdamPtrs ad,
@@ -1008,21 +1010,16 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
         }
         return q;
     };
-    // two-bit signs of many replicas: the words of the lane's own chunk, 16 fields at a time
-    bool counted = false;
-    if constexpr (VAL == 3) {
-        counted = count_signs(p);
-        if (counted) {
-            constexpr int kWords = (K + 15) / 16;
-            static_for<0, kWords>([&](auto w) {
-                const SignCounts counts(static_cast<const uint32_t*>(val_v) + (rows.first + own) * kWords + w,
-                                        val_stride, p.R);
-                static_for<0, (K - 16 * w < 16 ? K - 16 * w : 16)>(
-                    [&](auto f) { tile[lane * PR + 16 * w + f] = counts.sum(f); });
-            });
-        }
-    }
-    if (counted) {
+    if constexpr (COUNT) {
+        // the words of the lane's own chunk, 16 fields at a time
+        static_assert(VAL == 3, "two-bit signs");
+        constexpr int kWords = (K + 15) / 16;
+        static_for<0, kWords>([&](auto w) {
+            const SignCounts counts(static_cast<const uint32_t*>(val_v) + rows.first * kWords, own * kWords + w,
+                                    val_stride, p.R);
+            static_for<0, (K - 16 * w < 16 ? K - 16 * w : 16)>(
+                [&](auto f) { tile[lane * PR + 16 * w + f] = counts.sum(f); });
+        });
     } else if constexpr (K % 4 == 0) {
         float4 acc[K / 4];
 #pragma unroll

@@ -163,6 +163,8 @@ int64_t launch_decompress_split_scheme(const DecompressLaunch& a, int classes); 
 int64_t launch_decompress_split_amsgrad(const DecompressLaunch& a, int classes); // the same three,
 int64_t launch_decompress_split_narrow_amsgrad(const DecompressLaunch& a, int classes);   // AdamW
 int64_t launch_decompress_split_scheme_amsgrad(const DecompressLaunch& a, int classes);   // with amsgrad
+int64_t launch_decompress_split_scheme_counts(const DecompressLaunch& a, int classes);   // count_signs
+int64_t launch_decompress_split_scheme_counts_amsgrad(const DecompressLaunch& a, int classes);
 // Striding / Random on the momentum itself (raw_kernels.hip.h): (chunk size, pieces of four elements a
 // thread)
 #define DETO_RAW_COMPRESS_LIST(X) X(16, 2) X(32, 2) X(64, 2) X(96, 3) X(128, 2) X(128, 4) X(192, 3) X(256, 4)
@@ -538,6 +540,16 @@ inline bool few_chunks_decompress(const KParams& p, int64_t chunks, bool idx) {
     if (idx)
         return p.val_dtype == 3 && chunks <= 2560 && static_cast<int64_t>(p.R) * p.k >= 4 * p.s;
     return !p.use_dct && p.s >= 96 && p.R < 8 && chunks <= (p.adam ? 4096 : 2560);
+}
+
+// Two-bit signs on coefficients without indices: counted a word at a time (SignCounts), or decoded and added one by
+// one?  Counting costs the same for 16 and for 33 replicas and for every k up to 16, and where a wavefront has 16
+// chunks' words, most of its lanes idle.  Decompress, us, one by one / counted: 60 M bf16 32/16 R = 64 311 / 153, 64/21
+// R = 20 260 / 167, 64/5 R = 33 150 / 87, fp32 64/32 R = 64 AdamW 417 / 322; but 5 M bf16 128/16 R = 20 16.0 / 18.4,
+// 0.6 M fp32 64/2 R = 16 6.3 / 7.1, and few entries of 32 replicas 2.1 M fp32 16/1 11.6 / 12.4, bf16 96/3 14.6 / 15.5.
+// Over 300 random shapes 0.76 of the time of one by one.
+inline bool count_signs(const KParams& p) {
+    return p.val_dtype == 3 && (p.k > 16 ? p.R >= 16 : p.R >= (p.k >= 4 ? 32 : 48));
 }
 
 // ---- Striding and Random on the momentum itself (raw_kernels.hip.h).  Against the kernels before them (general

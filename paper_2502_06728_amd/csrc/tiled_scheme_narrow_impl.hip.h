@@ -27,14 +27,17 @@ void decompress_one(const DecompressLaunch& a) {
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
     const MaskWords mw{{a.stride_mask[0], a.stride_mask[1], a.stride_mask[2], a.stride_mask[3]}};
-    if (a.param_bf16)
-        decompress_tiled_scheme<S, K, true, V><<<grid, kWave, spare_lds(a), a.stream>>>(
-            a.p, mw, a.tiles, tail, a.val, a.val_stride, a.params,
-            AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);
-    else
-        decompress_tiled_scheme<S, K, false, V><<<grid, kWave, spare_lds(a), a.stream>>>(
-            a.p, mw, a.tiles, tail, a.val, a.val_stride, a.params,
-            AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);
+    constexpr bool kSigns = V == 3;
+#define LAUNCH(BF16, COUNT)                                                                     \
+    decompress_tiled_scheme<S, K, BF16, V, COUNT><<<grid, kWave, spare_lds(a), a.stream>>>(     \
+        a.p, mw, a.tiles, tail, a.val, a.val_stride, a.params,                                  \
+        AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg)
+    if (kSigns && a.p.count_signs) {
+        if (a.param_bf16) LAUNCH(true, kSigns); else LAUNCH(false, kSigns);
+    } else {
+        if (a.param_bf16) LAUNCH(true, false); else LAUNCH(false, false);
+    }
+#undef LAUNCH
 }
 
 }  // namespace

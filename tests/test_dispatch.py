@@ -47,6 +47,7 @@ extern "C" int lane_scheme(const int* a, int64_t) { return deto::lane_scheme(par
 extern "C" int scheme_classes(const int* a, int64_t n, int bf16) {
     return deto::scheme_classes(params(a), n, bf16, deto::lane_scheme(params(a)));
 }
+extern "C" int counts(const int* a, int64_t) { return deto::count_signs(params(a)); }
 extern "C" int stream_first(const int* a, int64_t) { return deto::stream_before_classes(params(a)); }
 """
 
@@ -257,3 +258,9 @@ def test_lane_kernels_of_the_schemes(rules):
 def test_scheme_classes(rules, s, k, val, adam, bf16, n, want):
     for dct in (False, True):
         assert rules("scheme_classes", s, k, n, 4, val, RANDOM, dct, adam, bf16) == want
+
+
+def test_signs_of_many_replicas_are_counted(rules):
+    for k, R in ((17, 16), (4, 32), (3, 48), (16, 32)):
+        assert rules("counts", 64, k, 0, R, SIGNS, RANDOM, True) and not rules("counts", 64, k, 0, R - 1, SIGNS, RANDOM, True)
+        assert not rules("counts", 64, k, 0, R, F16, RANDOM, True)

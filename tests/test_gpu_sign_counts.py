@@ -1,6 +1,6 @@
-"""Two-bit signs without transmitted indices, counted a word at a time where there are many replicas: both sides of those lines and
-of a batch of 33 replicas, words of one to sixteen entries and two a chunk, on a lane per chunk and on classes, all
-fields of a word the same in every replica, codes that count as zero, against the oracle."""
+"""Two-bit signs without transmitted indices, counted a word at a time where there are many replicas: both sides of those
+lines and replicas past one, two and three batches, words of one to sixteen entries and two a chunk, on a lane per chunk
+and on classes, all fields of a word the same in every replica, codes that count as zero, against the oracle."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("s,k,dct", [(32, 1, True), (32, 4, True), (32, 16, True), (32, 8, False), (64, 16, True),
                                      (64, 32, True), (64, 21, True), (16, 2, True), (128, 17, True), (256, 100, True)])
-@pytest.mark.parametrize("R", [16, 31, 33, 64])
+@pytest.mark.parametrize("R", [16, 31, 33, 48, 64])
 def test_counts(H, s, k, dct, R):
     scheme = oracle.SCHEME_STRIDE if R % 2 and s % k == 0 else oracle.SCHEME_RANDOM
     n = s * 64 + 5 * s + 7
