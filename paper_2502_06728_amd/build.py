@@ -25,6 +25,9 @@ HIPCC_FLAGS = [
 # one translation unit per kernel family, compiled side by side
 # (the longest-compiling units first)
 UNITS = [
+    # Striding / Random on the momentum itself
+    "raw_decompress.hip", "raw_decompress_adamw.hip", "raw_decompress_amsgrad.hip", "raw_decompress_signs.hip",
+    "raw_decompress_signs_adamw.hip", "raw_decompress_signs_amsgrad.hip",
     # a wavefront per coefficient class (chunk 96, 128, 192, 256; 64 on small shards)
     "split_compress_256.hip", "split_compress_192.hip", "split_compress_128.hip",
     "half_compress_256.hip",
@@ -48,8 +51,7 @@ UNITS = [
     "tiled_scheme.hip", "tiled_scheme_small.hip",
     "tiled_scheme_narrow_s32.hip", "tiled_scheme_narrow_s64.hip",
     "tiled_topk_s64.hip", "tiled_topk_s32.hip", "tiled_topk_s16.hip",
-    # Striding / Random on the momentum itself
-    "raw_decompress.hip", "raw_compress.hip",
+    "raw_compress.hip",
     # validation, dispatch, general kernels
     "detonation.hip",
 ]

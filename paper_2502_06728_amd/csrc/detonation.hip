@@ -209,12 +209,12 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
         } else {
             // no lane-per-chunk kernel for this (s, k, format): a wavefront per coefficient
             // class (k <= s/2; top-k from chunk 96 on, not for two-bit signs; Striding and Random
-            // from chunk 16 on unless there are few chunks), two lanes per chunk (top-k at chunk
+            // on coefficients from chunk 16 on), two lanes per chunk (top-k at chunk
             // 96, 128, 192, 256, k > s/2), direct sums on the matrix cores (top-k: two-bit signs,
             // chunk 16), the matrix-core kernel (top-k at other multiples of 32), which takes the
             // leading multiple of 32 chunks
             c0 = deto::launch_compress_split(a);
-            if (c0 == 0 && !stride_stream && !deto::few_chunks(p, C))
+            if (c0 == 0 && !deto::few_chunks(C))
                 c0 = deto::launch_compress_split_scheme(a);
             if (c0 == 0) c0 = deto::launch_compress_pair(a);
             if (c0 == 0) c0 = deto::launch_compress_direct(a);
@@ -347,7 +347,6 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
     // size and k without a lane-per-chunk kernel
     const bool stride_stream =
         !idx && p.scheme == DETO_SCHEME_STRIDE && !p.use_dct && val_dtype == DETO_F32;
-    const bool stream_first = stride_stream && deto::stream_before_classes(p);
     int64_t c0 = 0;
     const int64_t tiles = (n / p.s) / deto::kWave;
     // every replica's array must keep the alignment of a lane's access (four entries when k is
@@ -386,7 +385,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         // a lane per chunk or a wavefront per coefficient class
         if (idx)
             c0 = split(a, deto::decompress_classes(p, n, a.param_bf16, deto::lane_decompress(p)));
-        else if (!stream_first)
+        else
             c0 = split_scheme(a, deto::scheme_classes(p, n, a.param_bf16, deto::lane_scheme(p)));
         const bool done = (c0 > 0 || tiles == 0) ? false
                           : idx ? (deto::launch_decompress_idx_s64(a) ||

@@ -92,7 +92,8 @@ __device__ __forceinline__ void raw_quad(const KParams& p, int r, int col, const
     const int at = (p.scheme == 2 ? r * G::kWords : 0) + col / 32;
     const uint32_t word = mask[at];
     bits = word >> (col % 32);
-    entry = __umul24(static_cast<uint32_t>(r), static_cast<uint32_t>(p.k)) + before[at] + __popc(word & ((1u << (col % 32)) - 1u));
+    entry = __umul24(static_cast<uint32_t>(r), static_cast<uint32_t>(p.k)) + before[at] +
+            __popc(word & ((1u << (col % 32)) - 1u));
 }
 
 template <int S, int QUADS, bool GRAD_BF16>
@@ -258,36 +259,53 @@ __global__ __launch_bounds__(kRawThreads) void compress_raw(
 }
 
 // Sums over the replicas of the entries [0, entries) behind `val`, replica 0 first, into sums[]; the
-// threads [first, kRawThreads) share them.  VEC consecutive entries a thread.
-template <int VEC, int VAL>
+// threads [first, kRawThreads) share them, VEC consecutive entries a piece.  In flight: QN pieces of a thread, BATCH
+// of their replicas.  Single 16-bit entries are loaded without a branch (the last replica's again past it): behind
+// one such a load is widened, and so waited for, before the next one leaves (32/10, 32 replicas, fp16, 5.6 M 134 us
+// that way, 70 in the class kernels).
+template <int VEC, int VAL, int QN, int BATCH>
 __device__ __forceinline__ void raw_entry_sums(const KParams& p, int tid, int first, int entries,
                                                const void* __restrict__ val, int64_t val_stride,
                                                int64_t e0, float* sums) {
-    constexpr int kBatch = VEC == 1 ? 32 : VAL == 0 ? 8 : 16;     // replicas in flight
     using Piece = SplitPiece<VEC, VAL, true>;
     if (tid < first) return;
-    for (int q = tid - first; q < entries / VEC; q += kRawThreads - first) {
-        const int64_t at = e0 + VEC * q;
-        float sum[VEC];
+    constexpr bool kAlways = VEC == 1 && VAL != 0;
+    const int threads = kRawThreads - first, pieces = entries / VEC;
+    for (int q0 = tid - first; q0 < pieces; q0 += QN * threads) {
+        float sum[QN][VEC];
 #pragma unroll
-        for (int c = 0; c < VEC; ++c) sum[c] = 0.0f;
-        for (int r0 = 0; r0 < p.R; r0 += kBatch) {
-            Piece b[kBatch];
+        for (int c = 0; c < QN; ++c)
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                b[i].clear();
-                if (r0 + i < p.R) b[i].load_values(val, (r0 + i) * val_stride + at, 0);
+            for (int e = 0; e < VEC; ++e) sum[c][e] = 0.0f;
+        for (int r0 = 0; r0 < p.R; r0 += BATCH) {
+            Piece b[QN][BATCH];
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+#pragma unroll
+                for (int c = 0; c < QN; ++c) b[c][i].clear();
+                if (!kAlways && r0 + i >= p.R) continue;
+                // (a uniform base and a 32-bit offset of the lane)
+                const char* replica = static_cast<const char*>(val) +
+                                      (min(r0 + i, p.R - 1) * val_stride + e0) * (VAL == 0 ? 4 : 2);
+#pragma unroll
+                for (int c = 0; c < QN; ++c)
+                    b[c][i].load_values(replica, static_cast<uint32_t>(VEC * min(q0 + c * threads, pieces - 1)), 0);
             }
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                float x[VEC];
-                b[i].values(0u, x);
+            for (int i = 0; i < BATCH; ++i)
 #pragma unroll
-                for (int c = 0; c < VEC; ++c) sum[c] += x[c];   // (zero past the last replica)
-            }
+                for (int c = 0; c < QN; ++c) {
+                    float x[VEC];
+                    b[c][i].values(0u, x);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) sum[c][e] += !kAlways || r0 + i < p.R ? x[e] : 0.0f;
+                }
         }
 #pragma unroll
-        for (int c = 0; c < VEC; ++c) sums[VEC * q + c] = sum[c];
+        for (int c = 0; c < QN; ++c)
+            if (q0 + c * threads < pieces)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) sums[VEC * (q0 + c * threads) + e] = sum[c][e];
     }
 }
 
@@ -308,8 +326,10 @@ __device__ __forceinline__ void raw_sign_sums(const KParams& p, int tid, int fir
     }
 }
 
-// OPT: 0 plain update, 1 Decoupled AdamW, 2 with amsgrad
-template <int S, int QUADS, bool PARAM_BF16, int OPT>
+// OPT: 0 plain update, 1 Decoupled AdamW, 2 with amsgrad.  SIGNS: two-bit signs, in kernels of their own: with fewer
+// registers a wavefront per SIMD more than beside the sums of values (64, 2 pieces, bf16 57 against 65).  What a launch
+// of 2 - 8 M parameters takes follows the workgroups per CU: 256/8 R = 2 signs 4.7 M 4 a CU 10.7 us, 5 8.1, 6 7.7.
+template <int S, int QUADS, bool PARAM_BF16, int OPT, bool SIGNS>
 __global__ __launch_bounds__(kRawThreads) void decompress_raw(
     KParams p, int64_t n, int64_t n_chunks, const void* __restrict__ val, int64_t val_stride,
     void* __restrict__ params, AdamPtrs ad, float* __restrict__ presign_dbg) {
@@ -359,22 +379,40 @@ __global__ __launch_bounds__(kRawThreads) void decompress_raw(
                               ? (G::kChunks + kWave - 1) / kWave * kWave : 0;
         const int entries = live * k;
         const int64_t e0 = chunk0 * k;
-        auto entry_sums = [&](auto val_tag) {
-            constexpr int VAL = decltype(val_tag)::value;
-            // (one entry a thread keeps four times as many replicas in flight: where that takes no
-            // second turn, and the launch's latency counts)
-            if (k % 4 == 0 && (entries > kRawThreads || p.R <= 8 || n > kRawSmall))
-                raw_entry_sums<4, VAL>(p, tid, first, entries, val, val_stride, e0, sums);
-            else
-                raw_entry_sums<1, VAL>(p, tid, first, entries, val, val_stride, e0, sums);
-        };
-        if (p.val_dtype == 0) entry_sums(std::integral_constant<int, 0>{});
-        else if (p.val_dtype == 1) entry_sums(std::integral_constant<int, 1>{});
-        else if (p.val_dtype == 2) entry_sums(std::integral_constant<int, 2>{});
-        else
+        if constexpr (SIGNS) {
             raw_sign_sums(p, tid, first, live,
                           static_cast<const uint32_t*>(val) + chunk0 * ternary_words_per_chunk(k),
                           val_stride, sums);
+        } else {
+            auto entry_sums = [&](auto val_tag) {
+                constexpr int VAL = decltype(val_tag)::value;
+                auto sum = [&](auto vec, auto pieces, auto batch) {
+                    raw_entry_sums<decltype(vec)::value, VAL, decltype(pieces)::value, decltype(batch)::value>(
+                        p, tid, first, entries, val, val_stride, e0, sums);
+                };
+                constexpr std::integral_constant<int, 1> c1;
+                constexpr std::integral_constant<int, 2> c2;
+                constexpr std::integral_constant<int, 4> c4;
+                constexpr std::integral_constant<int, 8> c8;
+                // (one entry a thread keeps four times as many replicas in flight: where that takes no
+                // second turn, and the launch's latency counts)
+                if (k % 4 == 0 && (entries > kRawThreads || p.R <= 8 || n > kRawSmall)) {
+                    if (p.R <= 2) sum(c4, c4, c2);
+                    else if (p.R <= 4) sum(c4, c2, c4);
+                    else if constexpr (VAL == 0) sum(c4, c1, c8);
+                    else if (p.R <= 8) sum(c4, c2, c8);
+                    else sum(c4, c1, std::integral_constant<int, 16>{});
+                } else {
+                    if (p.R <= 4) sum(c1, c4, c4);
+                    else if (p.R <= 8) sum(c1, c2, c8);
+                    else if (VAL != 0 || p.R <= 16) sum(c1, c2, std::integral_constant<int, 16>{});
+                    else if constexpr (VAL == 0) sum(c1, c1, std::integral_constant<int, 32>{});
+                }
+            };
+            if (p.val_dtype == 0) entry_sums(std::integral_constant<int, 0>{});
+            else if (p.val_dtype == 1) entry_sums(std::integral_constant<int, 1>{});
+            else entry_sums(std::integral_constant<int, 2>{});
+        }
         lds_barrier();
 
         // ---- update

@@ -1266,8 +1266,8 @@ __device__ __forceinline__ void split_count_sums(const KParams& p, int lane, flo
 }
 
 // Decompress-and-update half (transmitted indices, DCT domain) on full tiles of 64 chunks, W
-// wavefronts per workgroup; NARROW as in compress_split.  SCHEME (with NARROW): Striding or Random
-// without transmitted indices, in either domain; one wavefront shuffles all 64 chunks of the tile
+// wavefronts per workgroup; NARROW as in compress_split.  SCHEME (with NARROW): Striding or Random on
+// coefficients without transmitted indices; one wavefront shuffles all 64 chunks of the tile
 // and lists their places in ascending order.
 //
 // Scatter-add: wavefront w owns the rows [64w/W, 64(w+1)/W) of the tile, so no two wavefronts
@@ -1437,8 +1437,8 @@ __attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_sp
     __syncthreads();
 
     // ---- the lane's class of the averaged coefficients: a[W*m + off] * alpha_j / R, and back
-    // (raw domain: the rows hold the sums themselves)
-    if (p.use_dct) {
+    // (transmitted indices in the raw domain: the rows hold the sums themselves)
+    if (SCHEME || p.use_dct) {
         const int off = split_off<W>(w);
         const float scale = p.alpha * p.inv_R;
         float c[Q];
@@ -1567,12 +1567,12 @@ __attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_sp
             }
         }
         };
-        auto update_early = [&](auto raw_tag) {
+        auto update_early = [&] {
 #pragma unroll
             for (int it = 0; it < kPieces; ++it) {
                 const int e4 = 4 * (tid + kThreads * it);
                 const int64_t u = piece(it);
-                const float4 y4 = output4(e4, raw_tag);
+                const float4 y4 = output4(e4, std::false_type{});
                 if (presign_dbg) st_f4<false>(presign_dbg + u + lane4, y4);
                 const float y[4] = {y4.x, y4.y, y4.z, y4.w};
                 const float old[4] = {__uint_as_float(early[it].x << 16),
@@ -1590,12 +1590,7 @@ __attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_sp
             }
         };
         if (params_early) {
-            if constexpr (SCHEME) {
-                if (p.use_dct) update_early(std::false_type{});
-                else update_early(std::true_type{});
-            } else {
-                update_early(std::false_type{});
-            }
+            update_early();
         } else {
             // (nothing is in flight here, but to the compiler the early parameters may be: without
             // this it waits between the loads of a batch that share registers with them.  vmcnt(0);
@@ -1604,12 +1599,9 @@ __attribute__((amdgpu_waves_per_eu(GANG && S == 32 ? 6 : 1))) void decompress_sp
             // Striding 32/16 80 M 258, 272, 32/4 147 M 519, 532)
             if constexpr (PARAM_BF16 && !AMSGRAD && (!SCHEME || S >= 192))
                 __builtin_amdgcn_s_waitcnt(0x0F70);
-            if (!p.use_dct) {
+            if (!SCHEME && !p.use_dct) {
                 // (transmitted indices in the raw domain: rare, one copy of the loop with the checks)
-                if (SCHEME && !partial)
-                    update(std::integral_constant<bool, !SCHEME>{}, std::true_type{});
-                else
-                    update(std::true_type{}, std::true_type{});
+                update(std::true_type{}, std::integral_constant<bool, !SCHEME>{});
             } else if (partial) {
                 update(std::true_type{}, std::false_type{});
             } else {

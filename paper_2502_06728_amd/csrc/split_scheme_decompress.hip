@@ -1,5 +1,5 @@
 // Striding / Random decompress-and-update without transmitted indices on the
-// wavefront-per-coefficient-class kernels: either domain, every payload format, any k <= S/2,
+// wavefront-per-coefficient-class kernels: on coefficients, every payload format, any k <= S/2,
 // plain SGD update or Decoupled AdamW, for what the lane-per-chunk kernels are not instantiated for.  (In units of
 // their own: amsgrad, split_scheme_decompress_amsgrad.hip, and counted signs, split_scheme_decompress_counts.hip.)
 #ifndef DETO_SPLIT_FN
@@ -19,7 +19,7 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
 #ifdef DETO_TILED_ONLY_64_32
     return 0;
 #else
-    if (a.idx || p.scheme == 0 || 2 * p.k > p.s) return 0;
+    if (a.idx || p.scheme == 0 || !p.use_dct || 2 * p.k > p.s) return 0;
     if (DETO_SPLIT_AMSGRAD != (p.adam && p.amsgrad) || DETO_SPLIT_COUNT != (p.count_signs != 0)) return 0;
     const int64_t tiles = (a.n / p.s) / kWave;
     // one workgroup per full tile and one for the chunks left over (a partial tile)

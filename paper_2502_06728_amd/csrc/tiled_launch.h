@@ -169,10 +169,16 @@ int64_t launch_decompress_split_scheme_counts_amsgrad(const DecompressLaunch& a,
 // thread)
 #define DETO_RAW_COMPRESS_LIST(X) X(16, 2) X(32, 2) X(64, 2) X(96, 3) X(128, 2) X(128, 4) X(192, 3) X(256, 4)
 #define DETO_RAW_DECOMPRESS_LIST(X) \
-    X(16, 2) X(16, 4) X(32, 2) X(32, 4) X(32, 8) X(64, 2) X(64, 4) X(64, 8) X(96, 3) X(96, 6) X(128, 2) \
-    X(128, 4) X(128, 8) X(192, 3) X(192, 6) X(256, 4) X(256, 8)
+    X(16, 2) X(16, 4) X(32, 2) X(32, 4) X(64, 2) X(64, 4) X(96, 3) X(96, 6) X(128, 2) X(128, 4) X(192, 3) \
+    X(192, 6) X(256, 4)
+#define DETO_RAW_DECOMPRESS_PLAIN_LIST(X) X(32, 8) X(64, 8) X(128, 8) X(256, 8)      // (not AdamW)
 int64_t launch_compress_raw(const CompressLaunch& a);
-int64_t launch_decompress_raw(const DecompressLaunch& a);
+int64_t launch_decompress_raw_values(const DecompressLaunch& a);             // plain update
+int64_t launch_decompress_raw_signs(const DecompressLaunch& a);
+int64_t launch_decompress_raw_adamw(const DecompressLaunch& a);
+int64_t launch_decompress_raw_signs_adamw(const DecompressLaunch& a);
+int64_t launch_decompress_raw_amsgrad(const DecompressLaunch& a);
+int64_t launch_decompress_raw_signs_amsgrad(const DecompressLaunch& a);
 // ... tiles in gangs (decompress_gangs says which):
 int64_t launch_decompress_split_gang(const DecompressLaunch& a, int classes);
 int64_t launch_decompress_split_narrow_gang(const DecompressLaunch& a, int classes);
@@ -510,36 +516,17 @@ inline unsigned spare_lds(const DecompressLaunch& a, int classes = 0) {
     return spare_lds(wgs, 4 * kWave * (s + 4) + places);
 }
 
-// Striding in the raw domain, fp32 values, no transmitted indices: the streaming kernel before the
-// wavefront-per-class kernels?  Not for AdamW at chunk sizes up to 64: those have the sums over the
-// replicas in registers, four values a load, where the stream gathers them element by element.
-// us, stream / wavefront per class: 64/8, bf16 parameters, R = 2 1 M 14.6 / 7.8, 30 M 144 / 110,
-// R = 16 361 / 142; fp32 R = 2 30 M 137 / 133.  At larger chunks the stream is ahead with fp32
-// parameters and few replicas: 128/4 R = 2 30 M 130 / 141, 256/32 1 M 12.8 / 15.5.
-inline bool stream_before_classes(const KParams& p) { return !(p.adam && p.s <= 64); }
-
 // Few chunks: a launch of the wavefront-per-class kernels is then a handful of workgroups whose own
 // duration counts, while the general kernels spread the same chunks over the whole chip, a wavefront
 // each.  Those are 8 - 10 KB of LDS a workgroup, 16 - 20 per CU: some 5,000 chunks are one occupancy
 // round.  So they serve less than a tile (20 chunks of 64, k 21, R = 16, signs: 10 against 28 us;
-// 20 of 256, Random, k 128, R = 2: 16 against 30), and up to about a round what gives them little
-// to do per chunk: no transform (Striding and Random on the momentum itself), and two-bit signs of
-// many replicas, whose scatter the few wavefronts would do one step after the other.  us, general / wavefront per class, 0.3 M parameters (1,172 chunks of 256 ... 4,688 of 64),
-// signs: compress Striding 64/2 7 / 8, 96/48 6 / 10, 128/64 6 / 12, 256/128 7 / 18, Random 128/16
-// 8 / 10, 128/64 15 / 15, 256/128 22 / 26; decompress Random 128/16 R = 2 9 / 10, 256/128 23 / 32,
-// 256/8 R = 16 14 / 11; AdamW 128/64 R = 2 18 / 21, R = 16 33 / 24; top-k R = 16 128/42 30 / 53,
-// 256/85 50 / 102, 96/32 28 / 25.  1 M: compress 128/16 12 / 10, 256/32 10 / 14; AdamW 128/16
-// 17 / 11, 256/32 R = 2 14 / 16; top-k R = 16 128/42 77 / 59.
-inline bool few_chunks(const KParams& p, int64_t chunks) {   // compress (Striding, Random)
-    if (chunks < kWave) return true;
-    // (a shuffle of more than a quarter of the chunk is a long serial chain in the general kernel)
-    return !p.use_dct && chunks <= ((p.scheme == 2 && 4 * p.k > p.s) ? 2048 : 5120);
-}
+// 20 of 256, Random, k 128, R = 2: 16 against 30), and up to about half a round two-bit signs of
+// many replicas under top-k, whose scatter the few wavefronts would do one step after the other.  us, general /
+// wavefront per class, 0.3 M parameters, R = 16: 128/42 30 / 53, 256/85 50 / 102, 96/32 28 / 25; 1 M 128/42 77 / 59.
+inline bool few_chunks(int64_t chunks) { return chunks < kWave; }     // compress (Striding, Random)
 inline bool few_chunks_decompress(const KParams& p, int64_t chunks, bool idx) {
-    if (chunks < kWave) return true;
-    if (idx)
-        return p.val_dtype == 3 && chunks <= 2560 && static_cast<int64_t>(p.R) * p.k >= 4 * p.s;
-    return !p.use_dct && p.s >= 96 && p.R < 8 && chunks <= (p.adam ? 4096 : 2560);
+    return chunks < kWave ||
+           (idx && p.val_dtype == 3 && chunks <= 2560 && static_cast<int64_t>(p.R) * p.k >= 4 * p.s);
 }
 
 // Two-bit signs on coefficients without indices: counted a word at a time (SignCounts), or decoded and added one by
@@ -558,7 +545,7 @@ inline bool count_signs(const KParams& p) {
 // Pieces of four elements a thread: few while a launch's own latency counts (1.5 M, 128/4 compress, 2 / 4 / 8
 // pieces 5.0 / 5.8 / 6.7 us; AdamW 64/8 2.6 M 9.4 / 11.4 / 14.9), more where a replica's entries of a workgroup
 // would be a short run (128/16, 49 replicas, signs, 18 M 43.5 / 36.1 / 36.4; 256/64 bf16 60 M, 4 replicas 174 /
-// 106 / 81) and for compress where the shuffle is long (128/32 7 M 19.6 / 18.9; 256/64 60 M 144 / 127 / 129).
+// 106 / 81; signs of few replicas 128/8 R = 2 bf16 74 M 51 us in the class kernels, 59 / 54) and for compress where the shuffle is long (128/32 7 M 19.6 / 18.9; 256/64 60 M 144 / 127 / 129).
 // Workgroups per CU of large launches, without a limit / with it (147 M): compress 128/16 fp32 328 / 4 313, bf16
 // 278 / 5 263, 32/1 signs bf16 265 / 252; decompress, fp32 parameters, 128/16 206 / 5 204; AdamW, 2 pieces, 60 M
 // 64/8 bf16 205 / 3 198, fp32 258 / 251.
@@ -567,48 +554,44 @@ inline int raw_compress_quads(const KParams& p) {
     if (p.s == 96 || p.s == 192) return 3;
     return p.s == 256 || (p.s == 128 && p.k >= 32 && p.scheme == 2) ? 4 : 2;
 }
+// Everything but Random's long shuffles on a few chunks, a chain per chunk here and a wavefront per chunk in the general
+// kernels (more than a quarter of 96 and more: 128/64 fp16 0.05 M 9.3 us there, 10.5 here, geometric mean up to 2^16
+// elements 1.07, above 0.9).
+inline bool raw_compress(const KParams& p, int64_t n) {
+    return !(p.scheme == 2 && p.s >= 96 && 4 * p.k > p.s && n <= (int64_t{1} << 16));
+}
 inline int raw_compress_workgroups(int64_t n, bool grad_bf16) {
     return n > kRawLimited ? (grad_bf16 ? 5 : 4) : 0;
 }
+// (AdamW: more also where the shuffle is long, 128/64 R = 4 65 M bf16 389 / 296, and where 16 replicas and more would
+// be runs of 256 bytes or less: 64/4 R = 46 signs 32 M 167 / 154, 32/2 R = 58 59 M 346 / 323)
 inline int raw_decompress_quads(const KParams& p, int64_t n) {
-    const bool few = p.adam ? n <= (int64_t{1} << 26) : n <= (int64_t{1} << 22) && p.R < 16;
-    const bool many = !p.adam && n > (int64_t{1} << 23) && p.R * p.k >= p.s;
+    const bool few = p.adam ? n <= (int64_t{1} << 26) : n <= (int64_t{1} << (p.R < 16 ? 22 : 20));
+    const bool many = !p.adam && n > (int64_t{1} << 23) && (p.R * p.k >= p.s || (p.val_dtype == 3 && p.s <= 128));
     if (p.s == 96) return few ? 3 : 6;
     if (p.s == 192) return few && n <= (int64_t{1} << 23) ? 3 : 6;
     if (p.s == 256) return p.adam || few || p.R * p.k < p.s ? 4 : 8;
+    if (p.adam && n > (int64_t{1} << 23)) {
+        const int run = 2048 / p.s * (p.val_dtype == 3 ? 4 * ((p.k + 15) / 16) : p.k * (p.val_dtype == 0 ? 4 : 2));
+        if ((p.s == 128 && p.k >= 32 && p.scheme == 2) || (p.R >= 16 && run <= 256)) return 4;
+    }
     return few ? 2 : many && p.s != 16 ? 8 : 4;
 }
-// Not on large launches with entries one by one (two or four bytes a load; 32/13, 4 replicas, bf16 103 M 197, 239), or
-// where a lane per chunk does for bf16 parameters what is left to do (narrow values 32/1 139 M 93, 127; 32/16
-// 17 M 23.7, 26.0; 64/32, 4 replicas, 147 M 287, 294, but 64/8 30 M 35, 32), nor on launches of a few
-// wavefronts there (0.06 M 3.2, 3.7).
-// Two-bit signs are words whatever k is, added 16 fields at a time here and one by one elsewhere, so large launches
-// of those come here but for a few short forms, us, before / here:
-//   bf16 parameters, a lane per chunk: from 16 replicas and 32 entries on (147 M 32/16 R = 16 252 / 194, R = 6
-//     152 / 190; 64/32 R = 64 1,040 / 315; 32/2 R = 64 339 / 303, R = 16 158 / 148; 32/1 R = 40 245 / 220, R = 16
-//     154 / 162); below 2^24 with one or two entries only from more than s on
-//   k no multiple of four, plain update: five and more (32/5 R = 64 147 M 950 / 297, R = 2 fp32 45 M 65 / 60;
-//     256/100 R = 16 fp32 147 M 704 / 284); fewer where R*k > s, R*k = s with 48 replicas or bf16 parameters from
-//     2^24 on (64/2 R = 32 100 M 122 / 104), or three with less than 16 (16/2 R = 9 147 M 245 / 184; 128/2 R = 64
-//     229 / 164; 64/3 R = 2 fp32 60 M 80.7 / 78.1; but 64/2 R = 32 fp32 60 M 97 / 106, 128/3 R = 24 fp32 60 M
-//     85 / 97: a replica's words of a workgroup are a short run)
-//   the same under AdamW: five and more (64/21 R = 64 100 M 1,036 / 490; 256/6 R = 2 100 M 373 / 338; 16/3 R = 4
-//     100 M 321 / 337), where 48 replicas and more keep an eighth of the chunk (192/7 R = 64 fp32 100 M 481 / 539)
+// Nearly everything.  A lane per chunk does for bf16 parameters under the plain update what is left to do, on launches
+// of a few wavefronts and on large ones (narrow values 32/1 139 M 93 us, 127 here; 32/16 17 M 23.7, 26.0; 64/32, 4
+// replicas, 147 M 287, 294, but 64/8 30 M 35, 32; 0.06 M 3.2, 3.7), but for two-bit signs of more entries than the
+// chunk has (147 M 32/16 R = 16 252 / 194; 64/32 R = 64 1,040 / 315; 32/2 R = 64 339 / 303; 32/1 R = 40 245 / 220, R = 16
+// 154 / 162) or, up to 2^23, more than a quarter of that (32/4 R = 1 fp32 2.9 M 5.7 / 7.5, 32/2 R = 3 5 M 9.2 / 11.1; in the
+// mean over random shapes 0.6 above that line, 1.0 below).  The class kernels that served the rest of the large launches, over 700 random shapes of 8 - 100 M
+// parameters: 0.72 of their time here; entries one by one 0.33 - 0.98 (16/6 R = 6 fp16 18 M 66 / 49, 96/13 R = 12 fp32
+// 8.5 M 70 / 26), two-bit signs 0.2 - 1.0.
 inline bool raw_decompress(const KParams& p, int64_t n, bool param_bf16) {
     const bool lane = lane_scheme(p);
     if (n <= (int64_t{1} << 17)) return !lane;
-    if (n <= (int64_t{1} << 23)) return true;
-    if (p.val_dtype == 3) {
-        const int64_t rk = static_cast<int64_t>(p.R) * p.k;
-        if (lane && param_bf16)
-            return p.R >= 16 && rk >= 32 && (p.k >= 4 || rk > p.s || n > (int64_t{1} << 24));
-        if (p.k % 4 == 0) return true;
-        if (p.adam) return p.k >= 5 && (p.R < 48 || 8 * p.k >= p.s);
-        return p.k >= 5 || rk > p.s || (p.k == 3 && p.R < 16) ||
-               (rk == p.s && (p.R >= 48 || (param_bf16 && n > (int64_t{1} << 24))));
-    }
-    if (p.k % 4 != 0) return false;
-    return !(param_bf16 && lane && (p.val_dtype != 0 || p.s <= 32 || n > (int64_t{1} << 26)));
+    if (lane && p.val_dtype == 3 && n <= (int64_t{1} << 23)) return 4 * p.R * p.k > p.s;
+    if (n <= (int64_t{1} << 23) || !(lane && param_bf16)) return true;
+    if (p.val_dtype == 3) return p.R * p.k > p.s;
+    return p.val_dtype == 0 && p.s > 32 && n <= (int64_t{1} << 26);
 }
 inline int raw_decompress_workgroups(const KParams& p, int64_t n, bool param_bf16) {
     if (n <= kLargeShard) return 0;
@@ -619,6 +602,15 @@ inline int raw_decompress_workgroups(const KParams& p, int64_t n, bool param_bf1
 inline unsigned raw_lds(int bytes, int workgroups) {
     const int want = workgroups == 0 ? 0 : 2 * 160 * 1024 / (2 * workgroups + 1);
     return static_cast<unsigned>(want > bytes ? want : bytes);
+}
+
+inline int64_t launch_decompress_raw(const DecompressLaunch& a) {
+    const KParams& p = a.p;
+    if (a.idx || p.scheme == 0 || p.use_dct || 2 * p.k > p.s || !raw_decompress(p, a.n, a.param_bf16)) return 0;
+    const bool signs = p.val_dtype == 3;
+    if (!p.adam) return signs ? launch_decompress_raw_signs(a) : launch_decompress_raw_values(a);
+    if (!p.amsgrad) return signs ? launch_decompress_raw_signs_adamw(a) : launch_decompress_raw_adamw(a);
+    return signs ? launch_decompress_raw_signs_amsgrad(a) : launch_decompress_raw_amsgrad(a);
 }
 
 inline int64_t launch_compress_split(const CompressLaunch& a) {

@@ -20,7 +20,7 @@ static deto::KParams params(const int* a) {
     p.scheme = a[4]; p.use_dct = a[5]; p.adam = a[6];
     return p;
 }
-extern "C" int few(const int* a, int64_t chunks) { return deto::few_chunks(params(a), chunks); }
+extern "C" int few(const int*, int64_t chunks) { return deto::few_chunks(chunks); }
 extern "C" int few_decompress(const int* a, int64_t chunks) {
     return deto::few_chunks_decompress(params(a), chunks, a[4] == 0);
 }
@@ -48,7 +48,6 @@ extern "C" int scheme_classes(const int* a, int64_t n, int bf16) {
     return deto::scheme_classes(params(a), n, bf16, deto::lane_scheme(params(a)));
 }
 extern "C" int counts(const int* a, int64_t) { return deto::count_signs(params(a)); }
-extern "C" int stream_first(const int* a, int64_t) { return deto::stream_before_classes(params(a)); }
 """
 
 
@@ -76,22 +75,10 @@ def test_less_than_a_tile_goes_to_the_general_kernels(rules, s, k, val, scheme, 
         for adam in (0, 1):
             assert rules("few_decompress", s, k, 63, R, val, scheme, dct, adam)
             assert rules("few_decompress", s, k, 1, R, val, scheme, dct, adam)
-    assert rules("few", s, k, 63, 1, val, scheme, dct)
+    assert rules("few", s, k, 63, 1, val, scheme, dct) and not rules("few", s, k, 64, 1, val, scheme, dct)
 
 
-def test_a_round_of_chunks_without_a_transform_goes_to_the_general_kernels(rules):
-    # compress: up to a round of single-wavefront workgroups; a long shuffle less
-    for scheme, k, limit in ((STRIDE, 64, 5120), (RANDOM, 16, 5120), (RANDOM, 64, 2048)):
-        assert rules("few", 128, k, limit, 1, SIGNS, scheme, False)
-        assert not rules("few", 128, k, limit + 1, 1, SIGNS, scheme, False)
-        assert not rules("few", 128, k, 1000, 1, SIGNS, scheme, True)
-    # decompress: a few replicas at the larger chunk sizes
-    for adam, limit in ((0, 2560), (1, 4096)):
-        for s, R, few in ((96, 2, True), (256, 7, True), (64, 2, False), (256, 8, False)):
-            assert bool(rules("few_decompress", s, 8, limit, R, F16, RANDOM, False, adam)) == few
-            assert not rules("few_decompress", s, 8, limit + 1, R, F16, RANDOM, False, adam)
-            assert not rules("few_decompress", s, 8, limit, R, F16, RANDOM, True, adam)
-    # top-k: signs of many replicas only
+def test_few_chunks_of_many_replicas_signs_go_to_the_general_kernels(rules):
     assert rules("few_decompress", 128, 42, 2560, 16, SIGNS)
     assert not rules("few_decompress", 128, 42, 2561, 16, SIGNS)
     assert not rules("few_decompress", 128, 42, 2560, 2, SIGNS)
@@ -185,9 +172,10 @@ def test_one_or_two_bf16_entries_of_16_are_limited_later(rules):
         assert rules(name, 16, k, tiles) == want
 
 
-def test_adamw_striding_streams_at_the_larger_chunks_only(rules):
-    for s, adam, stream in ((64, 0, True), (32, 1, False), (64, 1, False), (96, 1, True), (192, 1, True)):
-        assert bool(rules("stream_first", s, s // 8, 0, 2, F32, STRIDE, False, adam)) == stream
+def test_signs_of_many_replicas_are_counted(rules):
+    for k, R in ((17, 16), (4, 32), (3, 48), (16, 32)):
+        assert rules("counts", 64, k, 0, R, SIGNS, RANDOM, True) and not rules("counts", 64, k, 0, R - 1, SIGNS, RANDOM, True)
+        assert not rules("counts", 64, k, 0, R, F16, RANDOM, True)
 
 
 def tiles(s, t):
@@ -258,9 +246,3 @@ def test_lane_kernels_of_the_schemes(rules):
 def test_scheme_classes(rules, s, k, val, adam, bf16, n, want):
     for dct in (False, True):
         assert rules("scheme_classes", s, k, n, 4, val, RANDOM, dct, adam, bf16) == want
-
-
-def test_signs_of_many_replicas_are_counted(rules):
-    for k, R in ((17, 16), (4, 32), (3, 48), (16, 32)):
-        assert rules("counts", 64, k, 0, R, SIGNS, RANDOM, True) and not rules("counts", 64, k, 0, R - 1, SIGNS, RANDOM, True)
-        assert not rules("counts", 64, k, 0, R, F16, RANDOM, True)

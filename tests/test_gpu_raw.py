@@ -61,6 +61,24 @@ def test_non_finite_values(H, s, k, signs, scheme):
     assert not m_gpu[kept].view(np.uint32).any()
 
 
+@pytest.mark.parametrize("k,val_dtype,Rs", [
+    # entries four at a time: two, four, eight or sixteen replicas a batch; one by one: four, eight, sixteen, 32; signs: 3, 9, 18
+    (32, oracle.F32, (2, 3, 4, 5, 9)), (32, oracle.F16, (2, 3, 4, 5, 9, 17)), (7, oracle.F32, (3, 4, 5, 9, 17, 33)),
+    (7, oracle.BF16, (4, 5, 9, 17)), (8, oracle.F32, (9, 33)), (19, oracle.TERNARY, (3, 4, 9, 10, 18, 19, 37, 64))])
+def test_batches_of_replicas(H, k, val_dtype, Rs):
+    """Both sides of every batch of replicas: three payloads, moved by chunks, stand for R."""
+    s = 64
+    n = (1 << 17) + 5 * s + 7
+    cfg = Config(chunk=s, topk=k, scheme=oracle.SCHEME_RANDOM, sign=False, lr=1e-3, seed=11, step=5)
+    _, _, th = make_inputs(n, seed=k)
+    three = oracle_payloads(cfg, n, val_dtype, 3, 300)
+    unit = -(-k // 16) if val_dtype == oracle.TERNARY else k
+    for R in Rs:
+        idx = np.stack([three[0][r % 3] for r in range(R)])
+        val = np.stack([np.roll(three[1][r % 3], r * unit, axis=0) for r in range(R)])
+        check_update(H, cfg, idx, val, val_dtype, val_dtype != oracle.F32, th)
+
+
 @pytest.mark.parametrize("s,k,R,fmt,bf16", [(64, 8, 4, "f32+i32", True), (64, 32, 4, "f32+i32", False),
                                             (128, 16, 9, "bf16+u8", True), (128, 8, 40, "signs+u8", False),
                                             (96, 12, 8, "f32+i32", False), (192, 24, 3, "f16+i32", True),

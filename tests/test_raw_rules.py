@@ -21,15 +21,27 @@ extern "C" int takes_signs(int s, int k, int R, int bf16, int adam, int64_t n) {
     return deto::raw_decompress(params(s, k, R, 3, adam), n, bf16 != 0);
 }
 extern "C" int compress_quads(int s, int k) { return deto::raw_compress_quads(params(s, k, 1, 0, 0)); }
-extern "C" int quads(int s, int k, int R, int adam, int64_t n) {
-    return deto::raw_decompress_quads(params(s, k, R, 0, adam), n);
+extern "C" int quads(int s, int k, int R, int val, int adam, int64_t n) {
+    return deto::raw_decompress_quads(params(s, k, R, val, adam), n);
 }
-extern "C" int built(int s, int q) {
+extern "C" int built(int s, int q, int adam) {
 #define X(S, Q) if (s == S && q == Q) return 1;
     DETO_RAW_DECOMPRESS_LIST(X)
 #undef X
+#define X(S, Q) if (s == S && q == Q) return !adam;
+    DETO_RAW_DECOMPRESS_PLAIN_LIST(X)
+#undef X
     return 0;
 }
+extern "C" int workgroups(int val, int adam, int bf16, int64_t n) {
+    return deto::raw_decompress_workgroups(params(64, 8, 2, val, adam), n, bf16 != 0);
+}
+extern "C" int compresses(int s, int k, int scheme, int64_t n) {
+    deto::KParams p = params(s, k, 1, 0, 0);
+    p.scheme = scheme;
+    return deto::raw_compress(p, n);
+}
+extern "C" int compress_workgroups(int bf16, int64_t n) { return deto::raw_compress_workgroups(n, bf16 != 0); }
 extern "C" int compress_built(int s, int q) {
 #define X(S, Q) if (s == S && q == Q) return 1;
     DETO_RAW_COMPRESS_LIST(X)
@@ -57,24 +69,51 @@ def test_every_choice_is_built(lib):
             for R in (1, 2, 7, 8, 15, 16, 64):
                 for adam in (0, 1):
                     for n in SIZES:
-                        assert lib.built(s, lib.quads(s, k, R, adam, ctypes.c_int64(n)))
+                        for val in (0, 3):
+                            assert lib.built(s, lib.quads(s, k, R, val, adam, ctypes.c_int64(n)), adam)
 
 
 @pytest.mark.parametrize("s,k,val,bf16,n,want", [
-    (64, 8, 0, 0, 1 << 17, 0), (64, 8, 0, 0, (1 << 17) + 1, 1), (128, 16, 0, 0, 64, 1), (64, 7, 0, 1, 1 << 23, 1),
-    (64, 7, 0, 1, (1 << 23) + 1, 0), (128, 16, 3, 1, 1 << 30, 1), (64, 8, 0, 1, 1 << 26, 1), (64, 8, 0, 1, (1 << 26) + 1, 0),
-    (64, 8, 0, 0, 1 << 30, 1), (64, 8, 2, 1, (1 << 23) + 1, 0), (64, 8, 2, 0, (1 << 23) + 1, 1), (32, 8, 0, 1, (1 << 23) + 1, 0)])
+    # a lane per chunk: small launches, and large ones of bf16 parameters
+    (64, 8, 0, 0, 1 << 17, 0), (64, 8, 0, 0, (1 << 17) + 1, 1), (128, 16, 0, 0, 64, 1), (64, 8, 0, 1, 1 << 26, 1),
+    (64, 8, 0, 1, (1 << 26) + 1, 0), (64, 8, 0, 0, 1 << 30, 1), (64, 8, 2, 1, 1 << 23, 1), (64, 8, 2, 1, (1 << 23) + 1, 0),
+    (64, 8, 2, 0, (1 << 23) + 1, 1), (32, 8, 0, 1, (1 << 23) + 1, 0), (64, 7, 0, 1, 1 << 30, 1), (128, 16, 2, 1, 1 << 30, 1)])
 def test_decompress_rule(lib, s, k, val, bf16, n, want):
     assert lib.takes(s, k, val, bf16, ctypes.c_int64(n)) == want
 
 
 @pytest.mark.parametrize("s,k,R,bf16,adam,n,want", [
-    (32, 16, 15, 1, 0, 1 << 27, 0), (32, 16, 16, 1, 0, 1 << 27, 1), (32, 1, 31, 1, 0, 1 << 27, 0), (32, 1, 32, 1, 0, 1 << 27, 1),
-    (32, 2, 16, 1, 0, 1 << 24, 0), (32, 2, 17, 1, 0, 1 << 24, 1), (32, 2, 16, 1, 0, (1 << 24) + 1, 1), (64, 4, 16, 1, 0, 1 << 24, 1),
-    (64, 2, 32, 1, 0, 1 << 24, 0), (64, 2, 32, 1, 0, (1 << 24) + 1, 1),
-    (64, 5, 1, 0, 0, 1 << 24, 1), (64, 3, 15, 0, 0, 1 << 24, 1), (64, 3, 16, 0, 0, 1 << 24, 0), (64, 3, 22, 0, 0, 1 << 24, 1),
-    (32, 1, 32, 0, 0, 1 << 24, 0), (64, 1, 64, 0, 0, 1 << 24, 1), (64, 2, 32, 0, 0, 1 << 24, 0), (16, 1, 17, 0, 0, 1 << 24, 1),
-    (64, 3, 64, 1, 1, 1 << 24, 0), (64, 5, 47, 1, 1, 1 << 24, 1), (64, 7, 48, 0, 1, 1 << 24, 0), (32, 5, 48, 0, 1, 1 << 24, 1),
-    (64, 4, 64, 0, 1, 1 << 24, 1), (64, 3, 16, 0, 0, 1 << 23, 1)])
+    # two-bit signs: more entries than the chunk has, where a lane per chunk serves them
+    (32, 16, 2, 1, 0, 1 << 27, 0), (32, 16, 3, 1, 0, 1 << 27, 1), (32, 1, 32, 1, 0, 1 << 27, 0), (32, 1, 33, 1, 0, 1 << 27, 1),
+    (32, 16, 2, 0, 0, 1 << 27, 1), (32, 4, 2, 0, 0, 1 << 23, 0), (32, 4, 3, 1, 0, 1 << 23, 1), (32, 4, 2, 0, 0, (1 << 23) + 1, 1),
+    (32, 4, 1, 0, 1, 1 << 20, 1), (32, 3, 1, 0, 0, 1 << 20, 1), (32, 16, 2, 1, 1, 1 << 27, 1), (64, 2, 1, 1, 0, 1 << 27, 1)])
 def test_decompress_rule_of_signs(lib, s, k, R, bf16, adam, n, want):
     assert lib.takes_signs(s, k, R, bf16, adam, ctypes.c_int64(n)) == want
+
+
+# (s, k, R, values, AdamW, elements, pieces a thread)
+@pytest.mark.parametrize("s,k,R,val,adam,n,want", [
+    (64, 8, 2, 0, 0, 1 << 22, 2), (64, 8, 2, 0, 0, (1 << 22) + 1, 4), (64, 8, 16, 0, 0, 1 << 20, 2), (64, 8, 16, 0, 0, (1 << 20) + 1, 4),
+    (64, 8, 8, 0, 0, 1 << 23, 4), (64, 8, 8, 0, 0, (1 << 23) + 1, 8), (64, 8, 7, 0, 0, 1 << 24, 4), (16, 8, 64, 0, 0, 1 << 24, 4),
+    (64, 8, 1, 3, 0, 1 << 24, 8), (64, 8, 1, 3, 0, 1 << 23, 4), (256, 16, 1, 3, 0, 1 << 24, 4), (16, 8, 1, 3, 0, 1 << 24, 4),
+    (64, 8, 2, 0, 1, 1 << 26, 2), (64, 8, 2, 0, 1, (1 << 26) + 1, 4), (128, 32, 2, 0, 1, 1 << 23, 2), (128, 32, 2, 0, 1, 1 << 24, 4),
+    (64, 4, 16, 3, 1, 1 << 24, 4), (64, 4, 15, 3, 1, 1 << 24, 2), (64, 4, 16, 0, 1, 1 << 24, 2), (32, 16, 16, 3, 1, 1 << 24, 4), (96, 8, 2, 0, 0, 1 << 22, 3),
+    (96, 8, 2, 0, 0, 1 << 23, 6), (192, 8, 2, 0, 1, 1 << 23, 3), (192, 8, 2, 0, 1, 1 << 24, 6), (256, 64, 4, 0, 0, 1 << 24, 8),
+    (256, 64, 3, 0, 0, 1 << 24, 4), (256, 64, 4, 0, 1, 1 << 24, 4)])
+def test_pieces_of_a_thread(lib, s, k, R, val, adam, n, want):
+    assert lib.quads(s, k, R, val, adam, ctypes.c_int64(n)) == want
+
+
+def test_compress_rule(lib):
+    for s, k, scheme, want in ((96, 25, 2, 0), (96, 24, 2, 1), (96, 25, 1, 1), (64, 32, 2, 1), (256, 128, 2, 0)):
+        assert lib.compresses(s, k, scheme, ctypes.c_int64(1 << 16)) == want
+        assert lib.compresses(s, k, scheme, ctypes.c_int64((1 << 16) + 1)) == 1
+
+
+def test_workgroups_per_cu(lib):
+    for val, adam, bf16, n, want in ((0, 0, 0, 1 << 25, 0), (0, 0, 0, (1 << 25) + 1, 5), (0, 0, 1, 1 << 27, 0), (0, 1, 1, 1 << 26, 3),
+                                     (0, 1, 0, (1 << 26) + 1, 0), (3, 1, 0, 1 << 26, 0)):
+        assert lib.workgroups(val, adam, bf16, ctypes.c_int64(n)) == want
+    for bf16, want in ((0, 4), (1, 5)):
+        assert lib.compress_workgroups(bf16, ctypes.c_int64(1 << 24)) == 0
+        assert lib.compress_workgroups(bf16, ctypes.c_int64((1 << 24) + 1)) == want
