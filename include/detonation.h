@@ -42,8 +42,9 @@
  *   - Environment.  DETO_SMALL_SHARD_TILES (a count of 64-chunk tiles, default 8192; read at
  *     every call) is the shard size up to which the compress half at chunk size 64 and 128
  *     (top-k, fp32 + int32 payload) spreads a tile over more wavefronts: shorter launches on
- *     small shards, a few per cent longer ones on large shards.  0 switches it off.  The
- *     results of the two kernel choices agree to rounding.
+ *     small shards, a few per cent longer ones on large shards.  0 switches it off (no shard counts
+ *     as small: tiles of the compress half are interleaved at any size, else from 2^20 elements
+ *     on; the same bits).  The results of the two kernel choices agree to rounding.
  */
 #ifndef DETONATION_H
 #define DETONATION_H

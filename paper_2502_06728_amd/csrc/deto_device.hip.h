@@ -44,11 +44,11 @@ struct KParams {
 // ---- Which 64 chunks a tile is made of.  Not 64 in a row: kGang consecutive tiles (a gang) share
 // kGang * 64 chunks and take them in turn, a run of 2^lg chunks each, so that the workgroups in flight walk
 // through every array side by side, in windows of a run each, instead of each through a window of its own.
-// Memory is faster that way.  The traffic alone, without arithmetic, 147 M parameters, us, tiles in a
-// row / in turn by 32: 24 KiB read and 32 KiB written a tile, 8 wavefronts a CU 393 / 348; eight streams of
-// 8 KiB read and one rewritten 513 / 440; AdamW's three rewritten 366 / 325.  Eight tiles in turn give half of
-// that, 64 no more than 32.  (Plain stores of an interleaved stream give it away: non-temporal ones
-// there.)  The chunks that do not fill a gang are tiles of 64 in a row (lg = 6: no gangs at all).
+// Memory is faster that way.  The traffic alone, without arithmetic (membench), 147 M parameters, us, tiles in a
+// row / in gangs: eight streams of 8 KiB a tile read and one rewritten 517 / 465; 24 KiB read and 32 KiB written 379 /
+// 368 (plain stores 389 / 384: an interleaved stream wants non-temporal ones); AdamW's three rewritten 548 / 521.
+// Which launches are in gangs: compress_run_log2, decompress_gangs and decompress_run_log2 in tiled_launch.h.  The
+// chunks that do not fill a gang are tiles of 64 in a row (lg = 6: no gangs at all).
 //
 // A run is 512 elements or more (2 KiB of fp32: a wavefront's loads stay whole), and at least `run_bytes` of
 // every payload array, below which runs cost more lines than they save: decompress, plain update, us,
@@ -57,7 +57,7 @@ struct KParams {
 // than 16 chunks a run (32 at chunk 16) gain nothing: 32/16 signs 546 / 553.  Chunk 96 loses 3 - 6 %, chunk
 // 192 and 256 are bound by their arithmetic (256/32 decompress 246 / 262).
 constexpr int kGang = 32;
-constexpr int kRunElems = 512, kRunBytes = 128;
+constexpr int kRunElems = 512, kRunBytes = 128, kSchemeRunBytes = 1024;
 constexpr bool in_gangs(int s) { return s == 16 || s == 32 || s == 64 || s == 128; }
 // idx_bytes: of one transmitted index, 0 without indices
 __host__ __device__ constexpr int run_log2(int s, int k, int val_dtype, int idx_bytes, int run_bytes) {
@@ -76,6 +76,9 @@ __host__ __device__ constexpr int decompress_run_bytes(int s, int k, int R, bool
     if (adam) return R * k <= s ? 128 : 256;
     return 2 * R * k <= s && (s <= 32 || k >= 8) ? 256 : 1024;
 }
+
+// Striding and Random on coefficients, a lane per chunk, fp32 values: decompress kernels in gangs
+__host__ __device__ constexpr bool scheme_gangs(int s, int k) { return k >= 16 && (s == 32 || s == 64); }
 
 struct TileRows {
     int64_t first;      // chunk of row 0

@@ -143,9 +143,8 @@ int detonation_compress_packed(const deto_config* cfg, int64_t n, const void* gr
         return DETO_ERR_ALIGN;
 
     KParams p = resolve(cfg, 1, val_dtype, idx_dtype);
-    p.run_lg = deto::run_log2(p.s, p.k, val_dtype, idx_out ? static_cast<int>(idx_size(idx_dtype)) : 0,
-                              deto::kRunBytes);
     const int64_t C = chunks_of(n, p.s);
+    p.run_lg = deto::compress_run_log2(p, n);
     hipStream_t st = static_cast<hipStream_t>(stream);
     fresh_status();
 
@@ -294,10 +293,6 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         return DETO_ERR_ALIGN;
 
     KParams p = resolve(cfg, R, val_dtype, idx_dtype);
-    p.run_lg = n <= deto::kGangShard
-                   ? 6
-                   : deto::run_log2(p.s, p.k, val_dtype, idx ? static_cast<int>(idx_size(idx_dtype)) : 0,
-                                    deto::decompress_run_bytes(p.s, p.k, R, opt != nullptr));
     if (opt) {
         const double bc1 = 1.0 - std::pow(static_cast<double>(opt->beta1),
                                           static_cast<double>(opt->step));
@@ -313,6 +308,7 @@ int decompress_impl(const deto_config* cfg, const deto_adamw* opt, int64_t n, in
         p.step_size = static_cast<float>(static_cast<double>(cfg->lr) / bc1);
         p.inv_sqrt_bc2 = static_cast<float>(1.0 / std::sqrt(bc2));
     }
+    p.run_lg = deto::decompress_run_log2(p, n, idx != nullptr, param_dtype == DETO_BF16);
     p.count_signs = !idx && deto::count_signs(p);
     const int64_t C = chunks_of(n, p.s);
     const int64_t entries = C * p.k;

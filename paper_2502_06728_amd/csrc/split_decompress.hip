@@ -25,7 +25,7 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
 #else
     if (!a.idx || DETO_SPLIT_NARROW != (p.val_dtype != 0 || p.idx_u8)) return 0;
     if (DETO_SPLIT_AMSGRAD != (p.adam && p.amsgrad)) return 0;
-    if (DETO_SPLIT_GANG && !decompress_gangs(p, classes)) return 0;
+    if (DETO_SPLIT_GANG && !decompress_gangs(p, a.n, a.param_bf16, classes)) return 0;
     const int64_t tiles = (a.n / p.s) / kWave;
     // one workgroup per full tile and one for the chunks left over (a partial tile)
     const int64_t grid64 = tiles + (a.n_chunks > tiles * kWave ? 1 : 0);
@@ -37,9 +37,10 @@ int64_t DETO_SPLIT_FN(const DecompressLaunch& a, int classes) {
         <<<grid, W * kWave, spare, a.stream>>>(p, tiles, a.n, a.n_chunks, a.idx, a.idx_stride,  \
                                                a.val, a.val_stride, a.params, a.adam,           \
                                                a.presign_dbg)
+    // (two classes in gangs: fp32 parameters only)
 #define X(S, W)                                                                                 \
-    if (p.s == S && classes == W) {                                                             \
-        if (a.param_bf16) LAUNCH(S, W, true);                                                   \
+    if (p.s == S && classes == W && !(DETO_SPLIT_GANG && W == 2 && a.param_bf16)) {             \
+        if (a.param_bf16) LAUNCH(S, W, (!(DETO_SPLIT_GANG && W == 2)));                         \
         else LAUNCH(S, W, false);                                                               \
         return a.n_chunks;   /* the tail chunks ride along */                                   \
     }

@@ -874,7 +874,7 @@ __attribute__((amdgpu_waves_per_eu((S == 192 && TOP > 0) ? 3 : 2))) void compres
     }
     __syncthreads();
     {
-        // the tile's 64*k entries are contiguous in both payload arrays
+        // the tile's 64*k entries, in order (contiguous in both payload arrays, or in gangs a run of chunks at a time)
         const uint32_t magic = entry_magic(k);
         const unsigned long long tie_chunks = s_tie;
         // entries e .. e+3 of the tile (k a multiple of 4: they belong to one chunk)

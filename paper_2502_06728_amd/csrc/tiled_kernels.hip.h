@@ -299,7 +299,7 @@ __device__ __forceinline__ void compact_and_store_payload(const float (&c)[S],
             const int e = it * 256 + lane * 4;
             const int r = e / K, col = e % K;
             const int64_t ge = pbase + rows.block<K, LG, 256>(it);
-                const uint32_t at = rows.within_block<K, LG, 256>(it, lane * 4);
+            const uint32_t at = rows.within_block<K, LG, 256>(it, lane * 4);
             st_f4<DETO_NT_COMPRESS_PAYLOAD>(val_out + ge + at,
                                             *reinterpret_cast<const float4*>(tile + r * PR + col));
             if (idx_out) {
@@ -374,7 +374,8 @@ __device__ __forceinline__ ChunkMask<S> random_mask(uint64_t seed, uint64_t step
 // Compress half (top-k) on full tiles: chunks [0, 64*n_tiles), all complete.  Chunk sizes up
 // to 64: beyond that a chunk no longer fits one lane at two wavefronts per SIMD, and the
 // two-lanes-per-chunk kernels (pair_kernels.hip.h) take over.
-template <int S, int K, bool GRAD_BF16, int VAL = 0>
+// GANG: tiles in gangs (run_log2).
+template <int S, int K, bool GRAD_BF16, int VAL, bool GANG>
 __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_tiled_topk(
     KParams p, int64_t n_tiles, TailRange tail, const void* __restrict__ grad,
     float* __restrict__ mom, void* __restrict__ idx_out, void* __restrict__ val_out,
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
                                            idx_out, val_out, coeff_dbg);
         return;
     }
-    constexpr int kLg = run_log2(S, K, VAL, VAL ? 1 : 4, kRunBytes);
+    constexpr int kLg = GANG ? run_log2(S, K, VAL, VAL ? 1 : 4, kRunBytes) : 6;
     const TileRows rows = tile_rows(t, n_tiles, kLg);
     const int64_t own = rows.first + rows.chunk(lane);     // the lane's chunk
 
@@ -476,9 +477,10 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
 }
 
 // Compress half for Striding and Random on DCT coefficients, full tiles (on the momentum itself:
-// raw_kernels.hip.h).  Same three phases; the kept set is a bit pattern that does not depend on the data: `stride_mask` for Striding, a per-chunk shuffle for Random.
+// raw_kernels.hip.h).  Same three phases; the kept set is a bit pattern that does not depend on the
+// data: `stride_mask` for Striding, a per-chunk shuffle for Random.
 // VAL as in compact_and_store_payload (narrow formats: byte indices, if any are asked for).
-template <int S, int K, bool GRAD_BF16, int VAL = 0>
+template <int S, int K, bool GRAD_BF16, int VAL, bool GANG>
 __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_tiled_scheme(
     KParams p, MaskWords stride_mask, int64_t n_tiles, TailRange tail,
     const void* __restrict__ grad, float* __restrict__ mom, void* __restrict__ idx_out,
@@ -495,7 +497,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void compress_ti
                                            idx_out, val_out, coeff_dbg);
         return;
     }
-    constexpr int kLg = run_log2(S, K, VAL, 0, kRunBytes);
+    constexpr int kLg = GANG ? run_log2(S, K, VAL, 0, kRunBytes) : 6;
     const TileRows rows = tile_rows(t, n_tiles, kLg);
     const int64_t own = rows.first + rows.chunk(lane);     // the lane's chunk
 
@@ -552,12 +554,10 @@ struct PayloadRegs<K, 0> {
     static constexpr int kVec = (K % 4 == 0) ? K / 4 : 1;
     int4 i[kVec];
     float4 v[kVec];
-    // (entry u + e: a uniform part and the lane's)
-    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, uint32_t u,
-                                         uint32_t e) {
-        const uint4 iv = ld_u4<DETO_NT_DECOMPRESS_LD>(static_cast<const int32_t*>(ir) + u + e);
+    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, int e) {
+        const uint4 iv = ld_u4<DETO_NT_DECOMPRESS_LD>(static_cast<const int32_t*>(ir) + e);
         i[it] = make_int4(iv.x, iv.y, iv.z, iv.w);
-        v[it] = ld_f4<DETO_NT_DECOMPRESS_LD>(static_cast<const float*>(vr) + u + e);
+        v[it] = ld_f4<DETO_NT_DECOMPRESS_LD>(static_cast<const float*>(vr) + e);
     }
     template <int C>
     __device__ __forceinline__ uint32_t idx(int it) const {
@@ -574,10 +574,9 @@ struct PayloadRegs {
     static constexpr int kVec = (K % 4 == 0) ? K / 4 : 1;
     uint32_t i[kVec];
     uint2 v[kVec];
-    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, uint32_t u,
-                                         uint32_t e) {
-        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + u + e);
-        v[it] = ld_u2<DETO_NT_DECOMPRESS_LD>(static_cast<const uint16_t*>(vr) + u + e);
+    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, int e) {
+        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + e);
+        v[it] = ld_u2<DETO_NT_DECOMPRESS_LD>(static_cast<const uint16_t*>(vr) + e);
     }
     template <int C>
     __device__ __forceinline__ uint32_t idx(int it) const {
@@ -599,11 +598,9 @@ struct PayloadRegs<K, 3> {
     static constexpr int kChunkBytes = 4 * ((K + 15) / 16);
     uint32_t i[kVec];
     uint32_t v[kVec];
-    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, uint32_t u,
-                                         uint32_t e) {
-        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + u + e);
-        const uint32_t all = u + e;
-        v[it] = static_cast<const uint8_t*>(vr)[(all / K) * kChunkBytes + (all % K) / 4];
+    __device__ __forceinline__ void load(int it, const void* ir, const void* vr, int e) {
+        i[it] = ld_u1<DETO_NT_DECOMPRESS_LD>(static_cast<const uint8_t*>(ir) + e);
+        v[it] = static_cast<const uint8_t*>(vr)[(e / K) * kChunkBytes + (e % K) / 4];
     }
     template <int C>
     __device__ __forceinline__ uint32_t idx(int it) const {
@@ -616,14 +613,12 @@ struct PayloadRegs<K, 3> {
     }
 };
 
-template <int K, int VAL, int LG>
+template <int K, int VAL>
 __device__ __forceinline__ void load_payload(PayloadRegs<K, VAL>& r, const void* __restrict__ ir,
-                                             const void* __restrict__ vr, const TileRows& rows,
-                                             int lane) {
+                                             const void* __restrict__ vr, int lane) {
     static_assert(K % 4 == 0, "vector path");
 #pragma unroll
-    for (int it = 0; it < K / 4; ++it) 
-        r.load(it, ir, vr, rows.block<K, LG, 256>(it), rows.within_block<K, LG, 256>(it, lane * 4));
+    for (int it = 0; it < K / 4; ++it) r.load(it, ir, vr, it * 256 + lane * 4);
 }
 
 // a[chunk][index] += value; an index outside [0,S) lands in the row's padding slot S.
@@ -859,9 +854,8 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
                                               presign_dbg);
         return;
     }
-    constexpr int kLg = 6;      // (no gangs: what large launches gain by them runs on the classes)
-    const TileRows rows = tile_rows(t, n_tiles, kLg);
-    const uint32_t own = rows.chunk(lane);                 // the lane's chunk, from the first one
+    // (no gangs: what large launches gain by them runs on the classes)
+    const TileRows rows{t * kWave, 0u, 6};
     const int64_t pbase = rows.first * K;
     // replica r's entries of this tile, in bytes from the array bases
     // (ternary: ceil(K/16) words per chunk, replica stride in 32-bit words)
@@ -885,7 +879,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
         constexpr int kBuf = K > 32 ? 2 : (K > 8 ? 3 : 8);
         PayloadRegs<K, VAL> b[kBuf];
         auto fetch = [&](PayloadRegs<K, VAL>& dst, int r) {
-            load_payload<K, VAL, kLg>(dst, idx + r * idx_step, val + r * val_step, rows, lane);
+            load_payload<K, VAL>(dst, idx + r * idx_step, val + r * val_step, lane);
         };
 #pragma unroll
         for (int i = 0; i < kBuf; ++i)
@@ -911,22 +905,22 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
             for (int i = 0; i < kBatch; ++i) {
                 if (r0 + i < p.R) {
                     const int r = r0 + i;
-                    const char* ir = idx + r * idx_step + own * K * kIdxBytes;
+                    const char* ir = idx + r * idx_step + lane * K * kIdxBytes;
                     const char* vr = val + r * val_step;
                     if constexpr (VAL == 3) {
                         static_assert(K < 16, "one word per chunk");
-                        raw[i][0] = reinterpret_cast<const uint32_t*>(vr)[own];
+                        raw[i][0] = reinterpret_cast<const uint32_t*>(vr)[lane];
                     }
 #pragma unroll
                     for (int j = 0; j < K; ++j) {
                         if constexpr (VAL == 0) {
                             at[i][j] =
                                 static_cast<uint32_t>(reinterpret_cast<const int32_t*>(ir)[j]);
-                            raw[i][j] = reinterpret_cast<const uint32_t*>(vr)[own * K + j];
+                            raw[i][j] = reinterpret_cast<const uint32_t*>(vr)[lane * K + j];
                         } else {
                             at[i][j] = reinterpret_cast<const uint8_t*>(ir)[j];
                             if constexpr (VAL != 3)
-                                raw[i][j] = reinterpret_cast<const uint16_t*>(vr)[own * K + j];
+                                raw[i][j] = reinterpret_cast<const uint16_t*>(vr)[lane * K + j];
                         }
                     }
                 }
@@ -943,24 +937,24 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
         }
     }
     ParamRegs<S, PARAM_BF16> th;
-    load_params<S, kLg, PARAM_BF16>(th, params, rows, lane);
+    load_params<S, 6, PARAM_BF16>(th, params, rows, lane);
     wave_lds_sync();
 
     float* row = tile + lane * G::kRow;
     float y[S];
     row_to_regs<S>(row, y);
-    finish_chunk<S>(p, y, row, presign_dbg, rows.first + own);
+    finish_chunk<S>(p, y, row, presign_dbg, rows.first + lane);
     wave_lds_sync();
-    update_params_from_tile<S, kLg, PARAM_BF16>(p, tile, th, params, rows, lane);
+    update_params_from_tile<S, 6, PARAM_BF16>(p, tile, th, params, rows, lane);
 }
 
 // Decompress-and-update half for Striding and Random without transmitted indices: every
 // replica kept the same positions, so the R value arrays are summed entry by entry while
 // they stream in, and each chunk's lane spreads the k sums over the positions of its bit
 // pattern.
-// COUNT: two-bit signs of many replicas, counted a word at a time: kernels of
+// GANG: tiles in gangs (run_log2).  COUNT: two-bit signs of many replicas, counted a word at a time: kernels of
 // their own, since those of a few replicas lose registers to it (32/8 R = 4 11 M 13.4 us, 14.8 in one kernel).
-template <int S, int K, bool PARAM_BF16, int VAL = 0, bool COUNT = false>
+template <int S, int K, bool PARAM_BF16, int VAL, bool GANG, bool COUNT>
 __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_tiled_scheme(
     KParams p, MaskWords stride_mask, int64_t n_tiles, TailRange tail,
     const void* __restrict__ val_v, int64_t val_stride, void* __restrict__ params, AdamPtrs ad,
@@ -978,8 +972,7 @@ __global__ __launch_bounds__(kWave, TileGeom<S>::kWavesPerSimd) void decompress_
                                               presign_dbg);
         return;
     }
-    // (R is not known here: runs as for many replicas.  fp32 parameters: 64/32, coefficients, 147 M 388, 394)
-    constexpr int kLg = PARAM_BF16 ? run_log2(S, K, VAL, 0, 1024) : 6;
+    constexpr int kLg = GANG ? run_log2(S, K, VAL, 0, kSchemeRunBytes) : 6;
     const TileRows rows = tile_rows(t, n_tiles, kLg);
     const uint32_t own = rows.chunk(lane);                 // the lane's chunk, from the first one
     const int64_t pbase = rows.first * K;

@@ -11,6 +11,8 @@
 
 namespace deto {
 
+constexpr int64_t kLargeShard = int64_t{1} << 25;   // elements from which on memory decides, not latency
+
 struct CompressLaunch {
     KParams p;
     int64_t tiles;          // full 64-chunk tiles, one workgroup each
@@ -49,7 +51,6 @@ struct DecompressLaunch {
 // (chunk 64: two coefficient classes instead of a lane per chunk, and four up to 512 tiles; chunk 128:
 // four instead of two).  Measured on MI355X: 4 - 13 % shorter launches at 1,300 - 8,000 tiles, 4 - 5 % longer
 // ones at 36,000.  The environment variable DETO_SMALL_SHARD_TILES overrides the limit (0: never).
-constexpr int64_t kLargeShard = int64_t{1} << 25;   // elements
 inline int64_t small_shard_tiles() {
     const char* e = getenv("DETO_SMALL_SHARD_TILES");
     if (e && *e) {
@@ -342,24 +343,31 @@ inline int scheme_classes(const KParams& p, int64_t n, bool param_bf16, bool lan
 // shapes on rotating buffers (11 ... 147 M parameters compress, 36 ... 147 M decompress; both element
 // types); in brackets the time at the chosen number over the time without a limit.
 //   compress, a lane per chunk: chunk 32, top-k (k 1, 8, 16, fp32, fp16, signs) and coefficients 10
-//   (0.95 - 0.99; fewer lose where signs leave the transform as the bound: 32/16 30 M bf16 8 1.03), raw
-//   Striding / Random 8 (0.94 - 0.98); chunk 16 10, raw 8 (0.95 - 1.01; with one or two entries of bf16
-//   gradients 11 M 1.01, 30 M 1.01 - 1.02, 45 M 0.99, hence the second line); chunk 64 raw 6 (0.96 -
-//   0.99).
+//   (0.95 - 0.99; fewer lose where signs leave the transform as the bound: 32/16 30 M bf16 8 1.03); chunk 16
+//   10 (0.95 - 1.01; with one or two entries of bf16 gradients 11 M 1.01, 30 M 1.01 - 1.02, 45 M 0.99,
+//   hence the second line).
 constexpr int64_t kLimitedTiles = 10240;      // (40 tiles per CU)
 inline int compress_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) {
     if (tiles <= kLimitedTiles) return 0;
-    if (p.s == 16 && p.k <= 2 && grad_bf16 && tiles <= 32768) return 0;
-    const bool raw = p.scheme != 0 && !p.use_dct;
-    if (p.s == 64) return raw ? 6 : 0;
+    if (p.s == 16 && p.k <= 2 && grad_bf16) return 0;     // (up to 2^25 elements: above, compress_gang_workgroups)
     // (signs, top-k, chunk 32, 7: 32/16 147 M bf16 277, 273; 32/4 28 M fp32 65.0, 64.0; fp32 gradients from 2^25
     // elements on 5: 32/16 333, 321, 32/4 60 M 134, 128)
     if (p.s == 32 && p.scheme == 0 && p.val_dtype == 3)
         return !grad_bf16 && tiles * (kWave * p.s) > kLargeShard ? 5 : 7;
-    return p.s <= 32 ? (raw ? 8 : 10) : 0;
+    return p.s <= 32 ? 10 : 0;
 }
-// Tiles in gangs (run_log2): fewer of them are in flight at no loss.  us without a limit, or at the one above,
-// and at the chosen one (147 M; 60 M):
+// Tiles in gangs (run_log2), compress: from 2^20 elements on.  In gangs over in a row, geometric mean over random
+// shapes on rotating buffers (largest): chunk 16 1 - 4 M 0.96 (1.01), from 8 M on 0.97; chunk 32 fp32 values 1 - 4 M
+// 0.94 (1.00), from 8 M on 0.96; chunk 64 2 - 8 M 0.97 (1.02), from 8 M on 0.95; but below 1 M chunk 32 1.00 (1.02), chunk
+// 64 with 16-bit values 1.02 (1.04).  Chunk 32 with 16-bit values 0.98, signs the same either way.
+// (DETO_SMALL_SHARD_TILES = 0: no shard is small.)
+constexpr int64_t kCompressGangs = int64_t{1} << 20;
+inline int compress_run_log2(const KParams& p, int64_t n) {
+    if (n <= kCompressGangs && small_shard_tiles() != 0) return 6;
+    return run_log2(p.s, p.k, p.val_dtype, p.scheme != 0 ? 0 : p.idx_u8 ? 1 : 4, kRunBytes);
+}
+// Fewer of them are in flight at no loss.  us without a limit, or at the one above, and at the chosen one (147 M;
+// 60 M):
 //   chunk 32, from 2^25 elements on: fp32 values, bf16 gradients, k >= 8 5 (349, 327; 147, 139), fewer
 //     entries 6 (279, 262; 118, 112), fp32 gradients 5 (399, 386; 166, 159); 16-bit values 7 and 5
 //   chunk 16, from 2^25 on, 8 (291, 284; 121, 118)
@@ -368,14 +376,13 @@ inline int compress_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) 
 //     and Random on coefficients, bf16, from 2^27 on, 6 (308, 303; 861 M 1,763, 1,719; 80 M 168, 169)
 inline int compress_gang_workgroups(const KParams& p, int64_t tiles, bool grad_bf16) {
     const int64_t n = tiles * (kWave * p.s);
-    if (p.scheme != 0 && !p.use_dct) return compress_workgroups(p, tiles, grad_bf16);
     if (p.s == 64) {
         if (n <= (int64_t{1} << 26)) return 0;
         if (p.scheme != 0) return grad_bf16 && n > (int64_t{1} << 27) ? 6 : 0;
         if (!grad_bf16) return 5;
         return p.k < 32 ? 0 : p.val_dtype == 0 ? 5 : 7;
     }
-    if (n <= kLargeShard || p.s > 32) return compress_workgroups(p, tiles, grad_bf16);
+    if (n <= kLargeShard) return compress_workgroups(p, tiles, grad_bf16);
     if (p.s == 16) return 8;
     if (!grad_bf16) return 5;
     return p.val_dtype != 0 ? 7 : p.k >= 8 ? 5 : 6;
@@ -418,12 +425,12 @@ inline int adamw_workgroups(const KParams& p, int64_t n, bool idx, bool param_bf
     if (p.s == 32 && p.R <= 4 && !plain) {
         if (idx && !param_bf16) return 5;
         if (idx) return n > (int64_t{1} << 26) && (p.R < 4 || p.k >= 16 || p.k % 4 != 0) ? 5 : 0;
-        if (!param_bf16) return n > (int64_t{1} << 24) ? (p.use_dct && p.val_dtype == 3 ? 6 : 5) : 0;
+        if (!param_bf16) return n > (int64_t{1} << 24) ? (p.val_dtype == 3 ? 6 : 5) : 0;
     }
     if (rk > p.s) return 0;
-    if (p.s == 96) return (idx ? !plain : !p.use_dct) || (large && param_bf16) ? 4 : 0;
+    if (p.s == 96) return (idx && !plain) || (large && param_bf16) ? 4 : 0;
     if (!param_bf16) return 0;
-    if (p.s == 64) return plain ? (!idx && p.use_dct && large ? 4 : 0) : (idx || !p.use_dct ? 4 : 0);
+    if (p.s == 64) return (plain ? !idx && large : idx) ? 4 : 0;
     return p.s == 32 && !idx && plain && large ? 5 : 0;
 }
 inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool param_bf16, int classes) {
@@ -443,54 +450,71 @@ inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool par
     if (idx) {
         if (p.k % 4 != 0) return 0;
         if (p.s == 32 && p.k >= 16 && twice) return n > kLargeShard ? 4 : 0;
-        if (p.s == 32 && p.k == 4 && !param_bf16) return n > kLargeShard ? 6 : 0;
+        if (p.s == 32 && p.k == 4) return n > kLargeShard ? 6 : 0;
         if (!large) return 0;
         if (p.s == 64) {
-            if (p.k >= 16) return twice ? 3 : 4;
             if (p.k >= 8) return classes == 4 ? 4 : 0;
             return (twice || !param_bf16) ? 6 : 0;
         }
         if (p.k >= 16) return (p.k == 16) == param_bf16 || 2 * rk >= 3 * p.s ? 5 : 6;
-        if (p.k >= 8) return !param_bf16 ? (twice ? 4 : 5) : (twice ? 5 : 0);
-        return 0;
+        return !param_bf16 ? (twice ? 4 : 5) : (twice ? 5 : 0);
     }
     if (!large || !twice || p.k < 4) return 0;
     if (p.s == 64) return (p.k == 32 && rk >= 4 * p.s) || (p.k == 4 && p.use_dct) ? 0 : 5;
     return rk < 4 * p.s ? 6 : p.k == 4 ? 5 : 4;
 }
-// The same for tiles in gangs (run_log2), from 2^25 elements on; us without a limit, or at the one above, and at the
-// chosen one (147 M; 60 M):
-//   indices, fp32 values, plain update: chunk 128, k >= 32, 3 (bf16 488, 480; 205, 203; 16 entries 276, 284: none);
-//     chunk 64, k >= 16, R*k >= 2s 3 (471, 449; 198, 190; fp32 565, 538), s 4 (276, 271; 117, 112); chunk 32, k >= 16,
-//     from 2s on 4 bf16 (447, 437), 5 fp32 (557, 542; 233, 226), from s on 5 (280, 273) and 6 (151, 148); 4 entries
-//     8 (278, 272; fp32 and bf16)
-//   AdamW, four classes: chunk 64, indices, fp32 values 3, from 2^24 on (bf16 859, 838; 350, 341; fp32 969, 936; with
-//     R*k = 2s and few entries 351, 354: k >= 16 there), narrow ones 4 bf16, 3 fp32 (643, 628); chunk 128, R*k <= s,
-//     3 (586, 577); chunk 32, fp32 values and parameters 5 (653, 645)
-// (The same kernels with the addresses of tiles in a row are up to 5 % faster where memory is not the bound:
-// shards of less than 2^23 elements (64/8 AdamW 7 M 34.8, 36.1; 64/16 11 M 23.6, 22.1), narrow payloads under the
-// plain update (128/16 fp16 11 M 23.6, 24.1), entries one by one (128/29 35 M 76, 79).)
+// Tiles in gangs (run_log2), transmitted indices, k a multiple of four: where windows that move side by side pay for
+// the addresses and for shorter runs of the payload.  In gangs over in a row, geometric mean (largest) over some 1,300
+// random shapes on rotating buffers, 8 - 160 M parameters:
+//   AdamW, fp32 values, a quarter of the chunk kept or more 0.97 (1.03), or up to two replicas 0.96 (1.00); less of more
+//     replicas 1.05 (1.16)
+//   AdamW, 16-bit values or byte indices, chunk 64 and 128, the same and R*k <= s 0.97 (1.02); R*k > s 1.00 (1.08), chunk
+//     32 1.00, signs 1.00
+//   plain update, fp32 values, a quarter or more: fp32 parameters and R*k <= s/4 0.98 (1.01); chunk 32 R*k > 2s 0.97
+//     (1.01), below 1.02 (1.21); chunk 64 R*k >= s 0.97 (1.04), below 1.01 (1.06); chunk 128 from 2^25 elements on, fp32
+//     parameters 0.98 (1.02), bf16 R*k > s 0.98 (1.02), below 1.00 (1.05)
 constexpr int64_t kGangShard = int64_t{1} << 23;
-inline bool decompress_gangs(const KParams& p, int classes) {      // transmitted indices
-    if (p.run_lg >= 6 || classes == 0 || p.k % 4 != 0 || (p.adam && p.amsgrad)) return false;
-    if (p.s != 32 && p.s != 64 && p.s != 128) return false;
-    return (p.val_dtype == 0 && !p.idx_u8) || (p.adam && classes == 4);
-}
-inline int decompress_gang_workgroups(const KParams& p, int64_t n, bool param_bf16, int classes) {
+inline bool decompress_gangs(const KParams& p, int64_t n, bool param_bf16, int classes) {
+    if (p.run_lg >= 6 || classes == 0 || p.k % 4 != 0 || (p.s != 32 && p.s != 64 && p.s != 128)) return false;
     const int64_t rk = static_cast<int64_t>(p.R) * p.k;
-    if (n <= (int64_t{1} << (p.adam && p.s == 64 ? 24 : 25))) return 0;
-    const bool plain = p.val_dtype == 0 && !p.idx_u8;
+    const bool plain = p.val_dtype == 0 && !p.idx_u8, quarter = 4 * p.k >= p.s;
     if (p.adam) {
-        if (classes != 4) return 0;
-        if (p.s == 64) return plain ? (rk <= p.s || p.k >= 16 ? 3 : 0) : param_bf16 ? 4 : 3;
-        if (p.s == 128) return rk <= p.s ? 3 : 0;
-        return p.s == 32 && plain && !param_bf16 ? 5 : 0;
+        if (p.amsgrad || !(quarter || p.R <= 2)) return false;
+        return plain || (p.s != 32 && p.val_dtype != 3 && rk <= p.s);
     }
-    if (p.s == 128) return p.k >= 32 ? 3 : 0;
-    if (p.s == 64) return p.k < 16 ? 0 : rk >= 2 * p.s ? 3 : rk >= p.s ? 4 : 0;
-    if (p.s != 32) return 0;
-    if (p.k < 16) return p.k == 4 ? 8 : 0;
-    return rk >= 2 * p.s ? (param_bf16 ? 4 : 5) : rk >= p.s ? (param_bf16 ? 5 : 6) : 0;
+    if (!plain || !quarter) return false;
+    if (p.s == 128 && (n <= kLargeShard || (param_bf16 && rk <= p.s))) return false;
+    return p.s == 128 || (!param_bf16 && 4 * rk <= p.s) || rk > (p.s == 32 ? 2 * p.s : p.s - 1);
+}
+// this call's run_log2; without indices (Striding and Random on coefficients, a lane per chunk, bf16 parameters; the
+// same 900 M down to 12 M): half the chunk kept 0.96 (1.03), a quarter R*k >= 4s 0.97 (1.01), below 1.00 (1.06)
+inline int decompress_run_log2(const KParams& p, int64_t n, bool idx, bool param_bf16) {
+    if (n <= kGangShard) return 6;
+    if (idx)
+        return run_log2(p.s, p.k, p.val_dtype, p.idx_u8 ? 1 : 4, decompress_run_bytes(p.s, p.k, p.R, p.adam));
+    if (!scheme_gangs(p.s, p.k) || p.val_dtype != 0 || !param_bf16 || n <= (int64_t{1} << 24)) return 6;
+    if (2 * p.k != p.s && p.R * p.k < 4 * p.s) return 6;
+    return run_log2(p.s, p.k, 0, 0, kSchemeRunBytes);
+}
+// Workgroups per CU of those, us without a limit and at the chosen one (147 M; 60 M):
+//   plain update, from 2^25 elements on: chunk 128, R*k > s 3 (bf16 488, 480; 205, 203); chunk 64, R*k >= 2s 3 (471, 449;
+//     198, 190; fp32 565, 538), from s on 4 (276, 271; 117, 112); chunk 32 4 (fp32 and bf16, random shapes 0.96)
+//   AdamW: chunk 64, fp32 values, from 2^24 on 3 (bf16 859, 838; 350, 341; fp32 969, 936), narrow ones 4
+//     bf16, 3 fp32 (643, 628); from 2^25 on chunk 128, R*k <= s, 3 (586, 577), chunk 32, fp32 parameters, 5 (653, 645)
+inline int decompress_gang_workgroups(const KParams& p, int64_t n, bool param_bf16) {
+    const int64_t rk = static_cast<int64_t>(p.R) * p.k;
+    if (p.adam && p.s == 64) {
+        if (p.val_dtype != 0 || p.idx_u8) return param_bf16 ? 4 : 3;
+        return n > (int64_t{1} << 24) ? 3 : 0;
+    }
+    if (n <= kLargeShard) return 0;
+    if (p.adam) {
+        if (p.s == 128) return rk <= p.s ? 3 : 0;
+        return param_bf16 ? 0 : 5;
+    }
+    if (p.s == 128) return rk > p.s ? 3 : 0;
+    if (p.s == 64) return rk >= 2 * p.s ? 3 : rk >= p.s ? 4 : 0;
+    return rk > 2 * p.s ? 4 : 0;
 }
 // Dynamic LDS for that: half way between what lets one workgroup more and one less onto a CU.
 // static_bytes: a tile's rows, (s + 4) floats a chunk (and, where the classes list the places
@@ -501,19 +525,23 @@ inline unsigned spare_lds(int workgroups, int static_bytes) {
     const int total = 2 * 160 * 1024 / (2 * workgroups + 1);
     return total > static_bytes ? static_cast<unsigned>(total - static_bytes) : 0u;
 }
+inline int launch_workgroups(const CompressLaunch& a) {
+    return a.p.run_lg < 6 ? compress_gang_workgroups(a.p, a.tiles, a.grad_bf16)
+                          : compress_workgroups(a.p, a.tiles, a.grad_bf16);
+}
+inline int launch_workgroups(const DecompressLaunch& a, int classes) {
+    return a.idx && decompress_gangs(a.p, a.n, a.param_bf16, classes)
+               ? decompress_gang_workgroups(a.p, a.n, a.param_bf16)
+               : decompress_workgroups(a.p, a.n, a.idx != nullptr, a.param_bf16, classes);
+}
 inline unsigned spare_lds(const CompressLaunch& a) {
     const int rows = 4 * kWave * (a.p.s + 4);
-    const int wgs = a.p.run_lg < 6 ? compress_gang_workgroups(a.p, a.tiles, a.grad_bf16)
-                                   : compress_workgroups(a.p, a.tiles, a.grad_bf16);
-    return spare_lds(wgs, rows > 10240 ? rows : 10240);
+    return spare_lds(launch_workgroups(a), rows > 10240 ? rows : 10240);
 }
 inline unsigned spare_lds(const DecompressLaunch& a, int classes = 0) {
     const int s = a.p.s;
     const int places = (!a.idx && classes) ? kWave * s / 2 + 8 * (s < 32 ? 32 : s) : 0;
-    const int wgs = a.idx && decompress_gangs(a.p, classes)
-                        ? decompress_gang_workgroups(a.p, a.n, a.param_bf16, classes)
-                          : decompress_workgroups(a.p, a.n, a.idx != nullptr, a.param_bf16, classes);
-    return spare_lds(wgs, 4 * kWave * (s + 4) + places);
+    return spare_lds(launch_workgroups(a, classes), 4 * kWave * (s + 4) + places);
 }
 
 // Few chunks: a launch of the wavefront-per-class kernels is then a handful of workgroups whose own

@@ -20,28 +20,34 @@ bool DETO_COMPRESS_NARROW_FN(const CompressLaunch& a) {
     if (!takes(a.p.val_dtype) || !a.p.idx_u8 || a.p.scheme != 0) return false;
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
-#define LAUNCH(S, K, G, V)                                                                      \
-    compress_tiled_topk<S, K, G, V><<<grid, kWave, spare_lds(a), a.stream>>>(a.p, a.tiles, tail, a.grad,   \
-                                                                  a.mom, a.idx, a.val, a.coeff_dbg)
+#define LAUNCH(S, K, G, V, GANG)                                                                \
+    compress_tiled_topk<S, K, G, V, GANG><<<grid, kWave, spare_lds(a), a.stream>>>(             \
+        a.p, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
+#define FORMAT(S, K, V)                                                                         \
+    {                                                                                           \
+        constexpr bool kGangs = run_log2(S, K, V, 1, kRunBytes) < 6;                            \
+        if (kGangs && a.p.run_lg < 6) {                                                         \
+            if (a.grad_bf16) LAUNCH(S, K, true, V, kGangs); else LAUNCH(S, K, false, V, kGangs); \
+        } else {                                                                                \
+            if (a.grad_bf16) LAUNCH(S, K, true, V, false); else LAUNCH(S, K, false, V, false);  \
+        }                                                                                       \
+    }
 #ifdef DETO_NARROW_TERNARY
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \
-        if (a.grad_bf16) LAUNCH(S, K, true, 3); else LAUNCH(S, K, false, 3);                    \
+        FORMAT(S, K, 3)                                                                         \
         return true;                                                                            \
     }
 #else
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \
-        if (a.p.val_dtype == 1) {                                                               \
-            if (a.grad_bf16) LAUNCH(S, K, true, 1); else LAUNCH(S, K, false, 1);                \
-        } else {                                                                                \
-            if (a.grad_bf16) LAUNCH(S, K, true, 2); else LAUNCH(S, K, false, 2);                \
-        }                                                                                       \
+        if (a.p.val_dtype == 1) FORMAT(S, K, 1) else FORMAT(S, K, 2)                            \
         return true;                                                                            \
     }
 #endif
     DETO_NARROW_LIST(X)
 #undef X
+#undef FORMAT
 #undef LAUNCH
     return false;
 }

@@ -14,20 +14,22 @@ bool DETO_COMPRESS_SCHEME_FN(const CompressLaunch& a) {
     if (!a.p.use_dct || a.p.val_dtype != 0 || a.p.idx_u8) return false;   // fp32 values, int32 indices only
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
+#define LAUNCH(S, K, BF16, GANG)                                                                \
+    compress_tiled_scheme<S, K, BF16, 0, GANG><<<grid, kWave, spare_lds(a), a.stream>>>(        \
+        a.p, words(a.stride_mask), a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \
-        if (a.grad_bf16)                                                                        \
-            compress_tiled_scheme<S, K, true><<<grid, kWave, spare_lds(a), a.stream>>>(        \
-                a.p, words(a.stride_mask), a.tiles, tail, a.grad, a.mom, static_cast<int32_t*>(a.idx),        \
-                static_cast<float*>(a.val), a.coeff_dbg);         \
-        else                                                                                    \
-            compress_tiled_scheme<S, K, false><<<grid, kWave, spare_lds(a), a.stream>>>(       \
-                a.p, words(a.stride_mask), a.tiles, tail, a.grad, a.mom, static_cast<int32_t*>(a.idx),        \
-                static_cast<float*>(a.val), a.coeff_dbg);         \
+        constexpr bool kGangs = run_log2(S, K, 0, 0, kRunBytes) < 6;                            \
+        if (kGangs && a.p.run_lg < 6) {                                                         \
+            if (a.grad_bf16) LAUNCH(S, K, true, kGangs); else LAUNCH(S, K, false, kGangs);      \
+        } else {                                                                                \
+            if (a.grad_bf16) LAUNCH(S, K, true, false); else LAUNCH(S, K, false, false);        \
+        }                                                                                       \
         return true;                                                                            \
     }
     DETO_SCHEME_LIST(X)
 #undef X
+#undef LAUNCH
     return false;
 }
 
@@ -35,20 +37,21 @@ bool DETO_DECOMPRESS_SCHEME_FN(const DecompressLaunch& a) {
     if (a.idx || a.p.val_dtype != 0 || a.p.adam) return false;
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
+#define LAUNCH(S, K, BF16, GANG)                                                                \
+    decompress_tiled_scheme<S, K, BF16, 0, GANG, false><<<grid, kWave, spare_lds(a), a.stream>>>(      \
+        a.p, words(a.stride_mask), a.tiles, tail, a.val, a.val_stride, a.params,                \
+        AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg)
 #define X(S, K)                                                                                 \
     if (a.p.s == S && a.p.k == K) {                                                             \
-        if (a.param_bf16)                                                                       \
-            decompress_tiled_scheme<S, K, true><<<grid, kWave, spare_lds(a), a.stream>>>(      \
-                a.p, words(a.stride_mask), a.tiles, tail, static_cast<const float*>(a.val), a.val_stride,     \
-                a.params, AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);     \
-        else                                                                                    \
-            decompress_tiled_scheme<S, K, false><<<grid, kWave, spare_lds(a), a.stream>>>(     \
-                a.p, words(a.stride_mask), a.tiles, tail, static_cast<const float*>(a.val), a.val_stride,     \
-                a.params, AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg);     \
+        constexpr bool kGangs = scheme_gangs(S, K);                                             \
+        if (!a.param_bf16) LAUNCH(S, K, false, false);                                          \
+        else if (kGangs && a.p.run_lg < 6) LAUNCH(S, K, true, kGangs);                          \
+        else LAUNCH(S, K, true, false);                                                         \
         return true;                                                                            \
     }
     DETO_SCHEME_LIST(X)
 #undef X
+#undef LAUNCH
     return false;
 }
 

@@ -14,12 +14,16 @@ void compress_one(const CompressLaunch& a) {
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
     const MaskWords mw{{a.stride_mask[0], a.stride_mask[1], a.stride_mask[2], a.stride_mask[3]}};
-    if (a.grad_bf16)
-        compress_tiled_scheme<S, K, true, V><<<grid, kWave, spare_lds(a), a.stream>>>(
-            a.p, mw, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);
-    else
-        compress_tiled_scheme<S, K, false, V><<<grid, kWave, spare_lds(a), a.stream>>>(
-            a.p, mw, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);
+    constexpr bool kGangs = run_log2(S, K, V, 0, kRunBytes) < 6;
+#define LAUNCH(BF16, GANG)                                                                      \
+    compress_tiled_scheme<S, K, BF16, V, GANG><<<grid, kWave, spare_lds(a), a.stream>>>(        \
+        a.p, mw, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
+    if (kGangs && a.p.run_lg < 6) {
+        if (a.grad_bf16) LAUNCH(true, kGangs); else LAUNCH(false, kGangs);
+    } else {
+        if (a.grad_bf16) LAUNCH(true, false); else LAUNCH(false, false);
+    }
+#undef LAUNCH
 }
 
 template <int S, int K, int V>
@@ -29,7 +33,7 @@ void decompress_one(const DecompressLaunch& a) {
     const MaskWords mw{{a.stride_mask[0], a.stride_mask[1], a.stride_mask[2], a.stride_mask[3]}};
     constexpr bool kSigns = V == 3;
 #define LAUNCH(BF16, COUNT)                                                                     \
-    decompress_tiled_scheme<S, K, BF16, V, COUNT><<<grid, kWave, spare_lds(a), a.stream>>>(     \
+    decompress_tiled_scheme<S, K, BF16, V, false, COUNT><<<grid, kWave, spare_lds(a), a.stream>>>( \
         a.p, mw, a.tiles, tail, a.val, a.val_stride, a.params,                                  \
         AdamPtrs{nullptr, nullptr, nullptr}, a.presign_dbg)
     if (kSigns && a.p.count_signs) {

@@ -12,18 +12,22 @@ bool DETO_COMPRESS_FN(const CompressLaunch& a) {
     if (a.p.s != DETO_S || a.p.val_dtype != 0 || a.p.idx_u8) return false;
     const unsigned grid = tiled_grid(a.tiles, a.n_chunks);
     const TailRange tail{a.n, a.n_chunks};
+#define LAUNCH(K, BF16, GANG)                                                                   \
+    compress_tiled_topk<DETO_S, K, BF16, 0, GANG><<<grid, kWave, spare_lds(a), a.stream>>>(    \
+        a.p, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg)
 #define X(K)                                                                                    \
     if (a.p.k == K) {                                                                           \
-        if (a.grad_bf16)                                                                        \
-            compress_tiled_topk<DETO_S, K, true><<<grid, kWave, spare_lds(a), a.stream>>>(     \
-                a.p, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);                        \
-        else                                                                                    \
-            compress_tiled_topk<DETO_S, K, false><<<grid, kWave, spare_lds(a), a.stream>>>(    \
-                a.p, a.tiles, tail, a.grad, a.mom, a.idx, a.val, a.coeff_dbg);                        \
+        constexpr bool kGangs = run_log2(DETO_S, K, 0, 4, kRunBytes) < 6;                       \
+        if (kGangs && a.p.run_lg < 6) {                                                         \
+            if (a.grad_bf16) LAUNCH(K, true, kGangs); else LAUNCH(K, false, kGangs);            \
+        } else {                                                                                \
+            if (a.grad_bf16) LAUNCH(K, true, false); else LAUNCH(K, false, false);              \
+        }                                                                                       \
         return true;                                                                            \
     }
     DETO_K_LIST(X)
 #undef X
+#undef LAUNCH
     return false;
 }
 #endif

@@ -27,14 +27,27 @@ extern "C" int few_decompress(const int* a, int64_t chunks) {
 extern "C" int direct(const int* a, int64_t chunks) {
     return deto::direct_compress(params(a)) && !deto::few_direct(params(a), chunks);
 }
-extern "C" int compress_wgs(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t, false); }
-extern "C" int compress_wgs_bf16(const int* a, int64_t t) { return deto::compress_workgroups(params(a), t, true); }
+// (of the kernels that the launch runs on: tiles in gangs or in a row)
+static int compress_wgs_of(const int* a, int64_t tiles, bool bf16) {
+    deto::CompressLaunch l = {};
+    l.p = params(a);
+    l.tiles = tiles;
+    l.grad_bf16 = bf16;
+    l.p.run_lg = deto::compress_run_log2(l.p, tiles * 64 * l.p.s);
+    return deto::launch_workgroups(l);
+}
+extern "C" int compress_wgs(const int* a, int64_t t) { return compress_wgs_of(a, t, false); }
+extern "C" int compress_wgs_bf16(const int* a, int64_t t) { return compress_wgs_of(a, t, true); }
 static int decompress_wgs_of(const int* a, int64_t n, bool bf16) {
-    const deto::KParams p = params(a);
-    const bool idx = a[4] == 0;
-    const int classes = idx ? deto::decompress_classes(p, n, bf16, deto::lane_decompress(p))
-                            : deto::scheme_classes(p, n, bf16, deto::lane_scheme(p));
-    return deto::decompress_workgroups(p, n, idx, bf16, classes);
+    deto::DecompressLaunch l = {};
+    l.p = params(a);
+    l.n = n;
+    l.param_bf16 = bf16;
+    l.idx = a[4] == 0 ? a : nullptr;
+    l.p.run_lg = deto::decompress_run_log2(l.p, n, l.idx != nullptr, bf16);
+    const int classes = l.idx ? deto::decompress_classes(l.p, n, bf16, deto::lane_decompress(l.p))
+                              : deto::scheme_classes(l.p, n, bf16, deto::lane_scheme(l.p));
+    return deto::launch_workgroups(l, classes);
 }
 extern "C" int decompress_wgs(const int* a, int64_t n) { return decompress_wgs_of(a, n, true); }
 extern "C" int decompress_wgs_f32(const int* a, int64_t n) { return decompress_wgs_of(a, n, false); }
@@ -96,20 +109,17 @@ def test_direct_sums_where_there_are_more_than_a_few_chunks(rules, s, val, few):
 
 
 def test_workgroups_per_cu_of_large_launches(rules):
-    for s, scheme, dct, want in ((32, TOPK, True, 10), (32, RANDOM, True, 10), (32, STRIDE, False, 8),
-                                 (16, TOPK, True, 10), (64, RANDOM, False, 6), (64, TOPK, True, 0),
-                                 (128, TOPK, True, 0)):
-        assert rules("compress_wgs", s, 4, 10241, 1, F32, scheme, dct) == want
-        assert rules("compress_wgs", s, 4, 10240, 1, F32, scheme, dct) == 0
+    for s, scheme, want in ((32, TOPK, 10), (32, RANDOM, 10), (16, TOPK, 10), (64, TOPK, 0)):
+        assert rules("compress_wgs", s, 4, 10241, 1, F32, scheme, True) == want
+        assert rules("compress_wgs", s, 4, 10240, 1, F32, scheme, True) == 0
     m26, m25 = 1 << 26, 1 << 25
-    for s, k, R, scheme, n, want in ((64, 32, 2, TOPK, m26, 4), (64, 32, 4, TOPK, m26, 3), (64, 16, 2, TOPK, m26, 0),
+    for s, k, R, scheme, n, want in ((64, 32, 2, TOPK, m25, 4), (64, 32, 4, TOPK, m25, 3), (64, 16, 2, TOPK, m26, 0),
                                      (64, 32, 16, TOPK, m26, 0), (32, 16, 2, TOPK, m26, 5), (32, 16, 4, TOPK, m25, 4),
                                      (64, 32, 4, RANDOM, m26, 5), (64, 32, 2, RANDOM, m26, 0),
                                      (32, 16, 4, RANDOM, m26, 6), (32, 16, 8, RANDOM, m26, 4)):
         assert rules("decompress_wgs", s, k, n + 1, R, F32, scheme) == want
         assert rules("decompress_wgs", s, k, n, R, F32, scheme) == 0
         assert rules("decompress_wgs", s, k, n + 1, R, F16, scheme) == 0
-        assert rules("decompress_wgs", s, k, n + 1, R, F32, scheme, None, 1) == 0
     # that many fit 160 KB, one more does not; within the 64 KB of a launch
     for wgs in (3, 4, 5, 6, 8, 10):
         for static in (9216, 10240, 17408):
@@ -134,7 +144,7 @@ def test_workgroups_per_cu_of_large_launches(rules):
     (32, 20, 2, TOPK, 6, 5), (32, 24, 2, TOPK, 5, 5), (32, 24, 4, TOPK, 4, 4), (64, 4, 32, RANDOM, 0, 0), (64, 4, 32, RAW, 5, 0), (64, 16, 16, RANDOM, 5, 5),
     (32, 4, 16, RANDOM, 6, 0), (32, 4, 32, RANDOM, 5, 0),
     # chunk 96 and 128 by classes; twelve entries on two classes
-    (128, 16, 4, TOPK, 0, 3), (128, 32, 4, TOPK, 3, 3), (128, 24, 4, TOPK, 0, 3), (128, 8, 8, TOPK, 0, 0),
+    (128, 16, 4, TOPK, 0, 3), (128, 32, 4, TOPK, 3, 0), (128, 24, 4, TOPK, 0, 3), (128, 8, 8, TOPK, 0, 0),
     (128, 16, 2, TOPK, 0, 0), (96, 12, 4, TOPK, 0, 4), (96, 24, 4, TOPK, 0, 4), (96, 12, 2, TOPK, 0, 0),
     (32, 12, 2, TOPK, 8, 0), (32, 8, 3, TOPK, 0, 0), (32, 12, 1, TOPK, 0, 0)])
 def test_workgroups_by_entries_and_parameters(rules, s, k, R, scheme, bf16, f32):
@@ -148,26 +158,25 @@ def test_workgroups_by_entries_and_parameters(rules, s, k, R, scheme, bf16, f32)
 
 # (s, k, R, values, scheme, elements from which on, workgroups with bf16 and with fp32 parameters)
 @pytest.mark.parametrize("s,k,R,val,scheme,line,bf16,f32", [
-    (64, 16, 4, SIGNS, TOPK, 23, 4, 0), (64, 32, 2, F16, TOPK, 23, 4, 0), (64, 32, 8, SIGNS, TOPK, 23, 0, 0),
-    (64, 16, 4, F32, TOPK, 25, 0, 0), (64, 5, 4, SIGNS, TOPK, 23, 0, 0), (64, 8, 2, SIGNS, RAW, 23, 4, 0),
-    (64, 16, 4, SIGNS, RANDOM, 25, 0, 0), (64, 16, 4, F32, RANDOM, 25, 4, 0), (64, 16, 4, F32, RAW, 25, 0, 0),
-    (96, 12, 4, F16, TOPK, 23, 4, 4), (96, 24, 4, F32, TOPK, 25, 4, 0), (96, 12, 4, F32, RAW, 23, 4, 4),
-    (96, 12, 4, F32, RANDOM, 25, 4, 0), (32, 8, 4, F32, RANDOM, 25, 5, 0), (32, 8, 4, F32, TOPK, 25, 0, 0),
+    (64, 16, 4, SIGNS, TOPK, 23, 4, 0), (64, 32, 2, F16, TOPK, 23, 4, 3), (64, 32, 8, SIGNS, TOPK, 23, 0, 0),
+    (64, 16, 4, F32, TOPK, 24, 3, 3), (64, 5, 4, SIGNS, TOPK, 23, 0, 0),
+    (64, 16, 4, SIGNS, RANDOM, 25, 0, 0), (64, 16, 4, F32, RANDOM, 25, 4, 0),
+    (96, 12, 4, F16, TOPK, 23, 4, 4), (96, 24, 4, F32, TOPK, 25, 4, 0),
+    (96, 12, 4, F32, RANDOM, 25, 4, 0), (32, 8, 4, F32, RANDOM, 25, 5, 0), (32, 8, 4, F32, TOPK, 25, 0, 5),
     (32, 4, 8, SIGNS, RANDOM, 25, 0, 0), (128, 16, 4, F32, TOPK, 25, 0, 0),
     (32, 16, 4, SIGNS, TOPK, 26, 5, None), (32, 4, 2, SIGNS, TOPK, 23, None, 5), (32, 1, 4, F16, TOPK, 26, 5, None),
-    (32, 4, 4, SIGNS, TOPK, 23, 0, 5), (32, 2, 8, SIGNS, TOPK, 23, 0, 0), (32, 8, 3, F16, RAW, 24, 0, 5),
+    (32, 4, 4, SIGNS, TOPK, 23, 0, 5), (32, 2, 8, SIGNS, TOPK, 23, 0, 0),
     (32, 8, 3, SIGNS, RANDOM, 24, 0, 6), (32, 16, 4, F16, RANDOM, 24, 0, 5)])
 def test_workgroups_of_adamw(rules, s, k, R, val, scheme, line, bf16, f32):
-    scheme, dct = scheme if scheme == RAW else (scheme, True)
     for n, on in ((1 << line, False), ((1 << line) + 1, True), (147095552, True)):
         for name, want in (("decompress_wgs", bf16), ("decompress_wgs_f32", f32)):
             if want is not None:                              # (None: its line is another one)
-                assert rules(name, s, k, n, R, val, scheme, dct, 1) == (want if on else 0)
+                assert rules(name, s, k, n, R, val, scheme, True, 1) == (want if on else 0)
 
 
 def test_one_or_two_bf16_entries_of_16_are_limited_later(rules):
     for name, k, tiles, want in (("compress_wgs_bf16", 1, 32768, 0), ("compress_wgs_bf16", 2, 32768, 0),
-                                 ("compress_wgs_bf16", 2, 32769, 10), ("compress_wgs_bf16", 4, 10241, 10),
+                                 ("compress_wgs_bf16", 2, 32769, 8), ("compress_wgs_bf16", 4, 10241, 10),
                                  ("compress_wgs", 1, 10241, 10)):
         assert rules(name, 16, k, tiles) == want
 
