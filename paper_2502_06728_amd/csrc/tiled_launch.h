@@ -471,7 +471,8 @@ inline int decompress_workgroups(const KParams& p, int64_t n, bool idx, bool par
 //   AdamW, 16-bit values or byte indices, chunk 64 and 128, the same and R*k <= s 0.97 (1.02); R*k > s 1.00 (1.08), chunk
 //     32 1.00, signs 1.00
 //   plain update, fp32 values, a quarter or more: fp32 parameters and R*k <= s/4 0.98 (1.01); chunk 32 R*k > 2s 0.97
-//     (1.01), below 1.02 (1.21); chunk 64 R*k >= s 0.97 (1.04), below 1.01 (1.06); chunk 128 from 2^25 elements on, fp32
+//     (1.01), below 1.02 (1.21); chunk 64 R*k >= s 0.97 (1.04), below 1.01 (1.06) but for fp32 parameters and one replica
+//     0.97 (1.01) or R*k <= s/2 up to 2^24 0.97 (1.02; above 1.03); chunk 128 from 2^25 elements on, fp32
 //     parameters 0.98 (1.02), bf16 R*k > s 0.98 (1.02), below 1.00 (1.05)
 constexpr int64_t kGangShard = int64_t{1} << 23;
 inline bool decompress_gangs(const KParams& p, int64_t n, bool param_bf16, int classes) {
@@ -484,7 +485,9 @@ inline bool decompress_gangs(const KParams& p, int64_t n, bool param_bf16, int c
     }
     if (!plain || !quarter) return false;
     if (p.s == 128 && (n <= kLargeShard || (param_bf16 && rk <= p.s))) return false;
-    return p.s == 128 || (!param_bf16 && 4 * rk <= p.s) || rk > (p.s == 32 ? 2 * p.s : p.s - 1);
+    if (!param_bf16 && (4 * rk <= p.s || (p.s == 64 && (p.R == 1 || (2 * rk <= p.s && n <= (int64_t{1} << 24))))))
+        return true;
+    return p.s == 128 || rk > (p.s == 32 ? 2 * p.s : p.s - 1);
 }
 // this call's run_log2; without indices (Striding and Random on coefficients, a lane per chunk, bf16 parameters; the
 // same 900 M down to 12 M): half the chunk kept 0.96 (1.03), a quarter R*k >= 4s 0.97 (1.01), below 1.00 (1.06)

@@ -96,7 +96,9 @@ SGD, ADAM, AMSGRAD = 0, 1, 2
     (64, 32, 2, SIGNS, ADAM, 1, 1 << 26, -1), (128, 64, 2, SIGNS, ADAM, 1, 1 << 26, -1), (96, 24, 4, F32, ADAM, 1, 1 << 26, -1),
     # plain update, fp32 values
     (64, 32, 2, F32, SGD, 1, 1 << 25, -1), (64, 32, 2, F32, SGD, 1, (1 << 25) + 1, 4), (64, 32, 4, F32, SGD, 1, 1 << 26, 3),
-    (64, 32, 2, F32, SGD, 0, (1 << 23) + 1, 0), (64, 32, 1, F32, SGD, 0, 1 << 26, -1), (64, 16, 1, F32, SGD, 0, 1 << 26, 0),
+    (64, 32, 2, F32, SGD, 0, (1 << 23) + 1, 0), (64, 32, 1, F32, SGD, 0, 1 << 26, 0),
+    (64, 16, 2, F32, SGD, 0, 1 << 24, 0), (64, 16, 2, F32, SGD, 0, (1 << 24) + 1, -1), (64, 20, 2, F32, SGD, 0, 1 << 24, -1),
+    (64, 16, 2, F32, SGD, 1, 1 << 24, -1), (64, 16, 1, F32, SGD, 0, 1 << 26, 0),
     (64, 16, 1, F32, SGD, 1, 1 << 26, -1), (64, 12, 8, F32, SGD, 0, 1 << 26, -1), (64, 32, 4, F16, SGD, 0, 1 << 26, -1),
     (32, 16, 4, F32, SGD, 1, 1 << 26, -1), (32, 16, 5, F32, SGD, 1, 1 << 26, 4), (32, 8, 1, F32, SGD, 0, 1 << 26, 0),
     (128, 32, 4, F32, SGD, 0, 1 << 25, -1), (128, 32, 4, F32, SGD, 0, 1 << 26, 0), (128, 32, 5, F32, SGD, 0, 1 << 26, 3),
