@@ -11,7 +11,7 @@ int64_t launch_compress_raw(const CompressLaunch& a) {
 #else
     if (p.scheme == 0 || p.use_dct || 2 * p.k > p.s || !raw_compress(p, a.n)) return 0;
     const int quads = raw_compress_quads(p);
-    const int wgs_cu = raw_compress_workgroups(a.n, a.grad_bf16);
+    const int wgs_cu = raw_compress_workgroups(p, a.n, a.grad_bf16);
     auto launch = [&](auto S_tag, auto Q_tag, auto kernel) -> int64_t {
         using G = RawGeom<decltype(S_tag)::value, decltype(Q_tag)::value>;
         const int64_t wgs = (a.n_chunks + G::kChunks - 1) / G::kChunks;

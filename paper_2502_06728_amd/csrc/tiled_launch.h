@@ -571,12 +571,14 @@ inline bool count_signs(const KParams& p) {
 }
 
 // ---- Striding and Random on the momentum itself (raw_kernels.hip.h).  Against the kernels before them (general
-// ones, a lane per chunk, classes, the stream), geometric mean over random shapes of chunk 16 ... 256, formats,
-// optimizers and replicas: 0.74 of their time at 0.05 - 1 M elements, 0.70 at 1 - 10 M, 0.91 at 10 - 150 M.
+// ones, a lane per chunk, classes, the stream), geometric mean over 500 random shapes each of 0.07 - 40 M elements, chunk
+// 16 ... 256, formats, optimizers and 1 - 64 replicas: compress 0.73 of their time, decompress of values 0.60, of signs
+// 0.61.
 // Pieces of four elements a thread: few while a launch's own latency counts (1.5 M, 128/4 compress, 2 / 4 / 8
 // pieces 5.0 / 5.8 / 6.7 us; AdamW 64/8 2.6 M 9.4 / 11.4 / 14.9), more where a replica's entries of a workgroup
 // would be a short run (128/16, 49 replicas, signs, 18 M 43.5 / 36.1 / 36.4; 256/64 bf16 60 M, 4 replicas 174 /
-// 106 / 81; signs of few replicas 128/8 R = 2 bf16 74 M 51 us in the class kernels, 59 / 54) and for compress where the shuffle is long (128/32 7 M 19.6 / 18.9; 256/64 60 M 144 / 127 / 129).
+// 106 / 81; signs of few replicas 128/8 R = 2 bf16 74 M 51 us in the class kernels, 59 / 54) and for compress where the
+// shuffle is long (128/32 7 M 19.6 / 18.9; 256/64 60 M 144 / 127 / 129).
 // Workgroups per CU of large launches, without a limit / with it (147 M): compress 128/16 fp32 328 / 4 313, bf16
 // 278 / 5 263, 32/1 signs bf16 265 / 252; decompress, fp32 parameters, 128/16 206 / 5 204; AdamW, 2 pieces, 60 M
 // 64/8 bf16 205 / 3 198, fp32 258 / 251.
@@ -591,8 +593,21 @@ inline int raw_compress_quads(const KParams& p) {
 inline bool raw_compress(const KParams& p, int64_t n) {
     return !(p.scheme == 2 && p.s >= 96 && 4 * p.k > p.s && n <= (int64_t{1} << 16));
 }
-inline int raw_compress_workgroups(int64_t n, bool grad_bf16) {
-    return n > kRawLimited ? (grad_bf16 ? 5 : 4) : 0;
+// Workgroups per CU of large launches.  A workgroup whose shuffle is long for the elements it moves spends its time there,
+// and memory idles below a round of them: as many as fit up to 52 elements a step (us with the limit / without: 192/96
+// fp16 fp32 46 M 180 / 115, bf16 57 M 188 / 139; 256/128 bf16 78 M 254 / 186; 192/64 66 M 174 / 131), up to 80 for the
+// signs of bf16 gradients (64/32 37 M 90 / 72, 128/64 58 M 132 / 107) and 6 of fp32 ones (64/32 28 M 80 / 66), and one
+// more for values but where much is in flight already (16-bit ones 64/32 bf16 66 M 138 / 126, fp32 31 M 81 / 73; but
+// 128/64 bf16 71 M 145 / 152, 96/48 fp32 values 40 M 100 / 107).
+inline int raw_compress_workgroups(const KParams& p, int64_t n, bool grad_bf16) {
+    if (n <= kRawLimited) return 0;
+    const int elements = 1024 * raw_compress_quads(p);
+    if (p.scheme == 2 && elements <= 52 * p.k) return 0;
+    if (p.scheme == 2 && elements <= 80 * p.k) {
+        if (p.val_dtype == 3) return grad_bf16 ? 0 : 6;
+        if (p.s <= 64 || p.s >= 192) return grad_bf16 ? (p.val_dtype != 0 ? 6 : 5) : 5;
+    }
+    return grad_bf16 ? 5 : 4;
 }
 // (AdamW: more also where the shuffle is long, 128/64 R = 4 65 M bf16 389 / 296, and where 16 replicas and more would
 // be runs of 256 bytes or less: 64/4 R = 46 signs 32 M 167 / 154, 32/2 R = 58 59 M 346 / 323)
@@ -608,26 +623,34 @@ inline int raw_decompress_quads(const KParams& p, int64_t n) {
     }
     return few ? 2 : many && p.s != 16 ? 8 : 4;
 }
-// Nearly everything.  A lane per chunk does for bf16 parameters under the plain update what is left to do, on launches
-// of a few wavefronts and on large ones (narrow values 32/1 139 M 93 us, 127 here; 32/16 17 M 23.7, 26.0; 64/32, 4
-// replicas, 147 M 287, 294, but 64/8 30 M 35, 32; 0.06 M 3.2, 3.7), but for two-bit signs of more entries than the
-// chunk has (147 M 32/16 R = 16 252 / 194; 64/32 R = 64 1,040 / 315; 32/2 R = 64 339 / 303; 32/1 R = 40 245 / 220, R = 16
-// 154 / 162) or, up to 2^23, more than a quarter of that (32/4 R = 1 fp32 2.9 M 5.7 / 7.5, 32/2 R = 3 5 M 9.2 / 11.1; in the
-// mean over random shapes 0.6 above that line, 1.0 below).  The class kernels that served the rest of the large launches, over 700 random shapes of 8 - 100 M
-// parameters: 0.72 of their time here; entries one by one 0.33 - 0.98 (16/6 R = 6 fp16 18 M 66 / 49, 96/13 R = 12 fp32
-// 8.5 M 70 / 26), two-bit signs 0.2 - 1.0.
+// Nearly everything.  A lane per chunk does for bf16 parameters under the plain update what is left to do, on
+// launches of a few wavefronts and on large ones (narrow values 32/1 139 M 93 us, 127 here; 32/16 17 M 23.7, 26.0;
+// 64/32, 4 replicas, 147 M 287, 294, but 64/8 30 M 35, 32; 0.06 M 3.2, 3.7), but for two-bit signs of more entries
+// than the chunk has (147 M 32/16 R = 16 252 / 194; 64/32 R = 64 1,040 / 315; 32/2 R = 64 339 / 303; 32/1 R = 40
+// 245 / 220, R = 16 154 / 162) or, up to 2^23, more than a quarter of that (32/4 R = 1 fp32 2.9 M 5.7 / 7.5, 32/2 R
+// = 3 5 M 9.2 / 11.1; in the mean over random shapes 0.6 above that line, 1.0 below).  Half of a chunk of 32 is one
+// full word a lane: large launches from three times the chunk on (R = 4 25 M 23.4 / 27.9, Random 85 M 81 / 100, R =
+// 8 48 M 51 / 47).  The class kernels that served the rest of the large launches, over 700 random shapes of 8 - 100
+// M parameters: 0.72 of their time here; entries one by one 0.33 - 0.98 (16/6 R = 6 fp16 18 M 66 / 49, 96/13 R = 12
+// fp32 8.5 M 70 / 26), two-bit signs 0.2 - 1.0.
 inline bool raw_decompress(const KParams& p, int64_t n, bool param_bf16) {
     const bool lane = lane_scheme(p);
     if (n <= (int64_t{1} << 17)) return !lane;
     if (lane && p.val_dtype == 3 && n <= (int64_t{1} << 23)) return 4 * p.R * p.k > p.s;
     if (n <= (int64_t{1} << 23) || !(lane && param_bf16)) return true;
-    if (p.val_dtype == 3) return p.R * p.k > p.s;
+    if (p.val_dtype == 3) return p.R * p.k > (p.s == 32 && p.k == 16 ? 3 * p.s : p.s);
     return p.val_dtype == 0 && p.s > 32 && n <= (int64_t{1} << 26);
 }
+// AdamW, 3 up to 2^26: fp32 values, and with fp32 parameters every format (signs 32/16 R = 4 65 M 270 / 253, 64/32 R = 2
+// 39 M 165 / 156); but not where the shuffle is long for the workgroup's elements (signs 256/128 R = 4 34 M 162 / 201 with
+// the limit; fp32 values and bf16 parameters 256/128 60 M 278 / 355, 64/21 53 M 179 / 190, 96/48 42 M 153 / 165; but chunk
+// 128, 64 entries, R = 4 58 M 283 / 272).
 inline int raw_decompress_workgroups(const KParams& p, int64_t n, bool param_bf16) {
     if (n <= kLargeShard) return 0;
-    if (p.adam) return n <= (int64_t{1} << 26) && p.val_dtype == 0 ? 3 : 0;
-    return param_bf16 ? 0 : 5;
+    if (!p.adam) return param_bf16 ? 0 : 5;
+    if (n > (int64_t{1} << 26) || (p.val_dtype != 0 && param_bf16)) return 0;
+    const int elements = 1024 * raw_decompress_quads(p, n);
+    return p.scheme == 2 && p.s != 128 && elements <= (param_bf16 ? 100 : 52) * p.k ? 0 : 3;
 }
 // dynamic LDS of a launch that takes `bytes` and is to have that many workgroups per CU
 inline unsigned raw_lds(int bytes, int workgroups) {

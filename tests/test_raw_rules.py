@@ -33,15 +33,21 @@ extern "C" int built(int s, int q, int adam) {
 #undef X
     return 0;
 }
-extern "C" int workgroups(int val, int adam, int bf16, int64_t n) {
-    return deto::raw_decompress_workgroups(params(64, 8, 2, val, adam), n, bf16 != 0);
+extern "C" int workgroups(int s, int k, int scheme, int val, int adam, int bf16, int64_t n) {
+    deto::KParams p = params(s, k, 2, val, adam);
+    p.scheme = scheme;
+    return deto::raw_decompress_workgroups(p, n, bf16 != 0);
 }
 extern "C" int compresses(int s, int k, int scheme, int64_t n) {
     deto::KParams p = params(s, k, 1, 0, 0);
     p.scheme = scheme;
     return deto::raw_compress(p, n);
 }
-extern "C" int compress_workgroups(int bf16, int64_t n) { return deto::raw_compress_workgroups(n, bf16 != 0); }
+extern "C" int compress_workgroups(int s, int k, int scheme, int val, int bf16, int64_t n) {
+    deto::KParams p = params(s, k, 1, val, 0);
+    p.scheme = scheme;
+    return deto::raw_compress_workgroups(p, n, bf16 != 0);
+}
 extern "C" int compress_built(int s, int q) {
 #define X(S, Q) if (s == S && q == Q) return 1;
     DETO_RAW_COMPRESS_LIST(X)
@@ -84,7 +90,8 @@ def test_decompress_rule(lib, s, k, val, bf16, n, want):
 
 @pytest.mark.parametrize("s,k,R,bf16,adam,n,want", [
     # two-bit signs: more entries than the chunk has, where a lane per chunk serves them
-    (32, 16, 2, 1, 0, 1 << 27, 0), (32, 16, 3, 1, 0, 1 << 27, 1), (32, 1, 32, 1, 0, 1 << 27, 0), (32, 1, 33, 1, 0, 1 << 27, 1),
+    (32, 16, 6, 1, 0, 1 << 27, 0), (32, 16, 7, 1, 0, 1 << 27, 1), (64, 32, 2, 1, 0, 1 << 27, 0), (64, 32, 3, 1, 0, 1 << 27, 1),
+    (32, 8, 4, 1, 0, 1 << 27, 0), (32, 8, 5, 1, 0, 1 << 27, 1), (32, 1, 32, 1, 0, 1 << 27, 0), (32, 1, 33, 1, 0, 1 << 27, 1),
     (32, 16, 2, 0, 0, 1 << 27, 1), (32, 4, 2, 0, 0, 1 << 23, 0), (32, 4, 3, 1, 0, 1 << 23, 1), (32, 4, 2, 0, 0, (1 << 23) + 1, 1),
     (32, 4, 1, 0, 1, 1 << 20, 1), (32, 3, 1, 0, 0, 1 << 20, 1), (32, 16, 2, 1, 1, 1 << 27, 1), (64, 2, 1, 1, 0, 1 << 27, 1)])
 def test_decompress_rule_of_signs(lib, s, k, R, bf16, adam, n, want):
@@ -112,8 +119,18 @@ def test_compress_rule(lib):
 
 def test_workgroups_per_cu(lib):
     for val, adam, bf16, n, want in ((0, 0, 0, 1 << 25, 0), (0, 0, 0, (1 << 25) + 1, 5), (0, 0, 1, 1 << 27, 0), (0, 1, 1, 1 << 26, 3),
-                                     (0, 1, 0, (1 << 26) + 1, 0), (3, 1, 0, 1 << 26, 0)):
-        assert lib.workgroups(val, adam, bf16, ctypes.c_int64(n)) == want
-    for bf16, want in ((0, 4), (1, 5)):
-        assert lib.compress_workgroups(bf16, ctypes.c_int64(1 << 24)) == 0
-        assert lib.compress_workgroups(bf16, ctypes.c_int64((1 << 24) + 1)) == want
+                                     (0, 1, 0, (1 << 26) + 1, 0), (3, 1, 0, 1 << 26, 3), (3, 1, 1, 1 << 26, 0), (2, 1, 0, 1 << 25, 0)):
+        assert lib.workgroups(64, 8, 2, val, adam, bf16, ctypes.c_int64(n)) == want
+    # AdamW (fp32 parameters, bf16): none where Random's shuffle is long for the workgroup's elements
+    for s, k, scheme, f32, bf16 in ((64, 20, 2, 3, 3), (64, 21, 2, 3, 0), (64, 32, 1, 3, 3), (64, 32, 2, 3, 0), (128, 64, 2, 3, 3),
+                                    (256, 78, 2, 3, 0), (256, 79, 2, 0, 0), (256, 128, 1, 3, 3), (96, 30, 2, 3, 3), (96, 31, 2, 3, 0)):
+        for on_bf16, want in ((0, f32), (1, bf16)):
+            assert lib.workgroups(s, k, scheme, 0, 1, on_bf16, ctypes.c_int64(1 << 26)) == want
+    # compress (fp32 gradients, bf16): more where Random's shuffle is long for the workgroup's elements
+    for s, k, scheme, val, f32, bf16 in ((64, 32, 1, 0, 4, 5), (64, 25, 2, 3, 4, 5), (64, 26, 2, 3, 6, 0), (64, 26, 2, 2, 5, 6),
+                                         (64, 32, 2, 0, 5, 5), (96, 48, 2, 3, 6, 0), (96, 48, 2, 2, 4, 5), (128, 64, 2, 0, 4, 5),
+                                         (192, 59, 2, 1, 5, 6), (192, 60, 2, 1, 0, 0), (192, 38, 2, 1, 4, 5), (192, 39, 2, 0, 5, 5),
+                                         (256, 78, 2, 3, 6, 0), (256, 79, 2, 0, 0, 0), (256, 128, 1, 0, 4, 5), (256, 51, 2, 0, 4, 5)):
+        for on_bf16, want in ((0, f32), (1, bf16)):
+            assert lib.compress_workgroups(s, k, scheme, val, on_bf16, ctypes.c_int64(1 << 24)) == 0
+            assert lib.compress_workgroups(s, k, scheme, val, on_bf16, ctypes.c_int64((1 << 24) + 1)) == want
